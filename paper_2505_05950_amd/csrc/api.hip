@@ -115,15 +115,17 @@ bool mask_path_ok(int f) { return mask_words_per_task(f) <= 2048; }
 // workspace of the layer: per-task table, counts, mask words, v, idx, partial
 struct LayerWs {
     size_t table_off, expert_off, weight_off, tau_off, logit_off, count_off, mask_off, groups_off, ngroups_off, order_off, v_off, idx_off,
-        rows_off, missidx_off, missrows_off, misscount_off, urow_off, ucount_off, hbuf_off, partial_off, total;
+        rows_off, missidx_off, missrows_off, misscount_off, wgroups_off, urow_off, ucount_off, hbuf_off, hexp_off, trows_off, partial_off, total;
     int n_tasks, nblk, nblk_fused, fused_passes;
     bool batch_mfma;  // tokens of an expert share one pass over its codes (matrix-core up GEMV)
-    bool use_union;   // batches: one read of every row an expert group selected (gate_down_union.hip)
+    bool use_wide;    // batches: one read of every row an expert group selected, on the matrix cores (wide_batch.hip)
+    bool use_union;   // the same through an LDS ring (gate_down_union.hip; by tuning only)
     int chunk;        // tasks per token group
     UnionPlan up;
+    WidePlan wp;
 };
-LayerWs layer_ws(const floe_layer* L, int T) {
-    LayerWs w;
+LayerWs layer_plan(const floe_layer* L, int T, bool allow_wide) {
+    LayerWs w{};
     const int slots = L->top_k + L->n_shared;
     w.n_tasks = T * slots;
     w.nblk = gd_blocks(w.n_tasks, L->s.f);
@@ -136,12 +138,15 @@ LayerWs layer_ws(const floe_layer* L, int T) {
     // the grouped up GEMV: when forced, or where the fused kernel does not apply and grouping pays
     w.batch_mfma = T >= 2 && mfma_grouped_shape(L->s.d, L->s.bits, L->s.group) &&
                    (grouped_gemv_mode() == 1 || (!w.fused_passes && mfma_batch_pays(n_all, w.n_tasks, L->s.bits)));
-    w.use_union = union_kernels_for(n_all, w.n_tasks) != 3 && !L->gd_on_host && T >= 2 && (!w.fused_passes || w.batch_mfma) &&
-                  mask_path_ok(L->s.f) && union_shape_ok(L->s.d, L->s.f, w.up);
+    const bool share_rows = !L->gd_on_host && T >= 2 && (!w.fused_passes || w.batch_mfma) && mask_path_ok(L->s.f);
+    const int kernels = union_kernels_for(n_all, w.n_tasks, L->s.d, L->s.f);
+    w.use_wide = share_rows && kernels == 1 && allow_wide;
+    w.use_union = share_rows && kernels == 2 && union_shape_ok(L->s.d, L->s.f, w.up);
+    if (w.use_wide) w.wp = wide_plan(L->s.d, L->s.f, T, L->n_experts, L->top_k, L->n_shared);
     int nblk_alloc = w.nblk > w.nblk_fused ? w.nblk : w.nblk_fused;
-    if (w.use_union && w.up.nblk_down > nblk_alloc) nblk_alloc = w.up.nblk_down;
+    if (w.use_union && w.up.nblk > nblk_alloc) nblk_alloc = w.up.nblk;
     int count_parts = w.nblk_fused > 1 ? w.nblk_fused : 1;
-    if (w.use_union && w.up.nblk_gate > count_parts) count_parts = w.up.nblk_gate;
+    if (w.use_union && w.up.nblk > count_parts) count_parts = w.up.nblk;
     size_t o = 0;
     w.table_off = o;  o += align_up((size_t)w.n_tasks * sizeof(DevExpert));
     w.expert_off = o; o += align_up((size_t)w.n_tasks * 4);
@@ -157,20 +162,32 @@ LayerWs layer_ws(const floe_layer* L, int T) {
     w.ngroups_off = o; o += align_up(4);
     w.order_off = o;   o += align_up((size_t)w.n_tasks * 4);
     w.v_off = o;      o += align_up((size_t)w.n_tasks * L->s.f * 4);
-    w.idx_off = o;    o += align_up((size_t)w.n_tasks * L->s.f * 4);
+    w.idx_off = o;    o += w.use_wide ? 0 : align_up((size_t)w.n_tasks * L->s.f * 4);
     // host-resident gate/down: row map and miss lists of the prefetched decode
     const size_t per_list = L->gd_on_host ? align_up((size_t)w.n_tasks * L->s.f * 4) : 0;
     w.rows_off = o;      o += per_list;
     w.missidx_off = o;   o += per_list;
     w.missrows_off = o;  o += per_list;
     w.misscount_off = o; o += L->gd_on_host ? align_up((size_t)w.n_tasks * 4) : 0;
-    const size_t gblocks = w.use_union ? (size_t)w.up.max_groups * w.up.nblk_gate : 0;
-    w.urow_off = o;   o += w.use_union ? align_up(gblocks * w.up.cap * 4) : 0;
-    w.ucount_off = o; o += w.use_union ? align_up(gblocks * 4) : 0;
-    w.hbuf_off = o;   o += w.use_union ? align_up(gblocks * (w.up.cap / 16) * 64 * sizeof(uint4)) : 0;
-    w.partial_off = o; o += align_up((size_t)w.n_tasks * nblk_alloc * L->s.d * 4);
+    const size_t wgroups = w.use_wide ? (size_t)w.wp.max_groups : 0;
+    w.wgroups_off = o; o += w.use_wide ? align_up(wgroups * sizeof(WideGroup) + 4) : 0;  // (+ their number)
+    w.urow_off = o;    o += align_up(wgroups * L->s.f * 4);
+    w.ucount_off = o;  o += align_up(wgroups * 4);
+    w.hbuf_off = o;    o += align_up(wgroups * w.wp.pairs * w.wp.nt * 128 * sizeof(uint4));
+    w.hexp_off = o;    o += align_up(wgroups * w.wp.pairs * 4);
+    w.trows_off = o;   o += w.use_wide ? align_up((size_t)w.n_tasks * sizeof(int2)) : 0;
+    w.partial_off = o;
+    o += w.use_wide ? align_up(w.wp.partial_rows * L->s.d * 4) : align_up((size_t)w.n_tasks * nblk_alloc * L->s.d * 4);
     w.total = o;
     return w;
+}
+// The wide kernels need more workspace per task.  A layer call that fits the library's static scratch with the one-token
+// kernels goes on fitting it: there they are taken unless the wide ones fit as well.
+LayerWs layer_ws(const floe_layer* L, int T) {
+    const LayerWs w = layer_plan(L, T, true);
+    if (!w.use_wide || w.total <= FLOE_STATIC_SCRATCH_BYTES || union_mode() == 1) return w;
+    const LayerWs n = layer_plan(L, T, false);
+    return n.total <= FLOE_STATIC_SCRATCH_BYTES ? n : w;
 }
 
 int check_layer(const floe_layer* L) {
@@ -582,15 +599,21 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
         FLOE_LAUNCH(FLOE_KERNEL_FUSED_FFN, st, launch_fused(a, L->s.bits, st));
         nblk = w.nblk_fused;
         count_parts = w.nblk_fused;
-    } else if (w.use_union) {
-        // decode batch: [router] -> [token groups per expert] -> [up GEMV + mask bits] -> [gate on the union of the
-        // group's rows] -> [down]; every selected row is read once per expert group
+    } else if (w.use_wide || w.use_union) {
+        // decode batch: [router] -> [token groups per expert] -> [up GEMV + mask bits] -> [gate/down on the union of the
+        // group's rows]; every selected row is read once per expert group
         const RouterArgs ra = router_args(L, w, base, xh);
         FLOE_LAUNCH(FLOE_KERNEL_ROUTER, st, launch_router(ra, T, st));
         TokenGroup* groups = reinterpret_cast<TokenGroup*>(base + w.groups_off);
         int32_t* n_groups = reinterpret_cast<int32_t*>(base + w.ngroups_off);
         const int n_all = L->n_experts + L->n_shared;
-        FLOE_HIP(launch_group_tokens(task_expert, w.n_tasks, n_all, w.chunk, groups, n_groups, st));
+        WideGroup* wide = reinterpret_cast<WideGroup*>(base + w.wgroups_off);
+        int32_t* n_wide = reinterpret_cast<int32_t*>(wide + w.wp.max_groups);
+        int32_t* order = reinterpret_cast<int32_t*>(base + w.order_off);
+        if (w.use_wide)
+            FLOE_HIP(launch_group_tokens(task_expert, w.n_tasks, n_all, w.chunk, groups, n_groups, st, order, w.wp.chunk, wide, n_wide));
+        else
+            FLOE_HIP(launch_group_tokens(task_expert, w.n_tasks, n_all, w.chunk, groups, n_groups, st));
         if (batch_mfma)
             FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st,
                         launch_up_gemv_grouped(static_cast<const DevExpert*>(L->dev_table), groups, n_groups,
@@ -600,18 +623,32 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
             FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st,
                         launch_up_gemv(map, xh, nullptr, v, task_tau, mask, L->s.d, L->s.f, L->s.bits, L->s.group,
                                        w.n_tasks, st));
+        if (w.use_wide) {
+            WideArgs wa{};
+            wa.table = static_cast<const DevExpert*>(L->dev_table);
+            wa.groups = wide; wa.n_groups = n_wide; wa.order = order; wa.x = xh; wa.v = v;
+            wa.task_tau = task_tau; wa.task_scale = task_weight; wa.count = count;
+            wa.urow = reinterpret_cast<int32_t*>(base + w.urow_off);
+            wa.ucount = reinterpret_cast<int32_t*>(base + w.ucount_off);
+            wa.hbuf = reinterpret_cast<uint4*>(base + w.hbuf_off);
+            wa.hexp = reinterpret_cast<int32_t*>(base + w.hexp_off);
+            wa.task_rows = reinterpret_cast<int2*>(base + w.trows_off);
+            wa.partial = partial;
+            wa.slots = slots; wa.f = L->s.f;
+            FLOE_LAUNCH(FLOE_KERNEL_GATE_DOWN, st, launch_gate_down_wide(wa, w.wp, mask, L->s.d, st));
+            FLOE_LAUNCH(FLOE_KERNEL_COMBINE, st, launch_combine_wide(wa, w.wp, L->s.d, T, nullptr, reinterpret_cast<h16*>(y), st));
+            if (stats)
+                FLOE_HIP(launch_stats(task_expert, count, 0, task_weight, reinterpret_cast<SlotStat*>(stats), w.n_tasks, st));
+            return FLOE_OK;
+        }
         UnionArgs ua{};
         ua.table = static_cast<const DevExpert*>(L->dev_table);
         ua.groups = groups; ua.n_groups = n_groups; ua.x = xh; ua.v = v; ua.mask_words = mask;
         ua.task_scale = task_weight; ua.count = count; ua.partial = partial;
-        ua.urow = reinterpret_cast<int32_t*>(base + w.urow_off);
-        ua.ucount = reinterpret_cast<int32_t*>(base + w.ucount_off);
-        ua.hbuf = reinterpret_cast<uint4*>(base + w.hbuf_off);
-        ua.slots = slots; ua.f = L->s.f; ua.nt = w.up.nt; ua.cap = w.up.cap;
-        ua.nblk_gate = w.up.nblk_gate; ua.nblk_down = w.up.nblk_down;
+        ua.slots = slots; ua.f = L->s.f; ua.cap = w.up.cap; ua.nblk = w.up.nblk;
         FLOE_LAUNCH(FLOE_KERNEL_GATE_DOWN, st, launch_gate_down_union(ua, w.up, L->s.d, st));
-        nblk = w.up.nblk_down;
-        count_parts = w.up.nblk_gate;
+        nblk = w.up.nblk;
+        count_parts = w.up.nblk;
     } else if (mask_ok && !batch_mfma &&
                route_in_place_ok(L->s.d, L->s.bits, L->s.group, L->n_experts, L->top_k, L->n_shared)) {
         // larger batches of shapes without a matrix-core path: [router + up GEMV + mask] -> [compaction + gate/down]

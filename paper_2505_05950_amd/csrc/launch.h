@@ -115,8 +115,11 @@ inline bool mfma_batch_pays(int n_all, int n_tasks, int bits) {
     if (mode == 2) return false;
     return bits == 3 ? 2 * n_tasks >= 7 * n_all : n_tasks >= 2 * n_all;
 }
+struct WideGroup;
+// wide (optional, with order): the same tasks cut into as few groups of at most wide_chunk as possible, of equal size per expert
 hipError_t launch_group_tokens(const int32_t* task_expert, int n_tasks, int n_all, int chunk, TokenGroup* groups,
-                               int32_t* n_groups, hipStream_t stream, int32_t* order = nullptr);
+                               int32_t* n_groups, hipStream_t stream, int32_t* order = nullptr, int wide_chunk = 0,
+                               WideGroup* wide = nullptr, int32_t* n_wide = nullptr);
 hipError_t launch_up_gemv_grouped(const DevExpert* table, const TokenGroup* groups, const int32_t* n_groups,
                                   int max_groups, int chunk, const h16* x, int slots, float* v, const float* task_tau,
                                   uint32_t* mask_words, int d, int f, int bits, int group, hipStream_t stream);
@@ -135,20 +138,18 @@ hipError_t launch_gate_down(const TaskMap& map, const h16* staged, int gd_rows, 
                             float* partial, int d, int f, int n_tasks, int nblk, hipStream_t stream,
                             const int32_t* rows = nullptr, const int32_t* order = nullptr);
 
-// S4 + S5 for decode batches on the matrix cores, one read of every row that any token of an expert group selected
-// (gate_down_union.hip).  The groups are those of launch_group_tokens; mask_words / v come from the GEMV kernels.
+// S4 + S5 for decode batches, one read of every row that any token of an expert group selected, staged through an LDS ring
+// (gate_down_union.hip, union_mode 2).  The groups are those of launch_group_tokens; mask_words / v come from the GEMV kernels.
 struct UnionPlan {
-    int nblk_gate, nblk_down;  // channel blocks of the gate kernel; the down kernel takes nblk_gate / nblk_down of them each
-    int cap;                   // rows a gate block can hold (a multiple of 16)
-    int nt;                    // token rows kept in LDS: 8 or 16 (the group chunk)
+    int nblk;                  // channel blocks per group
+    int cap;                   // rows a block can hold (a multiple of 16)
     int max_groups;
-    bool matrix_cores, fused;  // which kernels run (union_mode)
 };
 constexpr int kStageWorkgroupsDefault = 32;  // 128 waves x 4 KiB in flight: the link is full, a GEMV beside it keeps most of its speed
 int stage_workgroups();
 void set_stage_workgroups(int n);  // 0 = default
 int union_mode();
-int union_kernels_for(int n_all, int n_tasks);  // 1 matrix cores, 2 LDS ring, 3 one-token kernels in expert order
+int union_kernels_for(int n_all, int n_tasks, int d, int f);  // 1 matrix cores (wide groups), 2 LDS ring, 3 one-token kernels in expert order
 void set_union_mode(int m);
 struct UnionArgs {
     const DevExpert* table;
@@ -158,16 +159,49 @@ struct UnionArgs {
     const float* v;               // [n_tasks][f]
     const uint32_t* mask_words;   // [n_tasks][words]
     const float* task_scale;      // [n_tasks] or nullptr
-    int32_t* count;               // [n_tasks][nblk_gate] selected channels per (task, gate block), or nullptr
-    float* partial;               // [n_tasks][nblk_down][d]
-    int32_t* urow;                // [max_groups][nblk_gate][cap] union rows, ascending
-    int32_t* ucount;              // [max_groups][nblk_gate]
-    uint4* hbuf;                  // [max_groups][nblk_gate][cap / 16][64] h fragments (hi, lo) in lane order
-    int32_t slots, f, nt, cap, nblk_gate, nblk_down;
+    int32_t* count;               // [n_tasks][nblk] selected channels per (task, block), or nullptr
+    float* partial;               // [n_tasks][nblk][d]
+    int32_t slots, f, cap, nblk;
 };
 UnionPlan union_plan(int d, int f, int n_tasks, int n_all, int chunk);
 bool union_shape_ok(int d, int f, const UnionPlan& p);
 hipError_t launch_gate_down_union(const UnionArgs& a, const UnionPlan& p, int d, hipStream_t stream);
+// Expected number of groups of `chunk` tokens when each of T tokens goes to top_k of n_experts experts uniformly
+double expected_token_groups(int n_experts, int T, int top_k, int chunk);
+
+// S4 + S5 on the matrix cores for batches in which experts see many tokens (wide_batch.hip): groups of up to 16 * nt tokens.
+struct WideGroup {
+    int32_t expert, n, first;  // tasks order[first .. first + n)
+};
+
+constexpr int kWideMaxMaskWords = 2048;  // f <= 65536
+struct WidePlan {
+    int nt, chunk, max_groups, est_groups;
+    int pairs;              // pairs of 16-row tiles an expert can have
+    int wg_gate, wg_down;   // workgroups (the down kernel: per 512 output columns)
+    size_t partial_rows;    // rows of d floats
+};
+struct WideArgs {
+    const DevExpert* table;
+    const WideGroup* groups;
+    const int32_t* n_groups;
+    const int32_t* order;     // [n_tasks] tasks sorted by expert
+    const h16* x;
+    const float* v;           // [n_tasks][f]
+    const float* task_tau;    // [n_tasks]
+    const float* task_scale;  // [n_tasks] or nullptr
+    int32_t* count;           // [n_tasks] selected channels
+    int32_t* urow;            // [max_groups][f] union rows, ascending
+    int32_t* ucount;          // [max_groups]
+    uint4* hbuf;              // [max_groups][pairs][nt][2][64] h (hi, lo) in lane order
+    int32_t* hexp;            // [max_groups][pairs] power of two the pair's h was divided by
+    int2* task_rows;          // [n_tasks] first partial row, number of partial rows (chunk rows apart)
+    float* partial;           // [partial_rows][d]
+    int32_t slots, f;
+};
+WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared);
+hipError_t launch_gate_down_wide(const WideArgs& a, const WidePlan& p, const uint32_t* mask_words, int d, hipStream_t stream);
+hipError_t launch_combine_wide(const WideArgs& a, const WidePlan& p, int d, int T, float* y_acc, h16* y_half, hipStream_t stream);
 
 // The other sparsification candidates of Sec. 3.2.1 (variants.hip): act = a_gate (which = 1) or a_down (which = 2) and
 // h = a_gate * a_up for every channel; then the down rows of the kept channels only.

@@ -473,7 +473,9 @@ __global__ __launch_bounds__(kMfmaThreads, BITS == 3 ? 4 : 1) void up_gemv_mfma_
 // ---------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(1024) void group_tokens_kernel(const int32_t* __restrict__ task_expert, int n_tasks,
                                                             int n_all, int chunk, TokenGroup* __restrict__ groups,
-                                                            int32_t* __restrict__ n_groups, int32_t* __restrict__ order) {
+                                                            int32_t* __restrict__ n_groups, int32_t* __restrict__ order,
+                                                            int wide_chunk, WideGroup* __restrict__ wide,
+                                                            int32_t* __restrict__ n_wide) {
     // A thread per task, 1024 tasks (16 waves of 64) at a time.  A task's place in its expert's list is
     //   (tasks of that expert in earlier tiles) + (in earlier waves of this tile) + (in lower lanes of this wave),
     // the last found by ballots over the distinct experts of the wave.  Every wave then stores its 64 tasks with two
@@ -484,6 +486,7 @@ __global__ __launch_bounds__(1024) void group_tokens_kernel(const int32_t* __res
     constexpr int kMaxExperts = 1024 + 64;  // 1024 routed + 64 shared
     __shared__ int first_group[kMaxExperts + 1];
     __shared__ int first_task[kMaxExperts + 1];  // tasks of the experts before this one (for `order`)
+    __shared__ int first_wide[kMaxExperts + 1];
     __shared__ int count[kMaxExperts];           // tasks per expert; in pass 2 the tasks placed by earlier tiles
     __shared__ __align__(16) uint8_t in_wave[kWaves][kMaxExperts];  // tasks of an expert inside one wave's 64 tasks of the tile
     const int tid = threadIdx.x;
@@ -503,30 +506,38 @@ __global__ __launch_bounds__(1024) void group_tokens_kernel(const int32_t* __res
         if (mine >= 0) atomicAdd(&count[mine], 1);  // integer adds in LDS: the order does not matter
     }
     __syncthreads();
-    for (int e = tid; e < n_all; e += kTile) first_group[e + 1] = (count[e] + chunk - 1) / chunk;
+    for (int e = tid; e < n_all; e += kTile) {
+        first_group[e + 1] = (count[e] + chunk - 1) / chunk;
+        first_wide[e + 1] = wide ? (count[e] + wide_chunk - 1) / wide_chunk : 0;
+    }
     __syncthreads();
     if (wave == 0) {  // prefix sums over the experts, 64 at a time
-        int run_g = 0, run_t = 0;
+        int run_g = 0, run_t = 0, run_w = 0;
         for (int e0 = 0; e0 < n_all; e0 += kWave) {
             const int e = e0 + lane;
             int sg = e < n_all ? first_group[e + 1] : 0;
             int st = e < n_all ? count[e] : 0;
+            int sw = e < n_all ? first_wide[e + 1] : 0;
 #pragma unroll
             for (int o = 1; o < kWave; o <<= 1) {
-                const int ug = __shfl_up(sg, o, kWave), ut = __shfl_up(st, o, kWave);
-                if (lane >= o) { sg += ug; st += ut; }
+                const int ug = __shfl_up(sg, o, kWave), ut = __shfl_up(st, o, kWave), uw = __shfl_up(sw, o, kWave);
+                if (lane >= o) { sg += ug; st += ut; sw += uw; }
             }
             if (e < n_all) {
                 first_group[e + 1] = run_g + sg;
                 first_task[e + 1] = run_t + st;
+                first_wide[e + 1] = run_w + sw;
             }
+            run_w += __shfl(sw, kWave - 1, kWave);
             run_g += __shfl(sg, kWave - 1, kWave);
             run_t += __shfl(st, kWave - 1, kWave);
         }
         if (lane == 0) {
             first_group[0] = 0;
             first_task[0] = 0;
+            first_wide[0] = 0;
             n_groups[0] = run_g;
+            if (wide) n_wide[0] = run_w;
         }
     }
     __syncthreads();
@@ -536,6 +547,15 @@ __global__ __launch_bounds__(1024) void group_tokens_kernel(const int32_t* __res
         for (int g = 0; g < ng; ++g) {
             groups[g0 + g].expert = e;
             groups[g0 + g].n = min(chunk, c - g * chunk);
+        }
+        if (wide) {
+            const int w0 = first_wide[e], nw = first_wide[e + 1] - w0;
+            const int len = nw ? (c + nw - 1) / nw : 0;  // equal sizes
+            for (int g = 0; g < nw; ++g) {
+                wide[w0 + g].expert = e;
+                wide[w0 + g].n = min(len, c - g * len);
+                wide[w0 + g].first = first_task[e] + g * len;
+            }
         }
         count[e] = 0;
     }
@@ -587,8 +607,10 @@ extern "C" int floe_debug_set_timeline_mfma(unsigned long long* p) {
 #endif
 
 hipError_t launch_group_tokens(const int32_t* task_expert, int n_tasks, int n_all, int chunk, TokenGroup* groups,
-                               int32_t* n_groups, hipStream_t stream, int32_t* order) {
-    group_tokens_kernel<<<dim3(1), dim3(1024), 0, stream>>>(task_expert, n_tasks, n_all, chunk, groups, n_groups, order);
+                               int32_t* n_groups, hipStream_t stream, int32_t* order, int wide_chunk, WideGroup* wide,
+                               int32_t* n_wide) {
+    group_tokens_kernel<<<dim3(1), dim3(1024), 0, stream>>>(task_expert, n_tasks, n_all, chunk, groups, n_groups, order,
+                                                            wide_chunk, wide, n_wide);
     return hipGetLastError();
 }
 

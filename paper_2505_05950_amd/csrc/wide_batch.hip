@@ -1,0 +1,668 @@
+// S4 + S5 for batches in which an expert sees many tokens (Alg. 1 steps 4-5; the paper itself is batch-1, each token keeps
+// its own threshold, mask and result).  The tokens of an expert form groups of up to 16 * NT (NT token tiles of the matrix
+// instruction); every row that any token of a group selected is read once for the whole group.
+//
+//   wide_rows_kernel   per group: ascending list of the union of the tokens' selected channels (from the mask bits), the
+//                      selected counts of its tasks.
+//   gate_wide_kernel   A[row][token] = gate_row . x_token.  A wave takes a pair of 16-row tiles; the rows stream from memory
+//                      straight into the registers that feed the matrix cores (two slices of 128 columns in flight, 16 KB
+//                      per wave), the group's activations pass through LDS in slices of 128 columns shared by the eight
+//                      waves.  h = SiLU(A) * v * weight where |v| > tau, else 0, leaves as two fp16 numbers (h = hi + lo)
+//                      in the lane order of the down kernel's operand.
+//   down_wide_kernel   Y[token][col] += h[token][row] * down[row][col].  A workgroup owns 512 output columns and a range of
+//                      row pairs; a lane fetches 8-byte pieces of eight rows per pair (four pairs in flight), a register
+//                      transpose (v_perm_b32) makes the operand, h passes through LDS.
+//   combine_wide       adds a task's partial results.
+//
+// Division of work: the row pairs of all groups form one sequence; the workgroups cut it into equal pieces, whatever the
+// routing did to the group sizes, so the launch is one even round and no compute unit waits for a crowded expert.
+//
+// What bounds it: the bytes a compute unit pulls in - rows, activations (gate) and h (down) - at 5.3 to 6.9 TB/s over the
+// chip; without its matrix instructions the gate kernel takes 254 us where it takes 286 with them.  Hence groups as large
+// as the accumulators allow (a second group reads the rows again), and rows requested two slices ahead.  Measured, gate +
+// down, 8 experts d 4096 f 14336 at 90 %: 64 tokens 364 -> 293 us (groups of at most 16 tokens before, half of the experts
+// read twice), 512 tokens 2425 (a workgroup set per task) -> 565 us.
+
+#include "floe_dev.h"
+#include "launch.h"
+
+namespace floe {
+
+typedef _Float16 h16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kWideWaves = 8;
+constexpr int kWideThreads = kWideWaves * 64;
+constexpr int kPairRows = 32;    // two tiles of 16 rows: one k-step of the down kernel's matrix instruction
+constexpr int kSliceCols = 128;  // columns of x that sit in LDS at a time
+constexpr int kDownCols = 512;   // output columns per workgroup of the down kernel (64 per wave)
+
+// pairs of union rows of group g
+__device__ __forceinline__ int wide_pairs(const int32_t* ucount, int g) { return (ucount[g] + kPairRows - 1) / kPairRows; }
+
+__device__ __forceinline__ int wave_inclusive_scan(int x, int lane) {
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int up = __shfl_up(x, o, kWave);
+        if (lane >= o) x += up;
+    }
+    return x;
+}
+__device__ __forceinline__ int wide_total(const WideArgs& a, int ng, int lane) {
+    int total = 0;
+    for (int g0 = 0; g0 < ng; g0 += kWave) {
+        const int p = g0 + lane < ng ? wide_pairs(a.ucount, g0 + lane) : 0;
+        total += __builtin_amdgcn_readlane(wave_inclusive_scan(p, lane), kWave - 1);
+    }
+    return total;
+}
+// a pointer that every lane holds alike, as a scalar (loads then take it as their base and a 32-bit offset per lane)
+__device__ __forceinline__ const unsigned char* scalar_ptr(const void* p) {
+    const uint64_t u = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+    return (const unsigned char*)(((uint64_t)hi << 32) | lo);
+}
+// the group that holds pair `pos` of the sequence (pos < total) and the position of its first pair; every lane the same
+__device__ __forceinline__ void wide_find(const WideArgs& a, int ng, int lane, int pos, int& g, int& base) {
+    int run = 0;
+    for (int g0 = 0; g0 < ng; g0 += kWave) {
+        const int p = g0 + lane < ng ? wide_pairs(a.ucount, g0 + lane) : 0;
+        const int inc = wave_inclusive_scan(p, lane);
+        const unsigned long long past = __ballot(run + inc > pos);
+        if (past) {
+            const int l = __ffsll((long long)past) - 1;
+            g = g0 + l;
+            base = run + __builtin_amdgcn_readlane(inc - p, l);
+            return;
+        }
+        run += __builtin_amdgcn_readlane(inc, kWave - 1);
+    }
+    g = ng - 1;  // not reached for pos < total
+    base = pos;
+}
+// piece w of W equal pieces starts at pair floor(total * w / W); pair p therefore belongs to piece ((p + 1) * W - 1) / total
+__device__ __forceinline__ int wide_cut(int total, int W, int w) { return (int)((long long)total * w / W); }
+__device__ __forceinline__ int wide_owner(int total, int W, int p) { return (int)(((long long)(p + 1) * W - 1) / total); }
+
+// Workgroups go to the eight XCDs in turn.  Neighbouring pieces run on one XCD, so that its L2 holds the activations of few
+// groups, and the groups of one expert, which read the same rows, are next to each other.
+__device__ __forceinline__ int wide_piece(int W) {
+    const int b = blockIdx.x;
+    return (W & 7) ? b : (b & 7) * (W >> 3) + (b >> 3);
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// union lists
+// ---------------------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(1024) void wide_rows_kernel(WideArgs a, const uint32_t* __restrict__ mask_words) {
+    constexpr int kWaves = 16;
+    __shared__ uint32_t u[kWideMaxMaskWords];
+    __shared__ int before[kWideMaxMaskWords];
+    __shared__ int wave_tot[kWaves];
+    const int g = blockIdx.x;
+    if (g >= a.n_groups[0]) return;  // the grid is sized for the worst case
+    const WideGroup grp = a.groups[g];
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int nwords = mask_words_per_task(a.f);
+    for (int w = tid; w < nwords; w += 1024) u[w] = 0u;
+    __syncthreads();
+    for (int i = wave; i < grp.n; i += kWaves) {  // a wave per task
+        const int task = a.order[grp.first + i];
+        const uint32_t* mw = mask_words + (size_t)task * nwords;
+        int c = 0;
+        for (int w0 = lane; w0 < nwords; w0 += 8 * kWave) {
+            uint32_t m[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) m[q] = w0 + q * kWave < nwords ? mw[w0 + q * kWave] : 0u;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                c += __popc(m[q]);
+                if (m[q]) atomicOr(&u[w0 + q * kWave], m[q]);
+            }
+        }
+        c = __builtin_amdgcn_readlane(wave_inclusive_scan(c, lane), kWave - 1);
+        if (lane == 0) {
+            a.count[task] = c;
+            a.task_rows[task] = make_int2(0, 0);  // filled in by the down kernel unless the group has no rows at all
+        }
+    }
+    __syncthreads();
+    // exclusive prefix of the words' populations; a thread owns two consecutive words
+    const int w2 = 2 * tid;
+    const int c0 = w2 < nwords ? __popc(u[w2]) : 0, c1 = w2 + 1 < nwords ? __popc(u[w2 + 1]) : 0;
+    const int inc = wave_inclusive_scan(c0 + c1, lane);
+    if (lane == kWave - 1) wave_tot[wave] = inc;
+    __syncthreads();
+    int run = inc - c0 - c1, all = 0;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        run += w < wave ? wave_tot[w] : 0;
+        all += wave_tot[w];
+    }
+    if (w2 < nwords) before[w2] = run;
+    if (w2 + 1 < nwords) before[w2 + 1] = run + c0;
+    if (tid == 0) a.ucount[g] = all;
+    __syncthreads();
+    int32_t* out = a.urow + (size_t)g * a.f;
+    for (int w0 = 2 * wave; w0 < nwords; w0 += 2 * kWaves) {  // two words per wave, a lane per bit
+        const int w = w0 + (lane >> 5), b = lane & 31;
+        if (w < nwords) {
+            const uint32_t m = u[w];
+            if ((m >> b) & 1u) out[before[w] + __popc(m & ((1u << b) - 1u))] = w * 32 + b;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// gate
+// ---------------------------------------------------------------------------------------------------------------
+template <int NT>
+__global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int d) {
+    constexpr int kTok = 16 * NT;
+    constexpr int kTokRound = kWideWaves * 4;  // x pieces (16 bytes) of a slice: kTokRound tokens x 16 pieces per round
+    constexpr int kRounds = (kTok + kTokRound - 1) / kTokRound;
+    constexpr int kSteps = kSliceCols / 32;
+    __shared__ uint4 xs[2][kTok * 16];  // [token][16 pieces], piece p of token t at position p ^ (t & 15)
+    __shared__ int s_task[kTok];
+    __shared__ float s_w[kTok], s_tau[kTok];
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int l16 = lane & 15, q4 = lane >> 4;
+    const int ng = a.n_groups[0];
+    const int total = wide_total(a, ng, lane);
+    const int W = gridDim.x, piece = wide_piece(W);
+    int pos = wide_cut(total, W, piece);
+    const int end = wide_cut(total, W, piece + 1);
+    const int ns = d / kSliceCols;  // a multiple of four (d % 512 == 0)
+    const int pmax = (a.f + kPairRows - 1) / kPairRows;
+
+    while (pos < end) {  // one group's part of this workgroup's piece at a time
+        int g, base;
+        wide_find(a, ng, lane, pos, g, base);
+        g = __builtin_amdgcn_readfirstlane(g);
+        base = __builtin_amdgcn_readfirstlane(base);
+        const WideGroup grp = a.groups[g];
+        const int count = a.ucount[g];
+        const int32_t* rows = a.urow + (size_t)g * a.f;
+        const unsigned char* gd = scalar_ptr(a.table[grp.expert].gd);
+        const int seg0 = pos - base, seg1 = min((count + kPairRows - 1) / kPairRows, end - base);
+        pos = base + seg1;
+        __syncthreads();  // the previous group's task arrays are no longer read
+        if (tid < kTok) {
+            const int task = a.order[grp.first + (tid < grp.n ? tid : 0)];  // dead token rows repeat the first one
+            s_task[tid] = task;
+            s_w[tid] = a.task_scale ? a.task_scale[task] : 1.0f;
+            s_tau[tid] = a.task_tau[task];
+        }
+        __syncthreads();
+        const h16* xp[kRounds];
+#pragma unroll
+        for (int r = 0; r < kRounds; ++r) {
+            const int tok = (tid >> 4) + kTokRound * r;
+            xp[r] = a.x + (size_t)(s_task[tok < kTok ? tok : 0] / a.slots) * d + (tid & 15) * 8;
+        }
+        // Workgroups start at different column slices: rows are 4 d bytes apart, so workgroups that walk the columns in step
+        // ask for the same few memory channels at the same time.  (Two groups of one expert that work on the same rows
+        // start alike and share them through the L2.)
+        const int rot = (int)((unsigned)(seg0 / 8) * 5u % (unsigned)ns);
+        auto col_slice = [&](int s) {  // s-th slice of this workgroup (past the last one: the last one again)
+            const int c = min(s, ns - 1) + rot;
+            return c < ns ? c : c - ns;
+        };
+        // equal passes of at most one pair per wave
+        const int len = seg1 - seg0;
+        const int np = (len + kWideWaves - 1) / kWideWaves;
+        const int per = (len + np - 1) / np;
+        for (int p0 = seg0; p0 < seg1; p0 += per) {
+            const int pair = p0 + wave;
+            const bool active = wave < per && pair < seg1;  // the others only help to bring x in
+            uint32_t wo[2];  // byte offsets from gd: at most f * 4 d <= 2^31
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int k = min(pair * kPairRows + 16 * t + l16, count - 1);  // rows past the end repeat the last one
+                wo[t] = (uint32_t)rows[k] * (uint32_t)(4 * d) + 16 * q4;
+            }
+            f32x4 acc[2][NT];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int n = 0; n < NT; ++n) acc[t][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+            uint4 xq[kRounds];
+            uint4 wq[2][2][kSteps];
+            // (every request below is unconditional - past the end it repeats the last slice - so that the compiler can count
+            // what is in flight: behind a conditional load it waits for everything)
+            auto load_x = [&](int s) {
+#pragma unroll
+                for (int r = 0; r < kRounds; ++r) xq[r] = gload16(xp[r] + col_slice(s) * kSliceCols);
+            };
+            auto store_x = [&](int buf) {
+#pragma unroll
+                for (int r = 0; r < kRounds; ++r) {
+                    const int tok = (tid >> 4) + kTokRound * r;
+                    if (tok < kTok) xs[buf][tok * 16 + ((tid & 15) ^ (tok & 15))] = xq[r];
+                }
+            };
+            auto load_w = [&](uint4 (&w)[2][kSteps], int s, int c) {  // k-steps 2 c and 2 c + 1 of slice s: both halves of a line
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int hf = 0; hf < 2; ++hf)
+                        w[t][2 * c + hf] = gload16(gd + (wo[t] + (uint32_t)(col_slice(s) * (2 * kSliceCols) + 128 * c + 64 * hf)));
+            };
+            load_x(0);
+            if (!active) {  // x only; the same barriers as the waves below
+                store_x(0);
+                load_x(1);
+                __syncthreads();
+                for (int s = 0; s < ns; ++s) {
+                    store_x((s & 1) ^ 1);
+                    load_x(s + 2);
+                    __syncthreads();
+                }
+                continue;
+            }
+            load_w(wq[0], 0, 0);
+            load_w(wq[0], 0, 1);
+            __builtin_amdgcn_sched_barrier(0);  // the waits of the loop count the requests in this order
+            store_x(0);
+            load_x(1);
+            __builtin_amdgcn_sched_barrier(0);
+            load_w(wq[1], 1, 0);
+            load_w(wq[1], 1, 1);
+            __syncthreads();
+            auto slice = [&](int s, uint4 (&w)[2][kSteps], int buf) {
+                store_x(buf ^ 1);
+                load_x(s + 2);
+#pragma unroll
+                for (int c = 0; c < kSteps / 2; ++c) {
+#pragma unroll
+                    for (int ks = 2 * c; ks < 2 * c + 2; ++ks)
+#pragma unroll
+                        for (int n = 0; n < NT; ++n) {
+                            const uint4 xf = xs[buf][(16 * n + l16) * 16 + ((4 * ks + q4) ^ l16)];
+#pragma unroll
+                            for (int t = 0; t < 2; ++t)
+                                acc[t][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h16x8, w[t][ks]),
+                                                                                   __builtin_bit_cast(h16x8, xf), acc[t][n], 0, 0, 0);
+                        }
+                    load_w(w, s + 2, c);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                __syncthreads();
+            };
+#pragma unroll 1
+            for (int s = 0; s < ns; s += 2) {
+                slice(s, wq[0], 0);
+                slice(s + 1, wq[1], 1);
+            }
+            // lane (l16, q4) holds A[row 16 t + 4 q4 + i][token 16 n + l16]
+            int row[2][4];
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int k = pair * kPairRows + 16 * t + 4 * q4 + i;
+                    row[t][i] = k < count ? rows[k] : -1;
+                }
+            int tok0 = l16;
+            asm volatile("" : "+v"(tok0));  // or the addresses below are formed ahead of the loop and held across it
+            bool big = false;
+            constexpr int kBatch = NT < 4 ? NT : 4;  // token tiles whose v are requested together
+#pragma unroll
+            for (int n0 = 0; n0 < NT; n0 += kBatch) {
+                float vv[kBatch][2][4];
+#pragma unroll
+                for (int n = n0; n < n0 + kBatch && n < NT; ++n) {
+                    const unsigned char* vt = reinterpret_cast<const unsigned char*>(a.v + (size_t)s_task[16 * n + tok0] * a.f);
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) vv[n - n0][t][i] = gloadf(vt + 4 * max(row[t][i], 0));
+                }
+#pragma unroll
+                for (int n = n0; n < n0 + kBatch && n < NT; ++n) {
+                    const float w = s_w[16 * n + tok0], tau = s_tau[16 * n + tok0];
+                    const bool live = 16 * n + tok0 < grp.n;
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const float v = vv[n - n0][t][i];
+                            const bool keep = live && row[t][i] >= 0 && fabsf(v) > tau;
+                            const float h = keep ? silu(acc[t][n][i]) * v * w : 0.0f;
+                            big |= !(fabsf(h) <= 32768.0f);
+                            acc[t][n][i] = h;
+                        }
+                }
+            }
+            // h beyond fp16's range: the pair is stored scaled down by a power of two, which the down kernel undoes
+            int e = 0;
+            if (__ballot(big)) {
+                float m = 0.0f;
+#pragma unroll
+                for (int n = 0; n < NT; ++n)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const float h = fabsf(acc[t][n][i]);
+                            m = h < 3.0e38f ? fmaxf(m, h) : m;
+                        }
+                m = wave_allreduce_max_nonneg(m);
+                e = m > 32768.0f ? ilogbf(m) - 14 : 0;
+            }
+            const float sc = ldexpf(1.0f, -e);
+            uint4* hb = a.hbuf + ((size_t)g * pmax + pair) * (NT * 128) + lane;
+#pragma unroll
+            for (int n = 0; n < NT; ++n) {
+                uint32_t hi[4], lo[4];
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        h16 hh[2], hl[2];
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) {
+                            const float h = acc[t][n][2 * p + i] * sc;
+                            hh[i] = (h16)h;
+                            hl[i] = fabsf(h) <= 65504.0f ? (h16)(h - (float)hh[i]) : (h16)0.0f;  // infinite or NaN: hi says it all
+                        }
+                        hi[2 * t + p] = as_u32(h16x2{hh[0], hh[1]});
+                        lo[2 * t + p] = as_u32(h16x2{hl[0], hl[1]});
+                    }
+                hb[n * 128] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+                hb[n * 128 + 64] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+            }
+            if (lane == 0) a.hexp[(size_t)g * pmax + pair] = e;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// down
+// ---------------------------------------------------------------------------------------------------------------
+// The h of SL pairs sits in LDS at a time; the rows of the next slice are in flight (four pairs, 16 KB per wave; two where
+// the accumulators of ten token tiles need the registers).
+template <int NT>
+__global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int d) {
+    constexpr int SL = NT <= 5 ? 4 : 2;
+    constexpr int kTok = 16 * NT;
+    constexpr int kRing = 4;                              // slices of row ids kept
+    constexpr int kHRounds = SL * NT * 128 / kWideThreads;
+    static_assert(SL * NT * 128 % kWideThreads == 0, "slice split");
+    __shared__ uint4 hs[2][SL * NT * 128];
+    __shared__ __align__(16) int ids[kRing][SL * kPairRows];
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int l16 = lane & 15, q4 = lane >> 4;
+    const int ng = a.n_groups[0];
+    const int total = wide_total(a, ng, lane);
+    // no more pieces than the actual rows fill with four pairs each: every piece up to the last one holds some rows, so the
+    // pieces of a group are consecutive and all of them write a partial result
+    const int W = min((int)gridDim.x, (total + 3) / 4), piece = wide_piece(gridDim.x);
+    if (piece >= W) return;
+    int pos = wide_cut(total, W, piece);
+    const int end = wide_cut(total, W, piece + 1);
+    const int pmax = (a.f + kPairRows - 1) / kPairRows;
+    const int col = blockIdx.y * kDownCols + wave * 64 + 4 * l16;  // this lane's four columns (d % 512 == 0)
+
+    while (pos < end) {
+        int g, base;
+        wide_find(a, ng, lane, pos, g, base);
+        g = __builtin_amdgcn_readfirstlane(g);
+        base = __builtin_amdgcn_readfirstlane(base);
+        const WideGroup grp = a.groups[g];
+        const int count = a.ucount[g];
+        const int32_t* rows = a.urow + (size_t)g * a.f;
+        const unsigned char* gd = scalar_ptr(a.table[grp.expert].gd);
+        const uint32_t dcol = 2 * (uint32_t)(d + col);
+        const int npairs = (count + kPairRows - 1) / kPairRows;
+        const int seg0 = pos - base, seg1 = min(npairs, end - base);
+        const int len = seg1 - seg0;
+        pos = base + seg1;
+        const int w_first = wide_owner(total, W, base);
+        if (piece == w_first && blockIdx.y == 0) {  // where a task's partial results are
+            const int slots = wide_owner(total, W, base + npairs - 1) - w_first + 1;
+            if (tid < grp.n) a.task_rows[a.order[grp.first + tid]] = make_int2(grp.first + tid + w_first * kTok, slots);
+        }
+        const unsigned char* hsrc = scalar_ptr(a.hbuf + ((size_t)g * pmax + seg0) * (NT * 128));
+        const int32_t* esrc = a.hexp + (size_t)g * pmax + seg0;
+        const int ns = (len + SL - 1) / SL;
+        uint4 hq[kHRounds];
+        int idq = 0, exq = 0;
+        // (requests are unconditional, as in the gate kernel: past the end they repeat a valid entry and the value is
+        // replaced by zero on its way into LDS)
+        auto load_h = [&](int s) {  // h (and exponents) of slice s
+#pragma unroll
+            for (int r = 0; r < kHRounds; ++r) {
+                const int i = tid + r * kWideThreads;
+                const int pr = min(s * SL + i / (NT * 128), len - 1);
+                hq[r] = gload16(hsrc + (uint32_t)(pr * (NT * 128) + i % (NT * 128)) * 16u);
+            }
+            exq = (int)gload4(esrc + min(s * SL + (tid & (SL - 1)), len - 1));
+        };
+        // Into LDS; returns the power of two the slice's h stand divided by (never less than e_now).  It is 0, and so is
+        // every pair's, unless some h left fp16's range.
+        auto store_h = [&](int s, int e_now) {
+            const int e_mine = s * SL + (tid & (SL - 1)) < len ? exq : e_now;
+            int e = e_now;
+            if (__builtin_expect(__ballot(e_mine != e_now) != 0ull, 0)) {
+                int m = max(e_mine, e_now);
+#pragma unroll
+                for (int o = 1; o < SL; o <<= 1) m = max(m, __shfl_xor(m, o, kWave));
+                e = __builtin_amdgcn_readfirstlane(m);
+#pragma unroll
+                for (int r = 0; r < kHRounds; ++r) {
+                    const int pr = (tid + r * kWideThreads) / (NT * 128);
+                    const h16 f = (h16)ldexpf(1.0f, __shfl(e_mine, pr, kWave) - e);  // (0 below 2^-24: beneath fp32 next to e)
+                    const h16x2 f2 = {f, f};
+                    hq[r].x = as_u32(as_h2(hq[r].x) * f2); hq[r].y = as_u32(as_h2(hq[r].y) * f2);
+                    hq[r].z = as_u32(as_h2(hq[r].z) * f2); hq[r].w = as_u32(as_h2(hq[r].w) * f2);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < kHRounds; ++r) {
+                const int i = tid + r * kWideThreads;
+                const bool live = s * SL + i / (NT * 128) < len;
+                hs[s & 1][i] = live ? hq[r] : make_uint4(0u, 0u, 0u, 0u);
+            }
+            return e;
+        };
+        auto load_ids = [&](int s) {
+            idq = (int)gload4(rows + min((seg0 + s * SL) * kPairRows + (tid & (SL * kPairRows - 1)), count - 1));
+        };
+        auto store_ids = [&](int s) {
+            if (tid < SL * kPairRows) ids[s & (kRing - 1)][tid] = idq;
+        };
+        uint2 dq[SL][8];
+        auto load_d = [&](uint2 (&q)[8], int s, int p) {
+            const int4 r0 = *reinterpret_cast<const int4*>(&ids[s & (kRing - 1)][p * kPairRows + 4 * q4]);
+            const int4 r1 = *reinterpret_cast<const int4*>(&ids[s & (kRing - 1)][p * kPairRows + 16 + 4 * q4]);
+            const int r[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
+#pragma unroll
+            for (int k = 0; k < 8; ++k) q[k] = gload8(gd + ((uint32_t)r[k] * (uint32_t)(4 * d) + dcol));
+        };
+        f32x4 acc[4][NT];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int n = 0; n < NT; ++n) acc[j][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        int e_acc = 0;
+
+        __syncthreads();  // the previous group's LDS contents are no longer read
+        load_ids(0);
+        load_h(0);
+        store_ids(0);
+        load_ids(1);
+        int e_next = store_h(0, 0);
+        e_acc = e_next;
+        store_ids(1);
+        __syncthreads();
+#pragma unroll
+        for (int p = 0; p < SL; ++p) {
+            load_d(dq[p], 0, p);
+            __builtin_amdgcn_sched_barrier(0);  // the waits of the loop count the requests in this order
+        }
+#pragma unroll 1
+        for (int s = 0; s < ns; ++s) {
+            const int buf = s & 1;
+            {   // 1 unless h left fp16's range in this slice (multiplied always: a branch here doubles the accumulators' registers)
+                const float m = ldexpf(1.0f, e_acc - e_next);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+#pragma unroll
+                    for (int n = 0; n < NT; ++n) acc[j][n] *= m;
+                e_acc = e_next;
+            }
+            load_h(s + 1);
+            load_ids(s + 2);
+#pragma unroll
+            for (int p = 0; p < SL; ++p) {
+                uint32_t b[4][4];  // operand of column j: rows 0..7 of this lane's quarter
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    b[0][k] = __builtin_amdgcn_perm(dq[p][2 * k + 1].x, dq[p][2 * k].x, 0x05040100u);
+                    b[1][k] = __builtin_amdgcn_perm(dq[p][2 * k + 1].x, dq[p][2 * k].x, 0x07060302u);
+                    b[2][k] = __builtin_amdgcn_perm(dq[p][2 * k + 1].y, dq[p][2 * k].y, 0x05040100u);
+                    b[3][k] = __builtin_amdgcn_perm(dq[p][2 * k + 1].y, dq[p][2 * k].y, 0x07060302u);
+                }
+#pragma unroll
+                for (int n = 0; n < NT; ++n) {
+                    const uint4 hi = hs[buf][(p * NT + n) * 128 + lane], lo = hs[buf][(p * NT + n) * 128 + 64 + lane];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const uint4 bj = make_uint4(b[j][0], b[j][1], b[j][2], b[j][3]);
+                        acc[j][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h16x8, hi), __builtin_bit_cast(h16x8, bj),
+                                                                           acc[j][n], 0, 0, 0);
+                        acc[j][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h16x8, lo), __builtin_bit_cast(h16x8, bj),
+                                                                           acc[j][n], 0, 0, 0);
+                    }
+                    if (NT > 2 && (n & 1)) __builtin_amdgcn_sched_barrier(0);  // keeps later LDS reads from piling up in registers
+                }
+                load_d(dq[p], s + 1, p);  // (past the last slice: ids repeat the last row, cache hits that nobody uses)
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            e_next = store_h(s + 1, e_acc);
+            store_ids(s + 2);
+            __syncthreads();
+        }
+        // lane (l16, q4) holds Y[token 16 n + 4 q4 + i][columns col .. col + 3]
+        const float back = ldexpf(1.0f, e_acc);
+        float* out = a.partial + ((size_t)grp.first + (size_t)piece * kTok) * d + col;
+        int tok0 = 4 * q4;
+        asm volatile("" : "+v"(tok0));  // or the addresses below are formed ahead of the loop and spilled across it
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int tok = 16 * n + tok0 + i;
+                if (tok < grp.n) {
+                    float* o = out + (size_t)tok * d;
+                    *reinterpret_cast<float4*>(o) = make_float4(acc[0][n][i] * back, acc[1][n][i] * back, acc[2][n][i] * back, acc[3][n][i] * back);
+                }
+            }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// S6: the partial results of a token's tasks, slot by slot, piece by piece (a fixed order)
+// ---------------------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(128) void combine_wide_kernel(const float* __restrict__ partial, const int2* __restrict__ task_rows,
+                                                           int stride, int slots, int d, float* __restrict__ y_acc,
+                                                           h16* __restrict__ y_half) {
+    const int t = blockIdx.y;
+    const int c = (blockIdx.x * 128 + threadIdx.x) * 4;
+    if (c >= d) return;
+    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int sl = 0; sl < slots; ++sl) {
+        const int2 tr = task_rows[(size_t)t * slots + sl];  // first row, number of pieces
+        const float* p = partial + (size_t)tr.x * d + c;
+        for (int k = 0; k < tr.y; k += 4) {
+            float4 q[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                q[i] = k + i < tr.y ? *reinterpret_cast<const float4*>(p + (size_t)(k + i) * stride * d) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) { s.x += q[i].x; s.y += q[i].y; s.z += q[i].z; s.w += q[i].w; }
+        }
+    }
+    if (y_acc) {
+        float4* y = reinterpret_cast<float4*>(y_acc + (size_t)t * d + c);
+        float4 o = *y;
+        o.x += s.x; o.y += s.y; o.z += s.z; o.w += s.w;
+        *y = o;
+    }
+    if (y_half) {
+        const h16x2 lo = {(h16)s.x, (h16)s.y}, hi = {(h16)s.z, (h16)s.w};
+        *reinterpret_cast<uint2*>(y_half + (size_t)t * d + c) = make_uint2(as_u32(lo), as_u32(hi));
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------------------------------------------
+WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared) {
+    WidePlan p{};
+    const int n_tasks = T * (top_k + n_shared), n_all = n_experts + n_shared;
+    // Token tiles per group: the fewest expected reads of the experts' rows, weighed by what a read costs.  Measured (8
+    // experts, d = 4096, f = 14336, 90 %, gate + down): 64 tokens 330 us with one tile (12 groups), 293 with two (8
+    // groups), 308 with three; 512 tokens 637 us with five tiles (16 groups, the two of an expert share rows in the L2),
+    // 565 with ten (8 groups: each workgroup passes twice the activations through LDS).
+    double best = 0.0;
+    for (const int nt : {1, 2, 3, 4, 5, 10}) {
+        const double groups = expected_token_groups(n_experts, T, top_k, 16 * nt) + (double)n_shared * ((T + 16 * nt - 1) / (16 * nt));
+        const double score = groups * (1.0 + (nt <= 5 ? 0.05 : 0.09) * nt);
+        if (p.nt == 0 || score < best) {
+            best = score;
+            p.nt = nt;
+            p.est_groups = groups < 1.0 ? 1 : (int)(groups + 0.5);
+        }
+    }
+    p.chunk = 16 * p.nt;
+    p.max_groups = (n_all < n_tasks ? n_all : n_tasks) + n_tasks / p.chunk;
+    p.pairs = (f + kPairRows - 1) / kPairRows;
+    const long long est_pairs = (long long)p.est_groups * p.pairs;
+    // one workgroup per compute unit; a piece is at least one pair (gate) or four (down: each piece costs a partial result)
+    p.wg_gate = (int)(est_pairs < num_cus() ? est_pairs : num_cus());
+    const int per_col = num_cus() / (d / kDownCols);
+    const long long by_len = (est_pairs + 3) / 4;
+    p.wg_down = (int)(by_len < per_col ? by_len : per_col);
+    if (p.wg_down > 8) p.wg_down &= ~7;  // (see wide_piece)
+    if (p.wg_down < 1) p.wg_down = 1;
+    if (p.wg_gate > 8) p.wg_gate &= ~7;
+    p.partial_rows = (size_t)n_tasks + (size_t)p.chunk * (p.wg_down - 1);
+    return p;
+}
+
+template <int NT>
+static hipError_t launch_wide_nt(const WideArgs& a, const WidePlan& p, int d, hipStream_t stream) {
+    gate_wide_kernel<NT><<<dim3(p.wg_gate), dim3(kWideThreads), 0, stream>>>(a, d);
+    hipError_t rc = hipGetLastError();
+    if (rc != hipSuccess) return rc;
+    down_wide_kernel<NT><<<dim3(p.wg_down, d / kDownCols), dim3(kWideThreads), 0, stream>>>(a, d);
+    return hipGetLastError();
+}
+
+hipError_t launch_gate_down_wide(const WideArgs& a, const WidePlan& p, const uint32_t* mask_words, int d, hipStream_t stream) {
+    if (d % kDownCols != 0 || mask_words_per_task(a.f) > kWideMaxMaskWords) return hipErrorInvalidValue;
+    wide_rows_kernel<<<dim3(p.max_groups), dim3(1024), 0, stream>>>(a, mask_words);
+    hipError_t rc = hipGetLastError();
+    if (rc != hipSuccess) return rc;
+    switch (p.nt) {
+        case 1: return launch_wide_nt<1>(a, p, d, stream);
+        case 2: return launch_wide_nt<2>(a, p, d, stream);
+        case 3: return launch_wide_nt<3>(a, p, d, stream);
+        case 4: return launch_wide_nt<4>(a, p, d, stream);
+        case 5: return launch_wide_nt<5>(a, p, d, stream);
+        case 10: return launch_wide_nt<10>(a, p, d, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_combine_wide(const WideArgs& a, const WidePlan& p, int d, int T, float* y_acc, h16* y_half, hipStream_t stream) {
+    combine_wide_kernel<<<dim3((d / 4 + 127) / 128, T), dim3(128), 0, stream>>>(a.partial, a.task_rows, p.chunk, a.slots, d, y_acc, y_half);
+    return hipGetLastError();
+}
+
+}  // namespace floe

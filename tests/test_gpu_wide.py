@@ -1,0 +1,83 @@
+"""GPU parity of the matrix-core gate/down kernels for many tokens per expert (wide groups): every number of token tiles,
+one and several groups, row counts off every tile edge, several pieces per group, h beyond the range of fp16."""
+import numpy as np
+import pytest
+import torch
+
+import floe_synth as S
+import oracle as O
+from test_gpu_layer import _run_layer_case, _threads  # noqa: F401  (the fixture sets the oracle's threads)
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _wide():
+    import paper_2505_05950_amd as F
+    F.load()
+    F.floe_tuning(F.TUNE_UNION_KERNELS, 1)
+    F.floe_tuning(F.TUNE_FUSED_TASKS, 1)
+    yield
+    F.floe_tuning(F.TUNE_UNION_KERNELS, 0)
+    F.floe_tuning(F.TUNE_FUSED_TASKS, 0)
+
+
+@pytest.mark.parametrize("d,f,bits,group,n,n_shared,top_k,T,pct", [
+    (512, 33, 4, 64, 0, 1, 0, 16, 40),      # one tile of tokens, one pair of row tiles and one row
+    (1024, 700, 2, 64, 0, 1, 0, 17, 80),    # two token tiles, the second with one token
+    (1536, 95, 4, 128, 0, 1, 0, 33, 50),    # three
+    (512, 1031, 8, 64, 0, 1, 0, 64, 95),    # four, full
+    (1024, 515, 3, 32, 0, 1, 0, 80, 0),     # five, full; every channel selected
+    (512, 3000, 2, 64, 0, 1, 0, 81, 97),    # ten
+    (512, 261, 4, 32, 0, 2, 0, 161, 60),    # several groups of an expert, two experts
+    (5120, 77, 2, 64, 3, 1, 2, 9, 70),      # more column blocks than rows fill
+    (1024, 64, 2, 64, 12, 0, 2, 20, 70),    # many small groups
+])
+def test_wide_groups(d, f, bits, group, n, n_shared, top_k, T, pct):
+    _run_layer_case(70 + T, 5, d, f, bits, group, n, n_shared, top_k, False, T, pct, gap=f * (100 - pct) >= 6400)
+
+
+def test_h_beyond_fp16():
+    """Large activations: |h| far beyond 65504 for some (row, token), ordinary for the others of the same group."""
+    import gpu_common as G
+    import paper_2505_05950_amd as F
+    d, f, bits, group, T, pct = 512, 1500, 4, 64, 40, 80
+    ex_np, ex_dev = G.make_expert(*S.expert_weights(91, 3, d, f), bits, group)
+    x = S.tokens(91, 3, T, d).astype(np.float32)
+    x[::3] *= 300.0                        # h ~ 2e4 typical, 1e5 and more at the tail
+    x = x.astype(np.float16)
+    tau = np.zeros((T, 1), np.float32)
+    peak = 0.0
+    for t in range(T):
+        v = O.up_gemv(*ex_np[:3], d, bits, group, x[t])
+        tau[t, 0], _ = G.tau_in_widest_gap(v, pct)
+        h = O.sparse_ffn(ex_np[3], x[t], v, O.select(v, float(tau[t, 0])))[0]
+        peak = max(peak, float(np.abs(h).max()))
+    assert peak > 2 * 65504
+    ref = O.moe_layer([ex_np], 1, 0, False, None, x, tau, bits, group)
+    assert np.abs(ref["y"]).max() < 60000
+    L = F.Layer([ex_dev], 1, 0, False, None, G.dev(tau), True)
+    y = F.floe_moe_layer_decode(L, G.dev(x)).cpu().numpy().astype(np.float64)
+    for t in range(T):
+        assert G.rel_err(y[t], ref["y"][t]) <= G.Y_TIGHT, (t, G.rel_err(y[t], ref["y"][t]))
+
+
+def test_groups_without_rows():
+    """Experts whose thresholds nobody passes leave nothing behind, also next to experts that select everything."""
+    import gpu_common as G
+    import paper_2505_05950_amd as F
+    d, f, bits, group, n, T = 512, 200, 4, 64, 3, 24
+    experts = [G.make_expert(*S.expert_weights(92, 3, d, f, 0, e), bits, group) for e in range(n)]
+    x = S.tokens(92, 3, T, d)
+    for silent in ((0,), (1,), (0, 2), (0, 1, 2)):
+        tau = np.zeros((T, n), np.float32)
+        tau[:, list(silent)] = 1e9
+        ref = O.moe_layer([e[0] for e in experts], n, 0, False, None, x, tau, bits, group)
+        L = F.Layer([e[1] for e in experts], n, 0, False, None, G.dev(tau), True)
+        stats = torch.zeros((T, n, 4), dtype=torch.int32, device=G.DEV)
+        y = F.floe_moe_layer_decode(L, G.dev(x), stats=stats).cpu().numpy().astype(np.float64)
+        assert np.array_equal(stats.cpu().numpy()[:, :, 1], np.where(tau > 0, 0, f))
+        if len(silent) == n:
+            assert not y.any()
+        else:
+            assert max(G.rel_err(y[t], ref["y"][t]) for t in range(T)) <= G.Y_TIGHT
