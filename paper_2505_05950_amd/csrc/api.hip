@@ -115,16 +115,18 @@ bool mask_path_ok(int f) { return mask_words_per_task(f) <= 2048; }
 // workspace of the layer: per-task table, counts, mask words, v, idx, partial
 struct LayerWs {
     size_t table_off, expert_off, weight_off, tau_off, logit_off, count_off, mask_off, groups_off, ngroups_off, order_off, v_off, idx_off,
-        rows_off, missidx_off, missrows_off, misscount_off, wgroups_off, urow_off, ucount_off, hbuf_off, hexp_off, trows_off, partial_off, total;
+        rows_off, missidx_off, missrows_off, misscount_off, wgroups_off, xfrag_off, urow_off, ucount_off, hbuf_off, hexp_off, trows_off, partial_off, total;
     int n_tasks, nblk, nblk_fused, fused_passes;
     bool batch_mfma;  // tokens of an expert share one pass over its codes (matrix-core up GEMV)
     bool use_wide;    // batches: one read of every row an expert group selected, on the matrix cores (wide_batch.hip)
+    bool up_wide;     // ... and so does the up projection (up_wide.hip)
     bool use_union;   // the same through an LDS ring (gate_down_union.hip; by tuning only)
     int chunk;        // tasks per token group
     UnionPlan up;
     WidePlan wp;
 };
-LayerWs layer_plan(const floe_layer* L, int T, bool allow_wide) {
+// max_down: at most so many pieces in the down kernel of the wide path (0: its own choice), -1: no wide path
+LayerWs layer_plan(const floe_layer* L, int T, int max_down) {
     LayerWs w{};
     const int slots = L->top_k + L->n_shared;
     w.n_tasks = T * slots;
@@ -140,9 +142,9 @@ LayerWs layer_plan(const floe_layer* L, int T, bool allow_wide) {
                    (grouped_gemv_mode() == 1 || (!w.fused_passes && mfma_batch_pays(n_all, w.n_tasks, L->s.bits)));
     const bool share_rows = !L->gd_on_host && T >= 2 && (!w.fused_passes || w.batch_mfma) && mask_path_ok(L->s.f);
     const int kernels = union_kernels_for(n_all, w.n_tasks, L->s.d, L->s.f);
-    w.use_wide = share_rows && kernels == 1 && allow_wide;
+    w.use_wide = share_rows && kernels == 1 && max_down >= 0;
     w.use_union = share_rows && kernels == 2 && union_shape_ok(L->s.d, L->s.f, w.up);
-    if (w.use_wide) w.wp = wide_plan(L->s.d, L->s.f, T, L->n_experts, L->top_k, L->n_shared);
+    if (w.use_wide) w.wp = wide_plan(L->s.d, L->s.f, T, L->n_experts, L->top_k, L->n_shared, max_down);
     int nblk_alloc = w.nblk > w.nblk_fused ? w.nblk : w.nblk_fused;
     if (w.use_union && w.up.nblk > nblk_alloc) nblk_alloc = w.up.nblk;
     int count_parts = w.nblk_fused > 1 ? w.nblk_fused : 1;
@@ -171,6 +173,8 @@ LayerWs layer_plan(const floe_layer* L, int T, bool allow_wide) {
     w.misscount_off = o; o += L->gd_on_host ? align_up((size_t)w.n_tasks * 4) : 0;
     const size_t wgroups = w.use_wide ? (size_t)w.wp.max_groups : 0;
     w.wgroups_off = o; o += w.use_wide ? align_up(wgroups * sizeof(WideGroup) + 4) : 0;  // (+ their number)
+    w.up_wide = w.use_wide && up_wide_pays(L->s.d, L->s.f, L->s.bits, L->s.group, n_all, w.n_tasks);
+    w.xfrag_off = o;   o += w.up_wide ? align_up(up_wide_scratch_bytes(T, L->s.d, L->s.group)) : 0;
     w.urow_off = o;    o += align_up(wgroups * L->s.f * 4);
     w.ucount_off = o;  o += align_up(wgroups * 4);
     w.hbuf_off = o;    o += align_up(wgroups * w.wp.pairs * w.wp.nt * 128 * sizeof(uint4));
@@ -182,12 +186,18 @@ LayerWs layer_plan(const floe_layer* L, int T, bool allow_wide) {
     return w;
 }
 // The wide kernels need more workspace per task.  A layer call that fits the library's static scratch with the one-token
-// kernels goes on fitting it: there they are taken unless the wide ones fit as well.
+// kernels goes on fitting it: there the wide ones are taken only if they fit as well, with fewer pieces in the down kernel
+// (each costs partial results) as long as these occupy a third of the chip.
 LayerWs layer_ws(const floe_layer* L, int T) {
-    const LayerWs w = layer_plan(L, T, true);
+    LayerWs w = layer_plan(L, T, 0);
     if (!w.use_wide || w.total <= FLOE_STATIC_SCRATCH_BYTES || union_mode() == 1) return w;
-    const LayerWs n = layer_plan(L, T, false);
-    return n.total <= FLOE_STATIC_SCRATCH_BYTES ? n : w;
+    const LayerWs n = layer_plan(L, T, -1);
+    if (n.total > FLOE_STATIC_SCRATCH_BYTES) return w;
+    for (int pieces = (w.wp.wg_down - 1) & ~7; pieces >= 8 && 3 * pieces * (L->s.d / 512) >= num_cus(); pieces -= 8) {
+        const LayerWs s = layer_plan(L, T, pieces);
+        if (s.total <= FLOE_STATIC_SCRATCH_BYTES) return s;
+    }
+    return n;
 }
 
 int check_layer(const floe_layer* L) {
@@ -614,7 +624,14 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
             FLOE_HIP(launch_group_tokens(task_expert, w.n_tasks, n_all, w.chunk, groups, n_groups, st, order, w.wp.chunk, wide, n_wide));
         else
             FLOE_HIP(launch_group_tokens(task_expert, w.n_tasks, n_all, w.chunk, groups, n_groups, st));
-        if (batch_mfma)
+        if (w.up_wide) {
+            UpWideArgs u{};
+            u.table = static_cast<const DevExpert*>(L->dev_table);
+            u.groups = wide; u.n_groups = n_wide; u.order = order; u.x = xh; u.v = v;
+            u.task_tau = task_tau; u.mask_words = mask; u.scratch = base + w.xfrag_off;
+            u.T = T; u.d = L->s.d; u.f = L->s.f; u.slots = slots; u.nt = w.wp.nt; u.est_groups = w.wp.est_groups;
+            FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st, launch_up_wide(u, L->s.bits, L->s.group, st));
+        } else if (batch_mfma)
             FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st,
                         launch_up_gemv_grouped(static_cast<const DevExpert*>(L->dev_table), groups, n_groups,
                                                w.up.max_groups, w.chunk, xh, slots, v, task_tau, mask, L->s.d, L->s.f,

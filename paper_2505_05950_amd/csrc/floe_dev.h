@@ -144,6 +144,22 @@ static __device__ unsigned long long* g_timeline = nullptr;  // one copy per tra
 #endif
 #define FLOE_TL(slot) FLOE_TL_AT(slot, 0)
 
+// ---- equal division of a launch's work (wide_batch.hip, up_wide.hip)
+// a pointer that every lane holds alike, as a scalar (loads then take it as their base and a 32-bit offset per lane)
+__device__ __forceinline__ const unsigned char* scalar_ptr(const void* p) {
+    const uint64_t u = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
+    return (const unsigned char*)(((uint64_t)hi << 32) | lo);
+}
+// piece w of W equal pieces starts at pair floor(total * w / W)
+__device__ __forceinline__ int wide_cut(int total, int W, int w) { return (int)((long long)total * w / W); }
+// Workgroups go to the eight XCDs in turn.  Neighbouring pieces run on one XCD, so that its L2 holds the activations of few
+// groups, and the groups of one expert, which read the same rows, are next to each other.
+__device__ __forceinline__ int wide_piece(int W) {
+    const int b = blockIdx.x;
+    return (W & 7) ? b : (b & 7) * (W >> 3) + (b >> 3);
+}
+
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + __expf(-g)); }
 
 }  // namespace floe

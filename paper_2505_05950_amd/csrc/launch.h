@@ -199,7 +199,36 @@ struct WideArgs {
     float* partial;           // [partial_rows][d]
     int32_t slots, f;
 };
-WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared);
+// S2 for the same groups (up_wide.hip)
+inline bool up_wide_shape(int d, int f, int bits, int group) {
+    return ((bits == 2 && group == 64) || ((bits == 3 || bits == 4) && (group == 32 || group == 64))) && d % 512 == 0 && f <= 65536;
+}
+// For shapes that the grouped kernel above takes as well, which of the two: it prepares the activations of at most 16 tokens
+// in every workgroup, this one prepares them once and shares a pass over the codes among up to 64.  Layer calls measured,
+// grouped / this, us (8 experts): INT2 g64 d 4096 f 14336 at 16 tasks per expert 375 / 392, 32: 529 / 491, 128: 907 / 792;
+// INT3 g64 d 2048 f 7000 at 16: 153 / 153, 32: 225 / 208, 128: 461 / 320; INT4 g32 d 2048 f 5632 at 128: 328 / 351;
+// INT3 g32 d 2048 f 1408 (66 experts) at 31: 373 / 410, 62: 525 / 480.
+inline bool up_wide_pays(int d, int f, int bits, int group, int n_all, int n_tasks) {
+    if (!up_wide_shape(d, f, bits, group)) return false;
+    if (!mfma_grouped_shape(d, bits, group)) return true;
+    return group == 64 ? n_tasks >= 32 * n_all : (bits == 3 && n_tasks >= 48 * n_all);
+}
+struct UpWideArgs {
+    const DevExpert* table;
+    const WideGroup* groups;
+    const int32_t* n_groups;
+    const int32_t* order;
+    const h16* x;
+    float* v;
+    const float* task_tau;
+    uint32_t* mask_words;
+    void* scratch;  // up_wide_scratch_bytes()
+    int32_t T, d, f, slots, nt, est_groups, parts, workgroups;  // (parts, workgroups: set by the launcher)
+};
+size_t up_wide_scratch_bytes(int T, int d, int group);
+hipError_t launch_up_wide(UpWideArgs a, int bits, int group, hipStream_t stream);
+
+WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared, int max_down);
 hipError_t launch_gate_down_wide(const WideArgs& a, const WidePlan& p, const uint32_t* mask_words, int d, hipStream_t stream);
 hipError_t launch_combine_wide(const WideArgs& a, const WidePlan& p, int d, int T, float* y_acc, h16* y_half, hipStream_t stream);
 

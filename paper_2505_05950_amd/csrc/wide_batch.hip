@@ -56,12 +56,6 @@ __device__ __forceinline__ int wide_total(const WideArgs& a, int ng, int lane) {
     }
     return total;
 }
-// a pointer that every lane holds alike, as a scalar (loads then take it as their base and a 32-bit offset per lane)
-__device__ __forceinline__ const unsigned char* scalar_ptr(const void* p) {
-    const uint64_t u = (uint64_t)p;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
-    return (const unsigned char*)(((uint64_t)hi << 32) | lo);
-}
 // the group that holds pair `pos` of the sequence (pos < total) and the position of its first pair; every lane the same
 __device__ __forceinline__ void wide_find(const WideArgs& a, int ng, int lane, int pos, int& g, int& base) {
     int run = 0;
@@ -80,16 +74,8 @@ __device__ __forceinline__ void wide_find(const WideArgs& a, int ng, int lane, i
     g = ng - 1;  // not reached for pos < total
     base = pos;
 }
-// piece w of W equal pieces starts at pair floor(total * w / W); pair p therefore belongs to piece ((p + 1) * W - 1) / total
-__device__ __forceinline__ int wide_cut(int total, int W, int w) { return (int)((long long)total * w / W); }
+// pair p belongs to piece ((p + 1) * W - 1) / total (see wide_cut)
 __device__ __forceinline__ int wide_owner(int total, int W, int p) { return (int)(((long long)(p + 1) * W - 1) / total); }
-
-// Workgroups go to the eight XCDs in turn.  Neighbouring pieces run on one XCD, so that its L2 holds the activations of few
-// groups, and the groups of one expert, which read the same rows, are next to each other.
-__device__ __forceinline__ int wide_piece(int W) {
-    const int b = blockIdx.x;
-    return (W & 7) ? b : (b & 7) * (W >> 3) + (b >> 3);
-}
 
 // ---------------------------------------------------------------------------------------------------------------
 // union lists
@@ -602,7 +588,7 @@ __global__ __launch_bounds__(128) void combine_wide_kernel(const float* __restri
 // ---------------------------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------------------------
-WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared) {
+WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared, int max_down) {
     WidePlan p{};
     const int n_tasks = T * (top_k + n_shared), n_all = n_experts + n_shared;
     // Token tiles per group: the fewest expected reads of the experts' rows, weighed by what a read costs.  Measured (8
@@ -628,6 +614,7 @@ WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared) 
     const int per_col = num_cus() / (d / kDownCols);
     const long long by_len = (est_pairs + 3) / 4;
     p.wg_down = (int)(by_len < per_col ? by_len : per_col);
+    if (max_down > 0 && p.wg_down > max_down) p.wg_down = max_down;
     if (p.wg_down > 8) p.wg_down &= ~7;  // (see wide_piece)
     if (p.wg_down < 1) p.wg_down = 1;
     if (p.wg_gate > 8) p.wg_gate &= ~7;
