@@ -91,10 +91,14 @@ TaskMap single_map(const floe_expert* e) {
 // workspace of the one-expert entry points: [v: T*f floats][mask words][counts][idx when not fused][partial: T*nblk*d floats]
 struct ExpertWs {
     size_t v_off, mask_off, count_off, idx_off, partial_off, total;
+    size_t table_off, order_off, wgroups_off, xfrag_off, urow_off, ucount_off, hbuf_off, hexp_off, trows_off;  // wide path
     int nblk, fused_passes, nblk_fused;
+    bool wide;  // many tokens: one read of every row that any of a group of tokens selected (wide_batch.hip)
+    WidePlan wp;
 };
+bool mask_path_ok(int f);
 ExpertWs expert_ws(const floe_shape* s, int T) {
-    ExpertWs w;
+    ExpertWs w{};
     w.nblk = gd_blocks(T, s->f);
     w.fused_passes = packed_fast_shape(s->d, s->bits, s->group) ? fused_passes(s->d, s->f, s->bits, T) : 0;
     w.nblk_fused = w.fused_passes ? fused_blocks(s->d, s->f, w.fused_passes) : 0;
@@ -104,7 +108,21 @@ ExpertWs expert_ws(const floe_shape* s, int T) {
     w.mask_off = o;    o += align_up((size_t)T * mask_words_per_task(s->f) * sizeof(uint32_t));
     w.count_off = o;   o += align_up((size_t)T * (w.nblk_fused > 1 ? w.nblk_fused : 1) * sizeof(int32_t));
     w.idx_off = o;     o += w.fused_passes ? 0 : align_up((size_t)T * s->f * sizeof(int32_t));  // list for callers that pass none
-    w.partial_off = o; o += align_up((size_t)T * nblk_alloc * s->d * sizeof(float));
+    w.wide = !w.fused_passes && T >= 2 && mask_path_ok(s->f) && union_kernels_for(1, T, s->d, s->f) == 1;
+    if (w.wide) {
+        w.wp = wide_plan(s->d, s->f, T, 1, 1, 0, 0);
+        w.table_off = o;   o += align_up(sizeof(DevExpert));
+        w.order_off = o;   o += align_up((size_t)T * 4);
+        w.wgroups_off = o; o += align_up((size_t)w.wp.max_groups * sizeof(WideGroup) + 4);
+        w.xfrag_off = o;   o += align_up(up_wide_scratch_bytes(T, s->d, s->group));
+        w.urow_off = o;    o += align_up((size_t)w.wp.max_groups * s->f * 4);
+        w.ucount_off = o;  o += align_up((size_t)w.wp.max_groups * 4);
+        w.hbuf_off = o;    o += align_up((size_t)w.wp.max_groups * w.wp.pairs * w.wp.nt * 128 * sizeof(uint4));
+        w.hexp_off = o;    o += align_up((size_t)w.wp.max_groups * w.wp.pairs * 4);
+        w.trows_off = o;   o += align_up((size_t)T * sizeof(int2));
+    }
+    const size_t rows = (size_t)T * nblk_alloc;
+    w.partial_off = o; o += align_up((w.wide && w.wp.partial_rows > rows ? w.wp.partial_rows : rows) * s->d * sizeof(float));
     w.total = o;
     return w;
 }
@@ -418,6 +436,39 @@ int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, cons
         FLOE_LAUNCH(FLOE_KERNEL_FUSED_FFN, st, launch_fused(a, e->s.bits, st));
         if (idx) FLOE_LAUNCH(FLOE_KERNEL_SELECT, st, launch_select(v, e->s.f, T, tau, idx, count, st));
         nblk = w.nblk_fused;
+    } else if (w.wide) {
+        char* base = static_cast<char*>(workspace);
+        DevExpert* table = reinterpret_cast<DevExpert*>(base + w.table_off);
+        WideGroup* groups = reinterpret_cast<WideGroup*>(base + w.wgroups_off);
+        int32_t* n_groups = reinterpret_cast<int32_t*>(groups + w.wp.max_groups);
+        int32_t* order = reinterpret_cast<int32_t*>(base + w.order_off);
+        FLOE_HIP(launch_wide_single(map.single, T, w.wp.chunk, table, groups, n_groups, order, st));
+        // (scales and zeros need no more than their own alignment here; the wide kernel loads them 16 bytes at a time)
+        if (up_wide_shape(e->s.d, e->s.f, e->s.bits, e->s.group) && aligned(e->up_scale, 16) && aligned(e->up_zero, 16)) {
+            UpWideArgs u{};
+            u.table = table; u.groups = groups; u.n_groups = n_groups; u.order = order; u.x = xh; u.v = v;
+            u.task_tau = tau; u.mask_words = mask; u.scratch = base + w.xfrag_off;
+            u.T = T; u.d = e->s.d; u.f = e->s.f; u.slots = 1; u.nt = w.wp.nt; u.est_groups = w.wp.est_groups;
+            FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st, launch_up_wide(u, e->s.bits, e->s.group, st));
+        } else {
+            FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st,
+                        launch_up_gemv(map, xh, nullptr, v, tau, mask, e->s.d, e->s.f, e->s.bits, e->s.group, T, st));
+        }
+        WideArgs wa{};
+        wa.table = table; wa.groups = groups; wa.n_groups = n_groups; wa.order = order; wa.x = xh; wa.v = v;
+        wa.task_tau = tau; wa.task_scale = out_scale;
+        wa.count = reinterpret_cast<int32_t*>(base + w.count_off);
+        wa.urow = reinterpret_cast<int32_t*>(base + w.urow_off);
+        wa.ucount = reinterpret_cast<int32_t*>(base + w.ucount_off);
+        wa.hbuf = reinterpret_cast<uint4*>(base + w.hbuf_off);
+        wa.hexp = reinterpret_cast<int32_t*>(base + w.hexp_off);
+        wa.task_rows = reinterpret_cast<int2*>(base + w.trows_off);
+        wa.partial = partial;
+        wa.slots = 1; wa.f = e->s.f;
+        FLOE_LAUNCH(FLOE_KERNEL_GATE_DOWN, st, launch_gate_down_wide(wa, w.wp, mask, e->s.d, st));
+        if (idx) FLOE_LAUNCH(FLOE_KERNEL_SELECT, st, launch_select(v, e->s.f, T, tau, idx, count, st));
+        FLOE_LAUNCH(FLOE_KERNEL_COMBINE, st, launch_combine_wide(wa, w.wp, e->s.d, T, y_acc, nullptr, st));
+        return FLOE_OK;
     } else {
         // a caller that wants no list still gets one built, in the workspace
         int32_t* idx_ws = idx ? idx : reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + w.idx_off);

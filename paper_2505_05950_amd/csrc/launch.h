@@ -230,6 +230,8 @@ hipError_t launch_up_wide(UpWideArgs a, int bits, int group, hipStream_t stream)
 
 WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared, int max_down);
 hipError_t launch_gate_down_wide(const WideArgs& a, const WidePlan& p, const uint32_t* mask_words, int d, hipStream_t stream);
+hipError_t launch_wide_single(const DevExpert& e, int n_tasks, int chunk, DevExpert* table, WideGroup* groups, int32_t* n_groups,
+                              int32_t* order, hipStream_t stream);
 hipError_t launch_combine_wide(const WideArgs& a, const WidePlan& p, int d, int T, float* y_acc, h16* y_half, hipStream_t stream);
 
 // The other sparsification candidates of Sec. 3.2.1 (variants.hip): act = a_gate (which = 1) or a_down (which = 2) and

@@ -585,6 +585,24 @@ __global__ __launch_bounds__(128) void combine_wide_kernel(const float* __restri
     }
 }
 
+// Groups, order and pointer table of a single expert that every task belongs to (the one-expert entry point).
+__global__ __launch_bounds__(256) void wide_single_kernel(DevExpert e, int n_tasks, int chunk, DevExpert* __restrict__ table,
+                                                          WideGroup* __restrict__ groups, int32_t* __restrict__ n_groups,
+                                                          int32_t* __restrict__ order) {
+    const int ng = (n_tasks + chunk - 1) / chunk, len = (n_tasks + ng - 1) / ng;
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n_tasks) order[i] = i;
+    if (i < ng) {
+        groups[i].expert = 0;
+        groups[i].n = max(0, min(len, n_tasks - i * len));
+        groups[i].first = min(i * len, n_tasks);
+    }
+    if (i == 0) {
+        table[0] = e;
+        n_groups[0] = ng;
+    }
+}
+
 // ---------------------------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------------------------
@@ -645,6 +663,12 @@ hipError_t launch_gate_down_wide(const WideArgs& a, const WidePlan& p, const uin
         case 10: return launch_wide_nt<10>(a, p, d, stream);
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_wide_single(const DevExpert& e, int n_tasks, int chunk, DevExpert* table, WideGroup* groups, int32_t* n_groups,
+                              int32_t* order, hipStream_t stream) {
+    wide_single_kernel<<<dim3((n_tasks + 255) / 256), dim3(256), 0, stream>>>(e, n_tasks, chunk, table, groups, n_groups, order);
+    return hipGetLastError();
 }
 
 hipError_t launch_combine_wide(const WideArgs& a, const WidePlan& p, int d, int T, float* y_acc, h16* y_half, hipStream_t stream) {

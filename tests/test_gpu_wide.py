@@ -81,3 +81,33 @@ def test_groups_without_rows():
             assert not y.any()
         else:
             assert max(G.rel_err(y[t], ref["y"][t]) for t in range(T)) <= G.Y_TIGHT
+
+
+@pytest.mark.parametrize("d,f,bits,group,T", [
+    (1024, 700, 2, 64, 20), (512, 333, 4, 32, 40), (1536, 515, 3, 64, 33), (2048, 300, 4, 128, 18), (512, 97, 3, 32, 65),
+    (1024, 130, 8, 64, 17),
+])
+def test_one_expert_many_tokens(d, f, bits, group, T):
+    """floe_expert_ffn_sparse beyond the one-kernel batch: with the list, without it, and y accumulated."""
+    import test_gpu_steps as steps
+    steps.test_expert_ffn_sparse_matches_oracle(d, f, bits, group, T, [(80, 0, 95, 50)[t % 4] for t in range(T)])
+    steps.test_expert_ffn_without_a_list_gives_the_same_result(d, f, bits, group, T)
+
+
+def test_one_expert_scales_with_their_own_alignment_only():
+    import gpu_common as G
+    import paper_2505_05950_amd as F
+    d, f, bits, group, T = 1024, 200, 2, 64, 24
+    ex_np, ex_dev = G.make_expert(*S.expert_weights(93, 3, d, f), bits, group)
+    x, tau = G.dev(S.tokens(93, 3, T, d)), G.dev(np.full((T,), 1.0, np.float32))
+    y = F.floe_expert_ffn_sparse(ex_dev, x, tau, None, torch.zeros((T, d), dtype=torch.float32, device=G.DEV))[0]
+
+    def moved(t):  # the same values two bytes off a 16-byte boundary
+        buf = torch.empty((t.numel() + 8,), dtype=t.dtype, device=t.device)
+        off = ((-buf.data_ptr()) % 16) // 2 + 1
+        buf[off: off + t.numel()] = t.flatten()
+        return buf[off: off + t.numel()]
+
+    odd = F.Expert(d, f, bits, group, ex_dev.up_codes, moved(ex_dev.up_scale), moved(ex_dev.up_zero), ex_dev.gd)
+    y2 = F.floe_expert_ffn_sparse(odd, x, tau, None, torch.zeros((T, d), dtype=torch.float32, device=G.DEV))[0]
+    assert G.rel_err(y2.cpu().numpy(), y.cpu().numpy()) <= 1e-4   # another kernel's order of summation
