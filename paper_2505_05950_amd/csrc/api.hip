@@ -434,8 +434,11 @@ int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, cons
         a.wg_count = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + w.count_off);
         a.d = e->s.d; a.f = e->s.f; a.group = e->s.group; a.n_tasks = T; a.passes = w.fused_passes;
         FLOE_LAUNCH(FLOE_KERNEL_FUSED_FFN, st, launch_fused(a, e->s.bits, st));
-        if (idx) FLOE_LAUNCH(FLOE_KERNEL_SELECT, st, launch_select(v, e->s.f, T, tau, idx, count, st));
         nblk = w.nblk_fused;
+        if (idx) {
+            FLOE_LAUNCH(FLOE_KERNEL_COMBINE, st, launch_combine_select(partial, e->s.d, T, nblk, y_acc, v, e->s.f, tau, idx, count, st));
+            return FLOE_OK;
+        }
     } else if (w.wide) {
         char* base = static_cast<char*>(workspace);
         DevExpert* table = reinterpret_cast<DevExpert*>(base + w.table_off);

@@ -246,6 +246,10 @@ hipError_t launch_down_rows(const h16* gd, const float* hval, const int32_t* idx
 hipError_t launch_combine(const float* partial, int d, int T, int slots, int nblk, float* y_acc, h16* y_half,
                           hipStream_t stream);
 
+// S6 of a one-expert call together with S3's index lists (from v and tau)
+hipError_t launch_combine_select(const float* partial, int d, int T, int nblk, float* y_acc, const float* v, int f, const float* tau,
+                                 int32_t* idx, int32_t* count, hipStream_t stream);
+
 // S1: router + per-task table (resolved expert pointers, weight, tau)
 struct RouterArgs {
     const h16* router_cm;

@@ -5,49 +5,14 @@
 // base + (selected channels before it), which keeps the list ascending without any sort.
 #include "floe_dev.h"
 #include "launch.h"
+#include "select_task.h"
 
 namespace floe {
 
 __global__ __launch_bounds__(1024) void select_kernel(const float* __restrict__ v, int f, const float* __restrict__ tau,
                                                       int32_t* __restrict__ idx, int32_t* __restrict__ count) {
-    constexpr int kWaves = 16;
-    __shared__ int wave_total[kWaves];
     const int task = blockIdx.x;
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
-    const float th = tau[task];
-    const float* vt = v + (size_t)task * f;
-    int32_t* it = idx + (size_t)task * f;
-    // slice of this wave: a multiple of 64 channels
-    const int chunks = (f + kWave - 1) / kWave;
-    const int chunks_per_wave = (chunks + kWaves - 1) / kWaves;
-    const int c0 = wave * chunks_per_wave;
-    const int c1 = min(chunks, c0 + chunks_per_wave);
-
-    int total = 0;
-    for (int c = c0; c < c1; ++c) {
-        const int j = c * kWave + lane;
-        const bool keep = j < f && fabsf(vt[j]) > th;
-        total += __popcll(__ballot(keep));
-    }
-    if (lane == 0) wave_total[wave] = total;
-    __syncthreads();
-    int base = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        const int n = wave_total[w];
-        base += w < wave ? n : 0;
-        all += n;
-    }
-    if (tid == 0) count[task] = all;
-    const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
-    for (int c = c0; c < c1; ++c) {
-        const int j = c * kWave + lane;
-        const bool keep = j < f && fabsf(vt[j]) > th;
-        const uint64_t m = __ballot(keep);
-        if (keep) it[base + __popcll(m & below)] = j;
-        base += __popcll(m);
-    }
+    select_task(v + (size_t)task * f, f, tau[task], idx + (size_t)task * f, count + task);
 }
 
 hipError_t launch_select(const float* v, int f, int n_tasks, const float* tau, int32_t* idx, int32_t* count,
