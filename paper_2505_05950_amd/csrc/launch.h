@@ -211,6 +211,7 @@ inline bool up_wide_shape(int d, int f, int bits, int group) {
 inline bool up_wide_pays(int d, int f, int bits, int group, int n_all, int n_tasks) {
     if (!up_wide_shape(d, f, bits, group)) return false;
     if (!mfma_grouped_shape(d, bits, group)) return true;
+    if (grouped_gemv_mode() == 2) return false;  // the caller wants one pass per task
     return group == 64 ? n_tasks >= 32 * n_all : (bits == 3 && n_tasks >= 48 * n_all);
 }
 struct UpWideArgs {

@@ -1,8 +1,8 @@
 // S3: mask = |v| > tau, ascending index list and its length (Alg. 1 line 3; S_t of Eq. 5 with the strict
 // comparison Alg. 1 uses).  One workgroup of 16 waves per task.  Each wave owns a contiguous slice of
-// the channels: pass 1 counts with wave ballots, an LDS prefix over the 16 wave totals gives every wave
-// its base offset, pass 2 repeats the ballots and writes each selected channel at
-// base + (selected channels before it), which keeps the list ascending without any sort.
+// the channels: pass 1 keeps and counts wave ballots, an LDS prefix over the 16 wave totals gives every
+// wave its base offset, pass 2 writes each selected channel at base + (selected channels before it), which keeps
+// the list ascending without any sort.
 #include "floe_dev.h"
 #include "launch.h"
 #include "select_task.h"

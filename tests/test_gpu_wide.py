@@ -111,3 +111,32 @@ def test_one_expert_scales_with_their_own_alignment_only():
     odd = F.Expert(d, f, bits, group, ex_dev.up_codes, moved(ex_dev.up_scale), moved(ex_dev.up_zero), ex_dev.gd)
     y2 = F.floe_expert_ffn_sparse(odd, x, tau, None, torch.zeros((T, d), dtype=torch.float32, device=G.DEV))[0]
     assert G.rel_err(y2.cpu().numpy(), y.cpu().numpy()) <= 1e-4   # another kernel's order of summation
+
+
+@pytest.mark.parametrize("T", [40, 200])   # grouped up projection, wide up projection
+def test_replayed_from_a_hip_graph(T):
+    import test_gpu_layer as layer
+    layer.test_layer_decode_replayed_from_a_hip_graph_matches_eager(T)
+
+
+def test_one_pass_per_task_stays_a_choice():
+    """FLOE_TUNE_GROUPED_GEMV = 2 keeps the up projection to one pass per (token, slot), also for large groups: no prepared
+    activations in the workspace, the same masks."""
+    import gpu_common as G
+    import paper_2505_05950_amd as F
+    d, f, n, T = 1024, 512, 2, 64
+    experts = [G.make_expert(*S.expert_weights(94, 3, d, f, 0, e), 2, 64)[1] for e in range(n)]
+    x = G.dev(S.tokens(94, 3, T, d))
+    L = F.Layer(experts, n, 0, False, None, G.dev(np.full((n,), 1.0, np.float32)), False)
+    stats, y, size = [], [], []
+    try:
+        for mode in (0, 2):
+            F.floe_tuning(F.TUNE_GROUPED_GEMV, mode)
+            size.append(F.floe_layer_workspace_bytes(L, T))
+            stats.append(torch.zeros((T, n, 4), dtype=torch.int32, device=G.DEV))
+            y.append(F.floe_moe_layer_decode(L, x, stats=stats[-1]).cpu().numpy())
+    finally:
+        F.floe_tuning(F.TUNE_GROUPED_GEMV, 0)
+    assert size[1] < size[0]
+    assert (stats[0][:, :, 1] - stats[1][:, :, 1]).abs().max() <= 1      # (a channel at the threshold)
+    assert G.rel_err(y[1], y[0]) <= 5e-3
