@@ -55,6 +55,16 @@ __device__ __forceinline__ void wait_vm_all_but() {  // s_waitcnt vmcnt(N) only 
     static_assert(N >= 0 && N < 64, "vmcnt has six bits");
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
+// the same for a count that is known once the surrounding loop has been unrolled (a count without a case waits for everything)
+__device__ __forceinline__ void wait_vm_all_but(int n) {
+#define FLOE_W(N) case N: wait_vm_all_but<N>(); break;
+    switch (n) {
+        FLOE_W(0) FLOE_W(3) FLOE_W(6) FLOE_W(9) FLOE_W(12) FLOE_W(15) FLOE_W(18) FLOE_W(21) FLOE_W(24) FLOE_W(27) FLOE_W(30)
+        FLOE_W(33) FLOE_W(36) FLOE_W(39) FLOE_W(42) FLOE_W(45)
+        default: wait_vm_all_but<0>(); break;
+    }
+#undef FLOE_W
+}
 // A lane's unit of 64 codes travels in kPieces loads of 16 bytes; piece k of all 64 lanes lands contiguously at
 // slot + k * 1024.  kPieces = 0: the width keeps its codes in registers.  Only INT2 is staged: INT4 (two pieces per
 // unit) measured slower that way (16.8 against 15.9 us per expert at 90 %), INT3 units are 24 bytes, 8-byte aligned.
@@ -224,6 +234,7 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
         constexpr bool kStaged = staged_codes<BITS>();
         constexpr int kSlot = stage_slot_bytes<BITS>();
         constexpr int kVmPerPass = St::kPieces + 2;  // requests per pass: the pieces, scale, zero
+        constexpr bool kSingleRound = kPasses != kFusedMaxPasses && kPasses == kDepth;  // n_pass is kPasses: all of them in flight at once
         unsigned char* stage = reinterpret_cast<unsigned char*>(&yred[kFusedCpp * wave][0]);
         static_assert(!kStaged || kDepth * kSlot <= kFusedCpp * d * 4, "the staging ring must fit the two slabs");
         static_assert(!kStaged || kVmPerPass * (kDepth - 1) < 64, "the wait counts outstanding requests in six bits");
@@ -291,7 +302,9 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
         // Staged codes come back from LDS one pass ahead.  A pass's codes have landed once only the requests made
         // after them are outstanding: kVmPerPass per pass, and kDepth - 1 passes are behind pass p at its own turn,
         // kDepth - 2 behind pass p + 1 at that time.  The counts are the same in every round because the last round
-        // keeps requesting (see below).  More may be outstanding - a store of v, say - which only makes a wait longer.
+        // keeps requesting (see below).  A launch of a single round requests nothing behind it (the compiler would drop the
+        // scales and zeros of such requests and leave their codes, one request per pass instead of three); there
+        // kDepth - 2 - i passes are behind pass i + 1.  More may be outstanding - a store of v, say - which only makes a wait longer.
         u32x4 cw_next;
         if constexpr (kStaged) {
             wait_vm_all_but<kVmPerPass * (kDepth - 1)>();
@@ -307,8 +320,8 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
                 if constexpr (kStaged) {
                     lds_piece_arrived(cw_next);
                     ld[i].cw[0] = cw_next.x; ld[i].cw[1] = cw_next.y; ld[i].cw[2] = cw_next.z; ld[i].cw[3] = cw_next.w;
-                    if constexpr (kDepth >= 2) {  // (past the last pass this reads a slot that nobody uses)
-                        wait_vm_all_but<kVmPerPass * (kDepth - 2)>();
+                    if (kSingleRound ? i + 1 < kDepth : kDepth >= 2) {  // (else past the last pass: a slot that nobody uses)
+                        wait_vm_all_but(kVmPerPass * (kSingleRound ? kDepth - 2 - i : kDepth - 2));
                         lds_piece_request(stage + ((i + 1) % kDepth) * kSlot + lane * 16, cw_next);
                     }
                 }
@@ -322,8 +335,10 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
                     // (a cache hit that nobody reads) so that every round has the same, unconditional sequence of
                     // requests: with a condition here the compiler has to assume that no request follows and makes
                     // each round wait for all of its loads at once.
-                    const int pn = p + kDepth < n_pass ? p + kDepth : n_pass - 1;
-                    issue(i, pn);
+                    if constexpr (!kSingleRound) {
+                        const int pn = p + kDepth < n_pass ? p + kDepth : n_pass - 1;
+                        issue(i, pn);
+                    }
                 } else {
                     if (p + kDepth < n_pass) issue(i, p + kDepth);
                 }

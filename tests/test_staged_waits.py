@@ -1,0 +1,55 @@
+"""The INT2 producer of the fused kernel waits for its direct-to-LDS loads with hand-counted s_waitcnt.  Its single-round kernels
+(seven passes, all in flight) are straight-line code: here the generated assembly is walked with the hardware's rule (loads
+return in the order they were issued) and every read-back of a pass must find that pass's load among the returned ones."""
+import os
+import re
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2505_05950_amd", "csrc")
+HIPCC = "/opt/rocm/bin/hipcc"
+
+
+def late_read_backs(lines):
+    """Passes whose codes are read back before their load is known to have arrived (loads, stores: the fewest that can be
+    outstanding, so a store - it depends on the channel or the workgroup - is left out)."""
+    issued, landed, requests, reads, bad, in_asm = 0, 0, [], 0, [], False
+    for raw in lines:
+        s = raw.strip()
+        if s.startswith(";;#ASMSTART") or s.startswith(";APP"):
+            in_asm = True
+        elif s.startswith(";;#ASMEND") or s.startswith(";NO_APP"):
+            in_asm = False
+        elif re.match(r"(global|flat|buffer|scratch)_load", s):
+            issued += 1
+            if s.startswith("global_load_lds"):
+                requests.append(issued)
+        elif s.startswith("s_waitcnt") and "vmcnt(" in s:
+            landed = max(landed, issued - int(re.search(r"vmcnt\((\d+)\)", s).group(1)))
+        elif in_asm and s.startswith("ds_read_b128"):
+            if reads < 7 and requests[reads] > landed:
+                bad.append(reads)
+            reads += 1
+    return bad, reads
+
+
+def check(asm):
+    seen = 0
+    for m in re.finditer(r"^(_ZN4floe16fused_ffn_kernelILi2E\w*Li7ELi7EE\w+):(.*?)^\.Lfunc_end", asm, re.M | re.S):
+        body = m.group(2).split("\n")
+        first = next(i for i, l in enumerate(body) if "global_load_lds_dwordx4" in l)
+        bad, reads = late_read_backs(body[first:])
+        assert reads >= 7, (m.group(1), reads)
+        assert not bad, (m.group(1), "read back too early: passes", bad)
+        seen += 1
+    return seen
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs the compiler")
+def test_every_pass_has_landed_before_it_is_read_back(tmp_path):
+    out = tmp_path / "fused_int2.s"
+    subprocess.run([HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc", "-Xclang", "-target-feature",
+                    "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument", "-S", "--cuda-device-only",
+                    os.path.join(CSRC, "fused_int2.hip"), "-o", str(out)], check=True)
+    assert check(out.read_text()) >= 6
