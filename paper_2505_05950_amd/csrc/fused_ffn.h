@@ -303,7 +303,8 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
         // after them are outstanding: kVmPerPass per pass, and kDepth - 1 passes are behind pass p at its own turn,
         // kDepth - 2 behind pass p + 1 at that time.  The counts are the same in every round because the last round
         // keeps requesting (see below).  A launch of a single round requests nothing behind it (the compiler would drop the
-        // scales and zeros of such requests and leave their codes, one request per pass instead of three); there
+        // scales and zeros of such requests and leave their codes, one request per pass instead of three; without them a call on
+        // one expert of d 1024 f 3584 takes 20.0 us instead of 22.5); there
         // kDepth - 2 - i passes are behind pass i + 1.  More may be outstanding - a store of v, say - which only makes a wait longer.
         u32x4 cw_next;
         if constexpr (kStaged) {
