@@ -24,6 +24,8 @@
 // one partial y; S6 (combine_kernel) adds the partials.
 #pragma once
 
+#include <type_traits>
+
 #include "floe_dev.h"
 #include "launch.h"
 #include "packed_unit.h"
@@ -299,20 +301,20 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
         FLOE_TL(4);
 
         int k = 0;  // entries pushed so far (wave-uniform)
+        int p0 = 0;
         // Staged codes come back from LDS one pass ahead.  A pass's codes have landed once only the requests made
         // after them are outstanding: kVmPerPass per pass, and kDepth - 1 passes are behind pass p at its own turn,
-        // kDepth - 2 behind pass p + 1 at that time.  The counts are the same in every round because the last round
-        // keeps requesting (see below).  A launch of a single round requests nothing behind it (the compiler would drop the
-        // scales and zeros of such requests and leave their codes, one request per pass instead of three; without them a call on
-        // one expert of d 1024 f 3584 takes 20.0 us instead of 22.5); there
-        // kDepth - 2 - i passes are behind pass i + 1.  More may be outstanding - a store of v, say - which only makes a wait longer.
+        // kDepth - 2 behind pass p + 1 at that time.  The last round requests nothing, so there kDepth - 2 - i passes are
+        // behind pass i + 1.  (It used to repeat the final pass: 8 experts of d 4096 f 14336, one token, 22.54 us against 22.31, and in
+        // single-round kernels the compiler dropped the unread scales and zeros that the counts relied on.)  More may be
+        // outstanding - a store of v, say - which only makes a wait longer.
         u32x4 cw_next;
         if constexpr (kStaged) {
             wait_vm_all_but<kVmPerPass * (kDepth - 1)>();
             lds_piece_request(stage + lane * 16, cw_next);
         }
-#pragma unroll 1
-        for (int p0 = 0; p0 < n_pass; p0 += kDepth) {
+        auto round = [&](auto last, int p0) __attribute__((always_inline)) {
+            constexpr bool kLast = decltype(last)::value;  // (staged codes) nothing is requested behind this round
 #pragma unroll
             for (int i = 0; i < kDepth; ++i) {
                 const int p = p0 + i;
@@ -321,8 +323,8 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
                 if constexpr (kStaged) {
                     lds_piece_arrived(cw_next);
                     ld[i].cw[0] = cw_next.x; ld[i].cw[1] = cw_next.y; ld[i].cw[2] = cw_next.z; ld[i].cw[3] = cw_next.w;
-                    if (kSingleRound ? i + 1 < kDepth : kDepth >= 2) {  // (else past the last pass: a slot that nobody uses)
-                        wait_vm_all_but(kVmPerPass * (kSingleRound ? kDepth - 2 - i : kDepth - 2));
+                    if (kLast ? i + 1 < kDepth : kDepth >= 2) {
+                        wait_vm_all_but(kVmPerPass * (kLast ? kDepth - 2 - i : kDepth - 2));
                         lds_piece_request(stage + ((i + 1) % kDepth) * kSlot + lane * 16, cw_next);
                     }
                 }
@@ -332,14 +334,7 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
                 else asm volatile("" : "+v"(ld[i].sh), "+v"(ld[i].zh));
                 float part = unit_value<BITS, UPC, G32>(ld[i], xs, Xoff, Xg, magic);
                 if constexpr (kStaged) {
-                    // In the last round there is nothing left to request; the slot asks for the final pass again
-                    // (a cache hit that nobody reads) so that every round has the same, unconditional sequence of
-                    // requests: with a condition here the compiler has to assume that no request follows and makes
-                    // each round wait for all of its loads at once.
-                    if constexpr (!kSingleRound) {
-                        const int pn = p + kDepth < n_pass ? p + kDepth : n_pass - 1;
-                        issue(i, pn);
-                    }
+                    if constexpr (!kLast) issue(i, p + kDepth);
                 } else {
                     if (p + kDepth < n_pass) issue(i, p + kDepth);
                 }
@@ -361,6 +356,16 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
                 }
                 __builtin_amdgcn_sched_barrier(0);  // keep the request for pass p + kDepth where it is
             }
+        };
+        if constexpr (kStaged) {
+            if constexpr (!kSingleRound) {
+#pragma unroll 1
+                for (; p0 + kDepth < n_pass; p0 += kDepth) round(std::false_type{}, p0);
+            }
+            round(std::true_type{}, p0);
+        } else {
+#pragma unroll 1
+            for (; p0 < n_pass; p0 += kDepth) round(std::false_type{}, p0);
         }
         if constexpr (kStaged) lds_piece_arrived(cw_next);  // the read-ahead of the last pass: its registers are free only now
         if constexpr (kStaged) wait_vm_all_but<0>();  // the ring lies in the consumers' result slabs: nothing may land later

@@ -1,6 +1,7 @@
-"""The INT2 producer of the fused kernel waits for its direct-to-LDS loads with hand-counted s_waitcnt.  Its single-round kernels
-(seven passes, all in flight) are straight-line code: here the generated assembly is walked with the hardware's rule (loads
-return in the order they were issued) and every read-back of a pass must find that pass's load among the returned ones."""
+"""The INT2 producer of the fused kernel waits for its direct-to-LDS loads with hand-counted s_waitcnt.  Here the
+generated assembly is walked with the hardware's rule (loads return in the order they were issued) and every read-back of a pass
+must find that pass's load among the returned ones: the single-round kernels (seven passes, all in flight), and the others over
+one round with requests and the last one without."""
 import os
 import re
 import subprocess
@@ -28,7 +29,7 @@ def late_read_backs(lines):
         elif s.startswith("s_waitcnt") and "vmcnt(" in s:
             landed = max(landed, issued - int(re.search(r"vmcnt\((\d+)\)", s).group(1)))
         elif in_asm and s.startswith("ds_read_b128"):
-            if reads < 7 and requests[reads] > landed:
+            if requests[reads] > landed:
                 bad.append(reads)
             reads += 1
     return bad, reads
@@ -36,11 +37,11 @@ def late_read_backs(lines):
 
 def check(asm):
     seen = 0
-    for m in re.finditer(r"^(_ZN4floe16fused_ffn_kernelILi2E\w*Li7ELi7EE\w+):(.*?)^\.Lfunc_end", asm, re.M | re.S):
-        body = m.group(2).split("\n")
+    for m in re.finditer(r"^(_ZN4floe16fused_ffn_kernelILi2E\w*Li(7|448)ELi(\d+)EE\w+):(.*?)^\.Lfunc_end", asm, re.M | re.S):
+        body = m.group(4).split("\n")
         first = next(i for i, l in enumerate(body) if "global_load_lds_dwordx4" in l)
         bad, reads = late_read_backs(body[first:])
-        assert reads >= 7, (m.group(1), reads)
+        assert reads == int(m.group(3)) * (1 if m.group(2) == "7" else 2), (m.group(1), reads)
         assert not bad, (m.group(1), "read back too early: passes", bad)
         seen += 1
     return seen
@@ -52,4 +53,4 @@ def test_every_pass_has_landed_before_it_is_read_back(tmp_path):
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc", "-Xclang", "-target-feature",
                     "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument", "-S", "--cuda-device-only",
                     os.path.join(CSRC, "fused_int2.hip"), "-o", str(out)], check=True)
-    assert check(out.read_text()) >= 6
+    assert check(out.read_text()) == 36
