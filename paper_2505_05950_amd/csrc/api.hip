@@ -91,7 +91,7 @@ TaskMap single_map(const floe_expert* e) {
 // workspace of the one-expert entry points: [v: T*f floats][mask words][counts][idx when not fused][partial: T*nblk*d floats]
 struct ExpertWs {
     size_t v_off, mask_off, count_off, idx_off, partial_off, total;
-    size_t table_off, order_off, wgroups_off, xfrag_off, urow_off, ucount_off, hbuf_off, hexp_off, trows_off;  // wide path
+    size_t table_off, order_off, wgroups_off, xfrag_off, urow_off, ucount_off, hbuf_off, hmax_off, trows_off;  // wide path
     int nblk, fused_passes, nblk_fused;
     bool wide;  // many tokens: one read of every row that any of a group of tokens selected (wide_batch.hip)
     WidePlan wp;
@@ -118,7 +118,7 @@ ExpertWs expert_ws(const floe_shape* s, int T) {
         w.urow_off = o;    o += align_up((size_t)w.wp.max_groups * s->f * 4);
         w.ucount_off = o;  o += align_up((size_t)w.wp.max_groups * 4);
         w.hbuf_off = o;    o += align_up((size_t)w.wp.max_groups * w.wp.pairs * w.wp.nt * 128 * sizeof(uint4));
-        w.hexp_off = o;    o += align_up((size_t)w.wp.max_groups * w.wp.pairs * 4);
+        w.hmax_off = o;    o += align_up((size_t)T * 4);
         w.trows_off = o;   o += align_up((size_t)T * sizeof(int2));
     }
     const size_t rows = (size_t)T * nblk_alloc;
@@ -133,7 +133,7 @@ bool mask_path_ok(int f) { return mask_words_per_task(f) <= 2048; }
 // workspace of the layer: per-task table, counts, mask words, v, idx, partial
 struct LayerWs {
     size_t table_off, expert_off, weight_off, tau_off, logit_off, count_off, mask_off, groups_off, ngroups_off, order_off, v_off, idx_off,
-        rows_off, missidx_off, missrows_off, misscount_off, wgroups_off, xfrag_off, urow_off, ucount_off, hbuf_off, hexp_off, trows_off, partial_off, total;
+        rows_off, missidx_off, missrows_off, misscount_off, wgroups_off, xfrag_off, urow_off, ucount_off, hbuf_off, hmax_off, trows_off, partial_off, total;
     int n_tasks, nblk, nblk_fused, fused_passes;
     bool batch_mfma;  // tokens of an expert share one pass over its codes (matrix-core up GEMV)
     bool use_wide;    // batches: one read of every row an expert group selected, on the matrix cores (wide_batch.hip)
@@ -196,7 +196,7 @@ LayerWs layer_plan(const floe_layer* L, int T, int max_down) {
     w.urow_off = o;    o += align_up(wgroups * L->s.f * 4);
     w.ucount_off = o;  o += align_up(wgroups * 4);
     w.hbuf_off = o;    o += align_up(wgroups * w.wp.pairs * w.wp.nt * 128 * sizeof(uint4));
-    w.hexp_off = o;    o += align_up(wgroups * w.wp.pairs * 4);
+    w.hmax_off = o;    o += w.use_wide ? align_up((size_t)w.n_tasks * 4) : 0;
     w.trows_off = o;   o += w.use_wide ? align_up((size_t)w.n_tasks * sizeof(int2)) : 0;
     w.partial_off = o;
     o += w.use_wide ? align_up(w.wp.partial_rows * L->s.d * 4) : align_up((size_t)w.n_tasks * nblk_alloc * L->s.d * 4);
@@ -464,7 +464,7 @@ int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, cons
         wa.urow = reinterpret_cast<int32_t*>(base + w.urow_off);
         wa.ucount = reinterpret_cast<int32_t*>(base + w.ucount_off);
         wa.hbuf = reinterpret_cast<uint4*>(base + w.hbuf_off);
-        wa.hexp = reinterpret_cast<int32_t*>(base + w.hexp_off);
+        wa.hmax = reinterpret_cast<uint32_t*>(base + w.hmax_off);
         wa.task_rows = reinterpret_cast<int2*>(base + w.trows_off);
         wa.partial = partial;
         wa.slots = 1; wa.f = e->s.f;
@@ -702,7 +702,7 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
             wa.urow = reinterpret_cast<int32_t*>(base + w.urow_off);
             wa.ucount = reinterpret_cast<int32_t*>(base + w.ucount_off);
             wa.hbuf = reinterpret_cast<uint4*>(base + w.hbuf_off);
-            wa.hexp = reinterpret_cast<int32_t*>(base + w.hexp_off);
+            wa.hmax = reinterpret_cast<uint32_t*>(base + w.hmax_off);
             wa.task_rows = reinterpret_cast<int2*>(base + w.trows_off);
             wa.partial = partial;
             wa.slots = slots; wa.f = L->s.f;

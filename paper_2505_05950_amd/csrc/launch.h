@@ -193,8 +193,8 @@ struct WideArgs {
     int32_t* count;           // [n_tasks] selected channels
     int32_t* urow;            // [max_groups][f] union rows, ascending
     int32_t* ucount;          // [max_groups]
-    uint4* hbuf;              // [max_groups][pairs][nt][2][64] h (hi, lo) in lane order
-    int32_t* hexp;            // [max_groups][pairs] power of two the pair's h was divided by
+    uint4* hbuf;              // [max_groups][pairs][nt][2][64] h (four floats: rows of a 16-row tile) in lane order
+    uint32_t* hmax;           // [n_tasks] bits of the largest finite |h| of task order[i]
     int2* task_rows;          // [n_tasks] first partial row, number of partial rows (chunk rows apart)
     float* partial;           // [partial_rows][d]
     int32_t slots, f;

@@ -7,11 +7,13 @@
 //   gate_wide_kernel   A[row][token] = gate_row . x_token.  A wave takes a pair of 16-row tiles; the rows stream from memory
 //                      straight into the registers that feed the matrix cores (two slices of 128 columns in flight, 16 KB
 //                      per wave), the group's activations pass through LDS in slices of 128 columns shared by the eight
-//                      waves.  h = SiLU(A) * v * weight where |v| > tau, else 0, leaves as two fp16 numbers (h = hi + lo)
-//                      in the lane order of the down kernel's operand.
+//                      waves.  h = SiLU(A) * v * weight where |v| > tau, else 0, leaves in fp32 in the lane order of the
+//                      down kernel's operand, and the largest |h| of each task beside it.
 //   down_wide_kernel   Y[token][col] += h[token][row] * down[row][col].  A workgroup owns 512 output columns and a range of
 //                      row pairs; a lane fetches 8-byte pieces of eight rows per pair (four pairs in flight), a register
-//                      transpose (v_perm_b32) makes the operand, h passes through LDS.
+//                      transpose (v_perm_b32) makes the operand.  h passes through LDS as two fp16 numbers (hi + lo),
+//                      scaled by a power of two of the token's own that brings its largest |h| to [2^14, 2^15): relative
+//                      to that the split is good to 2^-23, whatever the size of h, and no token depends on another.
 //   combine_wide       adds a task's partial results.
 //
 // Division of work: the row pairs of all groups form one sequence; the workgroups cut it into equal pieces, whatever the
@@ -110,6 +112,7 @@ __global__ __launch_bounds__(1024) void wide_rows_kernel(WideArgs a, const uint3
         c = __builtin_amdgcn_readlane(wave_inclusive_scan(c, lane), kWave - 1);
         if (lane == 0) {
             a.count[task] = c;
+            a.hmax[grp.first + i] = 0u;
             a.task_rows[task] = make_int2(0, 0);  // filled in by the down kernel unless the group has no rows at all
         }
     }
@@ -152,6 +155,7 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
     __shared__ uint4 xs[2][kTok * 16];  // [token][16 pieces], piece p of token t at position p ^ (t & 15)
     __shared__ int s_task[kTok];
     __shared__ float s_w[kTok], s_tau[kTok];
+    __shared__ uint32_t s_hmax[kTok];  // bits of the largest finite |h| of this workgroup's rows (ordered like the numbers)
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int l16 = lane & 15, q4 = lane >> 4;
@@ -180,6 +184,7 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
             s_task[tid] = task;
             s_w[tid] = a.task_scale ? a.task_scale[task] : 1.0f;
             s_tau[tid] = a.task_tau[task];
+            s_hmax[tid] = 0u;
         }
         __syncthreads();
         const h16* xp[kRounds];
@@ -293,7 +298,6 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
                 }
             int tok0 = l16;
             asm volatile("" : "+v"(tok0));  // or the addresses below are formed ahead of the loop and held across it
-            bool big = false;
             constexpr int kBatch = NT < 4 ? NT : 4;  // token tiles whose v are requested together
 #pragma unroll
             for (int n0 = 0; n0 < NT; n0 += kBatch) {
@@ -310,6 +314,7 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
                 for (int n = n0; n < n0 + kBatch && n < NT; ++n) {
                     const float w = s_w[16 * n + tok0], tau = s_tau[16 * n + tok0];
                     const bool live = 16 * n + tok0 < grp.n;
+                    uint32_t top = 0u;
 #pragma unroll
                     for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -317,51 +322,22 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
                             const float v = vv[n - n0][t][i];
                             const bool keep = live && row[t][i] >= 0 && fabsf(v) > tau;
                             const float h = keep ? silu(acc[t][n][i]) * v * w : 0.0f;
-                            big |= !(fabsf(h) <= 32768.0f);
                             acc[t][n][i] = h;
+                            const uint32_t m = __builtin_bit_cast(uint32_t, h) & 0x7FFFFFFFu;
+                            top = max(top, m < 0x7F800000u ? m : 0u);
                         }
+                    atomicMax(&s_hmax[16 * n + tok0], top);  // (no result wanted: fire and forget)
                 }
             }
-            // h beyond fp16's range: the pair is stored scaled down by a power of two, which the down kernel undoes
-            int e = 0;
-            if (__ballot(big)) {
-                float m = 0.0f;
-#pragma unroll
-                for (int n = 0; n < NT; ++n)
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const float h = fabsf(acc[t][n][i]);
-                            m = h < 3.0e38f ? fmaxf(m, h) : m;
-                        }
-                m = wave_allreduce_max_nonneg(m);
-                e = m > 32768.0f ? ilogbf(m) - 14 : 0;
-            }
-            const float sc = ldexpf(1.0f, -e);
             uint4* hb = a.hbuf + ((size_t)g * pmax + pair) * (NT * 128) + lane;
 #pragma unroll
-            for (int n = 0; n < NT; ++n) {
-                uint32_t hi[4], lo[4];
+            for (int n = 0; n < NT; ++n)
 #pragma unroll
-                for (int t = 0; t < 2; ++t)
-#pragma unroll
-                    for (int p = 0; p < 2; ++p) {
-                        h16 hh[2], hl[2];
-#pragma unroll
-                        for (int i = 0; i < 2; ++i) {
-                            const float h = acc[t][n][2 * p + i] * sc;
-                            hh[i] = (h16)h;
-                            hl[i] = fabsf(h) <= 65504.0f ? (h16)(h - (float)hh[i]) : (h16)0.0f;  // infinite or NaN: hi says it all
-                        }
-                        hi[2 * t + p] = as_u32(h16x2{hh[0], hh[1]});
-                        lo[2 * t + p] = as_u32(h16x2{hl[0], hl[1]});
-                    }
-                hb[n * 128] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
-                hb[n * 128 + 64] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
-            }
-            if (lane == 0) a.hexp[(size_t)g * pmax + pair] = e;
+                for (int t = 0; t < 2; ++t) hb[n * 128 + t * 64] = __builtin_bit_cast(uint4, acc[t][n]);
         }
+        __syncthreads();
+        // a maximum does not depend on the order in which the workgroups of a group arrive
+        if (tid < grp.n) atomicMax(&a.hmax[grp.first + tid], s_hmax[tid]);
     }
 }
 
@@ -377,7 +353,8 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
     constexpr int kRing = 4;                              // slices of row ids kept
     constexpr int kHRounds = SL * NT * 128 / kWideThreads;
     static_assert(SL * NT * 128 % kWideThreads == 0, "slice split");
-    __shared__ uint4 hs[2][SL * NT * 128];
+    __shared__ uint4 hs[2][SL * NT * 128];  // [pair][token tile][hi, lo][lane]
+    __shared__ float s_scale[kTok], s_back[kTok];  // the token's power of two and its reciprocal
     __shared__ __align__(16) int ids[kRing][SL * kPairRows];
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -413,53 +390,45 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
             if (tid < grp.n) a.task_rows[a.order[grp.first + tid]] = make_int2(grp.first + tid + w_first * kTok, slots);
         }
         const unsigned char* hsrc = scalar_ptr(a.hbuf + ((size_t)g * pmax + seg0) * (NT * 128));
-        const int32_t* esrc = a.hexp + (size_t)g * pmax + seg0;
         const int ns = (len + SL - 1) / SL;
         uint4 hq[kHRounds];
-        int idq = 0, exq = 0;
+        int idq = 0;
         // (requests are unconditional, as in the gate kernel: past the end they repeat a valid entry and the value is
         // replaced by zero on its way into LDS)
-        auto load_h = [&](int s) {  // h (and exponents) of slice s
+        auto load_h = [&](int s) {  // h of slice s
 #pragma unroll
             for (int r = 0; r < kHRounds; ++r) {
                 const int i = tid + r * kWideThreads;
                 const int pr = min(s * SL + i / (NT * 128), len - 1);
                 hq[r] = gload16(hsrc + (uint32_t)(pr * (NT * 128) + i % (NT * 128)) * 16u);
             }
-            exq = (int)gload4(esrc + min(s * SL + (tid & (SL - 1)), len - 1));
         };
-        // Into LDS; returns the power of two the slice's h stand divided by (never less than e_now).  It is 0, and so is
-        // every pair's, unless some h left fp16's range.
-        auto store_h = [&](int s, int e_now) {
-            const int e_mine = s * SL + (tid & (SL - 1)) < len ? exq : e_now;
-            int e = e_now;
-            if (__builtin_expect(__ballot(e_mine != e_now) != 0ull, 0)) {
-                int m = max(e_mine, e_now);
-#pragma unroll
-                for (int o = 1; o < SL; o <<= 1) m = max(m, __shfl_xor(m, o, kWave));
-                e = __builtin_amdgcn_readfirstlane(m);
-#pragma unroll
-                for (int r = 0; r < kHRounds; ++r) {
-                    const int pr = (tid + r * kWideThreads) / (NT * 128);
-                    const h16 f = (h16)ldexpf(1.0f, __shfl(e_mine, pr, kWave) - e);  // (0 below 2^-24: beneath fp32 next to e)
-                    const h16x2 f2 = {f, f};
-                    hq[r].x = as_u32(as_h2(hq[r].x) * f2); hq[r].y = as_u32(as_h2(hq[r].y) * f2);
-                    hq[r].z = as_u32(as_h2(hq[r].z) * f2); hq[r].w = as_u32(as_h2(hq[r].w) * f2);
-                }
-            }
+        auto store_h = [&](int s) {  // into LDS as hi + lo
 #pragma unroll
             for (int r = 0; r < kHRounds; ++r) {
-                const int i = tid + r * kWideThreads;
+                const int i = tid + r * kWideThreads;  // (pair and token tile, half t of the pair's rows, lane)
                 const bool live = s * SL + i / (NT * 128) < len;
-                hs[s & 1][i] = live ? hq[r] : make_uint4(0u, 0u, 0u, 0u);
+                const float scale = s_scale[16 * (i % (NT * 128) / 128) + l16];
+                const uint32_t w[4] = {hq[r].x, hq[r].y, hq[r].z, hq[r].w};
+                h16 hi[4], lo[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float h = live ? __builtin_bit_cast(float, w[k]) * scale : 0.0f;
+                    hi[k] = (h16)h;
+                    lo[k] = fabsf(h) <= 65504.0f ? (h16)(h - (float)hi[k]) : (h16)0.0f;  // infinite or NaN: hi says it all
+                }
+                uint2* out = reinterpret_cast<uint2*>(&hs[s & 1][(i / 128) * 128 + (i & 63)]) + ((i >> 6) & 1);
+                out[0] = make_uint2(as_u32(h16x2{hi[0], hi[1]}), as_u32(h16x2{hi[2], hi[3]}));
+                out[2 * 64] = make_uint2(as_u32(h16x2{lo[0], lo[1]}), as_u32(h16x2{lo[2], lo[3]}));
             }
-            return e;
         };
         auto load_ids = [&](int s) {
             idq = (int)gload4(rows + min((seg0 + s * SL) * kPairRows + (tid & (SL * kPairRows - 1)), count - 1));
         };
         auto store_ids = [&](int s) {
-            if (tid < SL * kPairRows) ids[s & (kRing - 1)][tid] = idq;
+            int k = tid;
+            asm volatile("" : "+v"(k));  // or the address is formed ahead of the loop and spilled: its reload waits for every request
+            if (k < SL * kPairRows) ids[s & (kRing - 1)][k] = idq;
         };
         uint2 dq[SL][8];
         auto load_d = [&](uint2 (&q)[8], int s, int p) {
@@ -474,15 +443,20 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
         for (int j = 0; j < 4; ++j)
 #pragma unroll
             for (int n = 0; n < NT; ++n) acc[j][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-        int e_acc = 0;
 
         __syncthreads();  // the previous group's LDS contents are no longer read
         load_ids(0);
+        const uint32_t m = a.hmax[grp.first + (tid < grp.n ? tid : 0)];
         load_h(0);
+        if (tid < kTok) {
+            const int e = max((int)(m >> 23) - 141, -126);  // |h| < 2^(e + 15); both powers below stay normal numbers
+            s_scale[tid] = __builtin_bit_cast(float, (uint32_t)(127 - e) << 23);
+            s_back[tid] = __builtin_bit_cast(float, (uint32_t)(127 + e) << 23);
+        }
         store_ids(0);
         load_ids(1);
-        int e_next = store_h(0, 0);
-        e_acc = e_next;
+        __syncthreads();
+        store_h(0);
         store_ids(1);
         __syncthreads();
 #pragma unroll
@@ -493,14 +467,6 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
 #pragma unroll 1
         for (int s = 0; s < ns; ++s) {
             const int buf = s & 1;
-            {   // 1 unless h left fp16's range in this slice (multiplied always: a branch here doubles the accumulators' registers)
-                const float m = ldexpf(1.0f, e_acc - e_next);
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int n = 0; n < NT; ++n) acc[j][n] *= m;
-                e_acc = e_next;
-            }
             load_h(s + 1);
             load_ids(s + 2);
 #pragma unroll
@@ -529,12 +495,11 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
                 load_d(dq[p], s + 1, p);  // (past the last slice: ids repeat the last row, cache hits that nobody uses)
                 __builtin_amdgcn_sched_barrier(0);
             }
-            e_next = store_h(s + 1, e_acc);
+            store_h(s + 1);
             store_ids(s + 2);
             __syncthreads();
         }
         // lane (l16, q4) holds Y[token 16 n + 4 q4 + i][columns col .. col + 3]
-        const float back = ldexpf(1.0f, e_acc);
         float* out = a.partial + ((size_t)grp.first + (size_t)piece * kTok) * d + col;
         int tok0 = 4 * q4;
         asm volatile("" : "+v"(tok0));  // or the addresses below are formed ahead of the loop and spilled across it
@@ -544,6 +509,7 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
             for (int i = 0; i < 4; ++i) {
                 const int tok = 16 * n + tok0 + i;
                 if (tok < grp.n) {
+                    const float back = s_back[tok];
                     float* o = out + (size_t)tok * d;
                     *reinterpret_cast<float4*>(o) = make_float4(acc[0][n][i] * back, acc[1][n][i] * back, acc[2][n][i] * back, acc[3][n][i] * back);
                 }

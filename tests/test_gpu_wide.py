@@ -140,3 +140,47 @@ def test_one_pass_per_task_stays_a_choice():
     assert size[1] < size[0]
     assert (stats[0][:, :, 1] - stats[1][:, :, 1]).abs().max() <= 1      # (a channel at the threshold)
     assert G.rel_err(y[1], y[0]) <= 5e-3
+
+
+def _one_expert(seed, d, f, bits, group, x, pct, out_scale, ex=None):
+    """floe_expert_ffn_sparse on x and its value in 64 bits -> (y [T][d] fp32, reference, expert)."""
+    import gpu_common as G
+    import paper_2505_05950_amd as F
+    ex_np, ex_dev = ex if ex is not None else G.make_expert(*S.expert_weights(seed, 3, d, f), bits, group)
+    T = x.shape[0]
+    tau, ref = np.zeros((T,), np.float32), np.zeros((T, d))
+    for t in range(T):
+        v = O.up_gemv(*ex_np[:3], d, bits, group, x[t])
+        tau[t], _ = G.tau_in_widest_gap(v, pct)
+        ref[t] = float(out_scale[t]) * O.sparse_ffn(ex_np[3], x[t], v, O.select(v, float(tau[t])))[1]
+    y = F.floe_expert_ffn_sparse(ex_dev, G.dev(x), G.dev(tau), G.dev(out_scale), torch.zeros((T, d), dtype=torch.float32, device=G.DEV),
+                                 want_list=False)[0]
+    return y.cpu().numpy().astype(np.float64), ref, (ex_np, ex_dev)
+
+
+# y is fp32 and so is everything it is made of: sums of about d products for v and the gate, of a few hundred for y, 2^-24 a
+# step, which adds up to about 1e-6 of y whatever its size.  Four times that.
+FP32_BAR = 5e-6
+
+
+@pytest.mark.parametrize("x_scale,out_scale", [(1.0, 1.0), (1.0, 1e-3), (1e-3, 1.0), (1.0, 1e-6), (1e-3, 1e-6), (1e-6, 1.0), (100.0, 1e5)])
+@pytest.mark.parametrize("d,f,bits,group,T", [(1024, 1500, 2, 64, 17), (512, 900, 4, 64, 130)])   # two token tiles, ten
+def test_small_and_large_results_keep_fp32_precision(d, f, bits, group, T, x_scale, out_scale):
+    import gpu_common as G
+    x = (S.tokens(95, 3, T, d).astype(np.float32) * x_scale).astype(np.float16)
+    scale = (out_scale * np.linspace(0.5, 1.5, T)).astype(np.float32)
+    y, ref, _ = _one_expert(95, d, f, bits, group, x, 70, scale)
+    err = max(G.rel_err(y[t], ref[t]) for t in range(T))
+    assert err <= FP32_BAR, err
+
+
+@pytest.mark.parametrize("d,f,bits,group,T", [(1024, 1500, 2, 64, 20), (512, 900, 4, 64, 130)])
+def test_a_token_with_huge_activations_costs_the_others_nothing(d, f, bits, group, T):
+    import gpu_common as G
+    x = S.tokens(96, 3, T, d).astype(np.float32)
+    x[3] *= 2e4 / np.abs(x[3]).max()       # |h| ~ 1e7
+    scale = np.ones((T,), np.float32)
+    scale[3] = 1e4
+    y, ref, _ = _one_expert(96, d, f, bits, group, x.astype(np.float16), 70, scale)
+    err = [G.rel_err(y[t], ref[t]) for t in range(T)]
+    assert max(err) <= FP32_BAR, (int(np.argmax(err)), max(err))
