@@ -404,9 +404,12 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
             }
         };
         auto store_h = [&](int s) {  // into LDS as hi + lo
+            int at = tid;  // (entry i of the slice: pair and token tile i / 128, half (i >> 6) & 1 of the pair's rows, lane)
+            asm volatile("" : "+v"(at));  // or the addresses are formed ahead of the loop and spilled: a reload waits for every request
+            uint2* out0 = reinterpret_cast<uint2*>(&hs[s & 1][(at / 128) * 128 + (at & 63)]) + ((at >> 6) & 1);
 #pragma unroll
             for (int r = 0; r < kHRounds; ++r) {
-                const int i = tid + r * kWideThreads;  // (pair and token tile, half t of the pair's rows, lane)
+                const int i = tid + r * kWideThreads;
                 const bool live = s * SL + i / (NT * 128) < len;
                 const float scale = s_scale[16 * (i % (NT * 128) / 128) + l16];
                 const uint32_t w[4] = {hq[r].x, hq[r].y, hq[r].z, hq[r].w};
@@ -417,7 +420,7 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
                     hi[k] = (h16)h;
                     lo[k] = fabsf(h) <= 65504.0f ? (h16)(h - (float)hi[k]) : (h16)0.0f;  // infinite or NaN: hi says it all
                 }
-                uint2* out = reinterpret_cast<uint2*>(&hs[s & 1][(i / 128) * 128 + (i & 63)]) + ((i >> 6) & 1);
+                uint2* out = out0 + r * kWideThreads * 2;
                 out[0] = make_uint2(as_u32(h16x2{hi[0], hi[1]}), as_u32(h16x2{hi[2], hi[3]}));
                 out[2 * 64] = make_uint2(as_u32(h16x2{lo[0], lo[1]}), as_u32(h16x2{lo[2], lo[3]}));
             }
@@ -501,6 +504,7 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
         }
         // lane (l16, q4) holds Y[token 16 n + 4 q4 + i][columns col .. col + 3]
         float* out = a.partial + ((size_t)grp.first + (size_t)piece * kTok) * d + col;
+        float odd = 0.0f;  // NaN once a sum is not finite
         int tok0 = 4 * q4;
         asm volatile("" : "+v"(tok0));  // or the addresses below are formed ahead of the loop and spilled across it
 #pragma unroll
@@ -511,9 +515,39 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
                 if (tok < grp.n) {
                     const float back = s_back[tok];
                     float* o = out + (size_t)tok * d;
-                    *reinterpret_cast<float4*>(o) = make_float4(acc[0][n][i] * back, acc[1][n][i] * back, acc[2][n][i] * back, acc[3][n][i] * back);
+                    const float4 y = make_float4(acc[0][n][i] * back, acc[1][n][i] * back, acc[2][n][i] * back, acc[3][n][i] * back);
+                    *reinterpret_cast<float4*>(o) = y;
+                    odd = fmaf(y.x, 0.0f, fmaf(y.y, 0.0f, fmaf(y.z, 0.0f, fmaf(y.w, 0.0f, odd))));
                 }
             }
+        // A row that a token did not select entered its sums as h = 0, and 0 times a weight that is not finite is NaN.  Such
+        // sums, seen here by their results, are formed again from the token's own rows alone.
+        if (__ballot(!(odd == 0.0f)) == 0ull) continue;
+        const float* hp = reinterpret_cast<const float*>(hsrc);
+#pragma unroll 1
+        for (int k = 0; k < 4 * NT; ++k) {
+            const int n = k >> 2, tok = 16 * n + 4 * q4 + (k & 3);
+            if (tok >= grp.n) continue;
+            float4* o = reinterpret_cast<float4*>(out + (size_t)tok * d);
+            const float4 y = *o;
+            if (fmaf(y.x, 0.0f, fmaf(y.y, 0.0f, fmaf(y.z, 0.0f, y.w * 0.0f))) == 0.0f) continue;
+            const int task = a.order[grp.first + tok];
+            const float* vt = a.v + (size_t)task * a.f;
+            const float tau = a.task_tau[task];
+            float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int r = seg0 * kPairRows, last = min(count, seg1 * kPairRows); r < last; ++r) {
+                const int row = rows[r], p = r / kPairRows - seg0, in = r % kPairRows;
+                if (!(fabsf(vt[row]) > tau)) continue;
+                const float h = hp[((size_t)(p * NT + n) * 128 + (in >> 4) * 64 + ((in >> 2) & 3) * 16 + (tok & 15)) * 4 + (in & 3)];
+                const uint2 w = gload8(gd + ((uint32_t)row * (uint32_t)(4 * d) + dcol));
+                const h16x2 lo = as_h2(w.x), hi = as_h2(w.y);
+                s.x = fmaf(h, (float)lo.x, s.x);
+                s.y = fmaf(h, (float)lo.y, s.y);
+                s.z = fmaf(h, (float)hi.x, s.z);
+                s.w = fmaf(h, (float)hi.y, s.w);
+            }
+            *o = s;
+        }
     }
 }
 

@@ -184,3 +184,28 @@ def test_a_token_with_huge_activations_costs_the_others_nothing(d, f, bits, grou
     y, ref, _ = _one_expert(96, d, f, bits, group, x.astype(np.float16), 70, scale)
     err = [G.rel_err(y[t], ref[t]) for t in range(T)]
     assert max(err) <= FP32_BAR, (int(np.argmax(err)), max(err))
+
+
+@pytest.mark.parametrize("d,f,bits,group,T", [(1024, 700, 2, 64, 20), (512, 900, 4, 64, 130)])
+def test_a_weight_that_is_not_finite_reaches_only_the_tokens_that_select_its_row(d, f, bits, group, T):
+    """Rows that a token did not select meet it as h = 0 in the matrix product, and rows past the end of a pair repeat the last
+    one: 0 times infinity must not show."""
+    import gpu_common as G
+    w_up, gd = S.expert_weights(97, 3, d, f)
+    gd = gd.copy()
+    gd[f - 1, 1, 5] = np.inf               # the last row (of the last pair, where some token selects it)
+    gd[f // 2, 1, :] = -np.inf
+    gd[f // 3, 1, d - 1] = np.nan
+    gd[7, 0, 3] = np.inf                   # a gate column: the channel's own h only
+    ex = G.make_expert(w_up, gd, bits, group)
+    x = S.tokens(97, 3, T, d)
+    with np.errstate(invalid="ignore"):
+        y, ref, _ = _one_expert(97, d, f, bits, group, x, 70, np.ones((T,), np.float32), ex=ex)
+    clean = np.isfinite(ref).all(axis=1)
+    assert 2 <= clean.sum() <= T - 2
+    for t in range(T):
+        fin = np.isfinite(ref[t])
+        wrong = np.flatnonzero((np.isfinite(y[t]) != fin) | (np.isnan(y[t]) != np.isnan(ref[t])) | (np.isinf(ref[t]) & (y[t] != ref[t])))
+        assert wrong.size == 0, (t, wrong.size, wrong[:8])
+        if fin.any():
+            assert G.rel_err(y[t][fin], ref[t][fin]) <= FP32_BAR, t
