@@ -97,7 +97,7 @@ struct ExpertWs {
     WidePlan wp;
 };
 bool mask_path_ok(int f);
-ExpertWs expert_ws(const floe_shape* s, int T) {
+ExpertWs expert_ws(const floe_shape* s, int T, bool may_go_wide = true) {
     ExpertWs w{};
     w.nblk = gd_blocks(T, s->f);
     w.fused_passes = packed_fast_shape(s->d, s->bits, s->group) ? fused_passes(s->d, s->f, s->bits, T) : 0;
@@ -108,7 +108,7 @@ ExpertWs expert_ws(const floe_shape* s, int T) {
     w.mask_off = o;    o += align_up((size_t)T * mask_words_per_task(s->f) * sizeof(uint32_t));
     w.count_off = o;   o += align_up((size_t)T * (w.nblk_fused > 1 ? w.nblk_fused : 1) * sizeof(int32_t));
     w.idx_off = o;     o += w.fused_passes ? 0 : align_up((size_t)T * s->f * sizeof(int32_t));  // list for callers that pass none
-    w.wide = !w.fused_passes && T >= 2 && mask_path_ok(s->f) && union_kernels_for(1, T, s->d, s->f) == 1;
+    w.wide = may_go_wide && !w.fused_passes && T >= 2 && mask_path_ok(s->f) && union_kernels_for(1, T, s->d, s->f) == 1;
     if (w.wide) {
         w.wp = wide_plan(s->d, s->f, T, 1, 1, 0, 0);
         w.table_off = o;   o += align_up(sizeof(DevExpert));
@@ -391,7 +391,7 @@ int floe_gate_down_sparse(const floe_expert* e, const floe_half* x, int T, const
     if (!aligned(e->gd, 16) || !aligned(x, 16) || !aligned(y_acc, 16) || !aligned(workspace, kAlign)) return FLOE_EINVAL;
     if (e->gd_is_staged && (T > 1 || e->gd_rows < 0)) return FLOE_EINVAL;
     if (!e->gd_is_staged && e->gd_rows != e->s.f) return FLOE_EINVAL;
-    const ExpertWs w = expert_ws(&e->s, T);
+    const ExpertWs w = expert_ws(&e->s, T, false);  // (the lists exist: nothing of the wide path runs here)
     if (workspace_bytes < w.total) return FLOE_EWORKSPACE;
     float* partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.partial_off);
     hipStream_t st = (hipStream_t)stream;

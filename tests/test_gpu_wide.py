@@ -209,3 +209,26 @@ def test_a_weight_that_is_not_finite_reaches_only_the_tokens_that_select_its_row
         assert wrong.size == 0, (t, wrong.size, wrong[:8])
         if fin.any():
             assert G.rel_err(y[t][fin], ref[t][fin]) <= FP32_BAR, t
+
+
+def test_gate_down_on_existing_lists_needs_no_wide_workspace():
+    """floe_gate_down_sparse runs the one-token kernels at every batch size: their workspace is enough."""
+    import gpu_common as G
+    import paper_2505_05950_amd as F
+    d, f, bits, group, T = 1024, 700, 2, 64, 24
+    _, ex = G.make_expert(*S.expert_weights(98, 3, d, f), bits, group)
+    x = G.dev(S.tokens(98, 3, T, d))
+    wide = F.floe_expert_workspace_bytes(d, f, bits, group, T)
+    F.floe_tuning(F.TUNE_UNION_KERNELS, 3)
+    small = F.floe_expert_workspace_bytes(d, f, bits, group, T)
+    F.floe_tuning(F.TUNE_UNION_KERNELS, 1)
+    assert small < wide
+    v = F.floe_up_gemv(ex.up_codes, ex.up_scale, ex.up_zero, x, d, bits, group)
+    idx, count = F.floe_select_channels(v, torch.full((T,), 1.0, device=G.DEV))
+    y = []
+    for size in (wide, small):
+        buf = torch.empty((size + 256,), dtype=torch.uint8, device=G.DEV)
+        off = (-buf.data_ptr()) % 256
+        y.append(F.floe_gate_down_sparse(ex, x, v, idx, count, None, torch.zeros((T, d), dtype=torch.float32, device=G.DEV),
+                                         workspace=buf[off: off + size]))
+    assert torch.equal(y[0], y[1])
