@@ -252,9 +252,11 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Inputs, outputs, results and
  * error codes are those of floe_moe_layer_decode; the workspace is a scratch array of FLOE_STATIC_SCRATCH_BYTES
  * that is part of the library's device image (each GPU the library runs on holds one copy until the process ends).
- * The call allocates and frees nothing.  Limit: floe_layer_workspace_bytes(L, T) must not exceed
+ * The call allocates and frees nothing.  Limit: a batch fits where floe_layer_workspace_bytes(L, T) does not exceed
  * FLOE_STATIC_SCRATCH_BYTES (ask that function: a Mixtral-shaped layer, d=4096 f=14336 top-2, needs 4.2 MiB per
- * token at T <= 3 and fits again, with other kernels, from T = 9 to about T = 48), otherwise FLOE_EWORKSPACE is
+ * token at T <= 3 and fits again, with other kernels, from T = 9 to about T = 48).  It also fits where kernels that
+ * need less workspace than those of floe_moe_layer_decode do (large batches of small layers); these then run, and the
+ * result is the same up to the order of summation.  Otherwise FLOE_EWORKSPACE is
  * returned and nothing is enqueued.  All calls on one GPU share the array: calls that overlap
  * on one GPU (two streams, two threads) race; calls on one stream are ordered and safe.  No kernel relies on what
  * an earlier call left in the array.

@@ -154,14 +154,16 @@ LayerWs layer_plan(const floe_layer* L, int T, int max_down) {
                          ? fused_passes(L->s.d, L->s.f, L->s.bits, w.n_tasks, fused_task_limit(n_all)) : 0;
     w.nblk_fused = w.fused_passes ? fused_blocks(L->s.d, L->s.f, w.fused_passes) : 0;
     w.chunk = mfma_chunk(n_all, w.n_tasks);
-    w.up = union_plan(L->s.d, L->s.f, w.n_tasks, n_all, w.chunk);
     // the grouped up GEMV: when forced, or where the fused kernel does not apply and grouping pays
     w.batch_mfma = T >= 2 && mfma_grouped_shape(L->s.d, L->s.bits, L->s.group) &&
                    (grouped_gemv_mode() == 1 || (!w.fused_passes && mfma_batch_pays(n_all, w.n_tasks, L->s.bits)));
     const bool share_rows = !L->gd_on_host && T >= 2 && (!w.fused_passes || w.batch_mfma) && mask_path_ok(L->s.f);
     const int kernels = union_kernels_for(n_all, w.n_tasks, L->s.d, L->s.f);
     w.use_wide = share_rows && kernels == 1 && max_down >= 0;
-    w.use_union = share_rows && kernels == 2 && union_shape_ok(L->s.d, L->s.f, w.up);
+    if (share_rows && kernels == 2) {
+        w.up = union_plan(L->s.d, L->s.f, w.n_tasks, n_all, w.chunk);
+        w.use_union = union_shape_ok(L->s.d, L->s.f, w.up);
+    }
     if (w.use_wide) w.wp = wide_plan(L->s.d, L->s.f, T, L->n_experts, L->top_k, L->n_shared, max_down);
     int nblk_alloc = w.nblk > w.nblk_fused ? w.nblk : w.nblk_fused;
     if (w.use_union && w.up.nblk > nblk_alloc) nblk_alloc = w.up.nblk;
@@ -203,19 +205,21 @@ LayerWs layer_plan(const floe_layer* L, int T, int max_down) {
     w.total = o;
     return w;
 }
-// The wide kernels need more workspace per task.  A layer call that fits the library's static scratch with the one-token
-// kernels goes on fitting it: there the wide ones are taken only if they fit as well, with fewer pieces in the down kernel
-// (each costs partial results) as long as these occupy a third of the chip.
-LayerWs layer_ws(const floe_layer* L, int T) {
+LayerWs layer_ws(const floe_layer* L, int T) { return layer_plan(L, T, 0); }
+// The plan of a call whose workspace is `limit` bytes, whatever the batch (the static scratch array); total > limit: none fits.
+// The wide kernels need more workspace per task.  A batch that fits with the one-token kernels keeps fitting: there the wide
+// ones are taken only if they fit as well, with fewer pieces in the down kernel (each costs partial results, and nothing else
+// in the plan depends on their number) as long as these occupy a third of the chip.
+LayerWs layer_fit(const floe_layer* L, int T, size_t limit) {
     LayerWs w = layer_plan(L, T, 0);
-    if (!w.use_wide || w.total <= FLOE_STATIC_SCRATCH_BYTES || union_mode() == 1) return w;
+    if (!w.use_wide || w.total <= limit || union_mode() == 1) return w;
     const LayerWs n = layer_plan(L, T, -1);
-    if (n.total > FLOE_STATIC_SCRATCH_BYTES) return w;
-    for (int pieces = (w.wp.wg_down - 1) & ~7; pieces >= 8 && 3 * pieces * (L->s.d / 512) >= num_cus(); pieces -= 8) {
-        const LayerWs s = layer_plan(L, T, pieces);
-        if (s.total <= FLOE_STATIC_SCRATCH_BYTES) return s;
-    }
-    return n;
+    if (n.total > limit) return w;
+    const size_t row = (size_t)L->s.d * 4, rest = w.partial_off + (size_t)w.n_tasks * row;
+    const size_t rows = rest < limit ? (limit - rest) / row : 0;  // for the pieces after the first
+    const int pieces = (int)(rows / w.wp.chunk + 1) & ~7;
+    if (rest > limit || pieces < 8 || 3 * pieces * (L->s.d / 512) < num_cus()) return n;
+    return layer_plan(L, T, pieces);
 }
 
 int check_layer(const floe_layer* L) {
@@ -602,8 +606,9 @@ size_t floe_layer_workspace_bytes(const floe_layer* L, int T) {
     return layer_ws(L, T).total;
 }
 
-int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_half* y, floe_slot_stat* stats,
-                          void* workspace, size_t workspace_bytes, void* stream) {
+// fit: the plan is made for the workspace given (FLOE_EWORKSPACE where no plan fits it)
+static int layer_decode(const floe_layer* L, const floe_half* x, int T, floe_half* y, floe_slot_stat* stats, void* workspace,
+                        size_t workspace_bytes, bool fit, void* stream) {
     int rc = check_layer(L);
     if (rc) return rc;
     if ((rc = check_T(T))) return rc;
@@ -611,7 +616,7 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
     if (!L->dev_table || !x || !y || !workspace) return FLOE_EINVAL;
     if (L->gd_on_host) return FLOE_EINVAL;  // host-resident gate/down: use floe_moe_layer_decode_offloaded
     if (!aligned(x, 16) || !aligned(y, 8) || !aligned(workspace, kAlign)) return FLOE_EINVAL;
-    const LayerWs w = layer_ws(L, T);
+    const LayerWs w = fit ? layer_fit(L, T, workspace_bytes) : layer_ws(L, T);
     if (workspace_bytes < w.total) return FLOE_EWORKSPACE;
     char* base = static_cast<char*>(workspace);
     DevExpert* task_table = reinterpret_cast<DevExpert*>(base + w.table_off);
@@ -688,7 +693,7 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
         } else if (batch_mfma)
             FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st,
                         launch_up_gemv_grouped(static_cast<const DevExpert*>(L->dev_table), groups, n_groups,
-                                               w.up.max_groups, w.chunk, xh, slots, v, task_tau, mask, L->s.d, L->s.f,
+                                               mfma_max_groups(n_all, w.n_tasks), w.chunk, xh, slots, v, task_tau, mask, L->s.d, L->s.f,
                                                L->s.bits, L->s.group, st));
         else
             FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st,
@@ -780,6 +785,11 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
     if (stats)
         FLOE_HIP(launch_stats(task_expert, count, count_parts, task_weight, reinterpret_cast<SlotStat*>(stats), w.n_tasks, st));
     return FLOE_OK;
+}
+
+int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_half* y, floe_slot_stat* stats,
+                          void* workspace, size_t workspace_bytes, void* stream) {
+    return layer_decode(L, x, T, y, stats, workspace, workspace_bytes, false, stream);
 }
 
 int floe_moe_layer_decode_offloaded(const floe_layer* L, const floe_offload* o, const floe_half* x, int T, floe_half* y,
@@ -1010,3 +1020,13 @@ int floe_stage_channels(const floe_half* host_gd, int d, int f, const int32_t* i
 }
 
 }  // extern "C"
+
+namespace floe {
+
+bool layer_fits(const floe_layer* L, int T, size_t bytes) { return check_layer(L) != FLOE_OK || layer_fit(L, T, bytes).total <= bytes; }
+int layer_decode_within(const floe_layer* L, const floe_half* x, int T, floe_half* y, floe_slot_stat* stats, void* workspace,
+                        size_t workspace_bytes, void* stream) {
+    return layer_decode(L, x, T, y, stats, workspace, workspace_bytes, true, stream);
+}
+
+}  // namespace floe

@@ -1,6 +1,7 @@
 // floe_moe_layer_decode_static: the layer decode for callers that cannot allocate (code under HIP graph capture,
 // tight serving loops, harnesses that forbid hipMalloc).  It is floe_moe_layer_decode run on a scratch array that
-// lives in the library's own device image instead of a caller-supplied workspace.
+// lives in the library's own device image instead of a caller-supplied workspace, with fewer workgroups or other kernels
+// where a large batch would need more than that.
 //
 // One array per GPU, held from the moment the library is loaded on that GPU until the process ends.  In host code
 // the array's name is only a handle: its device address is asked for once per device (with that device current) and
@@ -39,15 +40,20 @@ int static_scratch(void** out) {
 
 }  // namespace
 
+namespace floe {  // api.hip: the layer decode with the plan that fits a workspace of so many bytes
+bool layer_fits(const floe_layer* L, int T, size_t bytes);  // (an invalid layer fits: the call returns its error code)
+int layer_decode_within(const floe_layer* L, const floe_half* x, int T, floe_half* y, floe_slot_stat* stats, void* workspace,
+                        size_t workspace_bytes, void* stream);
+}  // namespace floe
+
 extern "C" int floe_moe_layer_decode_static(const floe_layer* L, const floe_half* x, int T, floe_half* y,
                                             floe_slot_stat* stats, void* stream) {
     if (!L || T < 0) return FLOE_EINVAL;
     if (T == 0) return FLOE_OK;
-    const size_t need = floe_layer_workspace_bytes(L, T);  // 0: the layer description itself is invalid
-    if (need > FLOE_STATIC_SCRATCH_BYTES) return FLOE_EWORKSPACE;  // decided before anything is touched or enqueued
+    if (!floe::layer_fits(L, T, FLOE_STATIC_SCRATCH_BYTES)) return FLOE_EWORKSPACE;  // decided before anything is touched or enqueued
     void* scratch = nullptr;
     const int rc = static_scratch(&scratch);
     if (rc != FLOE_OK) return rc;
     // (an invalid layer comes back from here with its proper error code)
-    return floe_moe_layer_decode(L, x, T, y, stats, scratch, FLOE_STATIC_SCRATCH_BYTES, stream);
+    return floe::layer_decode_within(L, x, T, y, stats, scratch, FLOE_STATIC_SCRATCH_BYTES, stream);
 }

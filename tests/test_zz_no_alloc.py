@@ -58,3 +58,24 @@ def test_static_scratch_entry_point_refuses_what_does_not_fit():
     assert err.value.status == -4
     torch.cuda.synchronize()
     assert bool((y == 7.0).all()), "a refused call must not touch the output"
+
+
+def test_only_the_static_entry_point_plans_for_the_scratch_array():
+    """A batch that fits the array with fewer workgroups only: the static call runs it so, the workspace call as it likes."""
+    import gpu_common as G
+    import paper_2505_05950_amd as F
+    L, T = _layer(F, G, 34, 1024, 3584, 2, 64, 8, 2), 96
+    assert F.floe_layer_workspace_bytes(L, T) > F.STATIC_SCRATCH_BYTES
+    F.floe_tuning(F.TUNE_UNION_KERNELS, 3)
+    fits = F.floe_layer_workspace_bytes(L, T) <= F.STATIC_SCRATCH_BYTES   # ... with the one-token kernels
+    F.floe_tuning(F.TUNE_UNION_KERNELS, 0)
+    assert fits
+    x = G.dev(S.tokens(35, 3, T, 1024))
+    st = [torch.zeros((T, 2, 4), dtype=torch.int32, device=G.DEV) for _ in range(2)]
+    ref = F.floe_moe_layer_decode(L, x, stats=st[0]).float()
+    y = torch.zeros((T, 1024), dtype=torch.float16, device=G.DEV)
+    F.floe_moe_layer_decode_static(L, x, y, st[1])
+    torch.cuda.synchronize()
+    assert torch.equal(st[0], st[1])
+    # two fp16 roundings of sums that differ in order only
+    assert float((y.float() - ref).abs().max() / ref.abs().max()) <= 2.0 ** -10
