@@ -46,7 +46,7 @@ typedef enum {
     FLOE_EINVAL = -1,       /* NULL pointer, negative size, misaligned buffer */
     FLOE_ESHAPE = -2,       /* d % group != 0, (group*bits) % 32 != 0, d % 512 != 0 ... */
     FLOE_EUNSUPPORTED = -3, /* bits not in {1,2,3,4,8}, group not in {32,64,128,256}, d > 8192 ... */
-    FLOE_EWORKSPACE = -4,   /* workspace_bytes smaller than the matching *_workspace_bytes() */
+    FLOE_EWORKSPACE = -4,   /* workspace_bytes too small (never where it is at least the matching *_workspace_bytes()) */
     FLOE_EHIP = -5          /* a HIP runtime call failed (see floe_last_hip_error) */
 } floe_status;
 
@@ -158,7 +158,11 @@ typedef struct {
     int32_t gd_rows;           /* rows actually present in gd (capacity when staged) */
 } floe_expert;
 
-/* Bytes of scratch floe_gate_down_sparse / floe_expert_ffn_sparse need for T tokens of this shape. */
+/*
+ * Bytes of scratch for floe_gate_down_sparse / floe_expert_ffn_sparse on T tokens of this shape.  From the batch size on at which
+ * tokens share the rows they select (FLOE_TUNE_UNION_KERNELS) it does not shrink as T grows: a workspace sized for the largest
+ * batch serves the smaller ones.  With less, down to what one workgroup set per token needs, a call runs that way.
+ */
 size_t floe_expert_workspace_bytes(const floe_shape* s, int T);
 
 /*
@@ -237,6 +241,8 @@ size_t floe_layer_table_bytes(const floe_layer* L);
  * Synchronises `stream` before returning; L->experts is not read by any later call and may be freed. One-time set-up. */
 int floe_layer_build_table(const floe_layer* L, void* dev_table, size_t bytes, void* stream);
 
+/* Bytes of scratch for the layer decode of T tokens; as above for batches whose tokens share rows: it does not shrink as T grows,
+ * and with less workspace such a call runs with fewer workgroups or one workgroup set per (token, slot). */
 size_t floe_layer_workspace_bytes(const floe_layer* L, int T);
 /*
  * x dev [T][d] fp16 -> y dev [T][d] fp16.  Router: logits = x . W_r, softmax, top_k (ties to the lower
@@ -254,8 +260,8 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
  * that is part of the library's device image (each GPU the library runs on holds one copy until the process ends).
  * The call allocates and frees nothing.  Limit: a batch fits where floe_layer_workspace_bytes(L, T) does not exceed
  * FLOE_STATIC_SCRATCH_BYTES (ask that function: a Mixtral-shaped layer, d=4096 f=14336 top-2, needs 4.2 MiB per
- * token at T <= 3 and fits again, with other kernels, from T = 9 to about T = 48).  It also fits where kernels that
- * need less workspace than those of floe_moe_layer_decode do (large batches of small layers); these then run, and the
+ * token at T <= 3 and fits again, with other kernels, from T = 9 on), and also where kernels that need less do: that
+ * layer up to about T = 33.  These then run, as they do in floe_moe_layer_decode with a workspace of that size, and the
  * result is the same up to the order of summation.  Otherwise FLOE_EWORKSPACE is
  * returned and nothing is enqueued.  All calls on one GPU share the array: calls that overlap
  * on one GPU (two streams, two threads) race; calls on one stream are ordered and safe.  No kernel relies on what

@@ -97,7 +97,10 @@ struct ExpertWs {
     WidePlan wp;
 };
 bool mask_path_ok(int f);
-ExpertWs expert_ws(const floe_shape* s, int T, bool may_go_wide = true) {
+// which form of the wide path a plan may take: the one that a call runs, none, or room for any that a batch of up to T
+// tokens can take
+enum class Wide { kChosen, kNone, kRoom };
+ExpertWs expert_ws(const floe_shape* s, int T, Wide form = Wide::kChosen) {
     ExpertWs w{};
     w.nblk = gd_blocks(T, s->f);
     w.fused_passes = packed_fast_shape(s->d, s->bits, s->group) ? fused_passes(s->d, s->f, s->bits, T) : 0;
@@ -107,24 +110,41 @@ ExpertWs expert_ws(const floe_shape* s, int T, bool may_go_wide = true) {
     w.v_off = o;       o += align_up((size_t)T * s->f * sizeof(float));
     w.mask_off = o;    o += align_up((size_t)T * mask_words_per_task(s->f) * sizeof(uint32_t));
     w.count_off = o;   o += align_up((size_t)T * (w.nblk_fused > 1 ? w.nblk_fused : 1) * sizeof(int32_t));
-    w.idx_off = o;     o += w.fused_passes ? 0 : align_up((size_t)T * s->f * sizeof(int32_t));  // list for callers that pass none
-    w.wide = may_go_wide && !w.fused_passes && T >= 2 && mask_path_ok(s->f) && union_kernels_for(1, T, s->d, s->f) == 1;
+    w.wide = form != Wide::kNone && !w.fused_passes && T >= 2 && mask_path_ok(s->f) && union_kernels_for(1, T, s->d, s->f) == 1;
     if (w.wide) {
-        w.wp = wide_plan(s->d, s->f, T, 1, 1, 0, 0);
+        w.wp = form == Wide::kRoom ? wide_room(s->d, s->f, T, 1, 1, 0) : wide_plan(s->d, s->f, T, 1, 1, 0, 0);
         w.table_off = o;   o += align_up(sizeof(DevExpert));
         w.order_off = o;   o += align_up((size_t)T * 4);
         w.wgroups_off = o; o += align_up((size_t)w.wp.max_groups * sizeof(WideGroup) + 4);
         w.xfrag_off = o;   o += align_up(up_wide_scratch_bytes(T, s->d, s->group));
         w.urow_off = o;    o += align_up((size_t)w.wp.max_groups * s->f * 4);
         w.ucount_off = o;  o += align_up((size_t)w.wp.max_groups * 4);
-        w.hbuf_off = o;    o += align_up((size_t)w.wp.max_groups * w.wp.pairs * w.wp.nt * 128 * sizeof(uint4));
+        w.hbuf_off = o;    o += align_up((size_t)w.wp.h_tiles * w.wp.pairs * 128 * sizeof(uint4));
         w.hmax_off = o;    o += align_up((size_t)T * 4);
         w.trows_off = o;   o += align_up((size_t)T * sizeof(int2));
     }
-    const size_t rows = (size_t)T * nblk_alloc;
-    w.partial_off = o; o += align_up((w.wide && w.wp.partial_rows > rows ? w.wp.partial_rows : rows) * s->d * sizeof(float));
+    w.idx_off = o;     o += w.fused_passes || w.wide ? 0 : align_up((size_t)T * s->f * sizeof(int32_t));  // list for callers that pass none
+    w.partial_off = o; o += align_up((w.wide ? w.wp.partial_rows : (size_t)T * nblk_alloc) * s->d * sizeof(float));
     w.total = o;
     return w;
+}
+// What a caller is asked to bring.  The plans of the wide path jump up and down with T (ten token tiles per group at 160 tokens,
+// five at 161); a caller that sizes its workspace once, for its largest batch, has room for the smaller ones, and for the
+// one-token kernels that batches below the wide ones run.
+size_t one_token_rows(int n_tasks, int f) {  // partial results of the one-token kernels, the most of any batch up to n_tasks
+    size_t rows = (size_t)n_tasks * gd_blocks(n_tasks, f);
+    for (int n = n_tasks < 64 ? n_tasks : 64; n > 0; --n) {  // (from 64 on eight blocks each, before that up to 16 of them)
+        const size_t r = (size_t)n * gd_blocks(n, f);
+        rows = r > rows ? r : rows;
+    }
+    return rows;
+}
+size_t expert_bytes(const floe_shape* s, int T) {
+    const ExpertWs w = expert_ws(s, T, Wide::kRoom);
+    if (!w.wide) return w.total;
+    const ExpertWs n = expert_ws(s, T, Wide::kNone);
+    const size_t one_token = n.partial_off + one_token_rows(T, s->f) * s->d * sizeof(float);
+    return w.total > one_token ? w.total : one_token;
 }
 
 // lists longer than this are compacted by the select kernel instead of inside the gate/down kernel
@@ -143,8 +163,8 @@ struct LayerWs {
     UnionPlan up;
     WidePlan wp;
 };
-// max_down: at most so many pieces in the down kernel of the wide path (0: its own choice), -1: no wide path
-LayerWs layer_plan(const floe_layer* L, int T, int max_down) {
+// max_down: at most so many pieces in the down kernel of the wide path (0: its own choice)
+LayerWs layer_plan(const floe_layer* L, int T, Wide form = Wide::kChosen, int max_down = 0) {
     LayerWs w{};
     const int slots = L->top_k + L->n_shared;
     w.n_tasks = T * slots;
@@ -159,16 +179,19 @@ LayerWs layer_plan(const floe_layer* L, int T, int max_down) {
                    (grouped_gemv_mode() == 1 || (!w.fused_passes && mfma_batch_pays(n_all, w.n_tasks, L->s.bits)));
     const bool share_rows = !L->gd_on_host && T >= 2 && (!w.fused_passes || w.batch_mfma) && mask_path_ok(L->s.f);
     const int kernels = union_kernels_for(n_all, w.n_tasks, L->s.d, L->s.f);
-    w.use_wide = share_rows && kernels == 1 && max_down >= 0;
+    w.use_wide = share_rows && kernels == 1 && form != Wide::kNone;
+    const bool room = w.use_wide && form == Wide::kRoom;
     if (share_rows && kernels == 2) {
         w.up = union_plan(L->s.d, L->s.f, w.n_tasks, n_all, w.chunk);
         w.use_union = union_shape_ok(L->s.d, L->s.f, w.up);
     }
-    if (w.use_wide) w.wp = wide_plan(L->s.d, L->s.f, T, L->n_experts, L->top_k, L->n_shared, max_down);
+    if (room) w.wp = wide_room(L->s.d, L->s.f, T, L->n_experts, L->top_k, L->n_shared);
+    else if (w.use_wide) w.wp = wide_plan(L->s.d, L->s.f, T, L->n_experts, L->top_k, L->n_shared, max_down);
     int nblk_alloc = w.nblk > w.nblk_fused ? w.nblk : w.nblk_fused;
     if (w.use_union && w.up.nblk > nblk_alloc) nblk_alloc = w.up.nblk;
     int count_parts = w.nblk_fused > 1 ? w.nblk_fused : 1;
     if (w.use_union && w.up.nblk > count_parts) count_parts = w.up.nblk;
+    if (w.use_wide) count_parts = 1;
     size_t o = 0;
     w.table_off = o;  o += align_up((size_t)w.n_tasks * sizeof(DevExpert));
     w.expert_off = o; o += align_up((size_t)w.n_tasks * 4);
@@ -177,10 +200,11 @@ LayerWs layer_plan(const floe_layer* L, int T, int max_down) {
     // router logits in memory: between the two launches of a split router, or in front of a fused kernel that picks in place
     const bool logits_kept = router_split_pays(L->n_experts, L->s.d, T) ||
                              (w.fused_passes && fused_route_mode(L->n_experts, L->top_k, L->n_shared) == 1);
-    w.logit_off = o;  o += logits_kept ? align_up((size_t)T * L->n_experts * 4) : 0;
+    w.logit_off = o;  o += logits_kept || room ? align_up((size_t)T * L->n_experts * 4) : 0;
     w.count_off = o;  o += align_up((size_t)w.n_tasks * count_parts * 4);
     w.mask_off = o;   o += align_up((size_t)w.n_tasks * mask_words_per_task(L->s.f) * 4);
-    w.groups_off = o; o += align_up((size_t)mfma_max_groups(L->n_experts + L->n_shared, w.n_tasks) * sizeof(TokenGroup));
+    const int mfma_groups = mfma_max_groups(n_all, w.n_tasks) + (room ? w.n_tasks / 8 : 0);  // (groups of 8, or of 16)
+    w.groups_off = o; o += align_up((size_t)mfma_groups * sizeof(TokenGroup));
     w.ngroups_off = o; o += align_up(4);
     w.order_off = o;   o += align_up((size_t)w.n_tasks * 4);
     w.v_off = o;      o += align_up((size_t)w.n_tasks * L->s.f * 4);
@@ -197,7 +221,7 @@ LayerWs layer_plan(const floe_layer* L, int T, int max_down) {
     w.xfrag_off = o;   o += w.up_wide ? align_up(up_wide_scratch_bytes(T, L->s.d, L->s.group)) : 0;
     w.urow_off = o;    o += align_up(wgroups * L->s.f * 4);
     w.ucount_off = o;  o += align_up(wgroups * 4);
-    w.hbuf_off = o;    o += align_up(wgroups * w.wp.pairs * w.wp.nt * 128 * sizeof(uint4));
+    w.hbuf_off = o;    o += align_up((size_t)w.wp.h_tiles * w.wp.pairs * 128 * sizeof(uint4));
     w.hmax_off = o;    o += w.use_wide ? align_up((size_t)w.n_tasks * 4) : 0;
     w.trows_off = o;   o += w.use_wide ? align_up((size_t)w.n_tasks * sizeof(int2)) : 0;
     w.partial_off = o;
@@ -205,21 +229,29 @@ LayerWs layer_plan(const floe_layer* L, int T, int max_down) {
     w.total = o;
     return w;
 }
-LayerWs layer_ws(const floe_layer* L, int T) { return layer_plan(L, T, 0); }
-// The plan of a call whose workspace is `limit` bytes, whatever the batch (the static scratch array); total > limit: none fits.
-// The wide kernels need more workspace per task.  A batch that fits with the one-token kernels keeps fitting: there the wide
-// ones are taken only if they fit as well, with fewer pieces in the down kernel (each costs partial results, and nothing else
-// in the plan depends on their number) as long as these occupy a third of the chip.
+// What a caller is asked to bring (see expert_bytes)
+size_t layer_bytes(const floe_layer* L, int T) {
+    const LayerWs w = layer_plan(L, T, Wide::kRoom);
+    if (!w.use_wide) return w.total;
+    const LayerWs n = layer_plan(L, T, Wide::kNone);
+    const size_t one_token = n.partial_off + one_token_rows(w.n_tasks, L->s.f) * L->s.d * 4;
+    const size_t most = one_token > n.total ? one_token : n.total;
+    return w.total > most ? w.total : most;
+}
+// The plan of a call with a workspace of `limit` bytes; total > limit: none fits.  With layer_bytes() that is the chosen one.  The
+// wide kernels need more workspace per task; a batch that fits less (the static scratch array, say) with the one-token kernels
+// keeps fitting: there the wide ones are taken only if they fit as well, with fewer pieces in the down kernel (each costs partial
+// results, and nothing else in the plan depends on their number) as long as these occupy a third of the chip.
 LayerWs layer_fit(const floe_layer* L, int T, size_t limit) {
-    LayerWs w = layer_plan(L, T, 0);
+    LayerWs w = layer_plan(L, T);
     if (!w.use_wide || w.total <= limit || union_mode() == 1) return w;
-    const LayerWs n = layer_plan(L, T, -1);
+    const LayerWs n = layer_plan(L, T, Wide::kNone);
     if (n.total > limit) return w;
     const size_t row = (size_t)L->s.d * 4, rest = w.partial_off + (size_t)w.n_tasks * row;
     const size_t rows = rest < limit ? (limit - rest) / row : 0;  // for the pieces after the first
     const int pieces = (int)(rows / w.wp.chunk + 1) & ~7;
     if (rest > limit || pieces < 8 || 3 * pieces * (L->s.d / 512) < num_cus()) return n;
-    return layer_plan(L, T, pieces);
+    return layer_plan(L, T, Wide::kChosen, pieces);
 }
 
 int check_layer(const floe_layer* L) {
@@ -380,7 +412,7 @@ int floe_select_channels(const float* v, int f, int T, const float* tau, int32_t
 
 size_t floe_expert_workspace_bytes(const floe_shape* s, int T) {
     if (check_shape(s) != FLOE_OK || T < 0) return 0;
-    return expert_ws(s, T).total;
+    return expert_bytes(s, T);
 }
 
 int floe_gate_down_sparse(const floe_expert* e, const floe_half* x, int T, const float* v, const int32_t* idx,
@@ -395,7 +427,7 @@ int floe_gate_down_sparse(const floe_expert* e, const floe_half* x, int T, const
     if (!aligned(e->gd, 16) || !aligned(x, 16) || !aligned(y_acc, 16) || !aligned(workspace, kAlign)) return FLOE_EINVAL;
     if (e->gd_is_staged && (T > 1 || e->gd_rows < 0)) return FLOE_EINVAL;
     if (!e->gd_is_staged && e->gd_rows != e->s.f) return FLOE_EINVAL;
-    const ExpertWs w = expert_ws(&e->s, T, false);  // (the lists exist: nothing of the wide path runs here)
+    const ExpertWs w = expert_ws(&e->s, T, Wide::kNone);  // (the lists exist: nothing of the wide path runs here)
     if (workspace_bytes < w.total) return FLOE_EWORKSPACE;
     float* partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.partial_off);
     hipStream_t st = (hipStream_t)stream;
@@ -420,7 +452,8 @@ int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, cons
         !aligned(workspace, kAlign))
         return FLOE_EINVAL;
     if (e->gd_is_staged || e->gd_rows != e->s.f) return FLOE_EINVAL;
-    const ExpertWs w = expert_ws(&e->s, T);
+    ExpertWs w = expert_ws(&e->s, T);
+    if (w.wide && workspace_bytes < w.total && union_mode() != 1) w = expert_ws(&e->s, T, Wide::kNone);
     if (workspace_bytes < w.total) return FLOE_EWORKSPACE;
     float* v = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.v_off);
     float* partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.partial_off);
@@ -521,7 +554,7 @@ VariantWs variant_ws(const floe_shape* s, int T) {
 
 size_t floe_expert_sparsified_workspace_bytes(const floe_shape* s, int T) {
     if (check_shape(s) != FLOE_OK || T < 0) return 0;
-    const size_t a = expert_ws(s, T).total, b = variant_ws(s, T).total;
+    const size_t a = expert_bytes(s, T), b = variant_ws(s, T).total;
     return a > b ? a : b;
 }
 
@@ -603,12 +636,11 @@ int floe_layer_build_table(const floe_layer* L, void* dev_table, size_t bytes, v
 
 size_t floe_layer_workspace_bytes(const floe_layer* L, int T) {
     if (check_layer(L) != FLOE_OK || T < 0) return 0;
-    return layer_ws(L, T).total;
+    return layer_bytes(L, T);
 }
 
-// fit: the plan is made for the workspace given (FLOE_EWORKSPACE where no plan fits it)
-static int layer_decode(const floe_layer* L, const floe_half* x, int T, floe_half* y, floe_slot_stat* stats, void* workspace,
-                        size_t workspace_bytes, bool fit, void* stream) {
+int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_half* y, floe_slot_stat* stats,
+                          void* workspace, size_t workspace_bytes, void* stream) {
     int rc = check_layer(L);
     if (rc) return rc;
     if ((rc = check_T(T))) return rc;
@@ -616,7 +648,7 @@ static int layer_decode(const floe_layer* L, const floe_half* x, int T, floe_hal
     if (!L->dev_table || !x || !y || !workspace) return FLOE_EINVAL;
     if (L->gd_on_host) return FLOE_EINVAL;  // host-resident gate/down: use floe_moe_layer_decode_offloaded
     if (!aligned(x, 16) || !aligned(y, 8) || !aligned(workspace, kAlign)) return FLOE_EINVAL;
-    const LayerWs w = fit ? layer_fit(L, T, workspace_bytes) : layer_ws(L, T);
+    const LayerWs w = layer_fit(L, T, workspace_bytes);
     if (workspace_bytes < w.total) return FLOE_EWORKSPACE;
     char* base = static_cast<char*>(workspace);
     DevExpert* task_table = reinterpret_cast<DevExpert*>(base + w.table_off);
@@ -787,11 +819,6 @@ static int layer_decode(const floe_layer* L, const floe_half* x, int T, floe_hal
     return FLOE_OK;
 }
 
-int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_half* y, floe_slot_stat* stats,
-                          void* workspace, size_t workspace_bytes, void* stream) {
-    return layer_decode(L, x, T, y, stats, workspace, workspace_bytes, false, stream);
-}
-
 int floe_moe_layer_decode_offloaded(const floe_layer* L, const floe_offload* o, const floe_half* x, int T, floe_half* y,
                                     floe_slot_stat* stats, void* workspace, size_t workspace_bytes, void* stream) {
     int rc = check_layer(L);
@@ -801,7 +828,7 @@ int floe_moe_layer_decode_offloaded(const floe_layer* L, const floe_offload* o, 
     if (!o || !o->staging || !o->ev_lists_ready || !o->ev_staged || o->capacity_rows <= 0) return FLOE_EINVAL;
     if (!L->dev_table || !L->gd_on_host || !x || !y || !workspace) return FLOE_EINVAL;
     if (!aligned(x, 16) || !aligned(y, 8) || !aligned(workspace, kAlign) || !aligned(o->staging, 16)) return FLOE_EINVAL;
-    const LayerWs w = layer_ws(L, T);
+    const LayerWs w = layer_plan(L, T);
     if (workspace_bytes < w.total) return FLOE_EWORKSPACE;
     char* base = static_cast<char*>(workspace);
     DevExpert* task_table = reinterpret_cast<DevExpert*>(base + w.table_off);
@@ -848,7 +875,7 @@ int floe_moe_layer_prefetch(const floe_layer* L, const floe_prefetch* p, const f
         return FLOE_EINVAL;
     if (!L->dev_table || !L->gd_on_host || !x_cur || !workspace) return FLOE_EINVAL;
     if (!aligned(x_cur, 16) || !aligned(workspace, kAlign) || !aligned(p->staging, 16)) return FLOE_EINVAL;
-    const LayerWs w = layer_ws(L, T);
+    const LayerWs w = layer_plan(L, T);
     if (workspace_bytes < w.total) return FLOE_EWORKSPACE;
     char* base = static_cast<char*>(workspace);
     hipStream_t st = (hipStream_t)stream, side = (hipStream_t)p->prefetch_stream;
@@ -883,7 +910,7 @@ int floe_moe_layer_decode_prefetched(const floe_layer* L, const floe_prefetch* p
     if (!m || !m->ev_lists_ready || !m->ev_staged) return FLOE_EINVAL;
     if (!L->dev_table || !L->gd_on_host || !x || !y || !workspace) return FLOE_EINVAL;
     if (!aligned(x, 16) || !aligned(y, 8) || !aligned(workspace, kAlign) || !aligned(p->staging, 16)) return FLOE_EINVAL;
-    const LayerWs w = layer_ws(L, T);
+    const LayerWs w = layer_plan(L, T);
     if (workspace_bytes < w.total) return FLOE_EWORKSPACE;
     char* base = static_cast<char*>(workspace);
     DevExpert* task_table = reinterpret_cast<DevExpert*>(base + w.table_off);
@@ -951,7 +978,7 @@ int floe_moe_layer_decode_cached(const floe_layer* L, const floe_channel_cache* 
     if (!m || !m->ev_lists_ready || !m->ev_staged) return FLOE_EINVAL;
     if (!L->dev_table || !L->gd_on_host || !x || !y || !workspace) return FLOE_EINVAL;
     if (!aligned(x, 16) || !aligned(y, 8) || !aligned(workspace, kAlign) || !aligned(c->pool, 16)) return FLOE_EINVAL;
-    const LayerWs w = layer_ws(L, T);
+    const LayerWs w = layer_plan(L, T);
     if (workspace_bytes < w.total) return FLOE_EWORKSPACE;
     char* base = static_cast<char*>(workspace);
     DevExpert* task_table = reinterpret_cast<DevExpert*>(base + w.table_off);
@@ -1024,9 +1051,5 @@ int floe_stage_channels(const floe_half* host_gd, int d, int f, const int32_t* i
 namespace floe {
 
 bool layer_fits(const floe_layer* L, int T, size_t bytes) { return check_layer(L) != FLOE_OK || layer_fit(L, T, bytes).total <= bytes; }
-int layer_decode_within(const floe_layer* L, const floe_half* x, int T, floe_half* y, floe_slot_stat* stats, void* workspace,
-                        size_t workspace_bytes, void* stream) {
-    return layer_decode(L, x, T, y, stats, workspace, workspace_bytes, true, stream);
-}
 
 }  // namespace floe

@@ -177,6 +177,7 @@ struct WideGroup {
 constexpr int kWideMaxMaskWords = 2048;  // f <= 65536
 struct WidePlan {
     int nt, chunk, max_groups, est_groups;
+    int h_tiles;            // token tiles that the groups can have together
     int pairs;              // pairs of 16-row tiles an expert can have
     int wg_gate, wg_down;   // workgroups (the down kernel: per 512 output columns)
     size_t partial_rows;    // rows of d floats
@@ -193,7 +194,7 @@ struct WideArgs {
     int32_t* count;           // [n_tasks] selected channels
     int32_t* urow;            // [max_groups][f] union rows, ascending
     int32_t* ucount;          // [max_groups]
-    uint4* hbuf;              // [max_groups][pairs][nt][2][64] h (four floats: rows of a 16-row tile) in lane order
+    uint4* hbuf;              // [h_tiles * pairs][2][64] h (four floats: rows of a 16-row tile) in lane order
     uint32_t* hmax;           // [n_tasks] bits of the largest finite |h| of task order[i]
     int2* task_rows;          // [n_tasks] first partial row, number of partial rows (chunk rows apart)
     float* partial;           // [partial_rows][d]
@@ -230,6 +231,7 @@ size_t up_wide_scratch_bytes(int T, int d, int group);
 hipError_t launch_up_wide(UpWideArgs a, int bits, int group, hipStream_t stream);
 
 WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared, int max_down);
+WidePlan wide_room(int d, int f, int T, int n_experts, int top_k, int n_shared);
 hipError_t launch_gate_down_wide(const WideArgs& a, const WidePlan& p, const uint32_t* mask_words, int d, hipStream_t stream);
 hipError_t launch_wide_single(const DevExpert& e, int n_tasks, int chunk, DevExpert* table, WideGroup* groups, int32_t* n_groups,
                               int32_t* order, hipStream_t stream);

@@ -40,10 +40,8 @@ int static_scratch(void** out) {
 
 }  // namespace
 
-namespace floe {  // api.hip: the layer decode with the plan that fits a workspace of so many bytes
-bool layer_fits(const floe_layer* L, int T, size_t bytes);  // (an invalid layer fits: the call returns its error code)
-int layer_decode_within(const floe_layer* L, const floe_half* x, int T, floe_half* y, floe_slot_stat* stats, void* workspace,
-                        size_t workspace_bytes, void* stream);
+namespace floe {
+bool layer_fits(const floe_layer* L, int T, size_t bytes);  // api.hip (an invalid layer fits: the call returns its error code)
 }  // namespace floe
 
 extern "C" int floe_moe_layer_decode_static(const floe_layer* L, const floe_half* x, int T, floe_half* y,
@@ -55,5 +53,5 @@ extern "C" int floe_moe_layer_decode_static(const floe_layer* L, const floe_half
     const int rc = static_scratch(&scratch);
     if (rc != FLOE_OK) return rc;
     // (an invalid layer comes back from here with its proper error code)
-    return floe::layer_decode_within(L, x, T, y, stats, scratch, FLOE_STATIC_SCRATCH_BYTES, stream);
+    return floe_moe_layer_decode(L, x, T, y, stats, scratch, FLOE_STATIC_SCRATCH_BYTES, stream);
 }

@@ -42,6 +42,11 @@ constexpr int kDownCols = 512;   // output columns per workgroup of the down ker
 // pairs of union rows of group g
 __device__ __forceinline__ int wide_pairs(const int32_t* ucount, int g) { return (ucount[g] + kPairRows - 1) / kPairRows; }
 
+// h of a group lies in [pair][token tile][half of the pair's rows][lane], the group's own tiles only, from this entry on.  The
+// groups before group g hold at most (first + 15 g) / 16 tiles, so no two of them meet.
+__device__ __forceinline__ int wide_tiles(int n) { return (n + 15) >> 4; }
+__device__ __forceinline__ size_t wide_h_first(int first, int g, int pmax) { return (size_t)((first + 15 * g) >> 4) * pmax * 128; }
+
 __device__ __forceinline__ int wave_inclusive_scan(int x, int lane) {
 #pragma unroll
     for (int o = 1; o < kWave; o <<= 1) {
@@ -329,11 +334,14 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
                     atomicMax(&s_hmax[16 * n + tok0], top);  // (no result wanted: fire and forget)
                 }
             }
-            uint4* hb = a.hbuf + ((size_t)g * pmax + pair) * (NT * 128) + lane;
+            const int tiles = wide_tiles(grp.n);
+            uint4* hb = a.hbuf + wide_h_first(grp.first, g, pmax) + (size_t)pair * tiles * 128 + lane;
 #pragma unroll
             for (int n = 0; n < NT; ++n)
+                if (n < tiles) {
 #pragma unroll
-                for (int t = 0; t < 2; ++t) hb[n * 128 + t * 64] = __builtin_bit_cast(uint4, acc[t][n]);
+                    for (int t = 0; t < 2; ++t) hb[n * 128 + t * 64] = __builtin_bit_cast(uint4, acc[t][n]);
+                }
         }
         __syncthreads();
         // a maximum does not depend on the order in which the workgroups of a group arrive
@@ -389,7 +397,8 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
             const int slots = wide_owner(total, W, base + npairs - 1) - w_first + 1;
             if (tid < grp.n) a.task_rows[a.order[grp.first + tid]] = make_int2(grp.first + tid + w_first * kTok, slots);
         }
-        const unsigned char* hsrc = scalar_ptr(a.hbuf + ((size_t)g * pmax + seg0) * (NT * 128));
+        const int tiles = wide_tiles(grp.n);
+        const unsigned char* hsrc = scalar_ptr(a.hbuf + wide_h_first(grp.first, g, pmax) + (size_t)seg0 * tiles * 128);
         const int ns = (len + SL - 1) / SL;
         uint4 hq[kHRounds];
         int idq = 0;
@@ -400,7 +409,8 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
             for (int r = 0; r < kHRounds; ++r) {
                 const int i = tid + r * kWideThreads;
                 const int pr = min(s * SL + i / (NT * 128), len - 1);
-                hq[r] = gload16(hsrc + (uint32_t)(pr * (NT * 128) + i % (NT * 128)) * 16u);
+                const int tile = min(i % (NT * 128) / 128, tiles - 1);  // (past the group's tiles: token rows that nobody reads)
+                hq[r] = gload16(hsrc + (uint32_t)((pr * tiles + tile) * 128 + i % 128) * 16u);
             }
         };
         auto store_h = [&](int s) {  // into LDS as hi + lo
@@ -538,7 +548,7 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
             for (int r = seg0 * kPairRows, last = min(count, seg1 * kPairRows); r < last; ++r) {
                 const int row = rows[r], p = r / kPairRows - seg0, in = r % kPairRows;
                 if (!(fabsf(vt[row]) > tau)) continue;
-                const float h = hp[((size_t)(p * NT + n) * 128 + (in >> 4) * 64 + ((in >> 2) & 3) * 16 + (tok & 15)) * 4 + (in & 3)];
+                const float h = hp[((size_t)(p * tiles + n) * 128 + (in >> 4) * 64 + ((in >> 2) & 3) * 16 + (tok & 15)) * 4 + (in & 3)];
                 const uint2 w = gload8(gd + ((uint32_t)row * (uint32_t)(4 * d) + dcol));
                 const h16x2 lo = as_h2(w.x), hi = as_h2(w.y);
                 s.x = fmaf(h, (float)lo.x, s.x);
@@ -606,25 +616,33 @@ __global__ __launch_bounds__(256) void wide_single_kernel(DevExpert e, int n_tas
 // ---------------------------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------------------------
-WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared, int max_down) {
-    WidePlan p{};
-    const int n_tasks = T * (top_k + n_shared), n_all = n_experts + n_shared;
-    // Token tiles per group: the fewest expected reads of the experts' rows, weighed by what a read costs.  Measured (8
-    // experts, d = 4096, f = 14336, 90 %, gate + down): 64 tokens 330 us with one tile (12 groups), 293 with two (8
-    // groups), 308 with three; 512 tokens 637 us with five tiles (16 groups, the two of an expert share rows in the L2),
-    // 565 with ten (8 groups: each workgroup passes twice the activations through LDS).
+// Token tiles per group: the fewest expected reads of the experts' rows, weighed by what a read costs.  Measured (8
+// experts, d = 4096, f = 14336, 90 %, gate + down): 64 tokens 330 us with one tile (12 groups), 293 with two (8
+// groups), 308 with three; 512 tokens 637 us with five tiles (16 groups, the two of an expert share rows in the L2),
+// 565 with ten (8 groups: each workgroup passes twice the activations through LDS).
+static int wide_tiles_for(int T, int n_experts, int top_k, int n_shared, double& groups) {
     double best = 0.0;
+    int best_nt = 0;
     for (const int nt : {1, 2, 3, 4, 5, 10}) {
-        const double groups = expected_token_groups(n_experts, T, top_k, 16 * nt) + (double)n_shared * ((T + 16 * nt - 1) / (16 * nt));
-        const double score = groups * (1.0 + (nt <= 5 ? 0.05 : 0.09) * nt);
-        if (p.nt == 0 || score < best) {
+        const double g = expected_token_groups(n_experts, T, top_k, 16 * nt) + (double)n_shared * ((T + 16 * nt - 1) / (16 * nt));
+        const double score = g * (1.0 + (nt <= 5 ? 0.05 : 0.09) * nt);
+        if (best_nt == 0 || score < best) {
             best = score;
-            p.nt = nt;
-            p.est_groups = groups < 1.0 ? 1 : (int)(groups + 0.5);
+            best_nt = nt;
+            groups = g;
         }
     }
-    p.chunk = 16 * p.nt;
-    p.max_groups = (n_all < n_tasks ? n_all : n_tasks) + n_tasks / p.chunk;
+    return best_nt;
+}
+
+// what follows from the token tiles; est_groups: the groups to be expected
+static WidePlan wide_plan_for(int nt, int max_groups, int est_groups, int d, int f, int n_tasks, int max_down) {
+    WidePlan p{};
+    p.nt = nt;
+    p.chunk = 16 * nt;
+    p.max_groups = max_groups;
+    p.est_groups = est_groups < 1 ? 1 : (est_groups < max_groups ? est_groups : max_groups);
+    p.h_tiles = (n_tasks + 15 * max_groups) / 16;
     p.pairs = (f + kPairRows - 1) / kPairRows;
     const long long est_pairs = (long long)p.est_groups * p.pairs;
     // one workgroup per compute unit; a piece is at least one pair (gate) or four (down: each piece costs a partial result)
@@ -638,6 +656,30 @@ WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared, 
     if (p.wg_gate > 8) p.wg_gate &= ~7;
     p.partial_rows = (size_t)n_tasks + (size_t)p.chunk * (p.wg_down - 1);
     return p;
+}
+
+WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared, int max_down) {
+    const int n_tasks = T * (top_k + n_shared), n_all = n_experts + n_shared;
+    double groups = 0.0;
+    const int nt = wide_tiles_for(T, n_experts, top_k, n_shared, groups);
+    return wide_plan_for(nt, (n_all < n_tasks ? n_all : n_tasks) + n_tasks / (16 * nt), (int)(groups + 0.5), d, f, n_tasks, max_down);
+}
+
+// No plan of this layer for up to T tokens needs more of anything: the groups of one tile, of which there are most, with as many
+// tiles as any of these batches takes.  (What a shared expert adds jumps behind each multiple of 16 tokens; between two jumps the
+// scores move one way, so the most tiles are taken at a multiple of 16 or right behind one.  Checked against every T up to 1500
+// for up to 160 routed and four shared experts.)
+WidePlan wide_room(int d, int f, int T, int n_experts, int top_k, int n_shared) {
+    const int n_tasks = T * (top_k + n_shared), n_all = n_experts + n_shared;
+    const int max_groups = (n_all < n_tasks ? n_all : n_tasks) + n_tasks / 16;
+    double groups = 0.0;
+    int nt = wide_tiles_for(T, n_experts, top_k, n_shared, groups);
+    for (int t = T / 16 * 16; t > 0 && nt < 10; t -= 16)
+        for (const int at : {t, t + 1 < T ? t + 1 : t}) {
+            const int n = wide_tiles_for(at, n_experts, top_k, n_shared, groups);
+            nt = n > nt ? n : nt;
+        }
+    return wide_plan_for(nt, max_groups, max_groups, d, f, n_tasks, 0);
 }
 
 template <int NT>

@@ -107,3 +107,40 @@ def test_layer_workspace_query_for_every_path_the_dispatch_can_take(lib):
     finally:
         for key in (1, 3, 4):
             lib.floe_tuning(key, 0)
+
+
+@pytest.mark.parametrize("d,f,bits,group,n,top_k,n_shared", [
+    (4096, 14336, 2, 64, 8, 2, 0), (2048, 1408, 3, 32, 64, 6, 2), (1024, 3584, 2, 64, 8, 2, 0), (2560, 6911, 4, 128, 6, 2, 0),
+    (512, 300, 8, 64, 34, 1, 1),
+])
+def test_a_workspace_sized_for_the_largest_batch_serves_the_smaller_ones(lib, d, f, bits, group, n, top_k, n_shared):
+    """The plans for tokens that share rows jump up and down with the batch size; what the queries ask for does not, and holds
+    each of them (forced here, so that no call falls back to a plan that needs less)."""
+    import torch
+    from paper_2505_05950_amd.binding import _Expert, _Layer, _Shape
+    if torch.cuda.is_available():
+        pytest.skip("the pointers below are made up: without a device the calls end at their first HIP call")
+    lib.floe_layer_workspace_bytes.restype = lib.floe_expert_workspace_bytes.restype = C.c_size_t
+    fake, ws = C.c_void_p(4096), C.c_void_p(1 << 20)
+    s = _Shape(d, f, bits, group)
+    L = _Layer(n, top_k, n_shared, 1, s, 4096, None, 4096, 0, 4096, 0)
+    e = _Expert(s, 4096, 4096, 4096, 4096, 0, f)
+
+    def sizes(T, mode):
+        lib.floe_tuning(1, mode)
+        return lib.floe_layer_workspace_bytes(C.byref(L), T), lib.floe_expert_workspace_bytes(C.byref(s), T)
+
+    try:
+        lib.floe_tuning(4, 1)
+        last = (0, 0)
+        for T in list(range(17, 340)) + [511, 512, 513, 1025, 4096]:
+            one_token, now = sizes(T, 3), sizes(T, 1)
+            assert all(a >= max(b, c) for a, b, c in zip(now, last, one_token)), (T, last, now, one_token)
+            last = now
+        for top in (81, 145, 160, 161, 257, 339):
+            layer_bytes, expert_bytes = (C.c_size_t(b) for b in sizes(top, 1))
+            for T in range(17, top + 1):
+                assert lib.floe_moe_layer_decode(C.byref(L), fake, T, fake, None, ws, layer_bytes, None) == -5, (T, top)
+                assert lib.floe_expert_ffn_sparse(C.byref(e), fake, T, fake, None, fake, None, None, ws, expert_bytes, None) == -5, (T, top)
+    finally:
+        lib.floe_tuning(1, 0), lib.floe_tuning(4, 0)

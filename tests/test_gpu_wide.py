@@ -215,7 +215,7 @@ def test_gate_down_on_existing_lists_needs_no_wide_workspace():
     """floe_gate_down_sparse runs the one-token kernels at every batch size: their workspace is enough."""
     import gpu_common as G
     import paper_2505_05950_amd as F
-    d, f, bits, group, T = 1024, 700, 2, 64, 24
+    d, f, bits, group, T = 1024, 700, 2, 64, 130
     _, ex = G.make_expert(*S.expert_weights(98, 3, d, f), bits, group)
     x = G.dev(S.tokens(98, 3, T, d))
     wide = F.floe_expert_workspace_bytes(d, f, bits, group, T)
@@ -232,3 +232,37 @@ def test_gate_down_on_existing_lists_needs_no_wide_workspace():
         y.append(F.floe_gate_down_sparse(ex, x, v, idx, count, None, torch.zeros((T, d), dtype=torch.float32, device=G.DEV),
                                          workspace=buf[off: off + size]))
     assert torch.equal(y[0], y[1])
+
+
+def test_one_workspace_serves_every_batch_and_a_smaller_one_other_kernels():
+    """Batches of every group size with the workspace of the largest one, and with what the one-token kernels need."""
+    import gpu_common as G
+    import paper_2505_05950_amd as F
+    d, f, bits, group, top = 1024, 500, 2, 64, 165
+    _, ex = G.make_expert(*S.expert_weights(99, 3, d, f), bits, group)
+    L = F.Layer([ex], 1, 0, False, None, G.dev(np.full((1,), 1.0, np.float32)), False)
+    x = G.dev(S.tokens(99, 3, top, d))
+    size_l, size_e = F.floe_layer_workspace_bytes(L, top), F.floe_expert_workspace_bytes(d, f, bits, group, top)
+
+    def cut(size):
+        buf = torch.full((size + 256,), 255, dtype=torch.uint8, device=G.DEV)
+        off = (-buf.data_ptr()) % 256
+        return buf[off: off + size]
+
+    def expert(T, ws):
+        y = torch.zeros((T, d), dtype=torch.float32, device=G.DEV)
+        return F.floe_expert_ffn_sparse(ex, x[:T], torch.full((T,), 1.0, device=G.DEV), None, y, workspace=ws, want_list=False)[0]
+
+    for T in (17, 40, 81, 140, 160, 161, top):
+        own = F.floe_moe_layer_decode(L, x[:T])
+        L._ws[T] = cut(size_l)
+        assert torch.equal(F.floe_moe_layer_decode(L, x[:T]), own), T
+        y = expert(T, None)
+        assert torch.equal(expert(T, cut(size_e)), y), T
+        F.floe_tuning(F.TUNE_UNION_KERNELS, 3)
+        small_l, small_e = F.floe_layer_workspace_bytes(L, T), F.floe_expert_workspace_bytes(d, f, bits, group, T)
+        F.floe_tuning(F.TUNE_UNION_KERNELS, 0)
+        L._ws[T] = cut(small_l)
+        assert G.rel_err(F.floe_moe_layer_decode(L, x[:T]).float().cpu().numpy(), own.float().cpu().numpy()) <= 2.0 ** -10, T
+        assert G.rel_err(expert(T, cut(small_e)).cpu().numpy(), y.cpu().numpy()) <= FP32_BAR, T
+        F.floe_tuning(F.TUNE_UNION_KERNELS, 1)
