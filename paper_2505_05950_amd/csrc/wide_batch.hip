@@ -413,6 +413,15 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
                 hq[r] = gload16(hsrc + (uint32_t)((pr * tiles + tile) * 128 + i % 128) * 16u);
             }
         };
+        // The powers of the tokens whose h this thread brings in (the same ones in every slice): in registers where there are
+        // some left, which saves the small segments a barrier in front of their first slice.
+        constexpr bool kScaleRegs = NT <= 4;
+        float scale_reg[kScaleRegs ? kHRounds : 1];
+        auto exponent = [&](int tok) {  // |h| < 2^(e + 15); 2^e and 2^-e stay normal numbers
+            const uint32_t m = gload4(a.hmax + grp.first + (tok < grp.n ? tok : 0));
+            return max((int)(m >> 23) - 141, -126);
+        };
+        auto power = [](int e) { return __builtin_bit_cast(float, (uint32_t)(127 + e) << 23); };
         auto store_h = [&](int s) {  // into LDS as hi + lo
             int at = tid;  // (entry i of the slice: pair and token tile i / 128, half (i >> 6) & 1 of the pair's rows, lane)
             asm volatile("" : "+v"(at));  // or the addresses are formed ahead of the loop and spilled: a reload waits for every request
@@ -421,7 +430,7 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
             for (int r = 0; r < kHRounds; ++r) {
                 const int i = tid + r * kWideThreads;
                 const bool live = s * SL + i / (NT * 128) < len;
-                const float scale = s_scale[16 * (i % (NT * 128) / 128) + l16];
+                const float scale = kScaleRegs ? scale_reg[kScaleRegs ? r : 0] : s_scale[16 * (i % (NT * 128) / 128) + l16];
                 const uint32_t w[4] = {hq[r].x, hq[r].y, hq[r].z, hq[r].w};
                 h16 hi[4], lo[4];
 #pragma unroll
@@ -459,16 +468,19 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
 
         __syncthreads();  // the previous group's LDS contents are no longer read
         load_ids(0);
-        const uint32_t m = a.hmax[grp.first + (tid < grp.n ? tid : 0)];
         load_h(0);
+        const int e = exponent(min(tid, kTok - 1));
+        if constexpr (kScaleRegs) {
+#pragma unroll
+            for (int r = 0; r < kHRounds; ++r) scale_reg[r] = power(-exponent(16 * ((tid + r * kWideThreads) % (NT * 128) / 128) + l16));
+        }
         if (tid < kTok) {
-            const int e = max((int)(m >> 23) - 141, -126);  // |h| < 2^(e + 15); both powers below stay normal numbers
-            s_scale[tid] = __builtin_bit_cast(float, (uint32_t)(127 - e) << 23);
-            s_back[tid] = __builtin_bit_cast(float, (uint32_t)(127 + e) << 23);
+            if constexpr (!kScaleRegs) s_scale[tid] = power(-e);
+            s_back[tid] = power(e);
         }
         store_ids(0);
         load_ids(1);
-        __syncthreads();
+        if constexpr (!kScaleRegs) __syncthreads();
         store_h(0);
         store_ids(1);
         __syncthreads();
