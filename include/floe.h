@@ -74,7 +74,7 @@ typedef enum {
     FLOE_KERNEL_QUANTIZE = 1,
     FLOE_KERNEL_ROUTER = 2,
     FLOE_KERNEL_UP_GEMV = 3,
-    FLOE_KERNEL_SELECT = 4,    /* one-expert calls of up to 16 tokens cut the list inside FLOE_KERNEL_COMBINE */
+    FLOE_KERNEL_SELECT = 4,    /* one-expert calls of up to 16 tokens cut the list beside the sums: that launch is this and COMBINE */
     FLOE_KERNEL_GATE_DOWN = 5,
     FLOE_KERNEL_COMBINE = 6,
     FLOE_KERNEL_STAGE = 7,

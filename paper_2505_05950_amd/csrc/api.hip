@@ -473,6 +473,7 @@ int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, cons
         FLOE_LAUNCH(FLOE_KERNEL_FUSED_FFN, st, launch_fused(a, e->s.bits, st));
         nblk = w.nblk_fused;
         if (idx) {
+            Bracket list(FLOE_KERNEL_SELECT, st);  // one launch that is both: whichever of the two is armed sees it
             FLOE_LAUNCH(FLOE_KERNEL_COMBINE, st, launch_combine_select(partial, e->s.d, T, nblk, y_acc, v, e->s.f, tau, idx, count, st));
             return FLOE_OK;
         }

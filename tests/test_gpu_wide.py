@@ -266,3 +266,22 @@ def test_one_workspace_serves_every_batch_and_a_smaller_one_other_kernels():
         assert G.rel_err(F.floe_moe_layer_decode(L, x[:T]).float().cpu().numpy(), own.float().cpu().numpy()) <= 2.0 ** -10, T
         assert G.rel_err(expert(T, cut(small_e)).cpu().numpy(), y.cpu().numpy()) <= FP32_BAR, T
         F.floe_tuning(F.TUNE_UNION_KERNELS, 1)
+
+
+def test_profiling_the_selection_sees_the_launch_that_carries_the_list():
+    """A one-expert call of up to 16 tokens cuts its list beside the sums: events armed for either are recorded."""
+    import gpu_common as G
+    import paper_2505_05950_amd as F
+    d, f, bits, group, T = 1024, 700, 2, 64, 2
+    _, ex = G.make_expert(*S.expert_weights(100, 3, d, f), bits, group)
+    x, tau = G.dev(S.tokens(100, 3, T, d)), torch.full((T,), 1.0, device=G.DEV)
+    for name in ("select", "combine"):
+        start, stop, before = (torch.cuda.Event(enable_timing=True) for _ in range(3))
+        start.record(), stop.record(), before.record()
+        F.floe_profile_kernel(name, start, stop)
+        try:
+            F.floe_expert_ffn_sparse(ex, x, tau, None, torch.zeros((T, d), dtype=torch.float32, device=G.DEV))
+        finally:
+            F.floe_profile_kernel("none")
+        torch.cuda.synchronize()
+        assert before.elapsed_time(start) > 0 and start.elapsed_time(stop) > 0, name
