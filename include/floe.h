@@ -87,7 +87,7 @@ int floe_profile_kernel(int kernel_id, void* start_event, void* stop_event);
  *   FLOE_TUNE_UNION_KERNELS  how Alg. 1 steps 4-5 run for decode batches (those beyond FLOE_TUNE_FUSED_TASKS), where
  *                            the tokens of an expert select overlapping rows:
  *                            0 = chosen per call (default): 1 once the experts see enough tokens each (five for large
- *                                layers, more for small ones), else 3;
+ *                                layers, dozens for small ones or a small expert on its own), else 3;
  *                            1 = per expert group (up to 160 tokens), the union of the selected rows read once, gate and
  *                                down projections on the matrix cores (dense token x row tiles);
  *                            2 = per expert group, the union of the selected rows read once into a ring in LDS, one

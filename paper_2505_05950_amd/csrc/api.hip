@@ -110,7 +110,7 @@ ExpertWs expert_ws(const floe_shape* s, int T, Wide form = Wide::kChosen) {
     w.v_off = o;       o += align_up((size_t)T * s->f * sizeof(float));
     w.mask_off = o;    o += align_up((size_t)T * mask_words_per_task(s->f) * sizeof(uint32_t));
     w.count_off = o;   o += align_up((size_t)T * (w.nblk_fused > 1 ? w.nblk_fused : 1) * sizeof(int32_t));
-    w.wide = form != Wide::kNone && !w.fused_passes && T >= 2 && mask_path_ok(s->f) && union_kernels_for(1, T, s->d, s->f) == 1;
+    w.wide = form != Wide::kNone && !w.fused_passes && T >= 2 && mask_path_ok(s->f) && union_kernels_for(1, T, s->d, s->f, s->bits, s->group) == 1;
     if (w.wide) {
         w.wp = form == Wide::kRoom ? wide_room(s->d, s->f, T, 1, 1, 0) : wide_plan(s->d, s->f, T, 1, 1, 0, 0);
         w.table_off = o;   o += align_up(sizeof(DevExpert));
@@ -178,7 +178,7 @@ LayerWs layer_plan(const floe_layer* L, int T, Wide form = Wide::kChosen, int ma
     w.batch_mfma = T >= 2 && mfma_grouped_shape(L->s.d, L->s.bits, L->s.group) &&
                    (grouped_gemv_mode() == 1 || (!w.fused_passes && mfma_batch_pays(n_all, w.n_tasks, L->s.bits)));
     const bool share_rows = !L->gd_on_host && T >= 2 && (!w.fused_passes || w.batch_mfma) && mask_path_ok(L->s.f);
-    const int kernels = union_kernels_for(n_all, w.n_tasks, L->s.d, L->s.f);
+    const int kernels = union_kernels_for(n_all, w.n_tasks, L->s.d, L->s.f, L->s.bits, L->s.group);
     w.use_wide = share_rows && kernels == 1 && form != Wide::kNone;
     const bool room = w.use_wide && form == Wide::kRoom;
     if (share_rows && kernels == 2) {

@@ -293,18 +293,41 @@ __global__ __launch_bounds__(kFusedUnionWaves * 64) void union_fused_kernel(Unio
 static std::atomic<int> g_union_mode{0};
 int union_mode() { return g_union_mode.load(std::memory_order_relaxed); }
 void set_union_mode(int m) { g_union_mode.store(m >= 0 && m <= 3 ? m : 0, std::memory_order_relaxed); }
-// The wide kernels read a row once for a whole group but bring three more launches and their dependent prologues (about
-// 20 us); the one-token kernels in expert order read the rows of a task each.  Layer calls measured, one-token / wide, us:
-//   8 experts  d 4096  f 14336 (1.9 GB of rows): 5 tasks per expert 253 / 219, 8: 305 / 301, 10: 360 / 312, 16: 460 / 374
-//   16 experts d 4096  f 4096  (1.1 GB):         8 tasks per expert 391 / 279
-//   66 experts d 2048  f 1408  (0.76 GB):        5.8 tasks per expert 188 / 197, 7.8: 214 / 212, 11.6: 265 / 239
-//   8 experts  d 1024  f 3584  (0.12 GB):        12 tasks per expert 56 / 73, 24: 81 / 78
-// which the line "4 + 1.9 GB / (bytes of all rows) tasks per expert" separates.
-int union_kernels_for(int n_all, int n_tasks, int d, int f) {
+// The wide kernels read a row once for a whole group, but bring three more launches with their prologues and the partial results
+// of all pieces (half a megabyte per token of a group, whatever the layer); the one-token kernels in expert order read the rows of
+// a task each.  What decides is therefore the rows that the tasks would read, in GB with all channels: q tasks per expert times
+// the bytes G of the experts' rows.  Measured (layers at 85 %, one expert at 90 %), one-token / wide, us:
+//   layers, large G: q >= 4 + 1.9 / G
+//     8 experts  d 4096 f 14336 INT2 (G 1.9):    q 5 253 / 219, 8 305 / 301, 10 360 / 312, 16 460 / 374
+//     16 experts d 4096 f 4096  INT2 (1.1):      q 5 187 / 187, 6 195 / 189, 8 250 / 230
+//   ... but at least q G = 4.2 where both ways run the same up projection
+//     8 experts  d 1024 f 3584  INT2 (0.12):     q 24 79 / 92, 32 103 / 110
+//     4 experts  d 1024 f 10000 INT2 (0.16):     q 16 81 / 97, 24 98 / 110, 32 130 / 118
+//     8 experts  d 2048 f 5632  INT4 (0.37):     q 8 88 / 105, 12 120 / 124, 20 165 / 149
+//     8 experts  d 2048 f 3000  INT2 g32 (0.20): q 16 131 / 146, 20 156 / 157, 24 183 / 175
+//     50 experts d 1024 f 1408  INT4 (0.29):     q 10 118 / 119, 16 147 / 139
+//   other layers take the wide up projection along and stay at the first line
+//     25 experts d 1536 f 2048  INT4 (0.32):     q 6 98 / 113, 8 123 / 121, 12 171 / 136
+//     8 experts  d 3072 f 4000  INT2 (0.39):     q 4 82 / 93, 8 143 / 118
+//   one expert, whose tokens go through the packed up projection one by one or the wide one: q G = 2.85
+//     d 1024 f 3584 INT2 (0.015): 160 tokens 79 / 104, 200 94 / 98     d 2048 f 5632 INT4 (0.046): 48 78 / 91, 64 89 / 89, 96 132 / 124
+//     d 4096 f 4096 INT2 (0.067): 32 78 / 88, 48 113 / 104             d 4096 f 14336 INT2 (0.23): 17 163 / 109
+//   one expert without a wide up projection: 3.6, for the smaller widths, whose rows are short against their partial results, 5
+//   (generic) and 10 (packed up projection)
+//     d 2560 f 6911 INT4 g128 (0.071): 32 85 / 101, 48 132 / 127       d 4096 f 8000 INT8 (0.13): 24 196 / 197, 48 353 / 332
+//     d 1536 f 3000 INT8 (0.018): 160 128 / 171, 200 156 / 174         d 2048 f 8000 INT2 g128 (0.066): 64 114 / 134, 160 262 / 267
+int union_kernels_for(int n_all, int n_tasks, int d, int f, int bits, int group) {
     const int m = union_mode();
     if (m != 0) return m;
     const double gb = 4e-9 * d * (double)f * n_all;
-    return n_tasks >= (4.0 + 1.9 / gb) * n_all ? 1 : 3;
+    const bool wide_up = up_wide_shape(d, f, bits, group), packed = packed_fast_shape(d, bits, group);
+    double least = 1.9 + 4.0 * gb;
+    double same_up = 0.0;
+    if (n_all > 1) same_up = !wide_up || mfma_grouped_shape(d, bits, group) ? 4.2 : 0.0;
+    else if (wide_up && packed) least = 2.85;
+    else if (!wide_up) least = d > 2048 ? 3.6 : (packed ? 10.0 : 5.0);
+    if (least < same_up) least = same_up;
+    return n_tasks * gb >= least * n_all ? 1 : 3;
 }
 
 // Per expert E[ceil(X / chunk)] = sum over k >= 0 of P(X > k * chunk), X binomial, by its normal approximation.  Terms further

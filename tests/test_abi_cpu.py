@@ -144,3 +144,43 @@ def test_a_workspace_sized_for_the_largest_batch_serves_the_smaller_ones(lib, d,
                 assert lib.floe_expert_ffn_sparse(C.byref(e), fake, T, fake, None, fake, None, None, ws, expert_bytes, None) == -5, (T, top)
     finally:
         lib.floe_tuning(1, 0), lib.floe_tuning(4, 0)
+
+
+@pytest.mark.parametrize("shape,layer,one_token,wide", [
+    ((1024, 3584, 2, 64), None, (17, 128, 160), (210, 320)),             # batches at which each way measured clearly faster
+    ((2048, 5632, 4, 64), None, (17, 48), (96, 200)),
+    ((4096, 4096, 2, 64), None, (17, 32), (48, 128)),
+    ((4096, 14336, 2, 64), None, (), (17, 24, 64)),
+    ((2048, 8000, 2, 128), None, (17, 64, 128), (200, 320)),
+    ((1024, 14336, 2, 32), None, (17, 96), (200, 320)),
+    ((4096, 14336, 4, 128), None, (), (17, 64)),
+    ((1536, 3000, 8, 64), None, (64, 200), ()),
+    ((2560, 6911, 2, 64), None, (17,), (48, 200)),
+    ((1024, 3584, 2, 64), (8, 2, 0), (64, 96, 128), (200, 512)),
+    ((4096, 14336, 2, 64), (8, 2, 0), (), (40, 64, 512)),
+    ((2048, 1408, 3, 32), (64, 6, 2), (33,), (82, 132, 512)),
+    ((2048, 3000, 2, 32), (8, 2, 0), (40, 64), (96, 128)),
+    ((2048, 5632, 4, 64), (8, 2, 0), (32, 40), (64, 128)),
+    ((1536, 2048, 4, 64), (24, 4, 1), (25,), (60, 160)),
+    ((3072, 4000, 2, 64), (8, 2, 0), (12,), (40, 128)),
+])
+def test_each_batch_runs_the_way_that_measured_faster(lib, shape, layer, one_token, wide):
+    """Seen by the workspace that is asked for: the same as with the one-token kernels forced, or not."""
+    from paper_2505_05950_amd.binding import _Layer, _Shape
+    lib.floe_layer_workspace_bytes.restype = lib.floe_expert_workspace_bytes.restype = C.c_size_t
+    s = _Shape(*shape)
+
+    def size(T, mode):
+        lib.floe_tuning(1, mode)
+        if layer is None:
+            return lib.floe_expert_workspace_bytes(C.byref(s), T)
+        n, top_k, n_shared = layer
+        return lib.floe_layer_workspace_bytes(C.byref(_Layer(n, top_k, n_shared, 1, s, 4096, None, 4096, 0, 4096, 0)), T)
+
+    try:
+        for T in one_token:
+            assert size(T, 0) == size(T, 3), T
+        for T in wide:
+            assert size(T, 0) == size(T, 1), T
+    finally:
+        lib.floe_tuning(1, 0)

@@ -64,16 +64,16 @@ def test_only_the_static_entry_point_plans_for_the_scratch_array():
     """A batch that fits the array with fewer workgroups only: the static call runs it so, the workspace call as it likes."""
     import gpu_common as G
     import paper_2505_05950_amd as F
-    L, T = _layer(F, G, 34, 1024, 3584, 2, 64, 8, 2), 96
+    L, T = _layer(F, G, 34, 1536, 2048, 4, 64, 8, 2), 96
     assert F.floe_layer_workspace_bytes(L, T) > F.STATIC_SCRATCH_BYTES
     F.floe_tuning(F.TUNE_UNION_KERNELS, 3)
     fits = F.floe_layer_workspace_bytes(L, T) <= F.STATIC_SCRATCH_BYTES   # ... with the one-token kernels
     F.floe_tuning(F.TUNE_UNION_KERNELS, 0)
     assert fits
-    x = G.dev(S.tokens(35, 3, T, 1024))
+    x = G.dev(S.tokens(35, 3, T, L.d))
     st = [torch.zeros((T, 2, 4), dtype=torch.int32, device=G.DEV) for _ in range(2)]
     ref = F.floe_moe_layer_decode(L, x, stats=st[0]).float()
-    y = torch.zeros((T, 1024), dtype=torch.float16, device=G.DEV)
+    y = torch.zeros((T, L.d), dtype=torch.float16, device=G.DEV)
     F.floe_moe_layer_decode_static(L, x, y, st[1])
     torch.cuda.synchronize()
     assert torch.equal(st[0], st[1])
