@@ -19,11 +19,11 @@
 // Division of work: the row pairs of all groups form one sequence; the workgroups cut it into equal pieces, whatever the
 // routing did to the group sizes, so the launch is one even round and no compute unit waits for a crowded expert.
 //
-// What bounds it: the bytes a compute unit pulls in - rows, activations (gate) and h (down) - at 5.3 to 6.9 TB/s over the
-// chip; without its matrix instructions the gate kernel takes 254 us where it takes 286 with them.  Hence groups as large
-// as the accumulators allow (a second group reads the rows again), and rows requested two slices ahead.  Measured, gate +
-// down, 8 experts d 4096 f 14336 at 90 %: 64 tokens 364 -> 293 us (groups of at most 16 tokens before, half of the experts
-// read twice), 512 tokens 2425 (a workgroup set per task) -> 565 us.
+// What bounds it: the bytes a compute unit pulls in - rows, activations (gate) and h (down) - at 5.8 to 6.6 TB/s over the
+// chip; the vector and matrix units of the gate kernel are busy for 14 and 26 % of the cycles with ten tiles.  Hence groups as
+// large as the accumulators allow (a second group reads the rows again), and rows requested two slices ahead.  Measured, gate +
+// down, 8 experts d 4096 f 14336 at 90 %: 64 tokens 364 -> 292 us (groups of at most 16 tokens before, half of the experts
+// read twice), 512 tokens 2425 (a workgroup set per task) -> 546 us.
 
 #include "floe_dev.h"
 #include "launch.h"
@@ -557,16 +557,29 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
             const float* vt = a.v + (size_t)task * a.f;
             const float tau = a.task_tau[task];
             float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-            for (int r = seg0 * kPairRows, last = min(count, seg1 * kPairRows); r < last; ++r) {
-                const int row = rows[r], p = r / kPairRows - seg0, in = r % kPairRows;
-                if (!(fabsf(vt[row]) > tau)) continue;
-                const float h = hp[((size_t)(p * tiles + n) * 128 + (in >> 4) * 64 + ((in >> 2) & 3) * 16 + (tok & 15)) * 4 + (in & 3)];
-                const uint2 w = gload8(gd + ((uint32_t)row * (uint32_t)(4 * d) + dcol));
-                const h16x2 lo = as_h2(w.x), hi = as_h2(w.y);
-                s.x = fmaf(h, (float)lo.x, s.x);
-                s.y = fmaf(h, (float)lo.y, s.y);
-                s.z = fmaf(h, (float)hi.x, s.z);
-                s.w = fmaf(h, (float)hi.y, s.w);
+            constexpr int kRows = 8;  // requested together
+            for (int r0 = seg0 * kPairRows, last = min(count, seg1 * kPairRows); r0 < last; r0 += kRows) {
+                int row[kRows];
+                float vr[kRows], h[kRows];
+                uint2 w[kRows];
+#pragma unroll
+                for (int i = 0; i < kRows; ++i) row[i] = rows[min(r0 + i, last - 1)];
+#pragma unroll
+                for (int i = 0; i < kRows; ++i) {
+                    const int p = min(r0 + i, last - 1) / kPairRows - seg0, in = min(r0 + i, last - 1) % kPairRows;
+                    vr[i] = vt[row[i]];
+                    h[i] = hp[((size_t)(p * tiles + n) * 128 + (in >> 4) * 64 + ((in >> 2) & 3) * 16 + (tok & 15)) * 4 + (in & 3)];
+                    w[i] = gload8(gd + ((uint32_t)row[i] * (uint32_t)(4 * d) + dcol));
+                }
+#pragma unroll
+                for (int i = 0; i < kRows; ++i) {
+                    if (!(r0 + i < last && fabsf(vr[i]) > tau)) continue;
+                    const h16x2 lo = as_h2(w[i].x), hi = as_h2(w[i].y);
+                    s.x = fmaf(h[i], (float)lo.x, s.x);
+                    s.y = fmaf(h[i], (float)lo.y, s.y);
+                    s.z = fmaf(h[i], (float)hi.x, s.z);
+                    s.w = fmaf(h[i], (float)hi.y, s.w);
+                }
             }
             *o = s;
         }
