@@ -305,8 +305,8 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
         // Staged codes come back from LDS one pass ahead.  A pass's codes have landed once only the requests made
         // after them are outstanding: kVmPerPass per pass, and kDepth - 1 passes are behind pass p at its own turn,
         // kDepth - 2 behind pass p + 1 at that time.  The last round requests nothing, so there kDepth - 2 - i passes are
-        // behind pass i + 1.  (It used to repeat the final pass: 8 experts of d 4096 f 14336, one token, 22.54 us against 22.31, and in
-        // single-round kernels the compiler dropped the unread scales and zeros that the counts relied on.)  More may be
+        // behind pass i + 1.  (It used to repeat the final pass, which took the same time, but in single-round kernels the
+        // compiler dropped the unread scales and zeros that the counts relied on.)  More may be
         // outstanding - a store of v, say - which only makes a wait longer.
         u32x4 cw_next;
         if constexpr (kStaged) {

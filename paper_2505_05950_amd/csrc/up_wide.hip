@@ -6,13 +6,14 @@
 //                   sums per quantization group, the factor that undoes the scaling.  (Every workgroup of the grouped
 //                   kernel prepares them for itself; with many tokens per expert that would be most of its work.)
 //   up_wide_kernel  a wave takes 32 channels (two tiles of 16) for all tokens of a group (up to 64: four token tiles); one
-//                   slice of activations brought into LDS serves the 512 channels of sixteen waves.  Codes stream from memory into registers, a slice of four units
-//                   (256 columns) ahead; activations pass through LDS in the same slices.
+//                   slice of activations brought into LDS serves the 512 channels of sixteen waves.  Codes stream from
+//                   memory into registers, a slice of four units (256 columns) ahead; activations pass through LDS in the
+//                   same slices.
 //
-// What bounds it: vector instructions beside the matrix ones (55 % and 28 % of the cycles at 512 tokens): 18 per tile and
+// What bounds it: vector instructions beside the matrix ones (54 % and 24 % of the cycles at 512 tokens): 18 per tile and
 // unit to mask the codes, 8 per tile, unit and token tile for scale and zero.  Tiles without tokens are skipped for that
-// reason.  8 experts d 4096 f 14336 INT2: 512 tokens 417 us with the grouped kernel -> 303 us (both kernels); tried: four
-// channel tiles per wave with eight waves 395 us, two workgroups of eight waves per compute unit 344 us.
+// reason.  8 experts d 4096 f 14336 INT2, 512 tokens: 386 us with the grouped kernel -> 296 us (both kernels; 280 on another
+// card); tried: four channel tiles per wave with eight waves 395 us, two workgroups of eight waves per compute unit 344 us.
 //
 // Division of work: the blocks of 32 channels of all groups form one sequence that is cut into equal pieces, one workgroup
 // each (see wide_batch.hip).
