@@ -300,20 +300,22 @@ void set_union_mode(int m) { g_union_mode.store(m >= 0 && m <= 3 ? m : 0, std::m
 //   layers, large G: q >= 4 + 1.9 / G
 //     8 experts  d 4096 f 14336 INT2 (G 1.9):    q 5 253 / 219, 8 305 / 301, 10 360 / 312, 16 460 / 374
 //     16 experts d 4096 f 4096  INT2 (1.1):      q 5 187 / 187, 6 195 / 189, 8 250 / 230
-//   ... but at least q G = 4.2 where both ways run the same up projection
+//   ... but at least q G = 4.4 where both ways run the same up projection
 //     8 experts  d 1024 f 3584  INT2 (0.12):     q 24 79 / 92, 32 103 / 110
 //     4 experts  d 1024 f 10000 INT2 (0.16):     q 16 81 / 97, 24 98 / 110, 32 130 / 118
 //     8 experts  d 2048 f 5632  INT4 (0.37):     q 8 88 / 105, 12 120 / 124, 20 165 / 149
 //     8 experts  d 2048 f 3000  INT2 g32 (0.20): q 16 131 / 146, 20 156 / 157, 24 183 / 175
+//     64 experts d 1024 f 2048  INT2 (0.54):     q 8 149 / 159, 10 169 / 175, 12 185 / 181
 //     50 experts d 1024 f 1408  INT4 (0.29):     q 10 118 / 119, 16 147 / 139
 //   other layers take the wide up projection along and stay at the first line
 //     25 experts d 1536 f 2048  INT4 (0.32):     q 6 98 / 113, 8 123 / 121, 12 171 / 136
 //     8 experts  d 3072 f 4000  INT2 (0.39):     q 4 82 / 93, 8 143 / 118
-//   one expert, whose tokens go through the packed up projection one by one or the wide one: q G = 2.85
-//     d 1024 f 3584 INT2 (0.015): 160 tokens 79 / 104, 200 94 / 98     d 2048 f 5632 INT4 (0.046): 48 78 / 91, 64 89 / 89, 96 132 / 124
+//   one expert, whose tokens go through the packed up projection one by one or the wide one: q G = 2.85, for the smaller widths,
+//   whose rows are short against their partial results, 3.4, with groups of 32 (more scales per code in the wide one) 5
+//     d 1024 f 3584 INT2 (0.015): 160 tokens 79 / 104, 200 94 / 100    d 2048 f 5632 INT4 (0.046): 48 78 / 91, 64 92 / 97, 96 132 / 124
 //     d 4096 f 4096 INT2 (0.067): 32 78 / 88, 48 113 / 104             d 4096 f 14336 INT2 (0.23): 17 163 / 109
-//   one expert without a wide up projection: 3.6, for the smaller widths, whose rows are short against their partial results, 5
-//   (generic) and 10 (packed up projection)
+//     d 1024 f 8000 INT3 (0.033): 96 103 / 111, 128 143 / 115          d 2048 f 1408 INT3 g32 (0.012): 200 91 / 124, 256 111 / 143
+//   one expert without a wide up projection: 3.6, for the smaller widths 5 (generic) and 10 (packed up projection)
 //     d 2560 f 6911 INT4 g128 (0.071): 32 85 / 101, 48 132 / 127       d 4096 f 8000 INT8 (0.13): 24 196 / 197, 48 353 / 332
 //     d 1536 f 3000 INT8 (0.018): 160 128 / 171, 200 156 / 174         d 2048 f 8000 INT2 g128 (0.066): 64 114 / 134, 160 262 / 267
 int union_kernels_for(int n_all, int n_tasks, int d, int f, int bits, int group) {
@@ -323,8 +325,8 @@ int union_kernels_for(int n_all, int n_tasks, int d, int f, int bits, int group)
     const bool wide_up = up_wide_shape(d, f, bits, group), packed = packed_fast_shape(d, bits, group);
     double least = 1.9 + 4.0 * gb;
     double same_up = 0.0;
-    if (n_all > 1) same_up = !wide_up || mfma_grouped_shape(d, bits, group) ? 4.2 : 0.0;
-    else if (wide_up && packed) least = 2.85;
+    if (n_all > 1) same_up = !wide_up || mfma_grouped_shape(d, bits, group) ? 4.4 : 0.0;
+    else if (wide_up && packed) least = d > 2048 ? 2.85 : (group == 32 ? 5.0 : 3.4);
     else if (!wide_up) least = d > 2048 ? 3.6 : (packed ? 10.0 : 5.0);
     if (least < same_up) least = same_up;
     return n_tasks * gb >= least * n_all ? 1 : 3;

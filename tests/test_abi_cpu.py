@@ -147,10 +147,11 @@ def test_a_workspace_sized_for_the_largest_batch_serves_the_smaller_ones(lib, d,
 
 
 @pytest.mark.parametrize("shape,layer,one_token,wide", [
-    ((1024, 3584, 2, 64), None, (17, 128, 160), (210, 320)),             # batches at which each way measured clearly faster
+    ((1024, 3584, 2, 64), None, (17, 128, 160), (256, 320)),             # batches at which each way measured clearly faster
     ((2048, 5632, 4, 64), None, (17, 48), (96, 200)),
     ((4096, 4096, 2, 64), None, (17, 32), (48, 128)),
     ((4096, 14336, 2, 64), None, (), (17, 24, 64)),
+    ((2048, 1408, 3, 32), None, (17, 200, 256), ()),
     ((2048, 8000, 2, 128), None, (17, 64, 128), (200, 320)),
     ((1024, 14336, 2, 32), None, (17, 96), (200, 320)),
     ((4096, 14336, 4, 128), None, (), (17, 64)),
@@ -159,6 +160,7 @@ def test_a_workspace_sized_for_the_largest_batch_serves_the_smaller_ones(lib, d,
     ((1024, 3584, 2, 64), (8, 2, 0), (64, 96, 128), (200, 512)),
     ((4096, 14336, 2, 64), (8, 2, 0), (), (40, 64, 512)),
     ((2048, 1408, 3, 32), (64, 6, 2), (33,), (82, 132, 512)),
+    ((1024, 2048, 2, 64), (64, 8, 0), (48, 64), (128, 256)),
     ((2048, 3000, 2, 32), (8, 2, 0), (40, 64), (96, 128)),
     ((2048, 5632, 4, 64), (8, 2, 0), (32, 40), (64, 128)),
     ((1536, 2048, 4, 64), (24, 4, 1), (25,), (60, 160)),
