@@ -103,7 +103,7 @@ int floe_profile_kernel(int kernel_id, void* start_event, void* stop_event);
  *                            tokens routed to one expert share one pass over its codes on the matrix cores:
  *                            0 = where the one-kernel path (FLOE_TUNE_FUSED_TASKS) does not apply and measurement says
  *                                it pays (about two tokens per expert; three to four for INT3; in larger groups from
- *                                32 or, INT3 g32, 48 tokens per expert),
+ *                                32 to 48 tokens per expert, for layers of a good 40,000 channels in all),
  *                            1 = whenever the shape allows, 2 = never (one pass per (token, slot)).
  *   FLOE_TUNE_FUSED_TASKS    up to how many (token, slot) pairs a layer call runs Alg. 1 in one kernel (every workgroup
  *                            takes a block of channels of one pair through all steps) instead of the batch kernels:

@@ -218,7 +218,8 @@ LayerWs layer_plan(const floe_layer* L, int T, Wide form = Wide::kChosen, int ma
     const size_t wgroups = w.use_wide ? (size_t)w.wp.max_groups : 0;
     w.wgroups_off = o; o += w.use_wide ? align_up(wgroups * sizeof(WideGroup) + 4) : 0;  // (+ their number)
     w.up_wide = w.use_wide && up_wide_pays(L->s.d, L->s.f, L->s.bits, L->s.group, n_all, w.n_tasks);
-    w.xfrag_off = o;   o += w.up_wide ? align_up(up_wide_scratch_bytes(T, L->s.d, L->s.group)) : 0;
+    const bool room_for_x = room && up_wide_shape(L->s.d, L->s.f, L->s.bits, L->s.group) && grouped_gemv_mode() != 2;
+    w.xfrag_off = o;   o += w.up_wide || room_for_x ? align_up(up_wide_scratch_bytes(T, L->s.d, L->s.group)) : 0;
     w.urow_off = o;    o += align_up(wgroups * L->s.f * 4);
     w.ucount_off = o;  o += align_up(wgroups * 4);
     w.hbuf_off = o;    o += align_up((size_t)w.wp.h_tiles * w.wp.pairs * 128 * sizeof(uint4));

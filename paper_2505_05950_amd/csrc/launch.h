@@ -208,12 +208,17 @@ inline bool up_wide_shape(int d, int f, int bits, int group) {
 // in every workgroup, this one prepares them once and shares a pass over the codes among up to 64.  Layer calls measured,
 // grouped / this, us (8 experts): INT2 g64 d 4096 f 14336 at 16 tasks per expert 375 / 392, 32: 529 / 491, 128: 907 / 792;
 // INT3 g64 d 2048 f 7000 at 16: 153 / 153, 32: 225 / 208, 128: 461 / 320; INT4 g32 d 2048 f 5632 at 128: 328 / 351;
-// INT3 g32 d 2048 f 1408 (66 experts) at 31: 373 / 410, 62: 525 / 480.
+// INT3 g32 d 2048 f 1408 (66 experts) at 31: 373 / 410, 62: 525 / 480; INT4 g64 d 4096 f 7000 (6) at 32: 250 / 306, 40: 307 / 293.
+// A wave takes 32 channels of an expert here; layers with few of them leave most waves idle: INT2 at 32 tasks per expert, 352
+// blocks of 32 channels (16 experts d 2048 f 700) 99 / 116, 704 (4, d 2048 f 5632) 112 / 126, 896 (8, d 1024 f 3584) 104 / 107,
+// 1252 (4, d 1024 f 10000) 119 / 120, 2048 (16, d 4096 f 4096) 325 / 327 and 423 / 380 at 64.
 inline bool up_wide_pays(int d, int f, int bits, int group, int n_all, int n_tasks) {
     if (!up_wide_shape(d, f, bits, group)) return false;
     if (!mfma_grouped_shape(d, bits, group)) return true;
     if (grouped_gemv_mode() == 2) return false;  // the caller wants one pass per task
-    return group == 64 ? n_tasks >= 32 * n_all : (bits == 3 && n_tasks >= 48 * n_all);
+    if (group == 32) return bits == 3 && n_tasks >= 48 * n_all;
+    if (bits == 3) return n_tasks >= 32 * n_all;
+    return n_tasks >= (bits == 2 ? 32 : 40) * n_all && n_all * ((f + 31) / 32) >= 1250;
 }
 struct UpWideArgs {
     const DevExpert* table;

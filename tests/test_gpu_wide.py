@@ -113,10 +113,36 @@ def test_one_expert_scales_with_their_own_alignment_only():
     assert G.rel_err(y2.cpu().numpy(), y.cpu().numpy()) <= 1e-4   # another kernel's order of summation
 
 
-@pytest.mark.parametrize("T", [40, 200])   # grouped up projection, wide up projection
+@pytest.mark.parametrize("T", [40, 200])   # grouped up projection, one and four groups of 16 tokens per expert
 def test_replayed_from_a_hip_graph(T):
     import test_gpu_layer as layer
     layer.test_layer_decode_replayed_from_a_hip_graph_matches_eager(T)
+
+
+@pytest.mark.parametrize("d,f,bits,group,n,T", [(1536, 700, 3, 64, 4, 40), (1024, 5120, 2, 64, 8, 160)])   # no grouped kernel; many channels
+def test_wide_up_projection_replayed_from_a_hip_graph(d, f, bits, group, n, T):
+    """Replays, with eager work and synchronisations between them, reproduce the eager result bit for bit."""
+    import gpu_common as G
+    import paper_2505_05950_amd as F
+    experts = [G.make_expert(*S.expert_weights(101, 3, d, f, 0, e), bits, group)[1] for e in range(n)]
+    L = F.Layer(experts, 0, 2, True, G.dev(S.router_weights(101, 3, n, d)), G.dev(np.full((n,), 1.0, np.float32)), False)
+    xs = [G.dev(S.tokens(101, 3, T, d, layer=i)) for i in range(3)]
+    eager = [F.floe_moe_layer_decode(L, x).clone() for x in xs]
+    x_in, y = xs[0].clone(), torch.empty((T, d), dtype=torch.float16, device=G.DEV)
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        F.floe_moe_layer_decode(L, x_in, y)
+        stream.synchronize()
+        with torch.cuda.graph(graph, stream=stream):
+            F.floe_moe_layer_decode(L, x_in, y)
+        for i in (0, 1, 2, 1, 0):
+            torch.add(xs[i], 0.0, out=x_in)     # (a kernel on the same stream writes the input)
+            y.fill_(float("nan"))
+            graph.replay()
+            stream.synchronize()
+            assert torch.equal(y, eager[i]), i
+            assert torch.equal(F.floe_moe_layer_decode(L, x_in), eager[i]), i
 
 
 def test_one_pass_per_task_stays_a_choice():
