@@ -526,7 +526,7 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
         }
         // lane (l16, q4) holds Y[token 16 n + 4 q4 + i][columns col .. col + 3]
         float* out = a.partial + ((size_t)grp.first + (size_t)piece * kTok) * d + col;
-        float odd = 0.0f;  // NaN once a sum is not finite
+        uint64_t odd = 0ull;  // bit 4 n + i: a sum of token 16 n + 4 q4 + i is not finite
         int tok0 = 4 * q4;
         asm volatile("" : "+v"(tok0));  // or the addresses below are formed ahead of the loop and spilled across it
 #pragma unroll
@@ -539,49 +539,56 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
                     float* o = out + (size_t)tok * d;
                     const float4 y = make_float4(acc[0][n][i] * back, acc[1][n][i] * back, acc[2][n][i] * back, acc[3][n][i] * back);
                     *reinterpret_cast<float4*>(o) = y;
-                    odd = fmaf(y.x, 0.0f, fmaf(y.y, 0.0f, fmaf(y.z, 0.0f, fmaf(y.w, 0.0f, odd))));
+                    if (!(fmaf(y.x, 0.0f, fmaf(y.y, 0.0f, fmaf(y.z, 0.0f, y.w * 0.0f))) == 0.0f)) odd |= 1ull << (4 * n + i);
                 }
             }
         // A row that a token did not select entered its sums as h = 0, and 0 times a weight that is not finite is NaN.  Such
-        // sums, seen here by their results, are formed again from the token's own rows alone.
-        if (__ballot(!(odd == 0.0f)) == 0ull) continue;
+        // sums, seen here by their results, are formed again from the token's own rows alone: four columns of one token at a
+        // time, the rows dealt to the lanes of the wave.
+        const uint64_t lanes = __ballot(odd != 0ull);
+        if (lanes == 0ull) continue;
+        __threadfence_block();  // the stores above are done before others to the same places
         const float* hp = reinterpret_cast<const float*>(hsrc);
-#pragma unroll 1
-        for (int k = 0; k < 4 * NT; ++k) {
-            const int n = k >> 2, tok = 16 * n + 4 * q4 + (k & 3);
-            if (tok >= grp.n) continue;
-            float4* o = reinterpret_cast<float4*>(out + (size_t)tok * d);
-            const float4 y = *o;
-            if (fmaf(y.x, 0.0f, fmaf(y.y, 0.0f, fmaf(y.z, 0.0f, y.w * 0.0f))) == 0.0f) continue;
-            const int task = a.order[grp.first + tok];
-            const float* vt = a.v + (size_t)task * a.f;
-            const float tau = a.task_tau[task];
-            float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-            constexpr int kRows = 8;  // requested together
-            for (int r0 = seg0 * kPairRows, last = min(count, seg1 * kPairRows); r0 < last; r0 += kRows) {
-                int row[kRows];
-                float vr[kRows], h[kRows];
-                uint2 w[kRows];
+        const int first = seg0 * kPairRows, last = min(count, seg1 * kPairRows);
+        for (uint64_t left = lanes; left != 0ull; left &= left - 1ull) {
+            const int src = __ffsll((long long)left) - 1;  // the lane that holds these columns, for a quarter of the tokens
+            uint64_t toks = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)odd, src) |
+                            (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(odd >> 32), src) << 32;
+            const int c0 = blockIdx.y * kDownCols + wave * 64 + 4 * (src & 15);
+            for (; toks != 0ull; toks &= toks - 1ull) {
+                const int bit = __ffsll((long long)toks) - 1, n = bit >> 2, tok = 16 * n + 4 * (src >> 4) + (bit & 3);
+                const int task = a.order[grp.first + tok];
+                const float* vt = a.v + (size_t)task * a.f;
+                const float tau = a.task_tau[task];
+                float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+                constexpr int kRows = 4;  // per lane, requested together
+                for (int r0 = first; r0 < last; r0 += kRows * kWave) {
+                    int row[kRows];
+                    float vr[kRows], h[kRows];
+                    uint2 w[kRows];
 #pragma unroll
-                for (int i = 0; i < kRows; ++i) row[i] = rows[min(r0 + i, last - 1)];
+                    for (int i = 0; i < kRows; ++i) row[i] = rows[min(r0 + i * kWave + lane, last - 1)];
 #pragma unroll
-                for (int i = 0; i < kRows; ++i) {
-                    const int p = min(r0 + i, last - 1) / kPairRows - seg0, in = min(r0 + i, last - 1) % kPairRows;
-                    vr[i] = vt[row[i]];
-                    h[i] = hp[((size_t)(p * tiles + n) * 128 + (in >> 4) * 64 + ((in >> 2) & 3) * 16 + (tok & 15)) * 4 + (in & 3)];
-                    w[i] = gload8(gd + ((uint32_t)row[i] * (uint32_t)(4 * d) + dcol));
+                    for (int i = 0; i < kRows; ++i) {
+                        const int r = min(r0 + i * kWave + lane, last - 1), p = r / kPairRows - seg0, in = r % kPairRows;
+                        vr[i] = vt[row[i]];
+                        h[i] = hp[((size_t)(p * tiles + n) * 128 + (in >> 4) * 64 + ((in >> 2) & 3) * 16 + (tok & 15)) * 4 + (in & 3)];
+                        w[i] = gload8(gd + ((uint32_t)row[i] * (uint32_t)(4 * d) + 2 * (uint32_t)(d + c0)));
+                    }
+#pragma unroll
+                    for (int i = 0; i < kRows; ++i) {
+                        if (!(r0 + i * kWave + lane < last && fabsf(vr[i]) > tau)) continue;
+                        const h16x2 lo = as_h2(w[i].x), hi = as_h2(w[i].y);
+                        sum.x = fmaf(h[i], (float)lo.x, sum.x);
+                        sum.y = fmaf(h[i], (float)lo.y, sum.y);
+                        sum.z = fmaf(h[i], (float)hi.x, sum.z);
+                        sum.w = fmaf(h[i], (float)hi.y, sum.w);
+                    }
                 }
-#pragma unroll
-                for (int i = 0; i < kRows; ++i) {
-                    if (!(r0 + i < last && fabsf(vr[i]) > tau)) continue;
-                    const h16x2 lo = as_h2(w[i].x), hi = as_h2(w[i].y);
-                    s.x = fmaf(h[i], (float)lo.x, s.x);
-                    s.y = fmaf(h[i], (float)lo.y, s.y);
-                    s.z = fmaf(h[i], (float)hi.x, s.z);
-                    s.w = fmaf(h[i], (float)hi.y, s.w);
-                }
+                const float4 y = make_float4(wave_allreduce_sum(sum.x), wave_allreduce_sum(sum.y), wave_allreduce_sum(sum.z), wave_allreduce_sum(sum.w));
+                if (lane == 0)
+                    *reinterpret_cast<float4*>(a.partial + ((size_t)grp.first + (size_t)piece * kTok + tok) * d + c0) = y;
             }
-            *o = s;
         }
     }
 }
