@@ -91,7 +91,7 @@ TaskMap single_map(const floe_expert* e) {
 // workspace of the one-expert entry points: [v: T*f floats][mask words][counts][idx when not fused][partial: T*nblk*d floats]
 struct ExpertWs {
     size_t v_off, mask_off, count_off, idx_off, partial_off, total;
-    size_t table_off, order_off, wgroups_off, xfrag_off, urow_off, ucount_off, hbuf_off, hmax_off, trows_off;  // wide path
+    size_t order_off, wgroups_off, xfrag_off, urow_off, ucount_off, hbuf_off, hmax_off, trows_off;  // wide path
     int nblk, fused_passes, nblk_fused;
     bool wide;  // many tokens: one read of every row that any of a group of tokens selected (wide_batch.hip)
     WidePlan wp;
@@ -100,6 +100,11 @@ bool mask_path_ok(int f);
 // which form of the wide path a plan may take: the one that a call runs, none, or room for any that a batch of up to T
 // tokens can take
 enum class Wide { kChosen, kNone, kRoom };
+// h of the wide groups; before it is formed the activations that up_split reads lie in the same place
+size_t wide_h_bytes(const WidePlan& p, int d, int group) {
+    const size_t h = (size_t)p.h_tiles * p.pairs * 128 * sizeof(uint4), x = up_split_scratch_bytes(p.h_tiles, d, group);
+    return h > x ? h : x;
+}
 ExpertWs expert_ws(const floe_shape* s, int T, Wide form = Wide::kChosen) {
     ExpertWs w{};
     w.nblk = gd_blocks(T, s->f);
@@ -113,13 +118,12 @@ ExpertWs expert_ws(const floe_shape* s, int T, Wide form = Wide::kChosen) {
     w.wide = form != Wide::kNone && !w.fused_passes && T >= 2 && mask_path_ok(s->f) && union_kernels_for(1, T, s->d, s->f, s->bits, s->group) == 1;
     if (w.wide) {
         w.wp = form == Wide::kRoom ? wide_room(s->d, s->f, T, 1, 1, 0) : wide_plan(s->d, s->f, T, 1, 1, 0, 0);
-        w.table_off = o;   o += align_up(sizeof(DevExpert));
         w.order_off = o;   o += align_up((size_t)T * 4);
         w.wgroups_off = o; o += align_up((size_t)w.wp.max_groups * sizeof(WideGroup) + 4);
         w.xfrag_off = o;   o += align_up(up_wide_scratch_bytes(T, s->d, s->group));
         w.urow_off = o;    o += align_up((size_t)w.wp.max_groups * s->f * 4);
         w.ucount_off = o;  o += align_up((size_t)w.wp.max_groups * 4);
-        w.hbuf_off = o;    o += align_up((size_t)w.wp.h_tiles * w.wp.pairs * 128 * sizeof(uint4));
+        w.hbuf_off = o;    o += align_up(wide_h_bytes(w.wp, s->d, s->group));
         w.hmax_off = o;    o += align_up((size_t)T * 4);
         w.trows_off = o;   o += align_up((size_t)T * sizeof(int2));
     }
@@ -158,6 +162,7 @@ struct LayerWs {
     bool batch_mfma;  // tokens of an expert share one pass over its codes (matrix-core up GEMV)
     bool use_wide;    // batches: one read of every row an expert group selected, on the matrix cores (wide_batch.hip)
     bool up_wide;     // ... and so does the up projection (up_wide.hip)
+    bool up_split;    // ... with the columns split over the waves (up_split.hip)
     bool use_union;   // the same through an LDS ring (gate_down_union.hip; by tuning only)
     int chunk;        // tasks per token group
     UnionPlan up;
@@ -217,12 +222,13 @@ LayerWs layer_plan(const floe_layer* L, int T, Wide form = Wide::kChosen, int ma
     w.misscount_off = o; o += L->gd_on_host ? align_up((size_t)w.n_tasks * 4) : 0;
     const size_t wgroups = w.use_wide ? (size_t)w.wp.max_groups : 0;
     w.wgroups_off = o; o += w.use_wide ? align_up(wgroups * sizeof(WideGroup) + 4) : 0;  // (+ their number)
-    w.up_wide = w.use_wide && up_wide_pays(L->s.d, L->s.f, L->s.bits, L->s.group, n_all, w.n_tasks);
+    w.up_split = w.use_wide && up_split_pays(L->s.d, L->s.f, L->s.bits, L->s.group, w.wp.nt);
+    w.up_wide = w.use_wide && !w.up_split && up_wide_pays(L->s.d, L->s.f, L->s.bits, L->s.group, n_all, w.n_tasks);
     const bool room_for_x = room && up_wide_shape(L->s.d, L->s.f, L->s.bits, L->s.group) && grouped_gemv_mode() != 2;
     w.xfrag_off = o;   o += w.up_wide || room_for_x ? align_up(up_wide_scratch_bytes(T, L->s.d, L->s.group)) : 0;
     w.urow_off = o;    o += align_up(wgroups * L->s.f * 4);
     w.ucount_off = o;  o += align_up(wgroups * 4);
-    w.hbuf_off = o;    o += align_up((size_t)w.wp.h_tiles * w.wp.pairs * 128 * sizeof(uint4));
+    w.hbuf_off = o;    o += w.use_wide ? align_up(wide_h_bytes(w.wp, L->s.d, L->s.group)) : 0;
     w.hmax_off = o;    o += w.use_wide ? align_up((size_t)w.n_tasks * 4) : 0;
     w.trows_off = o;   o += w.use_wide ? align_up((size_t)w.n_tasks * sizeof(int2)) : 0;
     w.partial_off = o;
@@ -480,24 +486,26 @@ int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, cons
         }
     } else if (w.wide) {
         char* base = static_cast<char*>(workspace);
-        DevExpert* table = reinterpret_cast<DevExpert*>(base + w.table_off);
         WideGroup* groups = reinterpret_cast<WideGroup*>(base + w.wgroups_off);
         int32_t* n_groups = reinterpret_cast<int32_t*>(groups + w.wp.max_groups);
         int32_t* order = reinterpret_cast<int32_t*>(base + w.order_off);
-        FLOE_HIP(launch_wide_single(map.single, T, w.wp.chunk, table, groups, n_groups, order, st));
         // (scales and zeros need no more than their own alignment here; the wide kernel loads them 16 bytes at a time)
         if (up_wide_shape(e->s.d, e->s.f, e->s.bits, e->s.group) && aligned(e->up_scale, 16) && aligned(e->up_zero, 16)) {
             UpWideArgs u{};
-            u.table = table; u.groups = groups; u.n_groups = n_groups; u.order = order; u.x = xh; u.v = v;
-            u.task_tau = tau; u.mask_words = mask; u.scratch = base + w.xfrag_off;
-            u.T = T; u.d = e->s.d; u.f = e->s.f; u.slots = 1; u.nt = w.wp.nt; u.est_groups = w.wp.est_groups;
-            FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st, launch_up_wide(u, e->s.bits, e->s.group, st));
+            const bool split = up_split_pays(e->s.d, e->s.f, e->s.bits, e->s.group, w.wp.nt);
+            u.groups = groups; u.n_groups = n_groups; u.order = order; u.x = xh; u.v = v;
+            u.task_tau = tau; u.mask_words = mask; u.scratch = base + (split ? w.hbuf_off : w.xfrag_off);
+            u.T = T; u.n_tasks = T; u.d = e->s.d; u.f = e->s.f; u.slots = 1; u.nt = w.wp.nt;
+            u.max_groups = w.wp.max_groups; u.est_groups = w.wp.est_groups;
+            u.single = &map.single; u.chunk = w.wp.chunk;
+            FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st, split ? launch_up_split(u, e->s.bits, e->s.group, st) : launch_up_wide(u, e->s.bits, e->s.group, st));
         } else {
+            FLOE_HIP(launch_wide_single(map.single, T, w.wp.chunk, groups, n_groups, order, st));
             FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st,
                         launch_up_gemv(map, xh, nullptr, v, tau, mask, e->s.d, e->s.f, e->s.bits, e->s.group, T, st));
         }
         WideArgs wa{};
-        wa.table = table; wa.groups = groups; wa.n_groups = n_groups; wa.order = order; wa.x = xh; wa.v = v;
+        wa.groups = groups; wa.n_groups = n_groups; wa.order = order; wa.x = xh; wa.v = v;
         wa.task_tau = tau; wa.task_scale = out_scale;
         wa.count = reinterpret_cast<int32_t*>(base + w.count_off);
         wa.urow = reinterpret_cast<int32_t*>(base + w.urow_off);
@@ -714,16 +722,18 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
         int32_t* n_wide = reinterpret_cast<int32_t*>(wide + w.wp.max_groups);
         int32_t* order = reinterpret_cast<int32_t*>(base + w.order_off);
         if (w.use_wide)
-            FLOE_HIP(launch_group_tokens(task_expert, w.n_tasks, n_all, w.chunk, groups, n_groups, st, order, w.wp.chunk, wide, n_wide));
+            FLOE_HIP(launch_group_tokens(task_expert, w.n_tasks, n_all, w.chunk, groups, n_groups, st, order, w.wp.chunk, wide, n_wide,
+                                         static_cast<const DevExpert*>(L->dev_table)));
         else
             FLOE_HIP(launch_group_tokens(task_expert, w.n_tasks, n_all, w.chunk, groups, n_groups, st));
-        if (w.up_wide) {
+        if (w.up_wide || w.up_split) {
             UpWideArgs u{};
-            u.table = static_cast<const DevExpert*>(L->dev_table);
             u.groups = wide; u.n_groups = n_wide; u.order = order; u.x = xh; u.v = v;
-            u.task_tau = task_tau; u.mask_words = mask; u.scratch = base + w.xfrag_off;
-            u.T = T; u.d = L->s.d; u.f = L->s.f; u.slots = slots; u.nt = w.wp.nt; u.est_groups = w.wp.est_groups;
-            FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st, launch_up_wide(u, L->s.bits, L->s.group, st));
+            u.task_tau = task_tau; u.mask_words = mask; u.scratch = base + (w.up_split ? w.hbuf_off : w.xfrag_off);
+            u.T = T; u.n_tasks = w.n_tasks; u.d = L->s.d; u.f = L->s.f; u.slots = slots; u.nt = w.wp.nt;
+            u.max_groups = w.wp.max_groups; u.est_groups = w.wp.est_groups;
+            FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st,
+                        w.up_split ? launch_up_split(u, L->s.bits, L->s.group, st) : launch_up_wide(u, L->s.bits, L->s.group, st));
         } else if (batch_mfma)
             FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st,
                         launch_up_gemv_grouped(static_cast<const DevExpert*>(L->dev_table), groups, n_groups,
@@ -735,7 +745,6 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
                                        w.n_tasks, st));
         if (w.use_wide) {
             WideArgs wa{};
-            wa.table = static_cast<const DevExpert*>(L->dev_table);
             wa.groups = wide; wa.n_groups = n_wide; wa.order = order; wa.x = xh; wa.v = v;
             wa.task_tau = task_tau; wa.task_scale = task_weight; wa.count = count;
             wa.urow = reinterpret_cast<int32_t*>(base + w.urow_off);

@@ -37,6 +37,11 @@ __device__ __forceinline__ uint4 gload16(const void* p) {
     const u32x4 q = *(const FLOE_GLOBAL u32x4*)p;
     return make_uint4(q.x, q.y, q.z, q.w);
 }
+__device__ __forceinline__ uint4 gload16u(const void* p) {  // from any multiple of four bytes
+    typedef u32x4 u32x4_4 __attribute__((aligned(4)));
+    const u32x4 q = *(const FLOE_GLOBAL u32x4_4*)p;
+    return make_uint4(q.x, q.y, q.z, q.w);
+}
 __device__ __forceinline__ uint2 gload8(const void* p) {
     const u32x2 q = *(const FLOE_GLOBAL u32x2*)p;
     return make_uint2(q.x, q.y);
@@ -143,6 +148,15 @@ static __device__ unsigned long long* g_timeline = nullptr;  // one copy per tra
     } while (0)
 #endif
 #define FLOE_TL(slot) FLOE_TL_AT(slot, 0)
+
+__device__ __forceinline__ int wave_inclusive_scan(int x, int lane) {
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int up = __shfl_up(x, o, kWave);
+        if (lane >= o) x += up;
+    }
+    return x;
+}
 
 // ---- equal division of a launch's work (wide_batch.hip, up_wide.hip)
 // a pointer that every lane holds alike, as a scalar (loads then take it as their base and a 32-bit offset per lane)

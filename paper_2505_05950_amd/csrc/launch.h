@@ -116,10 +116,10 @@ inline bool mfma_batch_pays(int n_all, int n_tasks, int bits) {
     return bits == 3 ? 2 * n_tasks >= 7 * n_all : n_tasks >= 2 * n_all;
 }
 struct WideGroup;
-// wide (optional, with order): the same tasks cut into as few groups of at most wide_chunk as possible, of equal size per expert
+// wide (optional, with order and table): the same tasks cut into as few groups of at most wide_chunk as possible, of equal size per expert
 hipError_t launch_group_tokens(const int32_t* task_expert, int n_tasks, int n_all, int chunk, TokenGroup* groups,
                                int32_t* n_groups, hipStream_t stream, int32_t* order = nullptr, int wide_chunk = 0,
-                               WideGroup* wide = nullptr, int32_t* n_wide = nullptr);
+                               WideGroup* wide = nullptr, int32_t* n_wide = nullptr, const DevExpert* table = nullptr);
 hipError_t launch_up_gemv_grouped(const DevExpert* table, const TokenGroup* groups, const int32_t* n_groups,
                                   int max_groups, int chunk, const h16* x, int slots, float* v, const float* task_tau,
                                   uint32_t* mask_words, int d, int f, int bits, int group, hipStream_t stream);
@@ -172,7 +172,22 @@ double expected_token_groups(int n_experts, int T, int top_k, int chunk);
 // S4 + S5 on the matrix cores for batches in which experts see many tokens (wide_batch.hip): groups of up to 16 * nt tokens.
 struct WideGroup {
     int32_t expert, n, first;  // tasks order[first .. first + n)
+    int32_t tile;              // number of its first token tile: (first + 15 * group) / 16, so that no two groups share one
+    DevExpert e;               // the expert's arrays, so that nobody has to look them up behind this load
 };
+static_assert(sizeof(WideGroup) == 48, "loaded as three vectors");
+
+// the groups of a single expert that all of n_tasks tasks belong to: as few of at most `chunk` as possible, of equal size
+__host__ __device__ inline int wide_single_groups(int n_tasks, int chunk) { return (n_tasks + chunk - 1) / chunk; }
+__host__ __device__ inline int wide_single_len(int n_tasks, int chunk) {
+    const int ng = wide_single_groups(n_tasks, chunk);
+    return (n_tasks + ng - 1) / ng;
+}
+__host__ __device__ inline WideGroup wide_single_group(const DevExpert& e, int n_tasks, int chunk, int g) {
+    const int len = wide_single_len(n_tasks, chunk), first = g * len < n_tasks ? g * len : n_tasks;
+    const int n = n_tasks - first < len ? n_tasks - first : len;
+    return WideGroup{0, n, first, (first + 15 * g) >> 4, e};
+}
 
 constexpr int kWideMaxMaskWords = 2048;  // f <= 65536
 struct WidePlan {
@@ -183,7 +198,6 @@ struct WidePlan {
     size_t partial_rows;    // rows of d floats
 };
 struct WideArgs {
-    const DevExpert* table;
     const WideGroup* groups;
     const int32_t* n_groups;
     const int32_t* order;     // [n_tasks] tasks sorted by expert
@@ -221,7 +235,6 @@ inline bool up_wide_pays(int d, int f, int bits, int group, int n_all, int n_tas
     return n_tasks >= (bits == 2 ? 32 : 40) * n_all && n_all * ((f + 31) / 32) >= 1250;
 }
 struct UpWideArgs {
-    const DevExpert* table;
     const WideGroup* groups;
     const int32_t* n_groups;
     const int32_t* order;
@@ -230,16 +243,34 @@ struct UpWideArgs {
     const float* task_tau;
     uint32_t* mask_words;
     void* scratch;  // up_wide_scratch_bytes()
-    int32_t T, d, f, slots, nt, est_groups, parts, workgroups;  // (parts, workgroups: set by the launcher)
+    int32_t T, n_tasks, d, f, slots, nt, max_groups, est_groups, parts, workgroups;  // (parts, workgroups: set by the launcher)
+    const DevExpert* single;  // one expert that every task belongs to: the launcher fills groups, n_groups and order in as well
+    int32_t chunk;            // (single) tasks per group at most
 };
 size_t up_wide_scratch_bytes(int T, int d, int group);
 hipError_t launch_up_wide(UpWideArgs a, int bits, int group, hipStream_t stream);
 
+// S2 for groups of up to two token tiles, the columns split over the waves of a workgroup (up_split.hip)
+inline bool up_split_shape(int d, int f, int bits, int group) { return up_wide_shape(d, f, bits, group) && d <= 4096; }
+// Which of the up projections a batch of wide groups takes.  Layer calls, grouped or wide kernel / this, us: INT2 g64 d 4096 f 14336
+// (8 experts, top-2) at 40 tokens 314 / 308, 96: 430 / 415; 4 experts 32 tokens 224 / 217; INT3 g64 d 2048 f 7000 at 64: 177 / 152;
+// INT3 g32 d 4096 f 4096 (16 experts) at 128: 420 / 284; d 2048 f 1408 (66 experts, top-6) at 64: 220 / 195, 128: 260 / 245;
+// INT4 g64 d 4096 f 7000 (6) at 48: 222 / 202; INT4 g32 d 2048 f 5632 at 64: 138 / 137; widths without a grouped kernel the same.
+// With one token tile INT2 leaves the grouped kernel little to share a pass with and less to unpack: 24 tokens 243 / 251.
+inline bool up_split_pays(int d, int f, int bits, int group, int nt) {
+    if (!up_split_shape(d, f, bits, group)) return false;
+    const bool grouped = mfma_grouped_shape(d, bits, group);
+    if (grouped && grouped_gemv_mode() == 2) return false;  // the caller wants one pass per task
+    return nt <= 2 && !(grouped && bits == 2 && nt == 1);
+}
+hipError_t launch_up_split(UpWideArgs a, int bits, int group, hipStream_t stream);
+size_t up_split_scratch_bytes(int tiles, int d, int group);  // tiles: token tiles that the groups can have together
+
 WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared, int max_down);
 WidePlan wide_room(int d, int f, int T, int n_experts, int top_k, int n_shared);
 hipError_t launch_gate_down_wide(const WideArgs& a, const WidePlan& p, const uint32_t* mask_words, int d, hipStream_t stream);
-hipError_t launch_wide_single(const DevExpert& e, int n_tasks, int chunk, DevExpert* table, WideGroup* groups, int32_t* n_groups,
-                              int32_t* order, hipStream_t stream);
+hipError_t launch_wide_single(const DevExpert& e, int n_tasks, int chunk, WideGroup* groups, int32_t* n_groups, int32_t* order,
+                              hipStream_t stream);
 hipError_t launch_combine_wide(const WideArgs& a, const WidePlan& p, int d, int T, float* y_acc, h16* y_half, hipStream_t stream);
 
 // The other sparsification candidates of Sec. 3.2.1 (variants.hip): act = a_gate (which = 1) or a_down (which = 2) and

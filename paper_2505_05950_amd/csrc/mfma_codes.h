@@ -119,4 +119,54 @@ __device__ __forceinline__ h16x8 as_h8(const uint32_t (&r)[4]) {
     return __builtin_bit_cast(h16x8, q);
 }
 
+__device__ __forceinline__ void transpose4(uint4& q) {  // across the four lane quarters: register k <- word g of quarter k's vector
+    u32x2 t;
+    t = __builtin_amdgcn_permlane32_swap(q.x, q.z, false, false); q.x = t.x; q.z = t.y;
+    t = __builtin_amdgcn_permlane32_swap(q.y, q.w, false, false); q.y = t.x; q.w = t.y;
+    t = __builtin_amdgcn_permlane16_swap(q.x, q.y, false, false); q.x = t.x; q.y = t.y;
+    t = __builtin_amdgcn_permlane16_swap(q.z, q.w, false, false); q.z = t.x; q.w = t.y;
+}
+
+// One slice (four units) of a channel tile: what a lane loads and the operand words it makes of it.  Quarter g of a
+// channel's four lanes loads unit g whole; the transposes hand every quarter its words of all four units.
+template <int BITS>
+struct CodeSlice {
+    static constexpr int kVec = BITS == 4 ? 2 : 1;  // 16-byte vectors per unit (INT3: three 8-byte ones)
+    static constexpr int kLaneWords = BITS == 2 ? 1 : 2;  // operand words per unit
+    uint4 raw[kVec];
+    uint32_t raw3[BITS == 3 ? 6 : 1];
+    __device__ __forceinline__ void load(const unsigned char* codes, uint32_t off) {
+        if constexpr (BITS == 3) {
+#pragma unroll
+            for (int r = 0; r < 3; ++r) {
+                const uint2 q = gload8(codes + (off + 8 * r));
+                raw3[2 * r] = q.x;
+                raw3[2 * r + 1] = q.y;
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < kVec; ++r) raw[r] = gload16(codes + (off + 16 * r));
+        }
+    }
+    __device__ __forceinline__ void deal(uint32_t (&wd)[4][kLaneWords]) const {  // [unit of the slice][word]
+        if constexpr (BITS == 3) {
+            // this lane's unit: two halves of 96 bits, four 24-bit fields each; field k goes to quarter k
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint32_t w0 = raw3[3 * h], w1 = raw3[3 * h + 1], w2 = raw3[3 * h + 2];
+                uint4 fld = make_uint4(w0, __builtin_amdgcn_alignbit(w1, w0, 24), __builtin_amdgcn_alignbit(w2, w1, 16), w2 >> 8);
+                transpose4(fld);
+                wd[0][h] = fld.x; wd[1][h] = fld.y; wd[2][h] = fld.z; wd[3][h] = fld.w;
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < kVec; ++r) {
+                uint4 w = raw[r];
+                transpose4(w);
+                wd[0][r] = w.x; wd[1][r] = w.y; wd[2][r] = w.z; wd[3][r] = w.w;
+            }
+        }
+    }
+};
+
 }  // namespace floe

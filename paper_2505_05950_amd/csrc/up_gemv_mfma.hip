@@ -379,7 +379,8 @@ __global__ __launch_bounds__(1024) void group_tokens_kernel(const int32_t* __res
                                                             int n_all, int chunk, TokenGroup* __restrict__ groups,
                                                             int32_t* __restrict__ n_groups, int32_t* __restrict__ order,
                                                             int wide_chunk, WideGroup* __restrict__ wide,
-                                                            int32_t* __restrict__ n_wide) {
+                                                            int32_t* __restrict__ n_wide,
+                                                            const DevExpert* __restrict__ table) {
     // A thread per task, 1024 tasks (16 waves of 64) at a time.  A task's place in its expert's list is
     //   (tasks of that expert in earlier tiles) + (in earlier waves of this tile) + (in lower lanes of this wave),
     // the last found by ballots over the distinct experts of the wave.  Every wave then stores its 64 tasks with two
@@ -456,9 +457,8 @@ __global__ __launch_bounds__(1024) void group_tokens_kernel(const int32_t* __res
             const int w0 = first_wide[e], nw = first_wide[e + 1] - w0;
             const int len = nw ? (c + nw - 1) / nw : 0;  // equal sizes
             for (int g = 0; g < nw; ++g) {
-                wide[w0 + g].expert = e;
-                wide[w0 + g].n = min(len, c - g * len);
-                wide[w0 + g].first = first_task[e] + g * len;
+                const int first = first_task[e] + g * len;
+                wide[w0 + g] = WideGroup{e, min(len, c - g * len), first, (first + 15 * (w0 + g)) >> 4, table[e]};
             }
         }
         count[e] = 0;
@@ -512,9 +512,9 @@ extern "C" int floe_debug_set_timeline_mfma(unsigned long long* p) {
 
 hipError_t launch_group_tokens(const int32_t* task_expert, int n_tasks, int n_all, int chunk, TokenGroup* groups,
                                int32_t* n_groups, hipStream_t stream, int32_t* order, int wide_chunk, WideGroup* wide,
-                               int32_t* n_wide) {
+                               int32_t* n_wide, const DevExpert* table) {
     group_tokens_kernel<<<dim3(1), dim3(1024), 0, stream>>>(task_expert, n_tasks, n_all, chunk, groups, n_groups, order,
-                                                            wide_chunk, wide, n_wide);
+                                                            wide_chunk, wide, n_wide, table);
     return hipGetLastError();
 }
 

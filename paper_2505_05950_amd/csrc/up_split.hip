@@ -1,0 +1,492 @@
+// S2 for token groups of up to 32 tokens: V = X . W_up^Q on the matrix cores with the columns split over the waves of a
+// workgroup (Alg. 1 line 2; the paper itself is batch-1, each token keeps its own threshold, mask and result).  The arithmetic
+// is that of up_gemv_mfma.hip: codes masked in place as fp16 subnormals, activations scaled by powers of two, scale and zero
+// applied per quantization group in fp32.
+//
+//   x_operand_kernel  per task, once: the activations in operand order, their group sums, the factor that undoes the scaling.
+//   up_split_kernel   a wave owns 512 columns (eight units) of every channel its workgroup works on.  The activations that meet
+//                     them are loaded once per group and stay in the wave's registers (64 per token tile; half of the second
+//                     tile's lie in LDS), so that nothing but codes, scales and zeros moves in the loop over channel blocks and
+//                     the next block is on its way while one is worked on.  The partial sums of the waves meet in LDS, two
+//                     buffers in turn, one barrier per block.
+//
+// What bounds it: vector instructions (12 per unit and channel tile to mask codes and widen scale and zero, 8 per token tile to
+// apply them: 29 of 42 us in the loop at 64 tokens on 8 experts of d 4096 f 14336 INT2), before them the cache's accesses: lanes that
+// read 16 bytes each from rows of their own cost one access apiece whatever they use, so a lane brings in two whole units, and the
+// quarters of a channel's lanes one vector of scales or zeros each, handed around by lane exchanges.  Measured, with the kernels in
+// front of it (grouped or wide kernel before / this, us): one expert d 4096 f 14336 INT2, 24 tokens 42.5 / 19.9 (256 workgroups of
+// up_wide.hip had two of sixteen waves at work); 8 such experts, 64 tokens 70 / 65; 64 + 2 experts d 2048 f 1408 INT3 g32, 128 tokens
+// 79 / 53.  Tried: one token tile and half the registers, so that four waves share a SIMD (116 against 73 us at 64 tokens: twice the
+// accesses); the four reducing waves of a block in turn (the same).
+//
+// Division of work: the channel blocks of all groups form one sequence that is cut into pieces of equal cost, one workgroup each.
+#include <atomic>
+#include <type_traits>
+
+#include "floe_dev.h"
+#include "launch.h"
+#include "mfma_codes.h"
+
+namespace floe {
+
+constexpr int kSpWaveUnits = 8;   // units of 64 columns that a wave owns
+constexpr int kSpParked = 4 * 2 * 64;  // vectors per wave: the second token tile's activations of four units lie in LDS
+
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+
+// word of quarter k -> rk in every lane
+__device__ __forceinline__ void quarters_to_all(uint32_t w, uint32_t& r0, uint32_t& r1, uint32_t& r2, uint32_t& r3) {
+    const u32x2 h = __builtin_amdgcn_permlane32_swap(w, w, false, false);  // lower and upper half, twice each
+    const u32x2 a = __builtin_amdgcn_permlane16_swap(h.x, h.x, false, false), b = __builtin_amdgcn_permlane16_swap(h.y, h.y, false, false);
+    r0 = a.x; r1 = a.y; r2 = b.x; r3 = b.y;
+}
+
+// A lane's codes (units 2 g and 2 g + 1 of quarter g) -> the operand words of units p, p + 2, p + 4, p + 6
+template <int BITS, int VECS, int WORDS>
+__device__ __forceinline__ void deal_units(const uint4 (&q)[VECS], int p, uint32_t (&wd)[4][WORDS]) {
+    if constexpr (BITS == 3) {
+        // a unit is two halves of 96 bits, four 24-bit fields each; field k goes to quarter k
+        const uint32_t w[12] = {q[0].x, q[0].y, q[0].z, q[0].w, q[1].x, q[1].y, q[1].z, q[1].w, q[2].x, q[2].y, q[2].z, q[2].w};
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t w0 = w[6 * p + 3 * h], w1 = w[6 * p + 3 * h + 1], w2 = w[6 * p + 3 * h + 2];
+            uint4 fld = make_uint4(w0, __builtin_amdgcn_alignbit(w1, w0, 24), __builtin_amdgcn_alignbit(w2, w1, 16), w2 >> 8);
+            transpose4(fld);
+            wd[0][h] = fld.x; wd[1][h] = fld.y; wd[2][h] = fld.z; wd[3][h] = fld.w;
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < WORDS; ++r) {
+            uint4 w = q[p * WORDS + r];
+            transpose4(w);
+            wd[0][r] = w.x; wd[1][r] = w.y; wd[2][r] = w.z; wd[3][r] = w.w;
+        }
+    }
+}
+
+// TILES channel tiles of 16 per block
+// The activations of every task as the operand of the matrix instruction, [token tile][unit][instruction of the unit][lane],
+// their sums per quantization group and the factor that undoes the scaling.  One task per workgroup, one unit per thread.  (Every
+// workgroup of the kernel below would otherwise gather them for itself, 16 bytes per lane from as many rows: 11 of its first 15 us.)
+// single: all tasks belong to one expert; groups and order are filled in here.
+template <int BITS, bool G32>
+__global__ __launch_bounds__(64) void x_operand_kernel(const h16* __restrict__ x, int slots, int d, WideGroup* __restrict__ groups,
+                                                       int32_t* __restrict__ n_groups, int32_t* __restrict__ order, int max_groups,
+                                                       bool single, DevExpert e, int n_tasks, int chunk, uint4* __restrict__ frag,
+                                                       float* __restrict__ gsum, float* __restrict__ back) {
+    using Tr = MfmaTraits<BITS, G32>;
+    constexpr int kGroups = G32 ? 2 : 1;
+    constexpr float kScaleBack = (float)(1 << (24 - Tr::kPmax));
+    const int i = blockIdx.x, U = threadIdx.x, units = d >> 6;
+    int task = i, row = 0;  // row: of the token tiles
+    if (single) {
+        const int len = wide_single_len(n_tasks, chunk), g = i / len;
+        row = ((i + 15 * g - (i - g * len)) >> 4) * 16 + (i - g * len);
+        if (U == 0) {
+            order[i] = i;
+            if (i < wide_single_groups(n_tasks, chunk)) groups[i] = wide_single_group(e, n_tasks, chunk, i);
+            if (i == 0) n_groups[0] = wide_single_groups(n_tasks, chunk);
+        }
+    } else {
+        task = order[i];
+        const int ng = n_groups[0];
+        for (int g0 = 0; g0 < ng; g0 += kWave) {
+            const WideGroup* mine = groups + min(g0 + U, max_groups - 1);
+            const int n = mine->n, first = mine->first, tile = mine->tile;
+            const unsigned long long m = __ballot(g0 + U < ng && i >= first && i < first + n);
+            if (m) {
+                const int l = __ffsll((long long)m) - 1;
+                row = __builtin_amdgcn_readlane(tile * 16 + i - first, l);
+                break;
+            }
+        }
+    }
+    const bool live = U < units;
+    uint4 q[8];
+    u16x2 top2 = {0, 0};
+    const uint4* xr = reinterpret_cast<const uint4*>(x + (size_t)(task / slots) * d) + (live ? U : 0) * 8;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) q[r] = xr[r];
+    uint32_t xv[32];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        xv[4 * r] = q[r].x; xv[4 * r + 1] = q[r].y; xv[4 * r + 2] = q[r].z; xv[4 * r + 3] = q[r].w;
+    }
+    // the largest magnitude, as the bits of a half (those of non-negative numbers order like integers; a NaN lands on top)
+#pragma unroll
+    for (int k = 0; k < 32; ++k) top2 = __builtin_elementwise_max(top2, __builtin_bit_cast(u16x2, xv[k] & 0x7FFF7FFFu));
+    const float amax = wave_allreduce_max_nonneg((float)__builtin_bit_cast(h16, (uint16_t)max((uint32_t)top2.x, (uint32_t)top2.y)));
+    const int down = (amax >= 512.0f && amax < 3.0e38f) ? ilogbf(amax) - 8 : 0;  // |x'| < 512: 2^(pmax - p) x' stays finite
+    if (U == 0) back[row] = ldexpf(1.0f, down) * kScaleBack;
+    if (!live) return;
+    const h16 ps = (h16)ldexpf(1.0f, -down);
+    const h16x2 ps2 = {ps, ps};
+    const int tile = row >> 4, c = row & 15;
+    uint4* out = frag + ((size_t)tile * units + U) * 128 + c;
+    float sum[2] = {0.0f, 0.0f};
+#pragma unroll
+    for (int k = 0; k < 32; ++k) sum[G32 ? (k >> 4) : 0] = __builtin_amdgcn_fdot2(as_h2(xv[k]), ps2, sum[G32 ? (k >> 4) : 0], false);
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            uint32_t w[4];
+#pragma unroll
+            for (int pr = 0; pr < 4; ++pr) {
+                const int lo = Tr::code(j, g, 2 * pr), hi = Tr::code(j, g, 2 * pr + 1);
+                const uint32_t wl = xv[lo >> 1], wh = xv[hi >> 1];
+                const uint32_t l16 = (lo & 1) ? (wl >> 16) : (wl & 0xFFFFu);
+                const uint32_t h16b = (hi & 1) ? (wh & 0xFFFF0000u) : (wh << 16);
+                const h16x2 mul = {(h16)(float)(1 << (Tr::kPmax - Tr::pos(j, 2 * pr))),
+                                   (h16)(float)(1 << (Tr::kPmax - Tr::pos(j, 2 * pr + 1)))};
+                w[pr] = as_u32(as_h2(l16 | h16b) * (mul * ps2));
+            }
+            out[j * 64 + g * 16] = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    // (times 2^(pmax - 24), which the matrix products carry and the zero-point term is subtracted under)
+#pragma unroll
+    for (int k = 0; k < kGroups; ++k) gsum[(((size_t)tile * units + U) * kGroups + k) * 16 + c] = sum[k] * (1.0f / kScaleBack);
+}
+
+template <int BITS, bool G32, int NT, int TILES>
+__global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restrict__ groups, const int32_t* __restrict__ n_groups,
+                                                       int max_groups, const int32_t* __restrict__ order, const uint4* __restrict__ frag,
+                                                       const float* __restrict__ gsum, const float* __restrict__ back,
+                                                       float* __restrict__ v, const float* __restrict__ task_tau,
+                                                       uint32_t* __restrict__ mask_words, int d, int f, int parts) {
+    constexpr int kTok = 16 * NT;
+    constexpr int kGroups = G32 ? 2 : 1;                 // quantization groups per unit
+    constexpr int kVec = BITS;                           // 16-byte vectors of codes per lane and tile: two units
+    constexpr int kMetaLoads = (TILES * 2 * kGroups + 3) / 4;
+    constexpr int kLaneWords = BITS == 2 ? 1 : 2;        // operand words per unit
+    constexpr int kCh = 16 * TILES;
+    extern __shared__ __align__(16) unsigned char lds[];
+    const int nw = blockDim.x >> 6;                      // d / 512
+    float2* red = reinterpret_cast<float2*>(lds);        // [2][nw][TILES * NT * 2][64]
+    uint4* park = reinterpret_cast<uint4*>(red + (size_t)2 * nw * (TILES * NT * 2 * 64));  // [nw][4][2][64] where NT == 2
+    float* xg = reinterpret_cast<float*>(park + (NT == 2 ? nw * kSpParked : 0));  // [nw][NT][8 * kGroups][16]
+    __shared__ __align__(8) int s_task[kTok];
+    __shared__ __align__(8) float s_tau[kTok], s_back[kTok];
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int c = lane & 15, g4 = lane >> 4;
+    const int units = d >> 6;
+    const int nwords = mask_words_per_task(f);
+    const int blocks = (32 * nwords + kCh - 1) / kCh;    // whole mask words
+    FLOE_TL(0);
+    // Equal pieces by what a block costs with one and with two token tiles (vector instructions: 20 and 28 per unit and channel
+    // tile, and the rest alike) and by what the start of a group costs.
+    const int ng = n_groups[0];
+    constexpr int kStart = 6;
+    auto weight = [](int n) { return n > 16 ? 4 : 3; };
+    auto group_weight = [&](int g0) {  // of lane's group (the load does not wait for ng)
+        const int n = groups[min(g0 + lane, max_groups - 1)].n;
+        return g0 + lane < ng ? (weight(n) * blocks + kStart) * parts : 0;
+    };
+    int total = 0;
+    for (int g0 = 0; g0 < ng; g0 += kWave) total += __builtin_amdgcn_readlane(wave_inclusive_scan(group_weight(g0), lane), kWave - 1);
+    const int piece = wide_piece(gridDim.x);
+    int pos = wide_cut(total, gridDim.x, piece);
+    const int end = wide_cut(total, gridDim.x, piece + 1);
+    uint16_t* mask16 = reinterpret_cast<uint16_t*>(mask_words);
+    uint4* my_park = park + wave * kSpParked + lane;
+    float* my_xg = xg + wave * (kSpWaveUnits * kGroups * kTok);
+
+    while (pos < end) {
+        int g = ng - 1, base = 0;  // the group that `pos` lies in and where it begins
+        for (int g0 = 0; g0 < ng; g0 += kWave) {
+            const int w = group_weight(g0);
+            const int inc = wave_inclusive_scan(w, lane);
+            const unsigned long long past = __ballot(base + inc > pos);
+            if (past) {
+                const int l = __ffsll((long long)past) - 1;
+                g = g0 + l;
+                base += __builtin_amdgcn_readlane(inc - w, l);
+                break;
+            }
+            base += __builtin_amdgcn_readlane(inc, kWave - 1);
+        }
+        const WideGroup grp = groups[__builtin_amdgcn_readfirstlane(g)];
+        const int wgt = weight(grp.n), part_weight = wgt * blocks + kStart;
+        // block k of a part belongs to the piece that holds the start of its share, kStart + k * wgt behind the part's
+        const int part = __builtin_amdgcn_readfirstlane((pos - base) / part_weight);
+        const int at = base + part * part_weight + kStart;
+        const int b0 = __builtin_amdgcn_readfirstlane(max(pos - at + wgt - 1, 0) / wgt);
+        const int len = __builtin_amdgcn_readfirstlane(min(blocks, max(end - at + wgt - 1, 0) / wgt)) - b0;
+        pos = at + blocks * wgt;  // the next part, or past the end
+        const int tok_first = 32 * part, n_tok = min(32, grp.n - tok_first);  // a group of more tokens than a pass takes comes in parts
+        if (len <= 0 || n_tok <= 0) continue;
+        const unsigned char* codes = scalar_ptr(grp.e.codes);
+        const unsigned char* scale = scalar_ptr(grp.e.scale);
+        const unsigned char* zero = scalar_ptr(grp.e.zero);
+
+        // ---- requests: block i's codes, scales and zeros (past the end the last block again: unconditional, so that the
+        // compiler can count what is in flight).  Quarter g of a channel's four lanes brings in units 2 g and 2 g + 1 of the
+        // wave's eight, and one vector of its scales and zeros.
+        uint4 cq[TILES][kVec], mq[kMetaLoads];
+        auto row_of = [&](int i, int t) { return (uint32_t)min((b0 + min(i, len - 1)) * kCh + 16 * t + c, f - 1); };  // clamped lanes never store
+        auto load_codes = [&](int i, int t, int k) {
+            cq[t][k] = gload16(codes + (row_of(i, t) * (uint32_t)(units * BITS * 8) + (uint32_t)((wave * kSpWaveUnits + 2 * g4) * (BITS * 8) + 16 * k)));
+        };
+        auto load_meta = [&](int i) {
+#pragma unroll
+            for (int k = 0; k < kMetaLoads; ++k) {
+                // vector 4 k + g of [tile][scales, zeros][kGroups]
+                const int vec = min(4 * k + g4, TILES * 2 * kGroups - 1), t = vec / (2 * kGroups), part = vec % kGroups;
+                const uint32_t o = (row_of(i, t) * (uint32_t)units + wave * kSpWaveUnits) * (2u * kGroups) + 16 * part;
+                mq[k] = gload16((vec / kGroups & 1 ? zero : scale) + o);
+            }
+        };
+        load_meta(0);
+#pragma unroll
+        for (int k = 0; k < kVec; ++k)
+#pragma unroll
+            for (int t = 0; t < TILES; ++t) load_codes(0, t, k);
+        __builtin_amdgcn_sched_barrier(0);  // the waits of the loop count the requests in this order
+        // ---- the activations of the wave's units: tile n, lane (c, g4)
+        const int tile0 = grp.tile + 2 * part;
+        uint4 xr[NT][kSpWaveUnits][2];
+#pragma unroll
+        for (int n = 0; n < NT; ++n) {
+            // (a second tile that the group does not have repeats the first: tiles past the last one do not exist)
+            const uint4* xt = frag + ((size_t)(tile0 + (16 * n < n_tok ? n : 0)) * units + wave * kSpWaveUnits) * 128 + lane;
+#pragma unroll
+            for (int u = 0; u < kSpWaveUnits; ++u)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) xr[n][u][j] = xt[u * 128 + j * 64];
+        }
+        FLOE_TL(1);
+        __syncthreads();  // the previous group's arrays are no longer read
+        if (tid < kTok) {
+            const int row = tid < n_tok ? tid : 0;  // dead token rows repeat the first one
+            const int task = order[grp.first + tok_first + row];
+            s_task[tid] = task;
+            s_tau[tid] = task_tau ? task_tau[task] : 0.0f;
+            s_back[tid] = back[tile0 * 16 + row];
+        }
+#pragma unroll
+        for (int n = 0; n < NT; ++n)  // the wave's group sums of a tile: 8 * kGroups * 16 numbers
+#pragma unroll
+            for (int k = 0; k < 2 * kGroups; ++k)
+                my_xg[(n * 2 * kGroups + k) * 64 + lane] =
+                    gsum[((size_t)(tile0 + (16 * n < n_tok ? n : 0)) * units + wave * kSpWaveUnits) * (16 * kGroups) + k * 64 + lane];
+        if constexpr (NT == 2) {
+#pragma unroll
+            for (int u = 4; u < kSpWaveUnits; ++u)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) my_park[(u - 4) * 128 + j * 64] = xr[1][u][j];
+        }
+        FLOE_TL(2);
+        __syncthreads();  // the group sums and s_back are complete
+        FLOE_TL(3);
+        // live: token tiles that hold tokens
+        auto body = [&](auto live, int i) __attribute__((always_inline)) {
+            constexpr int NL = decltype(live)::value;
+            f32x4 acc[TILES][NL];
+#pragma unroll
+            for (int t = 0; t < TILES; ++t)
+#pragma unroll
+                for (int n = 0; n < NL; ++n) acc[t][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+            f32x4 sg[2][NL][kGroups];  // group sums of this unit and, on their way, of the next
+            auto sums_at = [](int u) { return (u >> 1) & 1; };  // (units in the order 0 2 4 6 1 3 5 7)
+            auto load_sums = [&](int u) __attribute__((always_inline)) {
+#pragma unroll
+                for (int n = 0; n < NL; ++n)
+#pragma unroll
+                    for (int k = 0; k < kGroups; ++k)
+                        sg[sums_at(u)][n][k] = *reinterpret_cast<const f32x4*>(&my_xg[((n * kSpWaveUnits + u) * kGroups + k) * 16 + 4 * g4]);
+            };
+            load_sums(0);
+            // scales and zeros of the wave's eight units, to all four quarters of a channel
+            uint32_t meta[kMetaLoads * 4][4];  // [vector][word]
+#pragma unroll
+            for (int k = 0; k < kMetaLoads; ++k) {
+                const uint32_t w[4] = {mq[k].x, mq[k].y, mq[k].z, mq[k].w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) quarters_to_all(w[j], meta[4 * k][j], meta[4 * k + 1][j], meta[4 * k + 2][j], meta[4 * k + 3][j]);
+            }
+            load_meta(i + 1);
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {  // units p, p + 2, p + 4, p + 6
+                uint32_t wd[TILES][4][kLaneWords];
+#pragma unroll
+                for (int t = 0; t < TILES; ++t) deal_units<BITS>(cq[t], p, wd[t]);
+                // vectors that are used up
+#pragma unroll
+                for (int k = 0; k < kVec; ++k)
+                    if ((p == 0) == (k < BITS / 2)) {
+#pragma unroll
+                        for (int t = 0; t < TILES; ++t) load_codes(i + 1, t, k);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int us = 0; us < 4; ++us) {
+                    const int u = 2 * us + p, un = us < 3 ? u + 2 : 1;
+                    if (u != 7) load_sums(un);
+                    uint4 xf[NL][2];
+#pragma unroll
+                    for (int n = 0; n < NL; ++n)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            xf[n][j] = n == 1 && u >= 4 ? my_park[(u - 4) * 128 + 64 * j]
+                                                        : xr[n][u][j];
+#pragma unroll
+                    for (int t = 0; t < TILES; ++t) {
+                        float sc[kGroups], zr[kGroups];
+#pragma unroll
+                        for (int k = 0; k < kGroups; ++k) {
+                            const int m = u * kGroups + k, vec = t * 2 * kGroups + m / 8;  // (zeros: kGroups vectors on)
+                            const h16x2 s2 = as_h2(meta[vec][(m & 7) >> 1]), z2 = as_h2(meta[vec + kGroups][(m & 7) >> 1]);
+                            sc[k] = (float)((m & 1) ? s2.y : s2.x);
+                            zr[k] = (float)((m & 1) ? z2.y : z2.x);
+                            asm volatile("" : "+v"(sc[k]), "+v"(zr[k]));  // widened once; as halves they make mixed FMAs, at half the rate
+                        }
+                        uint32_t r0[4], r1[4];
+                        weight_frag24<BITS, G32>(wd[t][us], 0, r0);
+                        weight_frag24<BITS, G32>(wd[t][us], 1, r1);
+#pragma unroll
+                        for (int n = 0; n < NL; ++n) {
+                            const h16x8 x0 = __builtin_bit_cast(h16x8, xf[n][0]), x1 = __builtin_bit_cast(h16x8, xf[n][1]);
+                            const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+                            f32x4& ac = acc[t][n];
+                            if constexpr (G32) {
+                                const f32x4 c0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(x0, as_h8(r0), zero4, 0, 0, 0);
+                                const f32x4 c1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(x1, as_h8(r1), zero4, 0, 0, 0);
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) {
+                                    const float t0 = fmaf(-zr[0], sg[sums_at(u)][n][0][e], c0[e]);
+                                    const float t1 = fmaf(-zr[kGroups - 1], sg[sums_at(u)][n][kGroups - 1][e], c1[e]);
+                                    ac[e] = fmaf(sc[kGroups - 1], t1, fmaf(sc[0], t0, ac[e]));
+                                }
+                            } else {
+                                f32x4 cc = __builtin_amdgcn_mfma_f32_16x16x32_f16(x0, as_h8(r0), zero4, 0, 0, 0);
+                                cc = __builtin_amdgcn_mfma_f32_16x16x32_f16(x1, as_h8(r1), cc, 0, 0, 0);
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) ac[e] = fmaf(sc[0], fmaf(-zr[0], sg[sums_at(u)][n][0][e], cc[e]), ac[e]);
+                            }
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);  // or the operands of later units pile up in registers
+                }
+            }
+            // ---- the waves' shares meet: item (tile, token tile, half of the four tokens) of every lane
+            float2* mine = red + ((size_t)(i & 1) * nw + wave) * (TILES * NL * 2 * 64);
+#pragma unroll
+            for (int t = 0; t < TILES; ++t)
+#pragma unroll
+                for (int n = 0; n < NL; ++n)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) mine[((t * NL + n) * 2 + h) * 64 + lane] = make_float2(acc[t][n][2 * h], acc[t][n][2 * h + 1]);
+            __syncthreads();
+            const float2* all = red + (size_t)(i & 1) * nw * (TILES * NL * 2 * 64);
+            for (int it = wave; it < TILES * NL * 2; it += nw) {
+                const int t = it / (NL * 2), n = (it >> 1) % NL, h = it & 1;
+                const int tok0 = 16 * n + 4 * g4 + 2 * h;
+                const int2 task2 = *reinterpret_cast<const int2*>(&s_task[tok0]);
+                const float2 tau2 = *reinterpret_cast<const float2*>(&s_tau[tok0]), back2 = *reinterpret_cast<const float2*>(&s_back[tok0]);
+                float2 r = make_float2(0.f, 0.f);
+                for (int w0 = 0; w0 < nw; w0 += 4) {  // four reads under way at a time
+                    float2 a[4];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) a[k] = all[((size_t)min(w0 + k, nw - 1) * (TILES * NL * 2) + it) * 64 + lane];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        r.x += w0 + k < nw ? a[k].x : 0.f;
+                        r.y += w0 + k < nw ? a[k].y : 0.f;
+                    }
+                }
+                const int base = (b0 + i) * kCh + 16 * t, ch = base + c;
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const bool live = tok0 + e < n_tok;
+                    const int task = e ? task2.y : task2.x;
+                    const float val = e ? r.y * back2.y : r.x * back2.x;
+                    if (live && ch < f) v[(size_t)task * f + ch] = val;
+                    const uint64_t m = __ballot(live && ch < f && fabsf(val) > (e ? tau2.y : tau2.x));
+                    if (mask16 && live && c == 0 && base < 32 * nwords)
+                        mask16[(size_t)task * nwords * 2 + (base >> 4)] = (uint16_t)(m >> (16 * g4));
+                }
+            }
+        };
+        auto walk = [&](auto live) __attribute__((always_inline)) {
+#pragma unroll 1
+            for (int i = 0; i < len; ++i) {
+                body(live, i);
+                if (i == 0) FLOE_TL(4);
+            }
+        };
+        if constexpr (NT > 1) {
+            if (n_tok <= 16) {
+                walk(std::integral_constant<int, 1>{});
+                FLOE_TL(5);
+                continue;
+            }
+        }
+        walk(std::integral_constant<int, NT>{});
+    }
+    FLOE_TL(5);
+}
+
+#ifdef FLOE_TIMELINE
+extern "C" int floe_debug_set_timeline_up_split(unsigned long long* p) {
+    return (int)hipMemcpyToSymbol(HIP_SYMBOL(g_timeline), &p, sizeof(p));
+}
+#endif
+
+// token tiles that the groups can have together
+static int split_tiles(const UpWideArgs& a) { return (a.n_tasks + 15 * a.max_groups) / 16; }
+size_t up_split_scratch_bytes(int tiles, int d, int group) {
+    return (size_t)tiles * 16 * ((size_t)d * 2 + (size_t)(d / 64) * (group == 32 ? 2 : 1) * 4 + 4);
+}
+
+template <int BITS, bool G32, int NT>
+static hipError_t launch_split(const UpWideArgs& a, hipStream_t stream) {
+    // channel tiles per block: what the registers take beside the activations (64 per token tile)
+    constexpr int TILES = (BITS == 2 ? 4 : 2) / NT;
+    constexpr int kGroups = G32 ? 2 : 1;
+    const int nw = a.d / 512;
+    const size_t lds = (size_t)2 * nw * (TILES * NT * 2 * 64) * sizeof(float2) + (NT == 2 ? nw * kSpParked * sizeof(uint4) : 0) +
+                       (size_t)nw * kSpWaveUnits * kGroups * 16 * NT * sizeof(float);
+    // the attribute belongs to the function on one device: set once per device, from whichever thread comes first
+    constexpr int kMaxDevices = 64;
+    static std::atomic<bool> attr_set[kMaxDevices];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
+    const auto kernel = &up_split_kernel<BITS, G32, NT, TILES>;
+    if (!attr_set[dev].load(std::memory_order_acquire)) {
+        const hipError_t rc = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 152 * 1024);
+        if (rc != hipSuccess) return rc;
+        attr_set[dev].store(true, std::memory_order_release);
+    }
+    const long long blocks = (long long)a.est_groups * a.parts * ((32 * mask_words_per_task(a.f) + 16 * TILES - 1) / (16 * TILES));
+    const int room = num_cus() * (8 / nw > 1 ? 8 / nw : 1);  // workgroups that the registers hold at a time (eight waves per compute unit)
+    int wgs = (int)(blocks < room ? blocks : room);
+    if (wgs > 8) wgs &= ~7;  // (see wide_piece)
+    uint4* frag = static_cast<uint4*>(a.scratch);
+    const int tiles = split_tiles(a);
+    float* gsum = reinterpret_cast<float*>(frag + (size_t)tiles * a.d * 2);
+    float* back = gsum + (size_t)tiles * (a.d / 64) * (16 * kGroups);
+    x_operand_kernel<BITS, G32><<<dim3(a.n_tasks), dim3(64), 0, stream>>>(
+        a.x, a.slots, a.d, const_cast<WideGroup*>(a.groups), const_cast<int32_t*>(a.n_groups), const_cast<int32_t*>(a.order), a.max_groups,
+        a.single != nullptr, a.single ? *a.single : DevExpert{}, a.n_tasks, a.chunk, frag, gsum, back);
+    const hipError_t rc = hipGetLastError();
+    if (rc != hipSuccess) return rc;
+    kernel<<<dim3(wgs), dim3(64 * nw), lds, stream>>>(a.groups, a.n_groups, a.max_groups, a.order, frag, gsum, back, a.v, a.task_tau,
+                                                    a.mask_words, a.d, a.f, a.parts);
+    return hipGetLastError();
+}
+
+hipError_t launch_up_split(UpWideArgs a, int bits, int group, hipStream_t stream) {
+    if (!up_split_shape(a.d, a.f, bits, group)) return hipErrorInvalidValue;
+    a.parts = (a.nt + 1) / 2;
+    const bool g32 = group == 32, two = a.nt > 1;
+    if (bits == 2) return two ? launch_split<2, false, 2>(a, stream) : launch_split<2, false, 1>(a, stream);
+    if (bits == 3) {
+        if (g32) return two ? launch_split<3, true, 2>(a, stream) : launch_split<3, true, 1>(a, stream);
+        return two ? launch_split<3, false, 2>(a, stream) : launch_split<3, false, 1>(a, stream);
+    }
+    if (g32) return two ? launch_split<4, true, 2>(a, stream) : launch_split<4, true, 1>(a, stream);
+    return two ? launch_split<4, false, 2>(a, stream) : launch_split<4, false, 1>(a, stream);
+}
+
+}  // namespace floe

@@ -98,38 +98,8 @@ __global__ __launch_bounds__(128) void x_frag_kernel(const h16* __restrict__ x, 
     for (int k = 0; k < kGroups; ++k) gsum[((size_t)t * units + U) * kGroups + k] = sum[k] * (1.0f / kScaleBack);
 }
 
-__device__ __forceinline__ void transpose4(uint4& q) {  // across the four lane quarters: register k <- word g of quarter k's vector
-    u32x2 t;
-    t = __builtin_amdgcn_permlane32_swap(q.x, q.z, false, false); q.x = t.x; q.z = t.y;
-    t = __builtin_amdgcn_permlane32_swap(q.y, q.w, false, false); q.y = t.x; q.w = t.y;
-    t = __builtin_amdgcn_permlane16_swap(q.x, q.y, false, false); q.x = t.x; q.y = t.y;
-    t = __builtin_amdgcn_permlane16_swap(q.z, q.w, false, false); q.z = t.x; q.w = t.y;
-}
-
-// One slice (four units) of a channel tile: what a lane loads and the operand words it makes of it.  Quarter g of a
-// channel's four lanes loads unit g whole; the transposes hand every quarter its words of all four units.
-template <int BITS>
-struct CodeSlice {
-    static constexpr int kVec = BITS == 4 ? 2 : 1;  // 16-byte vectors per unit (INT3: three 8-byte ones)
-    uint4 raw[kVec];
-    uint32_t raw3[BITS == 3 ? 6 : 1];
-    __device__ __forceinline__ void load(const unsigned char* codes, uint32_t off) {
-        if constexpr (BITS == 3) {
-#pragma unroll
-            for (int r = 0; r < 3; ++r) {
-                const uint2 q = gload8(codes + (off + 8 * r));
-                raw3[2 * r] = q.x;
-                raw3[2 * r + 1] = q.y;
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < kVec; ++r) raw[r] = gload16(codes + (off + 16 * r));
-        }
-    }
-};
-
 template <int BITS, bool G32, int NT>
-__global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const DevExpert* __restrict__ table, const WideGroup* __restrict__ groups,
+__global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __restrict__ groups,
                                                              const int32_t* __restrict__ n_groups, const int32_t* __restrict__ order,
                                                              const uint4* __restrict__ frag, const float* __restrict__ gsum,
                                                              const float* __restrict__ back, int slots, float* __restrict__ v,
@@ -169,9 +139,9 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const DevExpert* __
         const int part_len = (grp.n + parts - 1) / parts;
         const int tok_first = (gi % parts) * part_len, n_tok = min(part_len, grp.n - tok_first);
         if (n_tok <= 0) continue;
-        const unsigned char* codes = scalar_ptr(table[grp.expert].codes);
-        const unsigned char* scale = scalar_ptr(table[grp.expert].scale);
-        const unsigned char* zero = scalar_ptr(table[grp.expert].zero);
+        const unsigned char* codes = scalar_ptr(grp.e.codes);
+        const unsigned char* scale = scalar_ptr(grp.e.scale);
+        const unsigned char* zero = scalar_ptr(grp.e.zero);
         __syncthreads();  // the previous part's arrays are no longer read
         if (tid < kTok) {
             const int task = order[grp.first + tok_first + (tid < n_tok ? tid : 0)];  // dead token rows repeat the first one
@@ -273,28 +243,9 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const DevExpert* __
             auto slice = [&](int s, int in_super, int mbuf) {
                 const int buf = s & 1;
                 // operand words of the four units: wd[t][u][k]
-                constexpr int kLw = BITS == 2 ? 1 : 2;
-                uint32_t wd[kUpTiles][kSliceUnits][kLw];
+                uint32_t wd[kUpTiles][kSliceUnits][CodeSlice<BITS>::kLaneWords];
 #pragma unroll
-                for (int t = 0; t < kUpTiles; ++t) {
-                    if constexpr (BITS == 3) {
-                        // this lane's unit: two halves of 96 bits, four 24-bit fields each; field k goes to quarter k
-#pragma unroll
-                        for (int h = 0; h < 2; ++h) {
-                            const uint32_t w0 = cs[t].raw3[3 * h], w1 = cs[t].raw3[3 * h + 1], w2 = cs[t].raw3[3 * h + 2];
-                            uint4 fld = make_uint4(w0, __builtin_amdgcn_alignbit(w1, w0, 24), __builtin_amdgcn_alignbit(w2, w1, 16), w2 >> 8);
-                            transpose4(fld);
-                            wd[t][0][h] = fld.x; wd[t][1][h] = fld.y; wd[t][2][h] = fld.z; wd[t][3][h] = fld.w;
-                        }
-                    } else {
-#pragma unroll
-                        for (int r = 0; r < CodeSlice<BITS>::kVec; ++r) {
-                            uint4 w = cs[t].raw[r];
-                            transpose4(w);
-                            wd[t][0][r] = w.x; wd[t][1][r] = w.y; wd[t][2][r] = w.z; wd[t][3][r] = w.w;
-                        }
-                    }
-                }
+                for (int t = 0; t < kUpTiles; ++t) cs[t].deal(wd[t]);
                 load_c(s + 1);
                 store_x(buf ^ 1);
                 load_x(s + 2);
@@ -398,7 +349,7 @@ size_t up_wide_scratch_bytes(int T, int d, int group) {
 template <int BITS, bool G32, int NT>
 static void launch_nt(const UpWideArgs& a, uint4* frag, float* gsum, float* back, hipStream_t stream) {
     up_wide_kernel<BITS, G32, NT><<<dim3(a.workgroups), dim3(kUpThreads), 0, stream>>>(
-        a.table, a.groups, a.n_groups, a.order, frag, gsum, back, a.slots, a.v, a.task_tau, a.mask_words, a.d, a.f, a.parts);
+        a.groups, a.n_groups, a.order, frag, gsum, back, a.slots, a.v, a.task_tau, a.mask_words, a.d, a.f, a.parts);
 }
 template <int BITS, bool G32>
 static hipError_t launch_bits(const UpWideArgs& a, hipStream_t stream) {
@@ -423,6 +374,11 @@ static hipError_t launch_bits(const UpWideArgs& a, hipStream_t stream) {
 
 hipError_t launch_up_wide(UpWideArgs a, int bits, int group, hipStream_t stream) {
     if (!up_wide_shape(a.d, a.f, bits, group)) return hipErrorInvalidValue;
+    if (a.single) {
+        const hipError_t rc = launch_wide_single(*a.single, a.n_tasks, a.chunk, const_cast<WideGroup*>(a.groups),
+                                                 const_cast<int32_t*>(a.n_groups), const_cast<int32_t*>(a.order), stream);
+        if (rc != hipSuccess) return rc;
+    }
     // token tiles that the registers take beside the codes: four for INT2, three for the wider codes
     const int max_tiles = bits == 2 ? 4 : 3;
     a.parts = (a.nt + max_tiles - 1) / max_tiles;

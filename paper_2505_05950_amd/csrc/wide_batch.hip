@@ -42,19 +42,10 @@ constexpr int kDownCols = 512;   // output columns per workgroup of the down ker
 // pairs of union rows of group g
 __device__ __forceinline__ int wide_pairs(const int32_t* ucount, int g) { return (ucount[g] + kPairRows - 1) / kPairRows; }
 
-// h of a group lies in [pair][token tile][half of the pair's rows][lane], the group's own tiles only, from this entry on.  The
-// groups before group g hold at most (first + 15 g) / 16 tiles, so no two of them meet.
+// h of a group lies in [pair][token tile][half of the pair's rows][lane], the group's own tiles only, from this entry on.
 __device__ __forceinline__ int wide_tiles(int n) { return (n + 15) >> 4; }
-__device__ __forceinline__ size_t wide_h_first(int first, int g, int pmax) { return (size_t)((first + 15 * g) >> 4) * pmax * 128; }
+__device__ __forceinline__ size_t wide_h_first(const WideGroup& g, int pmax) { return (size_t)g.tile * pmax * 128; }
 
-__device__ __forceinline__ int wave_inclusive_scan(int x, int lane) {
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int up = __shfl_up(x, o, kWave);
-        if (lane >= o) x += up;
-    }
-    return x;
-}
 __device__ __forceinline__ int wide_total(const WideArgs& a, int ng, int lane) {
     int total = 0;
     for (int g0 = 0; g0 < ng; g0 += kWave) {
@@ -180,7 +171,7 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
         const WideGroup grp = a.groups[g];
         const int count = a.ucount[g];
         const int32_t* rows = a.urow + (size_t)g * a.f;
-        const unsigned char* gd = scalar_ptr(a.table[grp.expert].gd);
+        const unsigned char* gd = scalar_ptr(grp.e.gd);
         const int seg0 = pos - base, seg1 = min((count + kPairRows - 1) / kPairRows, end - base);
         pos = base + seg1;
         __syncthreads();  // the previous group's task arrays are no longer read
@@ -335,7 +326,7 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
                 }
             }
             const int tiles = wide_tiles(grp.n);
-            uint4* hb = a.hbuf + wide_h_first(grp.first, g, pmax) + (size_t)pair * tiles * 128 + lane;
+            uint4* hb = a.hbuf + wide_h_first(grp, pmax) + (size_t)pair * tiles * 128 + lane;
 #pragma unroll
             for (int n = 0; n < NT; ++n)
                 if (n < tiles) {
@@ -386,7 +377,7 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
         const WideGroup grp = a.groups[g];
         const int count = a.ucount[g];
         const int32_t* rows = a.urow + (size_t)g * a.f;
-        const unsigned char* gd = scalar_ptr(a.table[grp.expert].gd);
+        const unsigned char* gd = scalar_ptr(grp.e.gd);
         const uint32_t dcol = 2 * (uint32_t)(d + col);
         const int npairs = (count + kPairRows - 1) / kPairRows;
         const int seg0 = pos - base, seg1 = min(npairs, end - base);
@@ -398,7 +389,7 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
             if (tid < grp.n) a.task_rows[a.order[grp.first + tid]] = make_int2(grp.first + tid + w_first * kTok, slots);
         }
         const int tiles = wide_tiles(grp.n);
-        const unsigned char* hsrc = scalar_ptr(a.hbuf + wide_h_first(grp.first, g, pmax) + (size_t)seg0 * tiles * 128);
+        const unsigned char* hsrc = scalar_ptr(a.hbuf + wide_h_first(grp, pmax) + (size_t)seg0 * tiles * 128);
         const int ns = (len + SL - 1) / SL;
         uint4 hq[kHRounds];
         int idq = 0;
@@ -627,22 +618,13 @@ __global__ __launch_bounds__(128) void combine_wide_kernel(const float* __restri
     }
 }
 
-// Groups, order and pointer table of a single expert that every task belongs to (the one-expert entry point).
-__global__ __launch_bounds__(256) void wide_single_kernel(DevExpert e, int n_tasks, int chunk, DevExpert* __restrict__ table,
-                                                          WideGroup* __restrict__ groups, int32_t* __restrict__ n_groups,
-                                                          int32_t* __restrict__ order) {
-    const int ng = (n_tasks + chunk - 1) / chunk, len = (n_tasks + ng - 1) / ng;
+// Groups and order of a single expert that every task belongs to (the one-expert entry point).
+__global__ __launch_bounds__(256) void wide_single_kernel(DevExpert e, int n_tasks, int chunk, WideGroup* __restrict__ groups,
+                                                          int32_t* __restrict__ n_groups, int32_t* __restrict__ order) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < n_tasks) order[i] = i;
-    if (i < ng) {
-        groups[i].expert = 0;
-        groups[i].n = max(0, min(len, n_tasks - i * len));
-        groups[i].first = min(i * len, n_tasks);
-    }
-    if (i == 0) {
-        table[0] = e;
-        n_groups[0] = ng;
-    }
+    if (i < wide_single_groups(n_tasks, chunk)) groups[i] = wide_single_group(e, n_tasks, chunk, i);
+    if (i == 0) n_groups[0] = wide_single_groups(n_tasks, chunk);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -739,9 +721,9 @@ hipError_t launch_gate_down_wide(const WideArgs& a, const WidePlan& p, const uin
     }
 }
 
-hipError_t launch_wide_single(const DevExpert& e, int n_tasks, int chunk, DevExpert* table, WideGroup* groups, int32_t* n_groups,
-                              int32_t* order, hipStream_t stream) {
-    wide_single_kernel<<<dim3((n_tasks + 255) / 256), dim3(256), 0, stream>>>(e, n_tasks, chunk, table, groups, n_groups, order);
+hipError_t launch_wide_single(const DevExpert& e, int n_tasks, int chunk, WideGroup* groups, int32_t* n_groups, int32_t* order,
+                              hipStream_t stream) {
+    wide_single_kernel<<<dim3((n_tasks + 255) / 256), dim3(256), 0, stream>>>(e, n_tasks, chunk, groups, n_groups, order);
     return hipGetLastError();
 }
 

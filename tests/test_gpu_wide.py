@@ -37,6 +37,18 @@ def test_wide_groups(d, f, bits, group, n, n_shared, top_k, T, pct):
     _run_layer_case(70 + T, 5, d, f, bits, group, n, n_shared, top_k, False, T, pct, gap=f * (100 - pct) >= 6400)
 
 
+@pytest.mark.parametrize("d,f,bits,group,n,n_shared,top_k,T,pct", [
+    (4096, 49, 2, 64, 0, 1, 0, 32, 50),      # eight waves that take turns; two full token tiles; one channel in the last block
+    (4096, 130, 4, 32, 3, 0, 2, 25, 60),     # groups of one and of two token tiles beside each other
+    (3584, 37, 3, 64, 0, 1, 0, 17, 0),       # seven waves
+    (2560, 16, 3, 32, 2, 0, 1, 9, 50),       # five; half a mask word
+    (1536, 95, 4, 64, 0, 2, 0, 31, 60),      # three waves, two workgroups per compute unit; two experts on the same tokens
+    (512, 50, 4, 64, 70, 2, 8, 20, 50),      # one wave; more groups than a wave scans at a time
+])
+def test_up_projection_split_over_columns(d, f, bits, group, n, n_shared, top_k, T, pct):
+    _run_layer_case(170 + T, 7, d, f, bits, group, n, n_shared, top_k, False, T, pct, gap=f * (100 - pct) >= 6400)
+
+
 def test_h_beyond_fp16():
     """Large activations: |h| far beyond 65504 for some (row, token), ordinary for the others of the same group."""
     import gpu_common as G
