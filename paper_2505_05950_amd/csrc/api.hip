@@ -105,6 +105,11 @@ size_t wide_h_bytes(const WidePlan& p, int d, int group) {
     const size_t h = (size_t)p.h_tiles * p.pairs * 128 * sizeof(uint4), x = up_split_scratch_bytes(p.h_tiles, d, group);
     return h > x ? h : x;
 }
+// partial results; before them the activations that the gate kernel reads
+size_t wide_partial_bytes(const WidePlan& p, int d) {
+    const size_t y = p.partial_rows * d * sizeof(float), x = (size_t)p.h_tiles * 16 * d * 2;
+    return y > x ? y : x;
+}
 ExpertWs expert_ws(const floe_shape* s, int T, Wide form = Wide::kChosen) {
     ExpertWs w{};
     w.nblk = gd_blocks(T, s->f);
@@ -128,7 +133,7 @@ ExpertWs expert_ws(const floe_shape* s, int T, Wide form = Wide::kChosen) {
         w.trows_off = o;   o += align_up((size_t)T * sizeof(int2));
     }
     w.idx_off = o;     o += w.fused_passes || w.wide ? 0 : align_up((size_t)T * s->f * sizeof(int32_t));  // list for callers that pass none
-    w.partial_off = o; o += align_up((w.wide ? w.wp.partial_rows : (size_t)T * nblk_alloc) * s->d * sizeof(float));
+    w.partial_off = o; o += align_up(w.wide ? wide_partial_bytes(w.wp, s->d) : (size_t)T * nblk_alloc * s->d * sizeof(float));
     w.total = o;
     return w;
 }
@@ -232,7 +237,7 @@ LayerWs layer_plan(const floe_layer* L, int T, Wide form = Wide::kChosen, int ma
     w.hmax_off = o;    o += w.use_wide ? align_up((size_t)w.n_tasks * 4) : 0;
     w.trows_off = o;   o += w.use_wide ? align_up((size_t)w.n_tasks * sizeof(int2)) : 0;
     w.partial_off = o;
-    o += w.use_wide ? align_up(w.wp.partial_rows * L->s.d * 4) : align_up((size_t)w.n_tasks * nblk_alloc * L->s.d * 4);
+    o += w.use_wide ? align_up(wide_partial_bytes(w.wp, L->s.d)) : align_up((size_t)w.n_tasks * nblk_alloc * L->s.d * 4);
     w.total = o;
     return w;
 }
@@ -258,7 +263,8 @@ LayerWs layer_fit(const floe_layer* L, int T, size_t limit) {
     const size_t rows = rest < limit ? (limit - rest) / row : 0;  // for the pieces after the first
     const int pieces = (int)(rows / w.wp.chunk + 1) & ~7;
     if (rest > limit || pieces < 8 || 3 * pieces * (L->s.d / 512) < num_cus()) return n;
-    return layer_plan(L, T, Wide::kChosen, pieces);
+    const LayerWs fewer = layer_plan(L, T, Wide::kChosen, pieces);
+    return fewer.total <= limit ? fewer : n;  // (the activations in operand order may need more than so few partial results)
 }
 
 int check_layer(const floe_layer* L) {
@@ -514,6 +520,7 @@ int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, cons
         wa.hmax = reinterpret_cast<uint32_t*>(base + w.hmax_off);
         wa.task_rows = reinterpret_cast<int2*>(base + w.trows_off);
         wa.partial = partial;
+        wa.xop = reinterpret_cast<uint4*>(partial);
         wa.slots = 1; wa.f = e->s.f;
         FLOE_LAUNCH(FLOE_KERNEL_GATE_DOWN, st, launch_gate_down_wide(wa, w.wp, mask, e->s.d, st));
         if (idx) FLOE_LAUNCH(FLOE_KERNEL_SELECT, st, launch_select(v, e->s.f, T, tau, idx, count, st));
@@ -753,6 +760,7 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
             wa.hmax = reinterpret_cast<uint32_t*>(base + w.hmax_off);
             wa.task_rows = reinterpret_cast<int2*>(base + w.trows_off);
             wa.partial = partial;
+            wa.xop = reinterpret_cast<uint4*>(partial);
             wa.slots = slots; wa.f = L->s.f;
             FLOE_LAUNCH(FLOE_KERNEL_GATE_DOWN, st, launch_gate_down_wide(wa, w.wp, mask, L->s.d, st));
             FLOE_LAUNCH(FLOE_KERNEL_COMBINE, st, launch_combine_wide(wa, w.wp, L->s.d, T, nullptr, reinterpret_cast<h16*>(y), st));

@@ -208,6 +208,7 @@ struct WideArgs {
     int32_t* count;           // [n_tasks] selected channels
     int32_t* urow;            // [max_groups][f] union rows, ascending
     int32_t* ucount;          // [max_groups]
+    uint4* xop;               // [h_tiles][d / 32][64] activations in operand order (in the place of `partial`, which nobody has written yet)
     uint4* hbuf;              // [h_tiles * pairs][2][64] h (four floats: rows of a 16-row tile) in lane order
     uint32_t* hmax;           // [n_tasks] bits of the largest finite |h| of task order[i]
     int2* task_rows;          // [n_tasks] first partial row, number of partial rows (chunk rows apart)

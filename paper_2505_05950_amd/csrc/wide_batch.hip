@@ -3,12 +3,11 @@
 // instruction); every row that any token of a group selected is read once for the whole group.
 //
 //   wide_rows_kernel   per group: ascending list of the union of the tokens' selected channels (from the mask bits), the
-//                      selected counts of its tasks.
-//   gate_wide_kernel   A[row][token] = gate_row . x_token.  A wave takes a pair of 16-row tiles; the rows stream from memory
-//                      straight into the registers that feed the matrix cores (two slices of 128 columns in flight, 16 KB
-//                      per wave), the group's activations pass through LDS in slices of 128 columns shared by the eight
-//                      waves.  h = SiLU(A) * v * weight where |v| > tau, else 0, leaves in fp32 in the lane order of the
-//                      down kernel's operand, and the largest |h| of each task beside it.
+//                      selected counts of its tasks.  Beside that the activations in the order of the gate kernel's operand.
+//   gate_wide_kernel   A[row][token] = gate_row . x_token.  A wave takes a pair of 16-row tiles.  Rows and activations travel
+//                      from memory straight into a ring of three or four slots in LDS, 64 columns of 256 rows and of the group's
+//                      tokens each; one barrier per slot.  h = SiLU(A) * v * weight where |v| > tau, else 0, leaves in fp32 in
+//                      the lane order of the down kernel's operand, and the largest |h| of each task beside it.
 //   down_wide_kernel   Y[token][col] += h[token][row] * down[row][col].  A workgroup owns 512 output columns and a range of
 //                      row pairs; a lane fetches 8-byte pieces of eight rows per pair (four pairs in flight), a register
 //                      transpose (v_perm_b32) makes the operand.  h passes through LDS as two fp16 numbers (hi + lo),
@@ -19,11 +18,16 @@
 // Division of work: the row pairs of all groups form one sequence; the workgroups cut it into equal pieces, whatever the
 // routing did to the group sizes, so the launch is one even round and no compute unit waits for a crowded expert.
 //
-// What bounds it: the bytes a compute unit pulls in - rows, activations (gate) and h (down) - at 5.8 to 6.6 TB/s over the
-// chip; the vector and matrix units of the gate kernel are busy for 14 and 26 % of the cycles with ten tiles.  Hence groups as
-// large as the accumulators allow (a second group reads the rows again), and rows requested two slices ahead.  Measured, gate +
-// down, 8 experts d 4096 f 14336 at 90 %: 64 tokens 364 -> 292 us (groups of at most 16 tokens before, half of the experts
-// read twice), 512 tokens 2425 (a workgroup set per task) -> 546 us.
+// What bounds it: the rows (a kernel that only reads them in these pieces runs at 5.9 TB/s whatever the pieces are) and what stands
+// between: the start of the streams, once per pass of eight pairs, SiLU behind them, and in the down kernel twice the matrix products.
+// Hence groups as large as the accumulators allow (a second group reads the rows again).  Rows that go to registers instead, 16 bytes per
+// lane from sixteen rows, cost the cache 64 accesses per request; with the activations' it was busy for half of the cycles and the
+// waves stood behind their own requests.  The same holds for v gathered by lane (a tenth of the kernel).  Measured, gate, 8 experts
+// d 4096 f 14336 at 90 %: 512 tokens 280 -> 232 us, 64 tokens 152 -> 144, one expert with 24 tokens 28.4 -> 24.6.  Gate + down before
+// groups of more than 16 tokens: 64 tokens 364 us, 512 tokens 2425.  Tried: pieces that end where groups end (one expert with 24 tokens
+// 24.6 -> 27.8, the others the same).
+
+#include <type_traits>
 
 #include "floe_dev.h"
 #include "launch.h"
@@ -36,7 +40,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kWideWaves = 8;
 constexpr int kWideThreads = kWideWaves * 64;
 constexpr int kPairRows = 32;    // two tiles of 16 rows: one k-step of the down kernel's matrix instruction
-constexpr int kSliceCols = 128;  // columns of x that sit in LDS at a time
+constexpr int kSliceCols = 64;   // columns of rows and activations per ring slot of the gate kernel
+constexpr int kSpan = 64;        // channels of v that a wave brings in for a pair of row tiles
 constexpr int kDownCols = 512;   // output columns per workgroup of the down kernel (64 per wave)
 
 // pairs of union rows of group g
@@ -78,11 +83,43 @@ __device__ __forceinline__ int wide_owner(int total, int W, int p) { return (int
 // ---------------------------------------------------------------------------------------------------------------
 // union lists
 // ---------------------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void wide_rows_kernel(WideArgs a, const uint32_t* __restrict__ mask_words) {
+// The activations of a token tile in the order of the matrix instruction's operand, [k-step of 32 columns][lane]: what the gate kernel
+// copies into LDS as it is.  A wave per token, one block per 2048 columns.  (Beside the lists in one launch: neither needs the other.)
+constexpr int kOperandCols = 2048;
+__device__ __forceinline__ void operand_tile(const WideArgs& a, int tile, int col0, int max_groups, int d) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int ng = a.n_groups[0];
+    int first = 0, n = 0;
+    for (int g0 = 0; g0 < ng; g0 += kWave) {
+        const WideGroup* mine = a.groups + min(g0 + lane, max_groups - 1);
+        const int t0 = mine->tile, len = mine->n, f0 = mine->first;
+        const unsigned long long m = __ballot(g0 + lane < ng && tile >= t0 && tile < t0 + wide_tiles(len));
+        if (m) {
+            const int l = __ffsll((long long)m) - 1;
+            first = __builtin_amdgcn_readlane(f0 + 16 * (tile - t0), l);
+            n = __builtin_amdgcn_readlane(len - 16 * (tile - t0), l);
+            break;
+        }
+    }
+    if (wave >= n) return;  // no such token: nobody looks at its results
+    // pieces of 16 bytes: piece p is quarter p % 4 of k-step p / 4; 64 of them per 512 columns
+    const uint4* x = reinterpret_cast<const uint4*>(a.x + (size_t)(a.order[first + wave] / a.slots) * d + col0) + lane;
+    uint4* out = a.xop + ((size_t)tile * (d / 32) + col0 / 32 + (lane >> 2)) * 64 + (lane & 3) * 16 + wave;
+    const int last = min(d - col0, kOperandCols) / 512 - 1;
+    const uint4 q0 = x[0], q1 = x[min(1, last) * kWave], q2 = x[min(2, last) * kWave], q3 = x[min(3, last) * kWave];
+    out[0] = q0;  // (past the last one the last one again: the same bytes)
+    out[min(1, last) * 1024] = q1;
+    out[min(2, last) * 1024] = q2;
+    out[min(3, last) * 1024] = q3;
+}
+
+__global__ __launch_bounds__(1024) void wide_rows_kernel(WideArgs a, const uint32_t* __restrict__ mask_words, int max_groups, int d) {
     constexpr int kWaves = 16;
     __shared__ uint32_t u[kWideMaxMaskWords];
     __shared__ int before[kWideMaxMaskWords];
     __shared__ int wave_tot[kWaves];
+    const int parts = (d + kOperandCols - 1) / kOperandCols, op = (int)blockIdx.x - max_groups;
+    if (op >= 0) return operand_tile(a, op / parts, op % parts * kOperandCols, max_groups, d);
     const int g = blockIdx.x;
     if (g >= a.n_groups[0]) return;  // the grid is sized for the worst case
     const WideGroup grp = a.groups[g];
@@ -139,16 +176,50 @@ __global__ __launch_bounds__(1024) void wide_rows_kernel(WideArgs a, const uint3
     }
 }
 
+// The kernels below exist for NT token tiles per group at most; their loops are unrolled for the tiles that a group fills: NT, or
+// one less, or two less of ten (the sizes that the plan of a launch meets; smaller groups run the smallest).
+template <int NT, class F>
+__device__ __forceinline__ void with_live_tiles(int tiles, F&& f) {
+    if constexpr (NT >= 10) {
+        if (tiles <= NT - 2) return f(std::integral_constant<int, NT - 2>{});
+    }
+    if constexpr (NT >= 2) {
+        if (tiles <= NT - 1) return f(std::integral_constant<int, NT - 1>{});
+    }
+    f(std::integral_constant<int, NT>{});
+}
+
 // ---------------------------------------------------------------------------------------------------------------
 // gate
 // ---------------------------------------------------------------------------------------------------------------
+// Rows and activations travel from memory straight into LDS (global_load_lds_dwordx4), in ring slots that are arrays of their own, so
+// that the compiler can tell which requests a read has to wait for.  The waits that matter are placed by hand, in front of the barrier
+// that makes a slot everybody's.
+#define FLOE_LDS __attribute__((address_space(3)))
+__device__ __forceinline__ void dma16(const void* src, uint4* lds_wave_base) {  // lane l's 16 bytes land at base + 16 l
+    __builtin_amdgcn_global_load_lds((const FLOE_GLOBAL void*)src, (FLOE_LDS void*)lds_wave_base, 16, 0, 0);
+}
+template <int N>
+__device__ __forceinline__ void wait_requests_all_but() {  // s_waitcnt vmcnt(N)
+    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+    asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void meet() {  // barrier alone: what is in flight stays in flight
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 template <int NT>
 __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int d) {
     constexpr int kTok = 16 * NT;
-    constexpr int kTokRound = kWideWaves * 4;  // x pieces (16 bytes) of a slice: kTokRound tokens x 16 pieces per round
-    constexpr int kRounds = (kTok + kTokRound - 1) / kTokRound;
-    constexpr int kSteps = kSliceCols / 32;
-    __shared__ uint4 xs[2][kTok * 16];  // [token][16 pieces], piece p of token t at position p ^ (t & 15)
+    constexpr int kSlots = NT <= 3 ? 4 : 3;                  // ring slots that fit 160 KB of LDS
+    constexpr int kRowVecs = kWideWaves * 256, kXVecs = 2 * NT * 64;  // per slot: 32 rows x 128 bytes per wave; two k-steps of x
+    __shared__ uint4 r0[kRowVecs], r1[kRowVecs], r2[kRowVecs], r3[kSlots > 3 ? kRowVecs : 1];
+    __shared__ uint4 x0[kXVecs], x1[kXVecs], x2[kXVecs], x3[kSlots > 3 ? kXVecs : 1];
     __shared__ int s_task[kTok];
     __shared__ float s_w[kTok], s_tau[kTok];
     __shared__ uint32_t s_hmax[kTok];  // bits of the largest finite |h| of this workgroup's rows (ordered like the numbers)
@@ -160,8 +231,10 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
     const int W = gridDim.x, piece = wide_piece(W);
     int pos = wide_cut(total, W, piece);
     const int end = wide_cut(total, W, piece + 1);
-    const int ns = d / kSliceCols;  // a multiple of four (d % 512 == 0)
+    const int ns = d / kSliceCols;  // a multiple of eight (d % 512 == 0)
     const int pmax = (a.f + kPairRows - 1) / kPairRows;
+    // where in its 128 bytes a row's piece lies in LDS: at piece ^ swizzle(row), so that the sixteen rows of a tile meet all banks
+    auto swizzle = [](int row) { return (row & 7) ^ ((row >> 3) & 1); };
 
     while (pos < end) {  // one group's part of this workgroup's piece at a time
         int g, base;
@@ -182,17 +255,12 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
             s_tau[tid] = a.task_tau[task];
             s_hmax[tid] = 0u;
         }
-        __syncthreads();
-        const h16* xp[kRounds];
-#pragma unroll
-        for (int r = 0; r < kRounds; ++r) {
-            const int tok = (tid >> 4) + kTokRound * r;
-            xp[r] = a.x + (size_t)(s_task[tok < kTok ? tok : 0] / a.slots) * d + (tid & 15) * 8;
-        }
+        const int tiles = wide_tiles(grp.n);
+        const unsigned char* xop = scalar_ptr(a.xop + (size_t)grp.tile * (d / 32) * 64);
         // Workgroups start at different column slices: rows are 4 d bytes apart, so workgroups that walk the columns in step
         // ask for the same few memory channels at the same time.  (Two groups of one expert that work on the same rows
         // start alike and share them through the L2.)
-        const int rot = (int)((unsigned)(seg0 / 8) * 5u % (unsigned)ns);
+        const int rot = (int)((unsigned)(seg0 / 8) * 10u % (unsigned)ns);
         auto col_slice = [&](int s) {  // s-th slice of this workgroup (past the last one: the last one again)
             const int c = min(s, ns - 1) + rot;
             return c < ns ? c : c - ns;
@@ -201,139 +269,196 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
         const int len = seg1 - seg0;
         const int np = (len + kWideWaves - 1) / kWideWaves;
         const int per = (len + np - 1) / np;
-        for (int p0 = seg0; p0 < seg1; p0 += per) {
-            const int pair = p0 + wave;
-            const bool active = wave < per && pair < seg1;  // the others only help to bring x in
-            uint32_t wo[2];  // byte offsets from gd: at most f * 4 d <= 2^31
+        // live: token tiles that this group fills, of NT at most (a tile without tokens would cost as much as any other)
+        auto segment = [&](auto live) __attribute__((always_inline)) {
+            constexpr int NL = decltype(live)::value;
+            constexpr int kXReq = (2 * NL + kWideWaves - 1) / kWideWaves;  // a wave's share of a slice's activations
+            constexpr int kReq = 4 + kXReq;                                // ... and its rows
+            for (int p0 = seg0; p0 < seg1; p0 += per) {
+                const int pair = p0 + wave;
+                const bool active = wave < per && pair < seg1;  // the others only help to bring x in
+                auto load_x = [&](uint4* x, int s) {
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int k = min(pair * kPairRows + 16 * t + l16, count - 1);  // rows past the end repeat the last one
-                wo[t] = (uint32_t)rows[k] * (uint32_t)(4 * d) + 16 * q4;
-            }
-            f32x4 acc[2][NT];
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int n = 0; n < NT; ++n) acc[t][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-            uint4 xq[kRounds];
-            uint4 wq[2][2][kSteps];
-            // (every request below is unconditional - past the end it repeats the last slice - so that the compiler can count
-            // what is in flight: behind a conditional load it waits for everything)
-            auto load_x = [&](int s) {
-#pragma unroll
-                for (int r = 0; r < kRounds; ++r) xq[r] = gload16(xp[r] + col_slice(s) * kSliceCols);
-            };
-            auto store_x = [&](int buf) {
-#pragma unroll
-                for (int r = 0; r < kRounds; ++r) {
-                    const int tok = (tid >> 4) + kTokRound * r;
-                    if (tok < kTok) xs[buf][tok * 16 + ((tid & 15) ^ (tok & 15))] = xq[r];
+                    for (int k = 0; k < kXReq; ++k) {
+                        const int it = min(wave + kWideWaves * k, 2 * NL - 1), ks = it / NL, n = it % NL;
+                        dma16(xop + ((uint32_t)(min(n, tiles - 1) * (d / 32) + 2 * col_slice(s) + ks) * 1024u + 16u * lane), x + it * 64);
+                    }
+                };
+                __syncthreads();  // the slots are no longer read
+                if (!active) {  // the same barriers as the waves below
+                    load_x(x0, 0);
+                    load_x(x1, 1);
+                    if constexpr (kSlots > 3) load_x(x2, 2);
+                    auto step = [&](uint4* next, int s) __attribute__((always_inline)) {
+                        wait_requests_all_but<(kSlots - 2) * kXReq>();
+                        meet();
+                        load_x(next, s + kSlots - 1);
+                    };
+                    int s = 0;
+#pragma unroll 1
+                    for (; s + kSlots <= ns; s += kSlots) {
+                        step(kSlots > 3 ? x3 : x2, s);
+                        step(x0, s + 1);
+                        step(x1, s + 2);
+                        if constexpr (kSlots > 3) step(x2, s + 3);
+                    }
+                    if constexpr (kSlots == 3) {
+                        if (s < ns) step(x2, s);
+                        if (s + 1 < ns) step(x0, s + 1);
+                    }
+                    continue;
                 }
-            };
-            auto load_w = [&](uint4 (&w)[2][kSteps], int s, int c) {  // k-steps 2 c and 2 c + 1 of slice s: both halves of a line
+                uint32_t wo[4];  // byte offsets from gd of the rows' pieces this lane brings in: at most f * 4 d <= 2^31
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int r = 8 * j + (lane >> 3);
+                    const int k = min(pair * kPairRows + r, count - 1);  // rows past the end repeat the last one
+                    wo[j] = (uint32_t)rows[k] * (uint32_t)(4 * d) + 16u * (uint32_t)((lane & 7) ^ swizzle(r));
+                }
+                auto load_rows = [&](uint4* r, int s) {
+                    const uint32_t c = (uint32_t)col_slice(s) * (2u * kSliceCols);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) dma16(gd + (wo[j] + c), r + wave * 256 + j * 64);
+                };
+                f32x4 acc[2][NL];
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
 #pragma unroll
-                    for (int hf = 0; hf < 2; ++hf)
-                        w[t][2 * c + hf] = gload16(gd + (wo[t] + (uint32_t)(col_slice(s) * (2 * kSliceCols) + 128 * c + 64 * hf)));
-            };
-            load_x(0);
-            if (!active) {  // x only; the same barriers as the waves below
-                store_x(0);
-                load_x(1);
-                __syncthreads();
-                for (int s = 0; s < ns; ++s) {
-                    store_x((s & 1) ^ 1);
-                    load_x(s + 2);
-                    __syncthreads();
-                }
-                continue;
-            }
-            load_w(wq[0], 0, 0);
-            load_w(wq[0], 0, 1);
-            __builtin_amdgcn_sched_barrier(0);  // the waits of the loop count the requests in this order
-            store_x(0);
-            load_x(1);
-            __builtin_amdgcn_sched_barrier(0);
-            load_w(wq[1], 1, 0);
-            load_w(wq[1], 1, 1);
-            __syncthreads();
-            auto slice = [&](int s, uint4 (&w)[2][kSteps], int buf) {
-                store_x(buf ^ 1);
-                load_x(s + 2);
-#pragma unroll
-                for (int c = 0; c < kSteps / 2; ++c) {
-#pragma unroll
-                    for (int ks = 2 * c; ks < 2 * c + 2; ++ks)
-#pragma unroll
-                        for (int n = 0; n < NT; ++n) {
-                            const uint4 xf = xs[buf][(16 * n + l16) * 16 + ((4 * ks + q4) ^ l16)];
-#pragma unroll
-                            for (int t = 0; t < 2; ++t)
-                                acc[t][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h16x8, w[t][ks]),
-                                                                                   __builtin_bit_cast(h16x8, xf), acc[t][n], 0, 0, 0);
-                        }
-                    load_w(w, s + 2, c);
+                    for (int n = 0; n < NL; ++n) acc[t][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+                auto step = [&](const uint4* r, const uint4* x, uint4* next_r, uint4* next_x, int s) __attribute__((always_inline)) {
+                    wait_requests_all_but<(kSlots - 2) * kReq>();  // slice s is here, for this wave ...
+                    meet();                                        // ... and for all; nobody reads the slot of slice s - 1 any more
+                    load_rows(next_r, s + kSlots - 1);
+                    load_x(next_x, s + kSlots - 1);
                     __builtin_amdgcn_sched_barrier(0);
+                    uint4 w[2][2];
+#pragma unroll
+                    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) w[ks][t] = r[wave * 256 + (16 * t + l16) * 8 + ((4 * ks + q4) ^ swizzle(l16))];
+                    // LDS reads a few ahead of the products that need them (left alone, the compiler lets each pair wait for its own)
+                    constexpr int kAhead = 2 * NL < 6 ? 2 * NL : 6;
+                    uint4 xf[kAhead];
+#pragma unroll
+                    for (int i = 0; i < kAhead; ++i) xf[i] = x[i * 64 + lane];
+#pragma unroll
+                    for (int i = 0; i < 2 * NL; ++i) {
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int t = 0; t < 2; ++t)
+                            acc[t][i % NL] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h16x8, w[i / NL][t]),
+                                                                                    __builtin_bit_cast(h16x8, xf[i % kAhead]), acc[t][i % NL], 0, 0, 0);
+                        if (i + kAhead < 2 * NL) xf[i % kAhead] = x[(i + kAhead) * 64 + lane];
+                    }
+                };
+                load_rows(r0, 0);
+                load_x(x0, 0);
+                load_rows(r1, 1);
+                load_x(x1, 1);
+                if constexpr (kSlots > 3) {
+                    load_rows(r2, 2);
+                    load_x(x2, 2);
                 }
-                __syncthreads();
-            };
+                int s = 0;
 #pragma unroll 1
-            for (int s = 0; s < ns; s += 2) {
-                slice(s, wq[0], 0);
-                slice(s + 1, wq[1], 1);
-            }
-            // lane (l16, q4) holds A[row 16 t + 4 q4 + i][token 16 n + l16]
-            int row[2][4];
-#pragma unroll
-            for (int t = 0; t < 2; ++t)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int k = pair * kPairRows + 16 * t + 4 * q4 + i;
-                    row[t][i] = k < count ? rows[k] : -1;
+                for (; s + kSlots <= ns; s += kSlots) {
+                    step(r0, x0, kSlots > 3 ? r3 : r2, kSlots > 3 ? x3 : x2, s);
+                    step(r1, x1, r0, x0, s + 1);
+                    step(r2, x2, r1, x1, s + 2);
+                    if constexpr (kSlots > 3) step(r3, x3, r2, x2, s + 3);
                 }
-            int tok0 = l16;
-            asm volatile("" : "+v"(tok0));  // or the addresses below are formed ahead of the loop and held across it
-            constexpr int kBatch = NT < 4 ? NT : 4;  // token tiles whose v are requested together
-#pragma unroll
-            for (int n0 = 0; n0 < NT; n0 += kBatch) {
-                float vv[kBatch][2][4];
-#pragma unroll
-                for (int n = n0; n < n0 + kBatch && n < NT; ++n) {
-                    const unsigned char* vt = reinterpret_cast<const unsigned char*>(a.v + (size_t)s_task[16 * n + tok0] * a.f);
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) vv[n - n0][t][i] = gloadf(vt + 4 * max(row[t][i], 0));
+                if constexpr (kSlots == 3) {
+                    if (s < ns) step(r0, x0, r2, x2, s);
+                    if (s + 1 < ns) step(r1, x1, r0, x0, s + 1);
                 }
+                wait_requests_all_but<0>();  // (repeats of the last slice) the wave's rows make room for v
+                // lane (l16, q4) holds A[row 16 t + 4 q4 + i][token 16 n + l16]
+                int row[2][4];
 #pragma unroll
-                for (int n = n0; n < n0 + kBatch && n < NT; ++n) {
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int k = pair * kPairRows + 16 * t + 4 * q4 + i;
+                        row[t][i] = k < count ? rows[k] : -1;
+                    }
+                int tok0 = l16;
+                asm volatile("" : "+v"(tok0));  // or the addresses below are formed ahead of the loop and held across it
+                // The v that meet these rows.  Gathered by the lane that needs them they are 64 accesses of 4 bytes to the cache per
+                // instruction and a tenth of the kernel's time; where the pair's rows lie within kSpan channels (half of the channels
+                // or more selected by somebody) the wave brings the whole span in instead, 16 bytes per lane, and picks from LDS.
+                const int last_row = __builtin_amdgcn_readfirstlane(rows[min((pair + 1) * kPairRows, count) - 1]);
+                const int row0 = min(__builtin_amdgcn_readfirstlane(rows[pair * kPairRows]), a.f - kSpan);
+                const bool span = row0 >= 0 && last_row - row0 < kSpan;
+                float* stage = reinterpret_cast<float*>(r0 + wave * 256);  // [16 tokens][64 channels], pieces of 16 bytes at piece ^ token
+                auto finish = [&](int n, const float (&vv)[2][4]) __attribute__((always_inline)) {
                     const float w = s_w[16 * n + tok0], tau = s_tau[16 * n + tok0];
-                    const bool live = 16 * n + tok0 < grp.n;
+                    const bool used = 16 * n + tok0 < grp.n;
                     uint32_t top = 0u;
 #pragma unroll
                     for (int t = 0; t < 2; ++t)
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            const float v = vv[n - n0][t][i];
-                            const bool keep = live && row[t][i] >= 0 && fabsf(v) > tau;
+                            const float v = vv[t][i];
+                            const bool keep = used && row[t][i] >= 0 && fabsf(v) > tau;
                             const float h = keep ? silu(acc[t][n][i]) * v * w : 0.0f;
                             acc[t][n][i] = h;
                             const uint32_t m = __builtin_bit_cast(uint32_t, h) & 0x7FFFFFFFu;
                             top = max(top, m < 0x7F800000u ? m : 0u);
                         }
                     atomicMax(&s_hmax[16 * n + tok0], top);  // (no result wanted: fire and forget)
+                };
+                if (span) {
+                    uint4 vq[2][4];
+                    auto load_v = [&](int n) {  // four tokens per request
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+                            vq[n & 1][k] = gload16u(a.v + (size_t)s_task[16 * n + 4 * k + q4] * a.f + row0 + 4 * tok0);
+                    };
+                    load_v(0);
+#pragma unroll
+                    for (int n = 0; n < NL; ++n) {
+                        if (n + 1 < NL) load_v(n + 1);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) *reinterpret_cast<uint4*>(&stage[(4 * k + q4) * kSpan + 4 * (tok0 ^ (4 * k + q4))]) = vq[n & 1][k];
+                        __builtin_amdgcn_wave_barrier();  // (a wave's LDS accesses stay in order)
+                        float vv[2][4];
+#pragma unroll
+                        for (int t = 0; t < 2; ++t)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const int ch = max(row[t][i] - row0, 0);
+                                vv[t][i] = stage[tok0 * kSpan + 4 * ((ch >> 2) ^ tok0) + (ch & 3)];
+                            }
+                        __builtin_amdgcn_wave_barrier();
+                        finish(n, vv);
+                    }
+                } else {
+                    constexpr int kBatch = NL < 4 ? NL : 4;  // token tiles whose v are requested together
+#pragma unroll
+                    for (int n0 = 0; n0 < NL; n0 += kBatch) {
+                        float vv[kBatch][2][4];
+#pragma unroll
+                        for (int n = n0; n < n0 + kBatch && n < NL; ++n) {
+                            const unsigned char* vt = reinterpret_cast<const unsigned char*>(a.v + (size_t)s_task[16 * n + tok0] * a.f);
+#pragma unroll
+                            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) vv[n - n0][t][i] = gloadf(vt + 4 * max(row[t][i], 0));
+                        }
+#pragma unroll
+                        for (int n = n0; n < n0 + kBatch && n < NL; ++n) finish(n, vv[n - n0]);
+                    }
                 }
+                uint4* hb = a.hbuf + wide_h_first(grp, pmax) + (size_t)pair * tiles * 128 + lane;
+#pragma unroll
+                for (int n = 0; n < NL; ++n)
+                    if (n < tiles) {
+#pragma unroll
+                        for (int t = 0; t < 2; ++t) hb[n * 128 + t * 64] = __builtin_bit_cast(uint4, acc[t][n]);
+                    }
             }
-            const int tiles = wide_tiles(grp.n);
-            uint4* hb = a.hbuf + wide_h_first(grp, pmax) + (size_t)pair * tiles * 128 + lane;
-#pragma unroll
-            for (int n = 0; n < NT; ++n)
-                if (n < tiles) {
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) hb[n * 128 + t * 64] = __builtin_bit_cast(uint4, acc[t][n]);
-                }
-        }
+        };
+        with_live_tiles<NT>(wide_tiles(grp.n), segment);
         __syncthreads();
         // a maximum does not depend on the order in which the workgroups of a group arrive
         if (tid < grp.n) atomicMax(&a.hmax[grp.first + tid], s_hmax[tid]);
@@ -707,7 +832,7 @@ static hipError_t launch_wide_nt(const WideArgs& a, const WidePlan& p, int d, hi
 
 hipError_t launch_gate_down_wide(const WideArgs& a, const WidePlan& p, const uint32_t* mask_words, int d, hipStream_t stream) {
     if (d % kDownCols != 0 || mask_words_per_task(a.f) > kWideMaxMaskWords) return hipErrorInvalidValue;
-    wide_rows_kernel<<<dim3(p.max_groups), dim3(1024), 0, stream>>>(a, mask_words);
+    wide_rows_kernel<<<dim3(p.max_groups + p.h_tiles * ((d + kOperandCols - 1) / kOperandCols)), dim3(1024), 0, stream>>>(a, mask_words, p.max_groups, d);
     hipError_t rc = hipGetLastError();
     if (rc != hipSuccess) return rc;
     switch (p.nt) {

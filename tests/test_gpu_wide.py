@@ -49,6 +49,17 @@ def test_up_projection_split_over_columns(d, f, bits, group, n, n_shared, top_k,
     _run_layer_case(170 + T, 7, d, f, bits, group, n, n_shared, top_k, False, T, pct, gap=f * (100 - pct) >= 6400)
 
 
+@pytest.mark.parametrize("d,f,n,n_shared,top_k,T,pct", [
+    (512, 300, 0, 1, 0, 140, 60),    # nine of ten token tiles; eight column slices on three ring slots: two behind the loop
+    (1024, 291, 0, 1, 0, 160, 99),   # ten; one behind the loop; rows so far apart that v is gathered
+    (1536, 64, 0, 1, 0, 75, 90),     # five tiles, no slice behind the loop; one span of v is the whole row
+    (2048, 63, 3, 0, 2, 30, 10),     # fewer channels than a span
+    (1024, 1100, 4, 0, 2, 120, 50),  # groups of different sizes: live tiles at and below what the launch is built for
+])
+def test_gate_rows_and_activations_through_lds(d, f, n, n_shared, top_k, T, pct):
+    _run_layer_case(270 + T, 9, d, f, 2, 64, n, n_shared, top_k, False, T, pct, gap=f * (100 - pct) >= 6400)
+
+
 def test_h_beyond_fp16():
     """Large activations: |h| far beyond 65504 for some (row, token), ordinary for the others of the same group."""
     import gpu_common as G
