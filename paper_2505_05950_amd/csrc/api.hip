@@ -91,7 +91,7 @@ TaskMap single_map(const floe_expert* e) {
 // workspace of the one-expert entry points: [v: T*f floats][mask words][counts][idx when not fused][partial: T*nblk*d floats]
 struct ExpertWs {
     size_t v_off, mask_off, count_off, idx_off, partial_off, total;
-    size_t order_off, wgroups_off, xfrag_off, urow_off, ucount_off, hbuf_off, hmax_off, trows_off;  // wide path
+    size_t order_off, wgroups_off, xsum_off, urow_off, ucount_off, hbuf_off, hmax_off, trows_off;  // wide path
     int nblk, fused_passes, nblk_fused;
     bool wide;  // many tokens: one read of every row that any of a group of tokens selected (wide_batch.hip)
     WidePlan wp;
@@ -100,9 +100,9 @@ bool mask_path_ok(int f);
 // which form of the wide path a plan may take: the one that a call runs, none, or room for any that a batch of up to T
 // tokens can take
 enum class Wide { kChosen, kNone, kRoom };
-// h of the wide groups; before it is formed the activations that up_split reads lie in the same place
-size_t wide_h_bytes(const WidePlan& p, int d, int group) {
-    const size_t h = (size_t)p.h_tiles * p.pairs * 128 * sizeof(uint4), x = up_split_scratch_bytes(p.h_tiles, d, group);
+// h of the wide groups; before it is formed the activations that the up projection reads lie in the same place
+size_t wide_h_bytes(const WidePlan& p, int d) {
+    const size_t h = (size_t)p.h_tiles * p.pairs * 128 * sizeof(uint4), x = (size_t)p.h_tiles * 16 * d * 2;
     return h > x ? h : x;
 }
 // partial results; before them the activations that the gate kernel reads
@@ -125,10 +125,10 @@ ExpertWs expert_ws(const floe_shape* s, int T, Wide form = Wide::kChosen) {
         w.wp = form == Wide::kRoom ? wide_room(s->d, s->f, T, 1, 1, 0) : wide_plan(s->d, s->f, T, 1, 1, 0, 0);
         w.order_off = o;   o += align_up((size_t)T * 4);
         w.wgroups_off = o; o += align_up((size_t)w.wp.max_groups * sizeof(WideGroup) + 4);
-        w.xfrag_off = o;   o += align_up(up_wide_scratch_bytes(T, s->d, s->group));
+        w.xsum_off = o;    o += align_up(x_operand_sum_bytes(w.wp.h_tiles, s->d, s->group));
         w.urow_off = o;    o += align_up((size_t)w.wp.max_groups * s->f * 4);
         w.ucount_off = o;  o += align_up((size_t)w.wp.max_groups * 4);
-        w.hbuf_off = o;    o += align_up(wide_h_bytes(w.wp, s->d, s->group));
+        w.hbuf_off = o;    o += align_up(wide_h_bytes(w.wp, s->d));
         w.hmax_off = o;    o += align_up((size_t)T * 4);
         w.trows_off = o;   o += align_up((size_t)T * sizeof(int2));
     }
@@ -162,7 +162,7 @@ bool mask_path_ok(int f) { return mask_words_per_task(f) <= 2048; }
 // workspace of the layer: per-task table, counts, mask words, v, idx, partial
 struct LayerWs {
     size_t table_off, expert_off, weight_off, tau_off, logit_off, count_off, mask_off, groups_off, ngroups_off, order_off, v_off, idx_off,
-        rows_off, missidx_off, missrows_off, misscount_off, wgroups_off, xfrag_off, urow_off, ucount_off, hbuf_off, hmax_off, trows_off, partial_off, total;
+        rows_off, missidx_off, missrows_off, misscount_off, wgroups_off, xsum_off, urow_off, ucount_off, hbuf_off, hmax_off, trows_off, partial_off, total;
     int n_tasks, nblk, nblk_fused, fused_passes;
     bool batch_mfma;  // tokens of an expert share one pass over its codes (matrix-core up GEMV)
     bool use_wide;    // batches: one read of every row an expert group selected, on the matrix cores (wide_batch.hip)
@@ -230,10 +230,10 @@ LayerWs layer_plan(const floe_layer* L, int T, Wide form = Wide::kChosen, int ma
     w.up_split = w.use_wide && up_split_pays(L->s.d, L->s.f, L->s.bits, L->s.group, w.wp.nt);
     w.up_wide = w.use_wide && !w.up_split && up_wide_pays(L->s.d, L->s.f, L->s.bits, L->s.group, n_all, w.n_tasks);
     const bool room_for_x = room && up_wide_shape(L->s.d, L->s.f, L->s.bits, L->s.group) && grouped_gemv_mode() != 2;
-    w.xfrag_off = o;   o += w.up_wide || room_for_x ? align_up(up_wide_scratch_bytes(T, L->s.d, L->s.group)) : 0;
+    w.xsum_off = o;    o += w.up_wide || w.up_split || room_for_x ? align_up(x_operand_sum_bytes(w.wp.h_tiles, L->s.d, L->s.group)) : 0;
     w.urow_off = o;    o += align_up(wgroups * L->s.f * 4);
     w.ucount_off = o;  o += align_up(wgroups * 4);
-    w.hbuf_off = o;    o += w.use_wide ? align_up(wide_h_bytes(w.wp, L->s.d, L->s.group)) : 0;
+    w.hbuf_off = o;    o += w.use_wide ? align_up(wide_h_bytes(w.wp, L->s.d)) : 0;
     w.hmax_off = o;    o += w.use_wide ? align_up((size_t)w.n_tasks * 4) : 0;
     w.trows_off = o;   o += w.use_wide ? align_up((size_t)w.n_tasks * sizeof(int2)) : 0;
     w.partial_off = o;
@@ -500,7 +500,7 @@ int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, cons
             UpWideArgs u{};
             const bool split = up_split_pays(e->s.d, e->s.f, e->s.bits, e->s.group, w.wp.nt);
             u.groups = groups; u.n_groups = n_groups; u.order = order; u.x = xh; u.v = v;
-            u.task_tau = tau; u.mask_words = mask; u.scratch = base + (split ? w.hbuf_off : w.xfrag_off);
+            u.task_tau = tau; u.mask_words = mask; u.x_frag = base + w.hbuf_off; u.x_sums = base + w.xsum_off;
             u.T = T; u.n_tasks = T; u.d = e->s.d; u.f = e->s.f; u.slots = 1; u.nt = w.wp.nt;
             u.max_groups = w.wp.max_groups; u.est_groups = w.wp.est_groups;
             u.single = &map.single; u.chunk = w.wp.chunk;
@@ -736,7 +736,7 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
         if (w.up_wide || w.up_split) {
             UpWideArgs u{};
             u.groups = wide; u.n_groups = n_wide; u.order = order; u.x = xh; u.v = v;
-            u.task_tau = task_tau; u.mask_words = mask; u.scratch = base + (w.up_split ? w.hbuf_off : w.xfrag_off);
+            u.task_tau = task_tau; u.mask_words = mask; u.x_frag = base + w.hbuf_off; u.x_sums = base + w.xsum_off;
             u.T = T; u.n_tasks = w.n_tasks; u.d = L->s.d; u.f = L->s.f; u.slots = slots; u.nt = w.wp.nt;
             u.max_groups = w.wp.max_groups; u.est_groups = w.wp.est_groups;
             FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st,

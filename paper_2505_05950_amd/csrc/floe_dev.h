@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace floe {
 
 typedef _Float16 h16;
@@ -158,6 +160,26 @@ __device__ __forceinline__ int wave_inclusive_scan(int x, int lane) {
     return x;
 }
 
+// ---- memory straight into LDS (global_load_lds_dwordx4).  Destinations are arrays of their own per ring slot: the compiler then knows which
+// requests a read of LDS has to wait for, instead of waiting for all of them.
+#define FLOE_LDS __attribute__((address_space(3)))
+__device__ __forceinline__ void dma16(const void* src, uint4* lds_wave_base) {  // lane l's 16 bytes land at base + 16 l
+    __builtin_amdgcn_global_load_lds((const FLOE_GLOBAL void*)src, (FLOE_LDS void*)lds_wave_base, 16, 0, 0);
+}
+template <int N>
+__device__ __forceinline__ void wait_requests_all_but() {  // s_waitcnt vmcnt(N)
+    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+    asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void meet() {  // barrier alone: what is in flight stays in flight
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // ---- equal division of a launch's work (wide_batch.hip, up_wide.hip)
 // a pointer that every lane holds alike, as a scalar (loads then take it as their base and a 32-bit offset per lane)
 __device__ __forceinline__ const unsigned char* scalar_ptr(const void* p) {
@@ -172,6 +194,20 @@ __device__ __forceinline__ int wide_cut(int total, int W, int w) { return (int)(
 __device__ __forceinline__ int wide_piece(int W) {
     const int b = blockIdx.x;
     return (W & 7) ? b : (b & 7) * (W >> 3) + (b >> 3);
+}
+
+__device__ __forceinline__ int wide_tiles(int n) { return (n + 15) >> 4; }  // token tiles of a group
+// The kernels of wide groups exist for NT token tiles per group at most; their loops are unrolled for the tiles that a group fills: NT, or
+// one less, or two less of nine and ten (the sizes that the plan of a launch meets; smaller groups run the smallest).
+template <int NT, class F>
+__device__ __forceinline__ void with_live_tiles(int tiles, F&& f) {
+    if constexpr (NT >= 9) {
+        if (tiles <= NT - 2) return f(std::integral_constant<int, NT - 2>{});
+    }
+    if constexpr (NT >= 2) {
+        if (tiles <= NT - 1) return f(std::integral_constant<int, NT - 1>{});
+    }
+    f(std::integral_constant<int, NT>{});
 }
 
 __device__ __forceinline__ float silu(float g) { return g / (1.0f + __expf(-g)); }

@@ -219,21 +219,17 @@ struct WideArgs {
 inline bool up_wide_shape(int d, int f, int bits, int group) {
     return ((bits == 2 && group == 64) || ((bits == 3 || bits == 4) && (group == 32 || group == 64))) && d % 512 == 0 && f <= 65536;
 }
-// For shapes that the grouped kernel above takes as well, which of the two: it prepares the activations of at most 16 tokens
-// in every workgroup, this one prepares them once and shares a pass over the codes among up to 64.  Layer calls measured,
-// grouped / this, us (8 experts): INT2 g64 d 4096 f 14336 at 16 tasks per expert 375 / 392, 32: 529 / 491, 128: 907 / 792;
-// INT3 g64 d 2048 f 7000 at 16: 153 / 153, 32: 225 / 208, 128: 461 / 320; INT4 g32 d 2048 f 5632 at 128: 328 / 351;
-// INT3 g32 d 2048 f 1408 (66 experts) at 31: 373 / 410, 62: 525 / 480; INT4 g64 d 4096 f 7000 (6) at 32: 250 / 306, 40: 307 / 293.
-// A wave takes 32 channels of an expert here; layers with few of them leave most waves idle: INT2 at 32 tasks per expert, 352
-// blocks of 32 channels (16 experts d 2048 f 700) 99 / 116, 704 (4, d 2048 f 5632) 112 / 126, 896 (8, d 1024 f 3584) 104 / 107,
-// 1252 (4, d 1024 f 10000) 119 / 120, 2048 (16, d 4096 f 4096) 325 / 327 and 423 / 380 at 64.
+// For shapes that the grouped kernel above takes as well, which of the two, where up_split.hip does not apply: it prepares the
+// activations of at most 16 tokens in every workgroup, this one prepares them once and shares a pass over the codes among up to 144.
+// Layer calls measured, grouped / this, us: INT4 g32 d 2048 f 5632 (8 experts) at 128 tasks per expert 324 / 275, d 1024 f 3000 (6) at
+// 167: 385 / 166; INT4 g32 d 4096 f 2000 (4) at 250: 224 / 196; INT3 g32 d 2048 f 1000 (8) at 125: 134 / 134.  INT2, a wave taking 32
+// channels of an expert, by the layer's blocks of 32 channels: 256 blocks (8 experts d 4096 f 1000) 137 / 161, 352 (16, d 2048 f 700)
+// 102 / 115, 704 (4, d 2048 f 5632) 101 / 97, 896 (8, d 1024 f 3584) 140 / 134, 1144 (26, d 2048 f 1408) 187 / 178.
 inline bool up_wide_pays(int d, int f, int bits, int group, int n_all, int n_tasks) {
     if (!up_wide_shape(d, f, bits, group)) return false;
     if (!mfma_grouped_shape(d, bits, group)) return true;
     if (grouped_gemv_mode() == 2) return false;  // the caller wants one pass per task
-    if (group == 32) return bits == 3 && n_tasks >= 48 * n_all;
-    if (bits == 3) return n_tasks >= 32 * n_all;
-    return n_tasks >= (bits == 2 ? 32 : 40) * n_all && n_all * ((f + 31) / 32) >= 1250;
+    return bits != 2 || (n_tasks >= 32 * n_all && n_all * ((f + 31) / 32) >= 600);
 }
 struct UpWideArgs {
     const WideGroup* groups;
@@ -243,12 +239,20 @@ struct UpWideArgs {
     float* v;
     const float* task_tau;
     uint32_t* mask_words;
-    void* scratch;  // up_wide_scratch_bytes()
+    void* x_frag;   // h_tiles * 16 * d halves: the activations as operands
+    void* x_sums;   // x_operand_sum_bytes()
     int32_t T, n_tasks, d, f, slots, nt, max_groups, est_groups, parts, workgroups;  // (parts, workgroups: set by the launcher)
     const DevExpert* single;  // one expert that every task belongs to: the launcher fills groups, n_groups and order in as well
     int32_t chunk;            // (single) tasks per group at most
 };
-size_t up_wide_scratch_bytes(int T, int d, int group);
+// the activations as matrix operands (up_split.hip)
+struct XOperand {
+    uint4* frag;   // [token tile][unit][two instructions][lane]
+    float* gsum;   // [token tile][unit][groups per unit][16]
+    float* back;   // [token tile][16]
+};
+size_t x_operand_sum_bytes(int tiles, int d, int group);  // tiles: token tiles that the groups can have together
+hipError_t launch_x_operand(const UpWideArgs& a, int bits, int group, XOperand& x, hipStream_t stream);
 hipError_t launch_up_wide(UpWideArgs a, int bits, int group, hipStream_t stream);
 
 // S2 for groups of up to two token tiles, the columns split over the waves of a workgroup (up_split.hip)
@@ -258,14 +262,16 @@ inline bool up_split_shape(int d, int f, int bits, int group) { return up_wide_s
 // INT3 g32 d 4096 f 4096 (16 experts) at 128: 420 / 284; d 2048 f 1408 (66 experts, top-6) at 64: 220 / 195, 128: 260 / 245;
 // INT4 g64 d 4096 f 7000 (6) at 48: 222 / 202; INT4 g32 d 2048 f 5632 at 64: 138 / 137; widths without a grouped kernel the same.
 // With one token tile INT2 leaves the grouped kernel little to share a pass with and less to unpack: 24 tokens 243 / 251.
+// More than two token tiles come in parts of two, which up_wide.hip does at once: INT2 at 130 tokens 485 / 470, d 2048 f 4096 (4 experts)
+// at 90: 89 / 86; the wider codes leave it fewer token tiles: INT4 g32 d 2048 f 5632 at 200 tokens, that or grouped kernel / this, 184 / 162,
+// INT3 g64 d 2048 f 7000 at 200: 196 / 182, INT3 g32 d 4096 f 3000 (4) at 90: 152 / 109.
 inline bool up_split_pays(int d, int f, int bits, int group, int nt) {
     if (!up_split_shape(d, f, bits, group)) return false;
     const bool grouped = mfma_grouped_shape(d, bits, group);
     if (grouped && grouped_gemv_mode() == 2) return false;  // the caller wants one pass per task
-    return nt <= 2 && !(grouped && bits == 2 && nt == 1);
+    return nt <= (bits == 2 ? 2 : 4) && !(grouped && bits == 2 && nt == 1);
 }
 hipError_t launch_up_split(UpWideArgs a, int bits, int group, hipStream_t stream);
-size_t up_split_scratch_bytes(int tiles, int d, int group);  // tiles: token tiles that the groups can have together
 
 WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared, int max_down);
 WidePlan wide_room(int d, int f, int T, int n_experts, int top_k, int n_shared);

@@ -127,46 +127,36 @@ __device__ __forceinline__ void transpose4(uint4& q) {  // across the four lane 
     t = __builtin_amdgcn_permlane16_swap(q.z, q.w, false, false); q.z = t.x; q.w = t.y;
 }
 
-// One slice (four units) of a channel tile: what a lane loads and the operand words it makes of it.  Quarter g of a
-// channel's four lanes loads unit g whole; the transposes hand every quarter its words of all four units.
-template <int BITS>
-struct CodeSlice {
-    static constexpr int kVec = BITS == 4 ? 2 : 1;  // 16-byte vectors per unit (INT3: three 8-byte ones)
-    static constexpr int kLaneWords = BITS == 2 ? 1 : 2;  // operand words per unit
-    uint4 raw[kVec];
-    uint32_t raw3[BITS == 3 ? 6 : 1];
-    __device__ __forceinline__ void load(const unsigned char* codes, uint32_t off) {
-        if constexpr (BITS == 3) {
+// word of quarter k -> rk in every lane
+__device__ __forceinline__ void quarters_to_all(uint32_t w, uint32_t& r0, uint32_t& r1, uint32_t& r2, uint32_t& r3) {
+    const u32x2 h = __builtin_amdgcn_permlane32_swap(w, w, false, false);  // lower and upper half, twice each
+    const u32x2 a = __builtin_amdgcn_permlane16_swap(h.x, h.x, false, false), b = __builtin_amdgcn_permlane16_swap(h.y, h.y, false, false);
+    r0 = a.x; r1 = a.y; r2 = b.x; r3 = b.y;
+}
+
+// A lane's codes (units 2 g and 2 g + 1 of quarter g) -> the operand words of units p, p + 2, p + 4, p + 6
+template <int BITS, int VECS, int WORDS>
+__device__ __forceinline__ void deal_units(const uint4 (&q)[VECS], int p, uint32_t (&wd)[4][WORDS]) {
+    if constexpr (BITS == 3) {
+        // a unit is two halves of 96 bits, four 24-bit fields each; field k goes to quarter k
+        const uint32_t w[12] = {q[0].x, q[0].y, q[0].z, q[0].w, q[1].x, q[1].y, q[1].z, q[1].w, q[2].x, q[2].y, q[2].z, q[2].w};
 #pragma unroll
-            for (int r = 0; r < 3; ++r) {
-                const uint2 q = gload8(codes + (off + 8 * r));
-                raw3[2 * r] = q.x;
-                raw3[2 * r + 1] = q.y;
-            }
-        } else {
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t w0 = w[6 * p + 3 * h], w1 = w[6 * p + 3 * h + 1], w2 = w[6 * p + 3 * h + 2];
+            uint4 fld = make_uint4(w0, __builtin_amdgcn_alignbit(w1, w0, 24), __builtin_amdgcn_alignbit(w2, w1, 16), w2 >> 8);
+            transpose4(fld);
+            wd[0][h] = fld.x; wd[1][h] = fld.y; wd[2][h] = fld.z; wd[3][h] = fld.w;
+        }
+    } else {
 #pragma unroll
-            for (int r = 0; r < kVec; ++r) raw[r] = gload16(codes + (off + 16 * r));
+        for (int r = 0; r < WORDS; ++r) {
+            uint4 w = q[p * WORDS + r];
+            transpose4(w);
+            wd[0][r] = w.x; wd[1][r] = w.y; wd[2][r] = w.z; wd[3][r] = w.w;
         }
     }
-    __device__ __forceinline__ void deal(uint32_t (&wd)[4][kLaneWords]) const {  // [unit of the slice][word]
-        if constexpr (BITS == 3) {
-            // this lane's unit: two halves of 96 bits, four 24-bit fields each; field k goes to quarter k
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const uint32_t w0 = raw3[3 * h], w1 = raw3[3 * h + 1], w2 = raw3[3 * h + 2];
-                uint4 fld = make_uint4(w0, __builtin_amdgcn_alignbit(w1, w0, 24), __builtin_amdgcn_alignbit(w2, w1, 16), w2 >> 8);
-                transpose4(fld);
-                wd[0][h] = fld.x; wd[1][h] = fld.y; wd[2][h] = fld.z; wd[3][h] = fld.w;
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < kVec; ++r) {
-                uint4 w = raw[r];
-                transpose4(w);
-                wd[0][r] = w.x; wd[1][r] = w.y; wd[2][r] = w.z; wd[3][r] = w.w;
-            }
-        }
-    }
-};
+}
+
+// TILES channel tiles of 16 per block
 
 }  // namespace floe

@@ -34,50 +34,20 @@ constexpr int kSpParked = 4 * 2 * 64;  // vectors per wave: the second token til
 
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 
-// word of quarter k -> rk in every lane
-__device__ __forceinline__ void quarters_to_all(uint32_t w, uint32_t& r0, uint32_t& r1, uint32_t& r2, uint32_t& r3) {
-    const u32x2 h = __builtin_amdgcn_permlane32_swap(w, w, false, false);  // lower and upper half, twice each
-    const u32x2 a = __builtin_amdgcn_permlane16_swap(h.x, h.x, false, false), b = __builtin_amdgcn_permlane16_swap(h.y, h.y, false, false);
-    r0 = a.x; r1 = a.y; r2 = b.x; r3 = b.y;
-}
-
-// A lane's codes (units 2 g and 2 g + 1 of quarter g) -> the operand words of units p, p + 2, p + 4, p + 6
-template <int BITS, int VECS, int WORDS>
-__device__ __forceinline__ void deal_units(const uint4 (&q)[VECS], int p, uint32_t (&wd)[4][WORDS]) {
-    if constexpr (BITS == 3) {
-        // a unit is two halves of 96 bits, four 24-bit fields each; field k goes to quarter k
-        const uint32_t w[12] = {q[0].x, q[0].y, q[0].z, q[0].w, q[1].x, q[1].y, q[1].z, q[1].w, q[2].x, q[2].y, q[2].z, q[2].w};
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const uint32_t w0 = w[6 * p + 3 * h], w1 = w[6 * p + 3 * h + 1], w2 = w[6 * p + 3 * h + 2];
-            uint4 fld = make_uint4(w0, __builtin_amdgcn_alignbit(w1, w0, 24), __builtin_amdgcn_alignbit(w2, w1, 16), w2 >> 8);
-            transpose4(fld);
-            wd[0][h] = fld.x; wd[1][h] = fld.y; wd[2][h] = fld.z; wd[3][h] = fld.w;
-        }
-    } else {
-#pragma unroll
-        for (int r = 0; r < WORDS; ++r) {
-            uint4 w = q[p * WORDS + r];
-            transpose4(w);
-            wd[0][r] = w.x; wd[1][r] = w.y; wd[2][r] = w.z; wd[3][r] = w.w;
-        }
-    }
-}
-
-// TILES channel tiles of 16 per block
 // The activations of every task as the operand of the matrix instruction, [token tile][unit][instruction of the unit][lane],
-// their sums per quantization group and the factor that undoes the scaling.  One task per workgroup, one unit per thread.  (Every
+// their sums per quantization group and the factor that undoes the scaling.  One task per workgroup, one unit per thread (d <= 8192).  (Every
 // workgroup of the kernel below would otherwise gather them for itself, 16 bytes per lane from as many rows: 11 of its first 15 us.)
 // single: all tasks belong to one expert; groups and order are filled in here.
 template <int BITS, bool G32>
-__global__ __launch_bounds__(64) void x_operand_kernel(const h16* __restrict__ x, int slots, int d, WideGroup* __restrict__ groups,
+__global__ __launch_bounds__(128) void x_operand_kernel(const h16* __restrict__ x, int slots, int d, WideGroup* __restrict__ groups,
                                                        int32_t* __restrict__ n_groups, int32_t* __restrict__ order, int max_groups,
                                                        bool single, DevExpert e, int n_tasks, int chunk, uint4* __restrict__ frag,
                                                        float* __restrict__ gsum, float* __restrict__ back) {
     using Tr = MfmaTraits<BITS, G32>;
     constexpr int kGroups = G32 ? 2 : 1;
     constexpr float kScaleBack = (float)(1 << (24 - Tr::kPmax));
-    const int i = blockIdx.x, U = threadIdx.x, units = d >> 6;
+    __shared__ float wave_max[2];
+    const int i = blockIdx.x, U = threadIdx.x, lane = U & 63, units = d >> 6;
     int task = i, row = 0;  // row: of the token tiles
     if (single) {
         const int len = wide_single_len(n_tasks, chunk), g = i / len;
@@ -91,9 +61,9 @@ __global__ __launch_bounds__(64) void x_operand_kernel(const h16* __restrict__ x
         task = order[i];
         const int ng = n_groups[0];
         for (int g0 = 0; g0 < ng; g0 += kWave) {
-            const WideGroup* mine = groups + min(g0 + U, max_groups - 1);
+            const WideGroup* mine = groups + min(g0 + lane, max_groups - 1);
             const int n = mine->n, first = mine->first, tile = mine->tile;
-            const unsigned long long m = __ballot(g0 + U < ng && i >= first && i < first + n);
+            const unsigned long long m = __ballot(g0 + lane < ng && i >= first && i < first + n);
             if (m) {
                 const int l = __ffsll((long long)m) - 1;
                 row = __builtin_amdgcn_readlane(tile * 16 + i - first, l);
@@ -115,7 +85,12 @@ __global__ __launch_bounds__(64) void x_operand_kernel(const h16* __restrict__ x
     // the largest magnitude, as the bits of a half (those of non-negative numbers order like integers; a NaN lands on top)
 #pragma unroll
     for (int k = 0; k < 32; ++k) top2 = __builtin_elementwise_max(top2, __builtin_bit_cast(u16x2, xv[k] & 0x7FFF7FFFu));
-    const float amax = wave_allreduce_max_nonneg((float)__builtin_bit_cast(h16, (uint16_t)max((uint32_t)top2.x, (uint32_t)top2.y)));
+    float amax = wave_allreduce_max_nonneg((float)__builtin_bit_cast(h16, (uint16_t)max((uint32_t)top2.x, (uint32_t)top2.y)));
+    if (blockDim.x > kWave) {  // (more than 64 units)
+        if (lane == 0) wave_max[U >> 6] = amax;
+        __syncthreads();
+        amax = fmaxf(wave_max[0], wave_max[1]);
+    }
     const int down = (amax >= 512.0f && amax < 3.0e38f) ? ilogbf(amax) - 8 : 0;  // |x'| < 512: 2^(pmax - p) x' stays finite
     if (U == 0) back[row] = ldexpf(1.0f, down) * kScaleBack;
     if (!live) return;
@@ -433,10 +408,23 @@ extern "C" int floe_debug_set_timeline_up_split(unsigned long long* p) {
 }
 #endif
 
-// token tiles that the groups can have together
-static int split_tiles(const UpWideArgs& a) { return (a.n_tasks + 15 * a.max_groups) / 16; }
-size_t up_split_scratch_bytes(int tiles, int d, int group) {
-    return (size_t)tiles * 16 * ((size_t)d * 2 + (size_t)(d / 64) * (group == 32 ? 2 : 1) * 4 + 4);
+size_t x_operand_sum_bytes(int tiles, int d, int group) { return (size_t)tiles * 16 * ((size_t)(d / 64) * (group == 32 ? 2 : 1) * 4 + 4); }
+
+template <int BITS, bool G32>
+static hipError_t operand_bits(const UpWideArgs& a, const XOperand& x, hipStream_t stream) {
+    x_operand_kernel<BITS, G32><<<dim3(a.n_tasks), dim3(a.d > 4096 ? 128 : 64), 0, stream>>>(
+        a.x, a.slots, a.d, const_cast<WideGroup*>(a.groups), const_cast<int32_t*>(a.n_groups), const_cast<int32_t*>(a.order), a.max_groups,
+        a.single != nullptr, a.single ? *a.single : DevExpert{}, a.n_tasks, a.chunk, x.frag, x.gsum, x.back);
+    return hipGetLastError();
+}
+hipError_t launch_x_operand(const UpWideArgs& a, int bits, int group, XOperand& x, hipStream_t stream) {
+    const size_t tiles = (size_t)(a.n_tasks + 15 * a.max_groups) / 16;  // that the groups can have together
+    x.frag = static_cast<uint4*>(a.x_frag);
+    x.gsum = static_cast<float*>(a.x_sums);
+    x.back = x.gsum + tiles * (a.d / 64) * (group == 32 ? 32 : 16);
+    if (bits == 2) return operand_bits<2, false>(a, x, stream);
+    if (bits == 3) return group == 32 ? operand_bits<3, true>(a, x, stream) : operand_bits<3, false>(a, x, stream);
+    return group == 32 ? operand_bits<4, true>(a, x, stream) : operand_bits<4, false>(a, x, stream);
 }
 
 template <int BITS, bool G32, int NT>
@@ -462,16 +450,10 @@ static hipError_t launch_split(const UpWideArgs& a, hipStream_t stream) {
     const int room = num_cus() * (8 / nw > 1 ? 8 / nw : 1);  // workgroups that the registers hold at a time (eight waves per compute unit)
     int wgs = (int)(blocks < room ? blocks : room);
     if (wgs > 8) wgs &= ~7;  // (see wide_piece)
-    uint4* frag = static_cast<uint4*>(a.scratch);
-    const int tiles = split_tiles(a);
-    float* gsum = reinterpret_cast<float*>(frag + (size_t)tiles * a.d * 2);
-    float* back = gsum + (size_t)tiles * (a.d / 64) * (16 * kGroups);
-    x_operand_kernel<BITS, G32><<<dim3(a.n_tasks), dim3(64), 0, stream>>>(
-        a.x, a.slots, a.d, const_cast<WideGroup*>(a.groups), const_cast<int32_t*>(a.n_groups), const_cast<int32_t*>(a.order), a.max_groups,
-        a.single != nullptr, a.single ? *a.single : DevExpert{}, a.n_tasks, a.chunk, frag, gsum, back);
-    const hipError_t rc = hipGetLastError();
+    XOperand x;
+    const hipError_t rc = launch_x_operand(a, BITS, G32 ? 32 : 64, x, stream);
     if (rc != hipSuccess) return rc;
-    kernel<<<dim3(wgs), dim3(64 * nw), lds, stream>>>(a.groups, a.n_groups, a.max_groups, a.order, frag, gsum, back, a.v, a.task_tau,
+    kernel<<<dim3(wgs), dim3(64 * nw), lds, stream>>>(a.groups, a.n_groups, a.max_groups, a.order, x.frag, x.gsum, x.back, a.v, a.task_tau,
                                                     a.mask_words, a.d, a.f, a.parts);
     return hipGetLastError();
 }

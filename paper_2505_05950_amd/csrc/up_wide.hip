@@ -2,390 +2,405 @@
 // batch-1, each token keeps its own threshold, mask and result).  The arithmetic is that of up_gemv_mfma.hip: codes masked
 // in place as fp16 subnormals, activations scaled by powers of two, scale and zero applied per quantization group in fp32.
 //
-//   x_frag_kernel   per token, once: the activations in the order and scaling of the matrix instruction's operand, their
-//                   sums per quantization group, the factor that undoes the scaling.  (Every workgroup of the grouped
-//                   kernel prepares them for itself; with many tokens per expert that would be most of its work.)
-//   up_wide_kernel  a wave takes 32 channels (two tiles of 16) for all tokens of a group (up to 64: four token tiles); one
-//                   slice of activations brought into LDS serves the 512 channels of sixteen waves.  Codes stream from
-//                   memory into registers, a slice of four units (256 columns) ahead; activations pass through LDS in the
-//                   same slices.
+//   up_wide_kernel  a wave takes two channel tiles of 16 for up to nine token tiles (INT3, INT4: five); the eight waves of a
+//                   workgroup share the activations, which travel from memory straight into a ring of four slots in LDS, two
+//                   units (128 columns) each, in operand order (x_operand_kernel in up_split.hip).  Codes, scales and zeros of
+//                   eight units go to registers, half of eight units ahead.
 //
-// What bounds it: vector instructions beside the matrix ones (54 % and 24 % of the cycles at 512 tokens): 18 per tile and
-// unit to mask the codes, 8 per tile, unit and token tile for scale and zero.  Tiles without tokens are skipped for that
-// reason.  8 experts d 4096 f 14336 INT2, 512 tokens: 386 us with the grouped kernel -> 296 us (both kernels; 280 on another
-// card); tried: four channel tiles per wave with eight waves 395 us, two workgroups of eight waves per compute unit 344 us.
+// What bounds it: vector instructions (per unit and wave 24 to mask codes and widen scale and zero, 16 per token tile to apply them)
+// and matrix products (four per token tile), which share the issue of the SIMD's two waves; the order in the loop deals products and
+// multiply-adds one to four.  8 experts d 4096 f 14336 INT2, 512 tokens: 286 -> 224 us (before: sixteen waves, four token tiles, the
+// codes unpacked three times); of that 8 to find the work, and per pass of 256 channels 6 until the ring is full and 8 for the
+// results.  Tried: four channel tiles and up to four token tiles 297; pieces that do not end where groups end 266; operands fetched
+// three items ahead (the same).
 //
-// Division of work: the blocks of 32 channels of all groups form one sequence that is cut into equal pieces, one workgroup
-// each (see wide_batch.hip).
+// Division of work: channel blocks of 32; each part of a group is cut into equal pieces, one workgroup each.
+#include <atomic>
+#include <type_traits>
+
 #include "floe_dev.h"
 #include "launch.h"
 #include "mfma_codes.h"
 
 namespace floe {
 
-constexpr int kUpWaves = 16;
+constexpr int kUpWaves = 8;
 constexpr int kUpThreads = kUpWaves * 64;
-constexpr int kUpTiles = 2;                  // channel tiles per wave
-constexpr int kUpChan = 16 * kUpTiles;       // channels per wave: one mask word
-constexpr int kUpWgChan = kUpWaves * kUpChan;
-constexpr int kSliceUnits = 4;               // units of 64 codes per slice
-
-// fragment order and scaling of up_gemv_mfma.hip, one token per workgroup, one unit per thread (d <= 8192)
-template <int BITS, bool G32>
-__global__ __launch_bounds__(128) void x_frag_kernel(const h16* __restrict__ x, int d, uint4* __restrict__ frag,
-                                                     float* __restrict__ gsum, float* __restrict__ back) {
-    using Tr = MfmaTraits<BITS, G32>;
-    constexpr int kGroups = G32 ? 2 : 1;
-    constexpr float kScaleBack = (float)(1 << (24 - Tr::kPmax));
-    __shared__ float wmax[2];
-    const int t = blockIdx.x, U = threadIdx.x, units = d >> 6;
-    const bool live = U < units;
-    uint4 q[8];
-    float amax = 0.0f;
-    const uint4* xr = reinterpret_cast<const uint4*>(x + (size_t)t * d) + (live ? U : 0) * 8;
-#pragma unroll
-    for (int r = 0; r < 8; ++r) q[r] = xr[r];
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        const uint32_t wds[4] = {q[r].x, q[r].y, q[r].z, q[r].w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const h16x2 p = as_h2(wds[k]);
-            amax = fmaxf(amax, fmaxf(fabsf((float)p.x), fabsf((float)p.y)));
-        }
-    }
-    amax = wave_allreduce_max_nonneg(amax);
-    if ((U & 63) == 0) wmax[U >> 6] = amax;
-    __syncthreads();
-    amax = fmaxf(wmax[0], wmax[1]);
-    const int down = (amax >= 512.0f && amax < 3.0e38f) ? ilogbf(amax) - 8 : 0;  // |x'| < 512: 2^(pmax - p) x' stays finite
-    if (U == 0) back[t] = ldexpf(1.0f, down) * kScaleBack;
-    if (!live) return;
-    const h16 ps = (h16)ldexpf(1.0f, -down);
-    const h16x2 ps2 = {ps, ps}, ones = {(h16)1.0f, (h16)1.0f};
-    uint32_t xv[32];
-    float sum[2] = {0.0f, 0.0f};
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        const uint32_t wds[4] = {q[r].x, q[r].y, q[r].z, q[r].w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const h16x2 p = as_h2(wds[k]) * ps2;
-            xv[4 * r + k] = as_u32(p);
-            sum[G32 ? (r >> 2) : 0] = __builtin_amdgcn_fdot2(p, ones, sum[G32 ? (r >> 2) : 0], false);
-        }
-    }
-    uint4* out = frag + ((size_t)t * units + U) * 8;
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            uint32_t w[4];
-#pragma unroll
-            for (int pr = 0; pr < 4; ++pr) {
-                const int lo = Tr::code(j, g, 2 * pr), hi = Tr::code(j, g, 2 * pr + 1);
-                const uint32_t wl = xv[lo >> 1], wh = xv[hi >> 1];
-                const uint32_t l16 = (lo & 1) ? (wl >> 16) : (wl & 0xFFFFu);
-                const uint32_t h16b = (hi & 1) ? (wh & 0xFFFF0000u) : (wh << 16);
-                const h16x2 mul = {(h16)(float)(1 << (Tr::kPmax - Tr::pos(j, 2 * pr))),
-                                   (h16)(float)(1 << (Tr::kPmax - Tr::pos(j, 2 * pr + 1)))};
-                w[pr] = as_u32(as_h2(l16 | h16b) * mul);
-            }
-            out[j * 4 + g] = make_uint4(w[0], w[1], w[2], w[3]);
-        }
-    // (times 2^(pmax - 24), which the matrix products carry and the zero-point term is subtracted under)
-#pragma unroll
-    for (int k = 0; k < kGroups; ++k) gsum[((size_t)t * units + U) * kGroups + k] = sum[k] * (1.0f / kScaleBack);
-}
+constexpr int kUpSlotUnits = 2;
 
 template <int BITS, bool G32, int NT>
-__global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __restrict__ groups,
-                                                             const int32_t* __restrict__ n_groups, const int32_t* __restrict__ order,
+__global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __restrict__ groups, const int32_t* __restrict__ n_groups,
+                                                             int max_groups, const int32_t* __restrict__ order,
                                                              const uint4* __restrict__ frag, const float* __restrict__ gsum,
-                                                             const float* __restrict__ back, int slots, float* __restrict__ v,
+                                                             const float* __restrict__ back, float* __restrict__ v,
                                                              const float* __restrict__ task_tau, uint32_t* __restrict__ mask_words,
-                                                             int d, int f, int parts) {
-    using Tr = MfmaTraits<BITS, G32>;
+                                                             int d, int f) {
+    constexpr int CT = 2;                                // channel tiles of 16 per wave: one mask word
     constexpr int kTok = 16 * NT;
-    constexpr int kGroups = G32 ? 2 : 1;                       // quantization groups per unit
-    constexpr int kPieces = kSliceUnits * 8;                   // 16-byte pieces of a token per slice
-    constexpr int kRounds = (kTok * kPieces + kUpThreads - 1) / kUpThreads;
-    constexpr int kSums = kSliceUnits * kGroups;               // group sums of a token per slice
-    constexpr int kSuperScales = 16;                           // scales per channel that sit in LDS at a time ...
-    constexpr int kSuper = kSuperScales / kSums;               // ... those of so many slices
-    __shared__ uint4 xs[2][kTok * kPieces];                    // [token][piece ^ (token & 15)]
-    __shared__ __align__(16) float xg[2][kSums * kTok];        // [sum][token]
-    __shared__ uint32_t meta[2][kSuperScales * kUpWgChan];  // [scale index][channel of the workgroup] (scale, zero)
-    __shared__ int s_task[kTok];
-    __shared__ float s_tau[kTok], s_back[kTok];
+    constexpr int kGroups = G32 ? 2 : 1;                 // quantization groups per unit
+    constexpr int kVec = BITS;                           // 16-byte vectors of codes per lane and tile: two units of eight
+    constexpr int kMetaLoads = (CT * 2 * kGroups + 3) / 4;
+    constexpr int kLaneWords = BITS == 2 ? 1 : 2;        // operand words per unit
+    constexpr int kCh = 16 * CT;                         // channels per wave
+    constexpr int kXVecs = kUpSlotUnits * 2 * NT * 64;   // per slot: activations, and behind them the group sums
+    constexpr int kSumVecs = (kUpSlotUnits * kGroups * NT * 4 + 63) / 64 * 64;
+    __shared__ uint4 x0[kXVecs + kSumVecs], x1[kXVecs + kSumVecs], x2[kXVecs + kSumVecs], x3[kXVecs + kSumVecs];
+    __shared__ __align__(16) int s_task[kTok];
+    __shared__ __align__(16) float s_tau[kTok], s_back[kTok];
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int c = lane & 15, g4 = lane >> 4;
-    const int units = d >> 6, ns = units / kSliceUnits;        // an even number of slices (d % 512 == 0)
-    const int blocks = (f + kUpChan - 1) / kUpChan;            // of 32 channels, per group
-    const int total = n_groups[0] * parts * blocks;
-    const int piece = wide_piece(gridDim.x);
-    int pos = wide_cut(total, gridDim.x, piece);
-    const int end = wide_cut(total, gridDim.x, piece + 1);
+    const int units = d >> 6;
+    const int blocks = (f + kCh - 1) / kCh;              // per part of a group
     const int nwords = mask_words_per_task(f);
+    // A block of channels costs as much as it has token tiles to do, and two more for its codes; a group of more than NT tiles comes in
+    // parts of equal size.
+    const int ng = n_groups[0];
+    auto parts_of = [](int n) { return (n + kTok - 1) / kTok; };
+    auto part_tiles = [&](int n) { return (wide_tiles(n) + parts_of(n) - 1) / parts_of(n); };
+    auto weight = [&](int n) { return part_tiles(n) + 2; };
+    struct Share { int parts, part_weight; };
+    auto share_of = [&](int g0) {  // lane's group (the load does not wait for ng)
+        const int n = groups[min(g0 + lane, max_groups - 1)].n;
+        return g0 + lane < ng ? Share{parts_of(n), weight(n) * blocks} : Share{0, 0};
+    };
+    int total = 0, n_parts = 0;
+    for (int g0 = 0; g0 < ng; g0 += kWave) {
+        const Share sh = share_of(g0);
+        total += __builtin_amdgcn_readlane(wave_inclusive_scan(sh.parts * sh.part_weight, lane), kWave - 1);
+        n_parts += __builtin_amdgcn_readlane(wave_inclusive_scan(sh.parts, lane), kWave - 1);
+    }
+    const int W = gridDim.x, piece = wide_piece(W);
+    // Pieces end where parts end: a pass of the workgroup takes as long with one wave at work as with eight, so a piece that holds the
+    // ends of two parts takes a pass more than its share, and the launch waits for it (512 tokens: 266 us, the mean piece 182).  Each
+    // part is cut into as few equal pieces of at most `most` as it takes, `most` the smallest that leaves no more than W pieces.
+    const bool whole = n_parts <= W;
+    int most = max((total + W - 1) / W, 1);
+    while (whole) {
+        int sum = 0;
+        for (int g0 = 0; g0 < ng; g0 += kWave) {
+            const Share sh = share_of(g0);
+            sum += __builtin_amdgcn_readlane(wave_inclusive_scan(sh.parts * ((sh.part_weight + most - 1) / most), lane), kWave - 1);
+        }
+        if (sum <= W) break;  // (at the largest part at the latest: a piece each)
+        most += (most + 31) / 32;
+    }
+    int pos = whole ? piece : wide_cut(total, W, piece);
+    const int end = whole ? piece + 1 : wide_cut(total, W, piece + 1);
 
     while (pos < end) {
-        const int gi = __builtin_amdgcn_readfirstlane(pos / blocks);
-        const int b0 = pos - gi * blocks;
-        const int len = min(blocks - b0, end - pos);
-        pos += len;
-        const WideGroup grp = groups[gi / parts];
-        // a group of more tokens than the accumulators take is cut into `parts`
-        const int part_len = (grp.n + parts - 1) / parts;
-        const int tok_first = (gi % parts) * part_len, n_tok = min(part_len, grp.n - tok_first);
-        if (n_tok <= 0) continue;
+        // the group that `pos` - a piece of the parts, or a share of the total cost - lies in, and where it begins
+        int g = -1, base = 0;
+        for (int g0 = 0; g0 < ng; g0 += kWave) {
+            const Share sh = share_of(g0);
+            const int w = sh.parts * (whole ? (sh.part_weight + most - 1) / most : sh.part_weight);
+            const int inc = wave_inclusive_scan(w, lane);
+            const unsigned long long past = __ballot(base + inc > pos);
+            if (past) {
+                const int l = __ffsll((long long)past) - 1;
+                g = g0 + l;
+                base += __builtin_amdgcn_readlane(inc - w, l);
+                break;
+            }
+            base += __builtin_amdgcn_readlane(inc, kWave - 1);
+        }
+        if (g < 0) break;  // fewer pieces than workgroups
+        const WideGroup grp = groups[__builtin_amdgcn_readfirstlane(g)];
+        const int wgt = weight(grp.n), part_weight = wgt * blocks;
+        const int in_part = whole ? (part_weight + most - 1) / most : part_weight;
+        const int part = __builtin_amdgcn_readfirstlane((pos - base) / in_part);
+        const int at = base + part * in_part;
+        int b0, len;
+        if (whole) {
+            b0 = blocks * (pos - at) / in_part;
+            len = blocks * (pos - at + 1) / in_part - b0;
+        } else {  // block k of a part belongs to the piece that holds the start of its share, k * wgt behind the part's
+            b0 = (pos - at + wgt - 1) / wgt;
+            len = min(blocks, max(end - at + wgt - 1, 0) / wgt) - b0;
+        }
+        b0 = __builtin_amdgcn_readfirstlane(b0);
+        len = __builtin_amdgcn_readfirstlane(len);
+        pos = whole ? end : at + part_weight;  // the next part, or past the end
+        const int tile0 = part * part_tiles(grp.n), tok_first = 16 * tile0;
+        const int n_tok = min(16 * part_tiles(grp.n), grp.n - tok_first);
+        if (len <= 0 || n_tok <= 0) continue;
+        const int tiles = wide_tiles(n_tok);
         const unsigned char* codes = scalar_ptr(grp.e.codes);
         const unsigned char* scale = scalar_ptr(grp.e.scale);
         const unsigned char* zero = scalar_ptr(grp.e.zero);
+        const unsigned char* xsrc = scalar_ptr(frag + (size_t)(grp.tile + tile0) * units * 128);
+        const unsigned char* ssrc = scalar_ptr(gsum + (size_t)(grp.tile + tile0) * units * (16 * kGroups));
         __syncthreads();  // the previous part's arrays are no longer read
         if (tid < kTok) {
-            const int task = order[grp.first + tok_first + (tid < n_tok ? tid : 0)];  // dead token rows repeat the first one
+            const int row = tok_first + (tid < n_tok ? tid : 0);  // dead token rows repeat the first one
+            const int task = order[grp.first + row];
             s_task[tid] = task;
             s_tau[tid] = task_tau ? task_tau[task] : 0.0f;
-            s_back[tid] = back[task / slots];
+            s_back[tid] = back[grp.tile * 16 + row];
         }
-        __syncthreads();
-        // byte offsets of this thread's pieces of a slice (T * d * 2 <= 64 MiB) and of its group sums: (token, unit of the slice)
-        uint32_t xo[kRounds];
-#pragma unroll
-        for (int r = 0; r < kRounds; ++r)
-            xo[r] = ((uint32_t)(s_task[min((tid + r * kUpThreads) / kPieces, kTok - 1)] / slots) * (uint32_t)units * 8u + tid % kPieces) * 16u;
-        const int sum_tok = min(tid / kSliceUnits, kTok - 1), sum_u = tid % kSliceUnits;
-        const uint32_t so = ((uint32_t)(s_task[sum_tok] / slots) * (uint32_t)units + sum_u) * (4u * kGroups);
-        const unsigned char* frag8 = reinterpret_cast<const unsigned char*>(frag);
-        const unsigned char* gsum8 = reinterpret_cast<const unsigned char*>(gsum);
-
         const int np = (len + kUpWaves - 1) / kUpWaves;
         const int per = (len + np - 1) / np;
-        for (int p0 = 0; p0 < len; p0 += per) {
-            const bool active = wave < per && p0 + wave < len;
-            const int ch0 = (b0 + p0 + wave) * kUpChan;
-            // Waves without channels repeat the last active one's requests (they are served by the cache): with their own,
-            // a launch of few blocks read the codes and scales of its neighbours' channels eight times over (one expert,
-            // 24 tokens, d 4096 f 14336: 36 -> 32 us).
-            const int n_active = min(per, len - p0);
-            const int load0 = (b0 + p0 + min(wave, n_active - 1)) * kUpChan;
-            uint4 xq[kRounds];
-            float sq[kGroups];
-            // (requests are unconditional - past the end they repeat the last slice - so that the compiler can count them)
-            auto load_x = [&](int s) {
-                const int ss = min(s, ns - 1);
-#pragma unroll
-                for (int r = 0; r < kRounds; ++r) xq[r] = gload16(frag8 + (xo[r] + (uint32_t)ss * (kPieces * 16)));
-#pragma unroll
-                for (int k = 0; k < kGroups; ++k) sq[k] = gloadf(gsum8 + (so + (uint32_t)(ss * kSums + k) * 4u));
-            };
-            auto store_x = [&](int buf) {
-#pragma unroll
-                for (int r = 0; r < kRounds; ++r) {
-                    const int i = tid + r * kUpThreads, tok = i / kPieces;
-                    if (tok < kTok) xs[buf][tok * kPieces + ((i % kPieces) ^ (tok & 15))] = xq[r];
-                }
-                if (tid < kTok * kSliceUnits) {
-#pragma unroll
-                    for (int k = 0; k < kGroups; ++k) xg[buf][(sum_u * kGroups + k) * kTok + sum_tok] = sq[k];
-                }
-            };
-            uint32_t co[kUpTiles];  // byte offsets of this lane's channels (f <= 65536 rows of at most 4 KiB)
-#pragma unroll
-            for (int t = 0; t < kUpTiles; ++t)
-                co[t] = (uint32_t)min(load0 + 16 * t + c, f - 1) * (uint32_t)(units * BITS * 8) + g4 * (BITS * 8);  // clamped lanes never store
-            // scales (lower half of the threads) and zeros (upper half): a thread brings in those of one channel
-            const int m_ch = tid % kUpWgChan, m_half = tid / kUpWgChan;
-            static_assert(kUpThreads == 2 * kUpWgChan, "a thread per channel for the scales and one for the zeros");
-            const uint32_t mo = (uint32_t)min((b0 + p0) * kUpChan + min(m_ch, n_active * kUpChan - 1), f - 1) * (uint32_t)(units * kGroups * 2);
-            const unsigned char* msrc = m_half ? zero : scale;
-            uint4 mq[2];
-            auto load_meta = [&](int super) {
-                const uint32_t o = mo + (uint32_t)min(super * kSuperScales, units * kGroups - 8) * 2u;
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    mq[h] = gload16(msrc + (o + (super * kSuperScales + 8 * h < units * kGroups ? 16u * h : 0u)));
-            };
-            auto store_meta = [&](int buf) {
-                uint16_t* m16 = reinterpret_cast<uint16_t*>(&meta[buf][m_ch]) + m_half;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const uint32_t w[4] = {mq[h].x, mq[h].y, mq[h].z, mq[h].w};
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) {
-                        m16[(8 * h + 2 * k) * 2 * kUpWgChan] = (uint16_t)w[k];
-                        m16[(8 * h + 2 * k + 1) * 2 * kUpWgChan] = (uint16_t)(w[k] >> 16);
-                    }
-                }
-            };
-            CodeSlice<BITS> cs[kUpTiles];
-            auto load_c = [&](int s) {
-                const uint32_t o = (uint32_t)min(s, ns - 1) * (kSliceUnits * BITS * 8);
-#pragma unroll
-                for (int t = 0; t < kUpTiles; ++t) cs[t].load(codes, co[t] + o);
-            };
-            load_meta(0);
-            load_x(0);
-            __builtin_amdgcn_sched_barrier(0);  // the waits of the loop count the requests in this order
-            load_c(0);
-            __builtin_amdgcn_sched_barrier(0);
-            store_meta(0);
-            store_x(0);
-            load_x(1);
-            __syncthreads();
-            f32x4 acc[kUpTiles][NT];
-#pragma unroll
-            for (int t = 0; t < kUpTiles; ++t)
-#pragma unroll
-                for (int n = 0; n < NT; ++n) acc[t][n] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-            auto slice = [&](int s, int in_super, int mbuf) {
-                const int buf = s & 1;
-                // operand words of the four units: wd[t][u][k]
-                uint32_t wd[kUpTiles][kSliceUnits][CodeSlice<BITS>::kLaneWords];
+        // live: token tiles that this part has, of NT at most
+        auto run = [&](auto live) __attribute__((always_inline)) {
+            constexpr int NL = decltype(live)::value;
+            constexpr int kPieces = kUpSlotUnits * 2 * NL, kSumPieces = (kUpSlotUnits * kGroups * NL * 4 + 63) / 64;
+            constexpr int kReq = (kPieces + kSumPieces + kUpWaves - 1) / kUpWaves;  // a wave's share of a slot
+            constexpr int kRegLoads = CT * kVec + kMetaLoads;
+            // where a lane's four sums are: [unit][group][tile][token quarter] in LDS, [tile][unit][group][16] in memory
+            auto sum_at = [&](int i) {
+                i = min(i, kUpSlotUnits * kGroups * NL * 4 - 1);
+                return (uint32_t)(min(i / 4 % NL, tiles - 1) * units * kGroups + i / (4 * NL)) * 64u + 16u * (uint32_t)(i & 3);
+            };
+            const uint32_t sum_off = sum_at(lane), sum_off2 = sum_at(64 + lane);
+            const int slots = units / kUpSlotUnits;  // a multiple of four (d % 512 == 0)
+            // slot s (past the last one: the last one again)
+            auto load_x = [&](uint4* x, int s) __attribute__((always_inline)) {
+                const int u0 = min(s, slots - 1) * kUpSlotUnits;
 #pragma unroll
-                for (int t = 0; t < kUpTiles; ++t) cs[t].deal(wd[t]);
-                load_c(s + 1);
-                store_x(buf ^ 1);
-                load_x(s + 2);
-                __builtin_amdgcn_sched_barrier(0);
-                if (active) {
-#pragma unroll
-                for (int u = 0; u < kSliceUnits; ++u) {
-                    {
-                        // scale and zero of the unit's group(s).  Widened once per tile and unit, and kept so: left as halves they
-                        // go into mixed-precision FMAs, which issue at half the rate of plain ones.
-                        float sc[kUpTiles][2], zr[kUpTiles][2];
-                        uint32_t r0[kUpTiles][4], r1[kUpTiles][4];
-#pragma unroll
-                        for (int tt = 0; tt < kUpTiles; ++tt) {
-                            const int t = tt;
-                            const uint32_t* mp = &meta[mbuf][(in_super * kSums + u * kGroups) * kUpWgChan + wave * kUpChan + 16 * t + c];
-#pragma unroll
-                            for (int k = 0; k < kGroups; ++k) {
-                                const h16x2 m = as_h2(mp[k * kUpWgChan]);
-                                sc[tt][k] = (float)m.x;
-                                zr[tt][k] = (float)m.y;
-                                asm volatile("" : "+v"(sc[tt][k]), "+v"(zr[tt][k]));
-                            }
-                            weight_frag24<BITS, G32>(wd[t][u], 0, r0[tt]);
-                            weight_frag24<BITS, G32>(wd[t][u], 1, r1[tt]);
-                        }
-#pragma unroll
-                        for (int n = 0; n < NT; ++n) {
-                            if (n > 0 && 16 * n >= n_tok) break;  // token tiles without tokens (the same for the whole workgroup)
-                            const h16x8 x0 = __builtin_bit_cast(h16x8, xs[buf][(16 * n + c) * kPieces + ((8 * u + g4) ^ c)]);
-                            const h16x8 x1 = __builtin_bit_cast(h16x8, xs[buf][(16 * n + c) * kPieces + ((8 * u + 4 + g4) ^ c)]);
-                            const f32x4 sg0 = *reinterpret_cast<const f32x4*>(&xg[buf][(u * kGroups) * kTok + 16 * n + 4 * g4]);
-                            const f32x4 sg1 = *reinterpret_cast<const f32x4*>(&xg[buf][(u * kGroups + kGroups - 1) * kTok + 16 * n + 4 * g4]);
-                            const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                            for (int tt = 0; tt < kUpTiles; ++tt) {
-                                f32x4& ac = acc[tt][n];
-                                if constexpr (G32) {
-                                    const f32x4 c0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(x0, as_h8(r0[tt]), zero4, 0, 0, 0);
-                                    const f32x4 c1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(x1, as_h8(r1[tt]), zero4, 0, 0, 0);
-#pragma unroll
-                                    for (int i = 0; i < 4; ++i) {
-                                        const float t0 = fmaf(-zr[tt][0], sg0[i], c0[i]);
-                                        const float t1 = fmaf(-zr[tt][kGroups - 1], sg1[i], c1[i]);
-                                        ac[i] = fmaf(sc[tt][kGroups - 1], t1, fmaf(sc[tt][0], t0, ac[i]));
-                                    }
-                                } else {
-                                    f32x4 cc = __builtin_amdgcn_mfma_f32_16x16x32_f16(x0, as_h8(r0[tt]), zero4, 0, 0, 0);
-                                    cc = __builtin_amdgcn_mfma_f32_16x16x32_f16(x1, as_h8(r1[tt]), cc, 0, 0, 0);
-#pragma unroll
-                                    for (int i = 0; i < 4; ++i) ac[i] = fmaf(sc[tt][0], fmaf(-zr[tt][0], sg0[i], cc[i]), ac[i]);
-                                }
-                                asm volatile("" : "+v"(ac));  // here, not later: the products of a whole slice would wait in registers
-                            }
-                        }
+                for (int k = 0; k < kReq; ++k) {
+                    const int it = min(wave + kUpWaves * k, kPieces + kSumPieces - 1);
+                    // piece it: 1 KB of (unit, tile, instruction of the unit), or behind them four sums per lane
+                    const int u = it / (2 * NL), n = it / 2 % NL, j = it & 1;
+                    const uint32_t xo = (uint32_t)((min(n, tiles - 1) * units + u0 + u) * 2 + j) * 1024u;
+                    if constexpr (kSumPieces == 1) {
+                        const bool sums = it == kPieces;
+                        dma16((sums ? ssrc + (uint32_t)u0 * (64u * kGroups) : xsrc + xo) + (sums ? sum_off : 16u * lane), x + (sums ? kXVecs : it * 64));
+                    } else {
+                        const bool sums = it >= kPieces;
+                        dma16((sums ? ssrc + (uint32_t)u0 * (64u * kGroups) : xsrc + xo) + (sums ? (it == kPieces ? sum_off : sum_off2) : 16u * lane),
+                              x + (sums ? kXVecs + (it - kPieces) * 64 : it * 64));
                     }
                 }
-                }
-                __syncthreads();
             };
-            for (int s0 = 0, mbuf = 0; s0 < ns; s0 += kSuper, mbuf ^= 1) {
-                load_meta(s0 / kSuper + 1);
-                const int n_in = min(kSuper, ns - s0);
+            for (int p0 = 0; p0 < len; p0 += per) {
+                const bool active = wave < per && p0 + wave < len;
+                const int ch0 = (b0 + p0 + wave) * kCh;
+                __syncthreads();  // the slots are no longer read
+                if (!active) {  // the same barriers as the waves below
+                    load_x(x0, 0);
+                    load_x(x1, 1);
+                    load_x(x2, 2);
+                    auto step = [&](uint4* next, int s) __attribute__((always_inline)) {
+                        wait_requests_all_but<2 * kReq>();
+                        meet();
+                        load_x(next, s + 3);
+                    };
 #pragma unroll 1
-                for (int k = 0; k < n_in; ++k) slice(s0 + k, k, mbuf);
-                store_meta(mbuf ^ 1);
-                __syncthreads();
-            }
-            if (!active) continue;
-            // lane (c, g4) holds channel ch0 + 16 t + c for tokens 16 n + 4 g4 + i
-            int tok0 = 4 * g4;
-            asm volatile("" : "+v"(tok0));  // or the addresses below are formed ahead of the loop and held across it
-#pragma unroll
-            for (int n = 0; n < NT; ++n)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int tok = 16 * n + tok0 + i;
-                    const bool live = tok < n_tok;
-                    const int task = s_task[tok];
-                    const float bk = s_back[tok], tau = s_tau[tok];
-                    float* vt = v + (size_t)task * f;
-                    uint32_t w = 0u;
-#pragma unroll
-                    for (int t = 0; t < kUpTiles; ++t) {
-                        const int ch = ch0 + 16 * t + c;
-                        const float val = acc[t][n][i] * bk;
-                        if (live && ch < f) vt[ch] = val;
-                        const uint64_t m = __ballot(live && ch < f && fabsf(val) > tau);
-                        w |= ((uint32_t)(m >> (16 * g4)) & 0xFFFFu) << (16 * t);
+                    for (int s = 0; s < slots; s += 4) {
+                        step(x3, s);
+                        step(x0, s + 1);
+                        step(x1, s + 2);
+                        step(x2, s + 3);
                     }
-                    if (mask_words && live && c == 0) mask_words[(size_t)task * nwords + ch0 / 32] = w;
+                    continue;
                 }
-        }
+                // codes: quarter g of a channel's four lanes brings in units 2 g and 2 g + 1 of eight, and one vector of its scales and
+                // zeros (clamped lanes never store)
+                uint4 cq[CT][kVec], mq[kMetaLoads];
+                auto row_of = [&](int t) { return (uint32_t)min(ch0 + 16 * t + c, f - 1) * (uint32_t)units; };
+                auto load_codes = [&](int s) __attribute__((always_inline)) {  // of the eight units from slot s on
+                    const uint32_t u0 = (uint32_t)min(s, slots - 4) * kUpSlotUnits;
+#pragma unroll
+                    for (int k = 0; k < kMetaLoads; ++k) {
+                        // vector 4 k + g of [tile][scales, zeros][kGroups]
+                        const int vec = min(4 * k + g4, CT * 2 * kGroups - 1), part_ = vec % kGroups;
+                        mq[k] = gload16((vec / kGroups & 1 ? zero : scale) + ((row_of(vec / (2 * kGroups)) + u0) * (2u * kGroups) + 16 * part_));
+                    }
+#pragma unroll
+                    for (int t = 0; t < CT; ++t)
+#pragma unroll
+                        for (int k = 0; k < kVec; ++k) cq[t][k] = gload16(codes + ((row_of(t) + u0 + 2 * g4) * (uint32_t)(BITS * 8) + 16 * k));
+                };
+                load_x(x0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                load_codes(0);
+                __builtin_amdgcn_sched_barrier(0);
+                load_x(x1, 1);
+                load_x(x2, 2);
+                f32x4 acc[CT][NL];
+#pragma unroll
+                for (int t = 0; t < CT; ++t)
+#pragma unroll
+                    for (int n = 0; n < NL; ++n) acc[t][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                for (int s = 0; s < slots; s += 4) {
+                    uint32_t wd[CT][2][4][kLaneWords];
+#pragma unroll
+                    for (int t = 0; t < CT; ++t)
+#pragma unroll
+                        for (int p = 0; p < 2; ++p) deal_units<BITS>(cq[t], p, wd[t][p]);
+                    uint4 mc[kMetaLoads];
+#pragma unroll
+                    for (int k = 0; k < kMetaLoads; ++k) {
+                        mc[k] = mq[k];
+                        asm volatile("" : "+v"(mc[k].x), "+v"(mc[k].y), "+v"(mc[k].z), "+v"(mc[k].w));  // a copy: mq is loaded again below
+                    }
+                    auto step = [&](auto slot, const uint4* x, uint4* next) __attribute__((always_inline)) {
+                        constexpr int k = decltype(slot)::value;
+                        // slot k is here: younger are the requests of two slots and, for the outer slots, those of the codes
+                        wait_requests_all_but<2 * kReq + (k == 0 || k == 3 ? kRegLoads : 0)>();
+                        meet();
+                        if constexpr (k == 2) load_codes(s + 4);  // (not sooner: half of the operand words make room for them)
+                        __builtin_amdgcn_sched_barrier(0);
+                        load_x(next, s + k + 3);
+                        __builtin_amdgcn_sched_barrier(0);
+                        // scales and zeros of the slot's units, to all quarters: word k (groups of 64), or words 2 (k & 1) + u of vector k / 2
+                        uint32_t sz[kMetaLoads * 4][kGroups];
+#pragma unroll
+                        for (int m = 0; m < kMetaLoads; ++m) {
+                            const uint32_t w[4] = {mc[m].x, mc[m].y, mc[m].z, mc[m].w};
+#pragma unroll
+                            for (int h = 0; h < kGroups; ++h) {
+                                const uint32_t word = kGroups == 1 ? w[k] : w[2 * (k & 1) + h];
+                                quarters_to_all(word, sz[4 * m][h], sz[4 * m + 1][h], sz[4 * m + 2][h], sz[4 * m + 3][h]);
+                            }
+                        }
+                        // Step i of the slot is token tile i % NL of unit i / NL.  Three of them are under way: the operands of a
+                        // later one come from LDS, the products of one are formed, the scales of the one before are applied, product by
+                        // product (a product takes the matrix unit as long as four of the multiply-adds take the vector unit).
+                        constexpr int kItems = kUpSlotUnits * NL, kAhead = 2;
+                        const f32x4* sums = reinterpret_cast<const f32x4*>(x + kXVecs);
+                        uint4 xf[kAhead + 1][2];
+                        f32x4 sg[kAhead + 1][kGroups];
+                        auto fetch = [&](int i) __attribute__((always_inline)) {
+                            const int u = i / NL, n = i % NL;
+#pragma unroll
+                            for (int j = 0; j < 2; ++j) xf[i % (kAhead + 1)][j] = x[(i * 2 + j) * 64 + lane];
+#pragma unroll
+                            for (int h = 0; h < kGroups; ++h) sg[i % (kAhead + 1)][h] = sums[((u * kGroups + h) * NL + n) * 4 + g4];
+                        };
+                        float sc[2][CT][kGroups], zr[2][CT][kGroups];  // of the unit of the products, and of the one before
+                        uint32_t r0[CT][4], r1[CT][4];
+                        auto unpack = [&](int u) __attribute__((always_inline)) {
+#pragma unroll
+                            for (int t = 0; t < CT; ++t) {
+#pragma unroll
+                                for (int h = 0; h < kGroups; ++h) {
+                                    // groups of 64: vectors [tile][scale, zero], half u of the word; groups of 32: vectors
+                                    // [tile][scale, zero][k / 2], word u, half h
+                                    const int vs = kGroups == 1 ? 2 * t : 4 * t + k / 2, vz = vs + kGroups;
+                                    const h16x2 s2 = as_h2(sz[vs][kGroups == 1 ? 0 : u]), z2 = as_h2(sz[vz][kGroups == 1 ? 0 : u]);
+                                    const bool hi = kGroups == 1 ? u : h;
+                                    sc[u][t][h] = (float)(hi ? s2.y : s2.x);
+                                    zr[u][t][h] = (float)(hi ? z2.y : z2.x);
+                                    asm volatile("" : "+v"(sc[u][t][h]), "+v"(zr[u][t][h]));  // widened once; as halves they make mixed FMAs, at half the rate
+                                }
+                                weight_frag24<BITS, G32>(wd[t][u][k], 0, r0[t]);
+                                weight_frag24<BITS, G32>(wd[t][u][k], 1, r1[t]);
+                            }
+                        };
+                        f32x4 cc[2][CT][kGroups];  // products of this item and of the one before
+                        // quarter q of the multiply-adds of item i
+                        auto apply = [&](int i, int q) __attribute__((always_inline)) {
+                            const int u = i / NL, n = i % NL, t = q >> 1;
+                            f32x4& ac = acc[t][n];
+#pragma unroll
+                            for (int e = 2 * (q & 1); e < 2 * (q & 1) + 2; ++e) {
+                                float v0 = ac[e];
+#pragma unroll
+                                for (int h = 0; h < kGroups; ++h)
+                                    v0 = fmaf(sc[u][t][h], fmaf(-zr[u][t][h], sg[i % (kAhead + 1)][h][e], cc[i & 1][t][h][e]), v0);
+                                asm volatile("" : "+v"(v0));  // here, not later: the products of a whole slot would wait in registers
+                                ac[e] = v0;
+                            }
+                        };
+                        auto product = [&](int i, int q) __attribute__((always_inline)) {  // q: first then second instruction of both tiles
+                            const int t = q & 1, j = q >> 1;
+                            const f32x4 zero4 = {0.f, 0.f, 0.f, 0.f};
+                            const h16x8 xa = __builtin_bit_cast(h16x8, xf[i % (kAhead + 1)][j]);
+                            const h16x8 w = j ? as_h8(r1[t]) : as_h8(r0[t]);
+                            f32x4& c0 = cc[i & 1][t][G32 ? j : 0];
+                            c0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(xa, w, G32 || j == 0 ? zero4 : c0, 0, 0, 0);
+                        };
+#pragma unroll
+                        for (int i = 0; i < kAhead; ++i) fetch(i);
+                        unpack(0);
+#pragma unroll
+                        for (int i = 0; i < kItems + 1; ++i) {
+                            if (i == NL) {
+                                unpack(1);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                if (i < kItems) product(i, q);
+                                if (i > 0) apply(i - 1, q);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                            if (i + kAhead < kItems) fetch(i + kAhead);
+                        }
+                    };
+                    step(std::integral_constant<int, 0>{}, x0, x3);
+                    step(std::integral_constant<int, 1>{}, x1, x0);
+                    step(std::integral_constant<int, 2>{}, x2, x1);
+                    step(std::integral_constant<int, 3>{}, x3, x2);
+                }
+                // lane (c, g4) holds channel ch0 + 16 t + c for tokens 16 n + 4 g4 + i
+                int tok0 = 4 * g4;
+                asm volatile("" : "+v"(tok0));  // or the addresses below are formed ahead of the loop and held across it
+#pragma unroll
+                for (int n = 0; n < NL; ++n) {
+                    const int4 task4 = *reinterpret_cast<const int4*>(&s_task[16 * n + tok0]);
+                    const float4 tau4 = *reinterpret_cast<const float4*>(&s_tau[16 * n + tok0]);
+                    const float4 back4 = *reinterpret_cast<const float4*>(&s_back[16 * n + tok0]);
+                    const int task[4] = {task4.x, task4.y, task4.z, task4.w};
+                    const float tau[4] = {tau4.x, tau4.y, tau4.z, tau4.w}, bk[4] = {back4.x, back4.y, back4.z, back4.w};
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const bool used = 16 * n + tok0 + i < n_tok;
+                        float* vt = v + (size_t)task[i] * f;
+#pragma unroll
+                        for (int t2 = 0; t2 < CT / 2; ++t2) {
+                            uint32_t w = 0u;
+#pragma unroll
+                            for (int h = 0; h < 2; ++h) {
+                                const int t = 2 * t2 + h, ch = ch0 + 16 * t + c;
+                                const float val = acc[t][n][i] * bk[i];
+                                if (used && ch < f) vt[ch] = val;
+                                const uint64_t m = __ballot(used && ch < f && fabsf(val) > tau[i]);
+                                w |= ((uint32_t)(m >> (16 * g4)) & 0xFFFFu) << (16 * h);
+                            }
+                            const int word = ch0 / 32 + t2;
+                            if (mask_words && used && c == 0 && word < nwords) mask_words[(size_t)task[i] * nwords + word] = w;
+                        }
+                    }
+                }
+            }
+        };
+        with_live_tiles<NT>(tiles, run);
     }
-}
-
-size_t up_wide_scratch_bytes(int T, int d, int group) {
-    return (size_t)T * d * 2 + (size_t)T * (d / 64) * (group == 32 ? 2 : 1) * 4 + (size_t)T * 4;
 }
 
 template <int BITS, bool G32, int NT>
-static void launch_nt(const UpWideArgs& a, uint4* frag, float* gsum, float* back, hipStream_t stream) {
-    up_wide_kernel<BITS, G32, NT><<<dim3(a.workgroups), dim3(kUpThreads), 0, stream>>>(
-        a.groups, a.n_groups, a.order, frag, gsum, back, a.slots, a.v, a.task_tau, a.mask_words, a.d, a.f, a.parts);
+static hipError_t launch_nt(const UpWideArgs& a, hipStream_t stream) {
+    const long long blocks = (long long)a.est_groups * ((a.f + 31) / 32);
+    int wgs = (int)(blocks < num_cus() ? blocks : num_cus());
+    if (wgs > 8) wgs &= ~7;  // (see wide_piece)
+    XOperand x;
+    const hipError_t rc = launch_x_operand(a, BITS, G32 ? 32 : 64, x, stream);
+    if (rc != hipSuccess) return rc;
+    up_wide_kernel<BITS, G32, NT><<<dim3(wgs), dim3(kUpThreads), 0, stream>>>(a.groups, a.n_groups, a.max_groups, a.order, x.frag, x.gsum,
+                                                                               x.back, a.v, a.task_tau, a.mask_words, a.d, a.f);
+    return hipGetLastError();
 }
 template <int BITS, bool G32>
 static hipError_t launch_bits(const UpWideArgs& a, hipStream_t stream) {
-    uint4* frag = static_cast<uint4*>(a.scratch);
-    float* gsum = reinterpret_cast<float*>(frag + (size_t)a.T * a.d / 8);
-    float* back = gsum + (size_t)a.T * (a.d / 64) * (G32 ? 2 : 1);
-    x_frag_kernel<BITS, G32><<<dim3(a.T), dim3(128), 0, stream>>>(a.x, a.d, frag, gsum, back);
     switch (a.nt) {
-        case 1: launch_nt<BITS, G32, 1>(a, frag, gsum, back, stream); break;
-        case 2: launch_nt<BITS, G32, 2>(a, frag, gsum, back, stream); break;
-        case 3: launch_nt<BITS, G32, 3>(a, frag, gsum, back, stream); break;
-        case 4:
-            if constexpr (BITS == 2) {
-                launch_nt<BITS, G32, 4>(a, frag, gsum, back, stream);
-                break;
-            }
-            return hipErrorInvalidValue;
+        case 1:
+        case 2: return launch_nt<BITS, G32, 2>(a, stream);
+        case 3: return launch_nt<BITS, G32, 3>(a, stream);
+        case 4: return launch_nt<BITS, G32, 4>(a, stream);
+        case 5: return launch_nt<BITS, G32, 5>(a, stream);
+        case 10:  // nine tiles fit the ring, and the registers of INT2
+            if constexpr (BITS == 2) return launch_nt<BITS, G32, 9>(a, stream);
+            else return launch_nt<BITS, G32, 5>(a, stream);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_up_wide(UpWideArgs a, int bits, int group, hipStream_t stream) {
     if (!up_wide_shape(a.d, a.f, bits, group)) return hipErrorInvalidValue;
-    if (a.single) {
-        const hipError_t rc = launch_wide_single(*a.single, a.n_tasks, a.chunk, const_cast<WideGroup*>(a.groups),
-                                                 const_cast<int32_t*>(a.n_groups), const_cast<int32_t*>(a.order), stream);
-        if (rc != hipSuccess) return rc;
-    }
-    // token tiles that the registers take beside the codes: four for INT2, three for the wider codes
-    const int max_tiles = bits == 2 ? 4 : 3;
-    a.parts = (a.nt + max_tiles - 1) / max_tiles;
-    a.nt = (a.nt + a.parts - 1) / a.parts;
-    const long long blocks = (long long)a.est_groups * a.parts * ((a.f + kUpChan - 1) / kUpChan);
-    a.workgroups = (int)(blocks < num_cus() ? blocks : num_cus());
-    if (a.workgroups > 8) a.workgroups &= ~7;  // (see wide_piece)
     const bool g32 = group == 32;
     if (bits == 2) return launch_bits<2, false>(a, stream);
     if (bits == 3) return g32 ? launch_bits<3, true>(a, stream) : launch_bits<3, false>(a, stream);

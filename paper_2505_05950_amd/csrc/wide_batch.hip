@@ -48,7 +48,6 @@ constexpr int kDownCols = 512;   // output columns per workgroup of the down ker
 __device__ __forceinline__ int wide_pairs(const int32_t* ucount, int g) { return (ucount[g] + kPairRows - 1) / kPairRows; }
 
 // h of a group lies in [pair][token tile][half of the pair's rows][lane], the group's own tiles only, from this entry on.
-__device__ __forceinline__ int wide_tiles(int n) { return (n + 15) >> 4; }
 __device__ __forceinline__ size_t wide_h_first(const WideGroup& g, int pmax) { return (size_t)g.tile * pmax * 128; }
 
 __device__ __forceinline__ int wide_total(const WideArgs& a, int ng, int lane) {
@@ -176,43 +175,12 @@ __global__ __launch_bounds__(1024) void wide_rows_kernel(WideArgs a, const uint3
     }
 }
 
-// The kernels below exist for NT token tiles per group at most; their loops are unrolled for the tiles that a group fills: NT, or
-// one less, or two less of ten (the sizes that the plan of a launch meets; smaller groups run the smallest).
-template <int NT, class F>
-__device__ __forceinline__ void with_live_tiles(int tiles, F&& f) {
-    if constexpr (NT >= 10) {
-        if (tiles <= NT - 2) return f(std::integral_constant<int, NT - 2>{});
-    }
-    if constexpr (NT >= 2) {
-        if (tiles <= NT - 1) return f(std::integral_constant<int, NT - 1>{});
-    }
-    f(std::integral_constant<int, NT>{});
-}
-
 // ---------------------------------------------------------------------------------------------------------------
 // gate
 // ---------------------------------------------------------------------------------------------------------------
 // Rows and activations travel from memory straight into LDS (global_load_lds_dwordx4), in ring slots that are arrays of their own, so
 // that the compiler can tell which requests a read has to wait for.  The waits that matter are placed by hand, in front of the barrier
 // that makes a slot everybody's.
-#define FLOE_LDS __attribute__((address_space(3)))
-__device__ __forceinline__ void dma16(const void* src, uint4* lds_wave_base) {  // lane l's 16 bytes land at base + 16 l
-    __builtin_amdgcn_global_load_lds((const FLOE_GLOBAL void*)src, (FLOE_LDS void*)lds_wave_base, 16, 0, 0);
-}
-template <int N>
-__device__ __forceinline__ void wait_requests_all_but() {  // s_waitcnt vmcnt(N)
-    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-    asm volatile("" ::: "memory");
-}
-__device__ __forceinline__ void meet() {  // barrier alone: what is in flight stays in flight
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-}
-
 template <int NT>
 __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int d) {
     constexpr int kTok = 16 * NT;

@@ -49,6 +49,19 @@ def test_up_projection_split_over_columns(d, f, bits, group, n, n_shared, top_k,
     _run_layer_case(170 + T, 7, d, f, bits, group, n, n_shared, top_k, False, T, pct, gap=f * (100 - pct) >= 6400)
 
 
+@pytest.mark.parametrize("d,f,bits,group,n,n_shared,top_k,T,pct", [
+    (512, 33, 2, 64, 0, 1, 0, 160, 50),      # ten token tiles: two parts of five; one channel in the second block
+    (1024, 290, 2, 64, 0, 1, 0, 112, 60),    # seven tiles in the body of seven; fewer blocks than waves in a pass
+    (8192, 64, 2, 64, 0, 1, 0, 40, 60),      # more units than lanes of a wave
+    (1536, 700, 3, 32, 0, 1, 0, 150, 60),    # ten tiles in two parts of five
+    (1024, 400, 4, 64, 3, 1, 2, 200, 70),    # groups of different sizes, a shared expert
+    (4608, 96, 4, 32, 0, 1, 0, 20, 50),      # a width that the columns are not split for
+    (512, 64, 2, 64, 40, 4, 6, 300, 60),     # more parts than a wave scans
+])
+def test_up_projection_of_many_tokens(d, f, bits, group, n, n_shared, top_k, T, pct):
+    _run_layer_case(370 + T, 11, d, f, bits, group, n, n_shared, top_k, False, T, pct, gap=f * (100 - pct) >= 6400)
+
+
 @pytest.mark.parametrize("d,f,n,n_shared,top_k,T,pct", [
     (512, 300, 0, 1, 0, 140, 60),    # nine of ten token tiles; eight column slices on three ring slots: two behind the loop
     (1024, 291, 0, 1, 0, 160, 99),   # ten; one behind the loop; rows so far apart that v is gathered
