@@ -110,10 +110,16 @@ size_t wide_partial_bytes(const WidePlan& p, int d) {
     const size_t y = p.partial_rows * d * sizeof(float), x = (size_t)p.h_tiles * 16 * d * 2;
     return y > x ? y : x;
 }
-ExpertWs expert_ws(const floe_shape* s, int T, Wide form = Wide::kChosen) {
+// Between the powers of two the fused kernel is what a call prefers, not what it needs: with less workspace (fuse =
+// false), or kernels that share rows chosen by hand, it runs the separate ones.
+bool fuse_optional(const floe_shape& s) { return !packed_fast_shape(s.d, s.bits, s.group); }
+bool fuse_shape(const floe_shape& s, bool fuse) {
+    return fused_shape(s.d, s.bits, s.group) && (!fuse_optional(s) || (fuse && union_mode() != 1 && union_mode() != 2));
+}
+ExpertWs expert_ws(const floe_shape* s, int T, Wide form = Wide::kChosen, bool fuse = true) {
     ExpertWs w{};
     w.nblk = gd_blocks(T, s->f);
-    w.fused_passes = packed_fast_shape(s->d, s->bits, s->group) ? fused_passes(s->d, s->f, s->bits, T) : 0;
+    w.fused_passes = fuse_shape(*s, fuse) ? fused_passes(s->d, s->f, s->bits, T) : 0;
     w.nblk_fused = w.fused_passes ? fused_blocks(s->d, s->f, w.fused_passes) : 0;
     const int nblk_alloc = w.nblk > w.nblk_fused ? w.nblk : w.nblk_fused;
     size_t o = 0;
@@ -148,10 +154,14 @@ size_t one_token_rows(int n_tasks, int f) {  // partial results of the one-token
     }
     return rows;
 }
-size_t expert_bytes(const floe_shape* s, int T) {
-    const ExpertWs w = expert_ws(s, T, Wide::kRoom);
+size_t expert_bytes(const floe_shape* s, int T, bool fuse = true) {
+    const ExpertWs w = expert_ws(s, T, Wide::kRoom, fuse);
+    if (w.fused_passes && fuse_optional(*s)) {  // (floe_gate_down_sparse runs the separate kernels' plan)
+        const size_t separate = expert_bytes(s, T, false);
+        return w.total > separate ? w.total : separate;
+    }
     if (!w.wide) return w.total;
-    const ExpertWs n = expert_ws(s, T, Wide::kNone);
+    const ExpertWs n = expert_ws(s, T, Wide::kNone, fuse);
     const size_t one_token = n.partial_off + one_token_rows(T, s->f) * s->d * sizeof(float);
     return w.total > one_token ? w.total : one_token;
 }
@@ -174,13 +184,13 @@ struct LayerWs {
     WidePlan wp;
 };
 // max_down: at most so many pieces in the down kernel of the wide path (0: its own choice)
-LayerWs layer_plan(const floe_layer* L, int T, Wide form = Wide::kChosen, int max_down = 0) {
+LayerWs layer_plan(const floe_layer* L, int T, Wide form = Wide::kChosen, int max_down = 0, bool fuse = true) {
     LayerWs w{};
     const int slots = L->top_k + L->n_shared;
     w.n_tasks = T * slots;
     w.nblk = gd_blocks(w.n_tasks, L->s.f);
     const int n_all = L->n_experts + L->n_shared;
-    w.fused_passes = packed_fast_shape(L->s.d, L->s.bits, L->s.group)
+    w.fused_passes = fuse_shape(L->s, fuse && !L->gd_on_host)
                          ? fused_passes(L->s.d, L->s.f, L->s.bits, w.n_tasks, fused_task_limit(n_all)) : 0;
     w.nblk_fused = w.fused_passes ? fused_blocks(L->s.d, L->s.f, w.fused_passes) : 0;
     w.chunk = mfma_chunk(n_all, w.n_tasks);
@@ -242,10 +252,14 @@ LayerWs layer_plan(const floe_layer* L, int T, Wide form = Wide::kChosen, int ma
     return w;
 }
 // What a caller is asked to bring (see expert_bytes)
-size_t layer_bytes(const floe_layer* L, int T) {
-    const LayerWs w = layer_plan(L, T, Wide::kRoom);
+size_t layer_bytes(const floe_layer* L, int T, bool fuse = true) {
+    const LayerWs w = layer_plan(L, T, Wide::kRoom, 0, fuse);
+    if (w.fused_passes && fuse_optional(L->s)) {
+        const size_t separate = layer_bytes(L, T, false);
+        return w.total > separate ? w.total : separate;
+    }
     if (!w.use_wide) return w.total;
-    const LayerWs n = layer_plan(L, T, Wide::kNone);
+    const LayerWs n = layer_plan(L, T, Wide::kNone, 0, fuse);
     const size_t one_token = n.partial_off + one_token_rows(w.n_tasks, L->s.f) * L->s.d * 4;
     const size_t most = one_token > n.total ? one_token : n.total;
     return w.total > most ? w.total : most;
@@ -254,16 +268,17 @@ size_t layer_bytes(const floe_layer* L, int T) {
 // wide kernels need more workspace per task; a batch that fits less (the static scratch array, say) with the one-token kernels
 // keeps fitting: there the wide ones are taken only if they fit as well, with fewer pieces in the down kernel (each costs partial
 // results, and nothing else in the plan depends on their number) as long as these occupy a third of the chip.
-LayerWs layer_fit(const floe_layer* L, int T, size_t limit) {
-    LayerWs w = layer_plan(L, T);
+LayerWs layer_fit(const floe_layer* L, int T, size_t limit, bool fuse = true) {
+    LayerWs w = layer_plan(L, T, Wide::kChosen, 0, fuse);
+    if (w.fused_passes && w.total > limit && fuse_optional(L->s)) return layer_fit(L, T, limit, false);
     if (!w.use_wide || w.total <= limit || union_mode() == 1) return w;
-    const LayerWs n = layer_plan(L, T, Wide::kNone);
+    const LayerWs n = layer_plan(L, T, Wide::kNone, 0, fuse);
     if (n.total > limit) return w;
     const size_t row = (size_t)L->s.d * 4, rest = w.partial_off + (size_t)w.n_tasks * row;
     const size_t rows = rest < limit ? (limit - rest) / row : 0;  // for the pieces after the first
     const int pieces = (int)(rows / w.wp.chunk + 1) & ~7;
     if (rest > limit || pieces < 8 || 3 * pieces * (L->s.d / 512) < num_cus()) return n;
-    const LayerWs fewer = layer_plan(L, T, Wide::kChosen, pieces);
+    const LayerWs fewer = layer_plan(L, T, Wide::kChosen, pieces, fuse);
     return fewer.total <= limit ? fewer : n;  // (the activations in operand order may need more than so few partial results)
 }
 
@@ -440,7 +455,7 @@ int floe_gate_down_sparse(const floe_expert* e, const floe_half* x, int T, const
     if (!aligned(e->gd, 16) || !aligned(x, 16) || !aligned(y_acc, 16) || !aligned(workspace, kAlign)) return FLOE_EINVAL;
     if (e->gd_is_staged && (T > 1 || e->gd_rows < 0)) return FLOE_EINVAL;
     if (!e->gd_is_staged && e->gd_rows != e->s.f) return FLOE_EINVAL;
-    const ExpertWs w = expert_ws(&e->s, T, Wide::kNone);  // (the lists exist: nothing of the wide path runs here)
+    const ExpertWs w = expert_ws(&e->s, T, Wide::kNone, false);  // (the lists exist: nothing of the wide path runs here)
     if (workspace_bytes < w.total) return FLOE_EWORKSPACE;
     float* partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.partial_off);
     hipStream_t st = (hipStream_t)stream;
@@ -466,7 +481,8 @@ int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, cons
         return FLOE_EINVAL;
     if (e->gd_is_staged || e->gd_rows != e->s.f) return FLOE_EINVAL;
     ExpertWs w = expert_ws(&e->s, T);
-    if (w.wide && workspace_bytes < w.total && union_mode() != 1) w = expert_ws(&e->s, T, Wide::kNone);
+    if (w.fused_passes && workspace_bytes < w.total && fuse_optional(e->s)) w = expert_ws(&e->s, T, Wide::kChosen, false);
+    if (w.wide && workspace_bytes < w.total && union_mode() != 1) w = expert_ws(&e->s, T, Wide::kNone, false);
     if (workspace_bytes < w.total) return FLOE_EWORKSPACE;
     float* v = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.v_off);
     float* partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.partial_off);

@@ -22,6 +22,11 @@
 // always holds the same channels in the same order, hence the sums are formed in a fixed order and the result
 // is reproducible bit for bit.  After the barrier the four accumulators meet in LDS and the workgroup stores
 // one partial y; S6 (combine_kernel) adds the partials.
+//
+// Widths between the powers of two (24, 40 or 48 units a channel): a channel still has 32 or 64 lanes, so that the sums stay DPP
+// steps within one wave; the lanes without a unit repeat its last one (same cache line, no further bytes) with activations of
+// zero.  The GEMV loses their share of its arithmetic, which the stream hides: INT4 g128 d 2560 f 6911, three tokens top-2 of six,
+// 38.3 us with separate kernels, 30.4 so (the traffic alone is 21 at the rate of a copy).
 #pragma once
 
 #include <type_traits>
@@ -102,7 +107,8 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
                                                                   float* __restrict__ partial,
                                                                   int32_t* __restrict__ wg_count) {
     constexpr int d = 64 * UPC;
-    constexpr int CPW = kWave / UPC;      // channels per wave pass
+    constexpr int LPC = fused_lanes(d);   // lanes per channel: those beyond UPC repeat its last unit with activations of zero
+    constexpr int CPW = kWave / LPC;      // channels per wave pass
     constexpr int NV = d / 512;           // uint4 per lane of a gate column / down row
     constexpr int kQ = kPasses * CPW;     // queue capacity
     // the small size runs exactly kPasses passes, the large one what the launch says
@@ -146,7 +152,7 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
     FLOE_TL(0);
 
     const bool producer = wave < kFusedProducers;
-    const int u = lane % UPC, sub = CPW == 1 ? 0 : lane / UPC;
+    const int u = UPC == LPC ? lane % LPC : min(lane % LPC, UPC - 1), sub = CPW == 1 ? 0 : lane / LPC;
     DevExpert e{};
     float tau = 0.0f;
     Pick16 pick{};
@@ -169,7 +175,7 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
             if (producer && lane < ro.n_experts) lg = ro.logits[(size_t)t * ro.n_experts + lane];
             __syncthreads();  // xlds, queues, flags and the table are set up
         } else {
-            constexpr int kParts = 2, NVR = d / 512 / kParts;
+            constexpr int kParts = NV % 2 == 0 ? 2 : 1, NVR = NV / kParts;  // pieces of a router row
             constexpr int NW = kFusedThreads / 64;
             constexpr int kItems = (16 * kParts + NW - 1) / NW;  // items a wave may have to take (<= 16 experts)
             const int n_items = ro.n_experts * kParts;
@@ -202,7 +208,7 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
             FLOE_TL(1);
             __syncthreads();
             const int l16 = lane & 15;
-            if (producer && l16 < ro.n_experts) lg = plog[2 * l16] + plog[2 * l16 + 1];
+            if (producer && l16 < ro.n_experts) lg = kParts == 2 ? plog[2 * l16] + plog[2 * l16 + 1] : plog[l16];
         }
         ex = ro.n_experts + (slot - ro.top_k);  // a shared expert
         if (producer) {
@@ -296,6 +302,16 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
         const int down = xprep_down<BITS>(amax);
         const float inv_p = ldexpf(1.0f, down);
         unit_prepare<BITS>(raw, down, xs, Xoff, Xg);
+        if constexpr (UPC != LPC) {
+            const bool has = lane % LPC < UPC;
+#pragma unroll
+            for (int r = 0; r < 32; ++r) xs[r] = has ? xs[r] : 0u;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                Xg[h] = has ? Xg[h] : 0.0f;
+                Xoff[h] = has ? Xoff[h] : 0.0f;
+            }
+        }
         uint32_t magic = 0x3C003C00u;
         asm volatile("" : "+v"(magic));  // keep it in a VGPR: v_and_or_b32 takes one scalar operand only
         FLOE_TL(4);
@@ -338,8 +354,9 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
                 } else {
                     if (p + kDepth < n_pass) issue(i, p + kDepth);
                 }
-                part = group_reduce_sum_to_last<UPC>(part) * inv_p;
-                const bool mine = u == UPC - 1 && p < n_pass && j < f;
+                if constexpr (UPC != LPC) part = lane % LPC < UPC ? part : 0.0f;  // (0 times a scale that is not finite is no zero)
+                part = group_reduce_sum_to_last<LPC>(part) * inv_p;
+                const bool mine = lane % LPC == LPC - 1 && p < n_pass && j < f;
                 if (v_out && mine) v_out[(size_t)task * f + j] = part;
                 const bool hit = mine && fabsf(part) > tau;
                 unsigned long long hits = __ballot(hit);
@@ -519,6 +536,21 @@ static hipError_t fused_launch_bits(const FusedArgs& a, hipStream_t stream) {
         case 4096: return g32 ? fused_launch_shape<BITS, 64, true>(a, gshift, stream) : fused_launch_shape<BITS, 64, false>(a, gshift, stream);
         case 2048: return g32 ? fused_launch_shape<BITS, 32, true>(a, gshift, stream) : fused_launch_shape<BITS, 32, false>(a, gshift, stream);
         case 1024: return g32 ? fused_launch_shape<BITS, 16, true>(a, gshift, stream) : fused_launch_shape<BITS, 16, false>(a, gshift, stream);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+// the widths between the powers of two: kernels of translation units of their own
+template <int BITS>
+static hipError_t fused_launch_between(const FusedArgs& a, hipStream_t stream) {
+    if (a.f == 0 || a.n_tasks == 0) return hipSuccess;
+    int gshift = 0;
+    while ((1 << gshift) < a.group) ++gshift;
+    const bool g32 = a.group == 32;
+    switch (a.d) {
+        case 3072: return g32 ? fused_launch_shape<BITS, 48, true>(a, gshift, stream) : fused_launch_shape<BITS, 48, false>(a, gshift, stream);
+        case 2560: return g32 ? fused_launch_shape<BITS, 40, true>(a, gshift, stream) : fused_launch_shape<BITS, 40, false>(a, gshift, stream);
+        case 1536: return g32 ? fused_launch_shape<BITS, 24, true>(a, gshift, stream) : fused_launch_shape<BITS, 24, false>(a, gshift, stream);
         default: return hipErrorInvalidValue;
     }
 }

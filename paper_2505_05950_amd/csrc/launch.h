@@ -49,6 +49,16 @@ inline int fused_route_mode(int n_experts, int top_k, int n_shared) {
 // With `route` the workgroup also routes in place (fused_route_mode); otherwise map / task_tau /
 // task_scale describe the tasks.  partial[task][blocks][d], wg_count[task][blocks] (selected channels per
 // workgroup), v_out (optional) [task][f].
+// Besides the widths of the packed GEMV also 1536, 2560 and 3072, where a quarter to three eighths of a channel's lanes have no
+// unit: the separate kernels there read codes with the generic GEMV.  Calls, separate kernels / this, us: INT4 g128 d 2560
+// f 6911 (6 experts, top-2) 1 token 24.4 / 16.0, 3 37.4 / 27.0, 8 67 / 53; INT2 g64 d 1536 f 5000 (8) 1 token 20.1 / 11.6,
+// 8 44 / 28; INT3 g64 d 3072 f 8000 (8) 4 tokens 61 / 40; INT4 g32 d 1536 f 1408 (66, top-6) 16 tokens 97 / 76.  Closest where the
+// separate kernels share rows among the tokens of an expert: 16 tokens on one, INT4 g64 d 3072 f 8192 57 / 53, INT2 d 2560 53 / 48.
+inline bool fused_shape(int d, int bits, int group) {
+    return (bits == 2 || bits == 3 || bits == 4) && group >= 32 && (packed_fast_shape(d, bits, group) || d == 1536 || d == 2560 || d == 3072);
+}
+// lanes that share a channel, a unit of 64 codes each; a width between two powers of two leaves some of them without one
+constexpr int fused_lanes(int d) { return d <= 1024 ? 16 : (d <= 2048 ? 32 : 64); }
 constexpr int fused_producers = 4;                          // producer waves per workgroup (+ 2 consumers each)
 constexpr int fused_wgs_per_cu = 1;                         // workgroups per compute unit the block length aims at
 // Channel passes per producer wave: a launch argument between these two.  The kernel exists in two sizes, for blocks of

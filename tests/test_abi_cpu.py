@@ -146,6 +146,37 @@ def test_a_workspace_sized_for_the_largest_batch_serves_the_smaller_ones(lib, d,
         lib.floe_tuning(1, 0), lib.floe_tuning(4, 0)
 
 
+@pytest.mark.parametrize("d,f,bits,group,n,top_k,n_shared,T", [
+    (3072, 14784, 4, 64, 32, 4, 0, 19), (2560, 6911, 4, 128, 6, 2, 0, 3), (1536, 64, 2, 32, 8, 2, 0, 1), (3072, 60000, 3, 64, 8, 2, 0, 2),
+])
+def test_one_kernel_between_the_powers_of_two_is_not_a_condition(lib, d, f, bits, group, n, top_k, n_shared, T):
+    """A workspace that holds the separate kernels serves a call that would rather run the fused one, a list-driven call among them."""
+    import torch
+    from paper_2505_05950_amd.binding import _Expert, _Layer, _Shape
+    if torch.cuda.is_available():
+        pytest.skip("the pointers below are made up: without a device the calls end at their first HIP call")
+    lib.floe_layer_workspace_bytes.restype = lib.floe_expert_workspace_bytes.restype = C.c_size_t
+    p, ws = C.c_void_p(4096), C.c_void_p(1 << 20)
+    s = _Shape(d, f, bits, group)
+    L, e = _Layer(n, top_k, n_shared, 1, s, 4096, None, 4096, 0, 4096, 0), _Expert(s, 4096, 4096, 4096, 4096, 0, f)
+    Te = min(T, 16)
+
+    def sizes():
+        return lib.floe_layer_workspace_bytes(C.byref(L), T), lib.floe_expert_workspace_bytes(C.byref(s), Te)
+
+    def tuned(key, value):  # no layer call small enough to be fused; one expert's tokens sharing rows
+        lib.floe_tuning(key, value)
+        try:
+            return sizes()
+        finally:
+            lib.floe_tuning(key, 0)
+
+    for layer_bytes, expert_bytes in ((tuned(4, 1)[0], tuned(1, 2)[1]), sizes()):
+        assert lib.floe_moe_layer_decode(C.byref(L), p, T, p, None, ws, C.c_size_t(layer_bytes), None) == -5
+        assert lib.floe_expert_ffn_sparse(C.byref(e), p, Te, p, None, p, None, None, ws, C.c_size_t(expert_bytes), None) == -5
+        assert lib.floe_gate_down_sparse(C.byref(e), p, Te, p, p, p, None, p, ws, C.c_size_t(expert_bytes), None) == -5
+
+
 @pytest.mark.parametrize("shape,layer,one_token,wide", [
     ((1024, 3584, 2, 64), None, (17, 128, 160), (256, 320)),             # batches at which each way measured clearly faster
     ((2048, 5632, 4, 64), None, (17, 48), (96, 200)),

@@ -149,6 +149,19 @@ def test_layer_small_batches_through_the_fused_kernel():
     _run_layer_case(27, 3, 4096, 200, 3, 128, 4, 0, 2, True, 1, 50)
 
 
+@pytest.mark.parametrize("d,f,bits,group,n,n_shared,top_k,T,pct", [
+    (2560, 333, 4, 128, 6, 0, 2, 3, 85),     # 40 units on 64 lanes; an odd number of pieces of a router row
+    (1536, 71, 2, 64, 5, 1, 2, 2, 60),       # two channels per pass, 24 units on 32 lanes each
+    (1536, 1500, 2, 128, 4, 0, 2, 8, 70),    # several rounds of the ring, twelve deep here
+    (3072, 130, 3, 32, 16, 0, 2, 1, 80),     # 48 units, groups of 32
+    (3072, 40, 2, 256, 20, 2, 4, 2, 0),      # picked in place on logits; every channel selected
+    (2560, 1, 3, 64, 0, 1, 0, 4, 0),         # one channel, no routing
+    (1536, 50, 4, 32, 70, 0, 2, 2, 50),      # router kernel in front
+])
+def test_layer_small_batches_at_widths_between_the_powers_of_two(d, f, bits, group, n, n_shared, top_k, T, pct):
+    _run_layer_case(50 + T, 5, d, f, bits, group, n, n_shared, top_k, True, T, pct, gap=f * (100 - pct) >= 6400)
+
+
 def test_layer_small_batches_pick_in_place_among_up_to_64_experts():
     """17 to 64 routed experts and at most 16 (token, slot) tasks: x . W_r is formed by a kernel in front, softmax and
     top-k run inside the fused kernel with a lane per expert.  64 experts (every lane live), 33 (one live lane in the

@@ -72,3 +72,10 @@ def test_every_pass_has_landed_before_it_is_read_back(tmp_path):
     out = tmp_path / "fused_int2.s"
     subprocess.run([HIPCC, *FLAGS, "-S", "--cuda-device-only", os.path.join(CSRC, "fused_int2.hip"), "-o", str(out)], check=True)
     assert check(out.read_text()) == 36
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs the compiler")
+def test_the_same_at_widths_between_the_powers_of_two(tmp_path):
+    out = tmp_path / "fused_between_int2.s"
+    subprocess.run([HIPCC, *FLAGS, "-S", "--cuda-device-only", os.path.join(CSRC, "fused_between_int2.hip"), "-o", str(out)], check=True)
+    assert check(out.read_text()) == 36
