@@ -25,7 +25,10 @@
 // waves stood behind their own requests.  The same holds for v gathered by lane (a tenth of the kernel).  Measured, gate, 8 experts
 // d 4096 f 14336 at 90 %: 512 tokens 280 -> 232 us, 64 tokens 152 -> 144, one expert with 24 tokens 28.4 -> 24.6.  Gate + down before
 // groups of more than 16 tokens: 64 tokens 364 us, 512 tokens 2425.  Tried: pieces that end where groups end (one expert with 24 tokens
-// 24.6 -> 27.8, the others the same).
+// 24.6 -> 27.8, the others the same).  Down, the same layer with 512 tokens 277 -> 254 us: half of its cycles were matrix products, a
+// fifth of these for token tiles that a group does not fill, and the waves stood for the LDS reads in front of each tile's.  (A body per
+// number of live tiles, as in the gate kernel, spills: 284.  So does reading one tile ahead with an address register per entry of h, 309:
+// a reload waits for every row in flight.)  Up to two tiles it is bound by the rows and did not change.
 
 #include <type_traits>
 
@@ -35,6 +38,7 @@
 namespace floe {
 
 typedef _Float16 h16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 h16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWideWaves = 8;
@@ -481,7 +485,7 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
             const int slots = wide_owner(total, W, base + npairs - 1) - w_first + 1;
             if (tid < grp.n) a.task_rows[a.order[grp.first + tid]] = make_int2(grp.first + tid + w_first * kTok, slots);
         }
-        const int tiles = wide_tiles(grp.n);
+        const int tiles = __builtin_amdgcn_readfirstlane(wide_tiles(grp.n));
         const unsigned char* hsrc = scalar_ptr(a.hbuf + wide_h_first(grp, pmax) + (size_t)seg0 * tiles * 128);
         const int ns = (len + SL - 1) / SL;
         uint4 hq[kHRounds];
@@ -491,10 +495,10 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
         auto load_h = [&](int s) {  // h of slice s
 #pragma unroll
             for (int r = 0; r < kHRounds; ++r) {
-                const int i = tid + r * kWideThreads;
-                const int pr = min(s * SL + i / (NT * 128), len - 1);
-                const int tile = min(i % (NT * 128) / 128, tiles - 1);  // (past the group's tiles: token rows that nobody reads)
-                hq[r] = gload16(hsrc + (uint32_t)((pr * tiles + tile) * 128 + i % 128) * 16u);
+                const int first = wave * kWave + r * kWideThreads;  // (a wave's entries belong to one pair and one tile)
+                const int pr = min(s * SL + first / (NT * 128), len - 1);
+                const int tile = min(first % (NT * 128) / 128, tiles - 1);  // (past the group's tiles: token rows that nobody reads)
+                hq[r] = gload16(hsrc + (uint32_t)(pr * tiles + tile) * 2048u + (uint32_t)(tid & 127) * 16u);
             }
         };
         // The powers of the tokens whose h this thread brings in (the same ones in every slice): in registers where there are
@@ -506,26 +510,28 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
             return max((int)(m >> 23) - 141, -126);
         };
         auto power = [](int e) { return __builtin_bit_cast(float, (uint32_t)(127 + e) << 23); };
-        auto store_h = [&](int s) {  // into LDS as hi + lo
-            int at = tid;  // (entry i of the slice: pair and token tile i / 128, half (i >> 6) & 1 of the pair's rows, lane)
-            asm volatile("" : "+v"(at));  // or the addresses are formed ahead of the loop and spilled: a reload waits for every request
+        // into LDS as hi + lo, the group's own tiles (what a wave skips or clears is a branch).  An infinite or NaN h has a lo of NaN: all sums of its token are then formed again below.
+        auto store_h = [&](int s) {
+            int at = tid, at16 = l16;  // (entry i of the slice: pair and token tile i / 128, half (i >> 6) & 1 of the pair's rows, lane)
+            asm volatile("" : "+v"(at), "+v"(at16));  // or the addresses are formed ahead of the loop and spilled: a reload waits for every request
             uint2* out0 = reinterpret_cast<uint2*>(&hs[s & 1][(at / 128) * 128 + (at & 63)]) + ((at >> 6) & 1);
 #pragma unroll
             for (int r = 0; r < kHRounds; ++r) {
-                const int i = tid + r * kWideThreads;
-                const bool live = s * SL + i / (NT * 128) < len;
-                const float scale = kScaleRegs ? scale_reg[kScaleRegs ? r : 0] : s_scale[16 * (i % (NT * 128) / 128) + l16];
-                const uint32_t w[4] = {hq[r].x, hq[r].y, hq[r].z, hq[r].w};
-                h16 hi[4], lo[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const float h = live ? __builtin_bit_cast(float, w[k]) * scale : 0.0f;
-                    hi[k] = (h16)h;
-                    lo[k] = fabsf(h) <= 65504.0f ? (h16)(h - (float)hi[k]) : (h16)0.0f;  // infinite or NaN: hi says it all
-                }
+                const int first = wave * kWave + r * kWideThreads, tile = first % (NT * 128) / 128;
+                if (tile >= tiles) continue;
                 uint2* out = out0 + r * kWideThreads * 2;
-                out[0] = make_uint2(as_u32(h16x2{hi[0], hi[1]}), as_u32(h16x2{hi[2], hi[3]}));
-                out[2 * 64] = make_uint2(as_u32(h16x2{lo[0], lo[1]}), as_u32(h16x2{lo[2], lo[3]}));
+                if (s * SL + first / (NT * 128) >= len) {
+                    out[0] = out[2 * 64] = make_uint2(0u, 0u);
+                    continue;
+                }
+                const float scale = kScaleRegs ? scale_reg[kScaleRegs ? r : 0] : s_scale[16 * tile + at16];
+                const f32x4 h = {__builtin_bit_cast(float, hq[r].x), __builtin_bit_cast(float, hq[r].y), __builtin_bit_cast(float, hq[r].z),
+                                 __builtin_bit_cast(float, hq[r].w)};
+                const h16x4 hi = __builtin_convertvector(h * scale, h16x4);
+                const f32x4 rest = {fmaf(h[0], scale, -(float)hi[0]), fmaf(h[1], scale, -(float)hi[1]), fmaf(h[2], scale, -(float)hi[2]),
+                                    fmaf(h[3], scale, -(float)hi[3])};
+                out[0] = __builtin_bit_cast(uint2, hi);
+                out[2 * 64] = __builtin_bit_cast(uint2, __builtin_convertvector(rest, h16x4));
             }
         };
         auto load_ids = [&](int s) {
@@ -588,19 +594,35 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
                     b[2][k] = __builtin_amdgcn_perm(dq[p][2 * k + 1].y, dq[p][2 * k].y, 0x05040100u);
                     b[3][k] = __builtin_amdgcn_perm(dq[p][2 * k + 1].y, dq[p][2 * k].y, 0x07060302u);
                 }
+                // a tile's hi and lo are requested behind the products with those of the tile before: with the requests in
+                // front of a tile's own products the matrix cores stand for every one of them
+                uint4 hi = hs[buf][p * NT * 128 + lane], lo = hs[buf][p * NT * 128 + 64 + lane];
+                auto products = [&](auto first) __attribute__((always_inline)) {  // two tiles
+                    constexpr int n0 = decltype(first)::value;
 #pragma unroll
-                for (int n = 0; n < NT; ++n) {
-                    const uint4 hi = hs[buf][(p * NT + n) * 128 + lane], lo = hs[buf][(p * NT + n) * 128 + 64 + lane];
+                    for (int n = n0; n < n0 + 2 && n < NT; ++n) {
+                        const int next = (p * NT + min(n + 1, NT - 1)) * 128 + lane;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const uint4 bj = make_uint4(b[j][0], b[j][1], b[j][2], b[j][3]);
-                        acc[j][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h16x8, hi), __builtin_bit_cast(h16x8, bj),
-                                                                           acc[j][n], 0, 0, 0);
-                        acc[j][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h16x8, lo), __builtin_bit_cast(h16x8, bj),
-                                                                           acc[j][n], 0, 0, 0);
+                        for (int j = 0; j < 4; ++j)
+                            acc[j][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h16x8, hi),
+                                                                               __builtin_bit_cast(h16x8, make_uint4(b[j][0], b[j][1], b[j][2], b[j][3])),
+                                                                               acc[j][n], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (n + 1 < NT) hi = hs[buf][next];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            acc[j][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h16x8, lo),
+                                                                               __builtin_bit_cast(h16x8, make_uint4(b[j][0], b[j][1], b[j][2], b[j][3])),
+                                                                               acc[j][n], 0, 0, 0);
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (n + 1 < NT) lo = hs[buf][next + 64];
                     }
-                    if (NT > 2 && (n & 1)) __builtin_amdgcn_sched_barrier(0);  // keeps later LDS reads from piling up in registers
-                }
+                };
+                products(std::integral_constant<int, 0>{});
+                if (NT > 2 && tiles > 2) products(std::integral_constant<int, 2>{});
+                if (NT > 4 && tiles > 4) products(std::integral_constant<int, 4>{});
+                if (NT > 6 && tiles > 6) products(std::integral_constant<int, 6>{});
+                if (NT > 8 && tiles > 8) products(std::integral_constant<int, 8>{});
                 load_d(dq[p], s + 1, p);  // (past the last slice: ids repeat the last row, cache hits that nobody uses)
                 __builtin_amdgcn_sched_barrier(0);
             }

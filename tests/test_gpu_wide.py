@@ -73,6 +73,15 @@ def test_gate_rows_and_activations_through_lds(d, f, n, n_shared, top_k, T, pct)
     _run_layer_case(270 + T, 9, d, f, 2, 64, n, n_shared, top_k, False, T, pct, gap=f * (100 - pct) >= 6400)
 
 
+@pytest.mark.parametrize("d,f,n,n_shared,top_k,T,pct", [
+    (1024, 300, 3, 1, 1, 150, 60),   # ten tiles, of which the routed experts fill two to four; an odd number of pairs
+    (512, 97, 2, 1, 1, 155, 30),     # five to six; one row in the last pair
+    (512, 260, 5, 0, 2, 130, 50),    # groups of three to five tiles
+])
+def test_down_products_of_live_tiles_only(d, f, n, n_shared, top_k, T, pct):
+    _run_layer_case(300 + T, 9, d, f, 2, 64, n, n_shared, top_k, False, T, pct, gap=f * (100 - pct) >= 6400)
+
+
 def test_h_beyond_fp16():
     """Large activations: |h| far beyond 65504 for some (row, token), ordinary for the others of the same group."""
     import gpu_common as G
