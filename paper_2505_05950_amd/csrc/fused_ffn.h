@@ -1,6 +1,6 @@
 // (S1 +) S2-S5 of a small decode batch in ONE kernel (Sec. 3.3 router; Alg. 1 steps 2-5 with the quantized up
-// projection of Sec. 3.2.2 and the compact [gate | down] chunks of Sec. 3.4.2).  Template for every bit width;
-// instantiated in fused_int2.hip / fused_int3.hip / fused_int4.hip.
+// projection of Sec. 3.2.2 and the compact [gate | down] chunks of Sec. 3.4.2).  Template for every bit width; instantiated
+// in fused_int2.hip / fused_int3.hip / fused_int4.hip and, for widths between the powers of two, fused_between_int*.hip.
 //
 // Why one kernel: the threshold test of Alg. 1 is per channel, so a workgroup that has computed v for a block
 // of channels knows, without hearing from anybody else, which of ITS channels take part in steps 4-5; it can
@@ -25,8 +25,12 @@
 //
 // Widths between the powers of two (24, 40 or 48 units a channel): a channel still has 32 or 64 lanes, so that the sums stay DPP
 // steps within one wave; the lanes without a unit repeat its last one (same cache line, no further bytes) with activations of
-// zero.  The GEMV loses their share of its arithmetic, which the stream hides: INT4 g128 d 2560 f 6911, three tokens top-2 of six,
-// 38.3 us with separate kernels, 30.4 so (the traffic alone is 21 at the rate of a copy).
+// zero.  The GEMV loses their share of its arithmetic, which the stream hides for a few tasks: INT4 g128 d 2560 f 6911, three tokens
+// top-2 of six, 37.4 us with separate kernels, 28.5 so (the traffic alone is 21 at the rate of a copy).  Separate kernels at these
+// widths read codes as subnormals, without an offset in the sums, and so do these instances: error of v against 64 bits 7e-8
+// (norm), with the packed kernels' offset 1.7e-6 .. 3.2e-6.  It costs 1 to 7 %: offset / this, us, INT2 g64 d 3072 f 8192 (8 experts,
+// top-2, 90 %) 1 token 19.5 / 20.5, 4 33.5 / 36.0; INT4 g128 d 2560 f 6911 3 tokens 27.1 / 28.5.  (Tried: the 1 taken off by a packed
+// subtraction and v_dot2 kept: 22.0, 40.2, 28.3, as exact.)
 #pragma once
 
 #include <type_traits>
@@ -108,6 +112,7 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
                                                                   int32_t* __restrict__ wg_count) {
     constexpr int d = 64 * UPC;
     constexpr int LPC = fused_lanes(d);   // lanes per channel: those beyond UPC repeat its last unit with activations of zero
+    constexpr bool kSub = UPC != LPC;     // the arithmetic of subnormal_unit.h (see above)
     constexpr int CPW = kWave / LPC;      // channels per wave pass
     constexpr int NV = d / 512;           // uint4 per lane of a gate column / down row
     constexpr int kQ = kPasses * CPW;     // queue capacity
@@ -299,18 +304,16 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
         float Xg[2], Xoff[2];
         // every group of UPC lanes holds the whole token, so the wave-wide maximum is the token's
         const float amax = wave_allreduce_max_nonneg(unit_amax(raw));
-        const int down = xprep_down<BITS>(amax);
-        const float inv_p = ldexpf(1.0f, down);
-        unit_prepare<BITS>(raw, down, xs, Xoff, Xg);
+        const int down = kSub ? sub_down<BITS>(amax) : xprep_down<BITS>(amax);
+        const float inv_p = ldexpf(1.0f, down) * (kSub ? (float)(1 << (24 - SubTraits<BITS>::kPmax)) : 1.0f);
+        if constexpr (kSub) sub_prepare<BITS>(raw, down, xs, Xg);
+        else unit_prepare<BITS>(raw, down, xs, Xoff, Xg);
         if constexpr (UPC != LPC) {
             const bool has = lane % LPC < UPC;
 #pragma unroll
             for (int r = 0; r < 32; ++r) xs[r] = has ? xs[r] : 0u;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                Xg[h] = has ? Xg[h] : 0.0f;
-                Xoff[h] = has ? Xoff[h] : 0.0f;
-            }
+            for (int h = 0; h < 2; ++h) Xg[h] = has ? Xg[h] : 0.0f;
         }
         uint32_t magic = 0x3C003C00u;
         asm volatile("" : "+v"(magic));  // keep it in a VGPR: v_and_or_b32 takes one scalar operand only
@@ -348,7 +351,9 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
                 // the first round, and with it a wait for every load of that round)
                 if constexpr (G32) asm volatile("" : "+v"(ld[i].s), "+v"(ld[i].z));
                 else asm volatile("" : "+v"(ld[i].sh), "+v"(ld[i].zh));
-                float part = unit_value<BITS, UPC, G32>(ld[i], xs, Xoff, Xg, magic);
+                float part;
+                if constexpr (kSub) part = unit_value_sub<BITS, UPC, G32>(ld[i], xs, Xg);
+                else part = unit_value<BITS, UPC, G32>(ld[i], xs, Xoff, Xg, magic);
                 if constexpr (kStaged) {
                     if constexpr (!kLast) issue(i, p + kDepth);
                 } else {

@@ -50,10 +50,11 @@ inline int fused_route_mode(int n_experts, int top_k, int n_shared) {
 // task_scale describe the tasks.  partial[task][blocks][d], wg_count[task][blocks] (selected channels per
 // workgroup), v_out (optional) [task][f].
 // Besides the widths of the packed GEMV also 1536, 2560 and 3072, where a quarter to three eighths of a channel's lanes have no
-// unit: the separate kernels there read codes with the generic GEMV.  Calls, separate kernels / this, us: INT4 g128 d 2560
-// f 6911 (6 experts, top-2) 1 token 24.4 / 16.0, 3 37.4 / 27.0, 8 67 / 53; INT2 g64 d 1536 f 5000 (8) 1 token 20.1 / 11.6,
-// 8 44 / 28; INT3 g64 d 3072 f 8000 (8) 4 tokens 61 / 40; INT4 g32 d 1536 f 1408 (66, top-6) 16 tokens 97 / 76.  Closest where the
-// separate kernels share rows among the tokens of an expert: 16 tokens on one, INT4 g64 d 3072 f 8192 57 / 53, INT2 d 2560 53 / 48.
+// unit: the separate kernels there read codes with the generic GEMV, whose precision these instances keep (fused_ffn.h).  The widths
+// left, 512 and 3584, have no instances (36 kernels each) and run the separate kernels; unmeasured.
+// Calls, separate kernels / this, us: INT4 g128 d 2560 f 6911 (6 experts, top-2) 1 token 25.0 / 17.2, 3 37.4 / 28.5, 8 66.9 / 55.6;
+// INT2 g64 d 1536 f 5000 (8) 1 token 20.7 / 12.8, 8 45.5 / 29.5; INT3 g64 d 3072 f 8000 (8) 4 tokens 61.2 / 39.6; INT4 g32 d 1536
+// f 1408 (64 + 2, top-6) 16 tokens 72.7 / 54.0.
 inline bool fused_shape(int d, int bits, int group) {
     return (bits == 2 || bits == 3 || bits == 4) && group >= 32 && (packed_fast_shape(d, bits, group) || d == 1536 || d == 2560 || d == 3072);
 }

@@ -3,6 +3,7 @@
 #pragma once
 
 #include "floe_dev.h"
+#include "subnormal_unit.h"
 #include "xprep.h"
 
 namespace floe {
@@ -71,6 +72,17 @@ __device__ __forceinline__ float unit_value(const UnitLoad<BITS, UPC, G32>& L, c
     }
     const float sc = (float)L.sh, z = (float)L.zh;
     return sc * fmaf(-z, Xg[0] + Xg[1], (dot0 + dot1) - (Xoff[0] + Xoff[1]));
+}
+// the same in the arithmetic of subnormal_unit.h (xs and Xg of sub_prepare; the result carries its 2^(kPmax - 24))
+template <int BITS, int UPC, bool G32>
+__device__ __forceinline__ float unit_value_sub(const UnitLoad<BITS, UPC, G32>& L, const uint32_t (&xs)[32], const float (&Xg)[2]) {
+    const float dot0 = sub_half_dot<BITS>(L.cw, xs, 0), dot1 = sub_half_dot<BITS>(L.cw, xs, 1);
+    if (G32) {
+        const h16x2 s2 = as_h2(L.s), z2 = as_h2(L.z);
+        return fmaf((float)s2.x, fmaf(-(float)z2.x, Xg[0], dot0), (float)s2.y * fmaf(-(float)z2.y, Xg[1], dot1));
+    }
+    const float z = (float)L.zh;  // (per half unit, like the generic kernel: what cancels does so before the next rounding)
+    return (float)L.sh * (fmaf(-z, Xg[0], dot0) + fmaf(-z, Xg[1], dot1));
 }
 
 }  // namespace floe

@@ -35,3 +35,34 @@ def test_up_gemv_of_untuned_shapes(d, f, bits, group, T, scale):
         # the size of what cancels: one rounding of a partial sum is measured against it
         size = np.sqrt(np.mean(wd ** 2 @ x[t].astype(np.float64) ** 2))
         assert np.abs(v[t] - ref).max() <= BAR * size, (t, np.abs(v[t] - ref).max() / size)
+
+
+@pytest.mark.parametrize("d,f,bits,group,T,scale", [
+    (1536, 200, 2, 64, 1, 1.0), (2560, 333, 4, 128, 3, 1.0), (3072, 130, 3, 64, 16, 1.0), (1536, 70, 4, 32, 2, 1.0),
+    (2560, 77, 2, 256, 1, 1.0), (3072, 40, 3, 32, 2, 1.0), (1536, 1500, 3, 128, 8, 1.0),
+    (2560, 130, 2, 64, 2, 3000.0), (3072, 150, 4, 64, 1, 8000.0), (1536, 160, 3, 32, 1, 1e-5), (2560, 170, 4, 128, 2, 1e-5),
+])
+def test_v_inside_a_one_expert_call_at_widths_between_the_powers_of_two(d, f, bits, group, T, scale):
+    """The same bar for the v that a small call forms on its way to y: gate columns whose sum is 32 (SiLU leaves it as it is) and
+    down rows with a single one make y = 32 v, exactly."""
+    import gpu_common as G
+    import paper_2505_05950_amd as F
+    w_up, _ = S.expert_weights(96, 3, d, f)
+    gd = np.zeros((f, 2, d), np.float16)
+    x0 = np.float16(2.0 ** int(np.log2(scale)))  # (as large as the other activations: subnormal in the smallest case)
+    gd[:, 0, :64] = np.float16(0.5 / x0)
+    gd[np.arange(f), 1, np.arange(f)] = 1.0
+    ex_np, ex_dev = G.make_expert(w_up, gd, bits, group)
+    x = (S.tokens(96, 3, T, d).astype(np.float32) * scale).astype(np.float16)
+    x[:, :64] = x0
+    tau = np.full((T,), -1.0, np.float32)  # every channel
+    y, idx, count = F.floe_expert_ffn_sparse(ex_dev, G.dev(x), G.dev(tau), None, torch.zeros((T, d), device=G.DEV))
+    torch.cuda.synchronize()
+    y, idx, count = y.cpu().numpy().astype(np.float64), idx.cpu().numpy(), count.cpu().numpy()
+    assert (count == f).all() and (idx == np.arange(f)).all() and not y[:, f:].any()
+    wd = O.dequantize(*ex_np[:3], d, bits, group).astype(np.float64)
+    for t in range(T):
+        ref = O.up_gemv(*ex_np[:3], d, bits, group, x[t]).astype(np.float64)
+        size = np.sqrt(np.mean(wd ** 2 @ x[t].astype(np.float64) ** 2))
+        err = np.abs(y[t, :f] / 32.0 - ref).max() / size
+        assert err <= BAR, (t, err)
