@@ -128,7 +128,7 @@ __global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restri
                                                        int max_groups, const int32_t* __restrict__ order, const uint4* __restrict__ frag,
                                                        const float* __restrict__ gsum, const float* __restrict__ back,
                                                        float* __restrict__ v, const float* __restrict__ task_tau,
-                                                       uint32_t* __restrict__ mask_words, int d, int f, int parts) {
+                                                       uint32_t* __restrict__ mask_words, int d, int f) {
     constexpr int kTok = 16 * NT;
     constexpr int kGroups = G32 ? 2 : 1;                 // quantization groups per unit
     constexpr int kVec = BITS;                           // 16-byte vectors of codes per lane and tile: two units
@@ -149,14 +149,19 @@ __global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restri
     const int nwords = mask_words_per_task(f);
     const int blocks = (32 * nwords + kCh - 1) / kCh;    // whole mask words
     FLOE_TL(0);
-    // Equal pieces by what a block costs with one and with two token tiles (vector instructions: 20 and 28 per unit and channel
-    // tile, and the rest alike) and by what the start of a group costs.
+    // Equal pieces by what a block costs with one and with two token tiles and by what the start of a part costs.  INT2 with two channel
+    // tiles per block: vector instructions, 20 and 28 per unit and channel tile, and the rest alike; the wider codes, one channel tile
+    // and more to unpack, 7 to 8 (8 experts d 4096 f 14336 INT4, 150 tokens: 544 us with 3 to 4, 534; 190 tokens 544, 533).
     const int ng = n_groups[0];
-    constexpr int kStart = 6;
-    auto weight = [](int n) { return n > 16 ? 4 : 3; };
+    constexpr int kStart = 12;
+    auto weight = [](int n) { return n > 16 ? 8 : (BITS == 2 ? 6 : 7); };
+    // a group of more than 32 tokens comes in parts of 32 and a last one of the rest: what the last one and a full one weigh
+    auto parts_of = [](int n) { return (n + 31) >> 5; };
+    const int full_weight = weight(32) * blocks + kStart;
+    auto last_weight = [&](int n) { return weight(n - 32 * (parts_of(n) - 1)) * blocks + kStart; };
     auto group_weight = [&](int g0) {  // of lane's group (the load does not wait for ng)
         const int n = groups[min(g0 + lane, max_groups - 1)].n;
-        return g0 + lane < ng ? (weight(n) * blocks + kStart) * parts : 0;
+        return g0 + lane < ng ? (parts_of(n) - 1) * full_weight + last_weight(n) : 0;
     };
     int total = 0;
     for (int g0 = 0; g0 < ng; g0 += kWave) total += __builtin_amdgcn_readlane(wave_inclusive_scan(group_weight(g0), lane), kWave - 1);
@@ -182,15 +187,14 @@ __global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restri
             base += __builtin_amdgcn_readlane(inc, kWave - 1);
         }
         const WideGroup grp = groups[__builtin_amdgcn_readfirstlane(g)];
-        const int wgt = weight(grp.n), part_weight = wgt * blocks + kStart;
+        const int part = __builtin_amdgcn_readfirstlane(min((pos - base) / full_weight, parts_of(grp.n) - 1));
+        const int tok_first = 32 * part, n_tok = min(32, grp.n - tok_first);
         // block k of a part belongs to the piece that holds the start of its share, kStart + k * wgt behind the part's
-        const int part = __builtin_amdgcn_readfirstlane((pos - base) / part_weight);
-        const int at = base + part * part_weight + kStart;
+        const int wgt = weight(n_tok), at = base + part * full_weight + kStart;
         const int b0 = __builtin_amdgcn_readfirstlane(max(pos - at + wgt - 1, 0) / wgt);
         const int len = __builtin_amdgcn_readfirstlane(min(blocks, max(end - at + wgt - 1, 0) / wgt)) - b0;
         pos = at + blocks * wgt;  // the next part, or past the end
-        const int tok_first = 32 * part, n_tok = min(32, grp.n - tok_first);  // a group of more tokens than a pass takes comes in parts
-        if (len <= 0 || n_tok <= 0) continue;
+        if (len <= 0) continue;
         const unsigned char* codes = scalar_ptr(grp.e.codes);
         const unsigned char* scale = scalar_ptr(grp.e.scale);
         const unsigned char* zero = scalar_ptr(grp.e.zero);
@@ -454,7 +458,7 @@ static hipError_t launch_split(const UpWideArgs& a, hipStream_t stream) {
     const hipError_t rc = launch_x_operand(a, BITS, G32 ? 32 : 64, x, stream);
     if (rc != hipSuccess) return rc;
     kernel<<<dim3(wgs), dim3(64 * nw), lds, stream>>>(a.groups, a.n_groups, a.max_groups, a.order, x.frag, x.gsum, x.back, a.v, a.task_tau,
-                                                    a.mask_words, a.d, a.f, a.parts);
+                                                    a.mask_words, a.d, a.f);
     return hipGetLastError();
 }
 

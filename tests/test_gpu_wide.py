@@ -44,6 +44,8 @@ def test_wide_groups(d, f, bits, group, n, n_shared, top_k, T, pct):
     (2560, 16, 3, 32, 2, 0, 1, 9, 50),       # five; half a mask word
     (1536, 95, 4, 64, 0, 2, 0, 31, 60),      # three waves, two workgroups per compute unit; two experts on the same tokens
     (512, 50, 4, 64, 70, 2, 8, 20, 50),      # one wave; more groups than a wave scans at a time
+    (1024, 300, 4, 64, 2, 0, 1, 70, 60),     # three token tiles: groups of one and of two parts
+    (2048, 90, 3, 32, 0, 1, 0, 49, 50),      # four: the second part holds one tile and one token
 ])
 def test_up_projection_split_over_columns(d, f, bits, group, n, n_shared, top_k, T, pct):
     _run_layer_case(170 + T, 7, d, f, bits, group, n, n_shared, top_k, False, T, pct, gap=f * (100 - pct) >= 6400)
