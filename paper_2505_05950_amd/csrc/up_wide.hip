@@ -223,6 +223,10 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __
                 for (int t = 0; t < CT; ++t)
 #pragma unroll
                     for (int n = 0; n < NL; ++n) acc[t][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+                // The codes of the coming four slots are here, the two slots requested behind them may still be under way.  (Said by
+                // hand, here and at the end of the loop: with requests to LDS among them the compiler waits for all of them.  No call
+                // got faster by it, the slots are long enough: 512 tokens on 8 experts 737 us either way.)
+                wait_requests_all_but<2 * kReq>();
 #pragma unroll 1
                 for (int s = 0; s < slots; s += 4) {
                     uint32_t wd[CT][2][4][kLaneWords];
@@ -238,8 +242,8 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __
                     }
                     auto step = [&](auto slot, const uint4* x, uint4* next) __attribute__((always_inline)) {
                         constexpr int k = decltype(slot)::value;
-                        // slot k is here: younger are the requests of two slots and, for the outer slots, those of the codes
-                        wait_requests_all_but<2 * kReq + (k == 0 || k == 3 ? kRegLoads : 0)>();
+                        // slot k is here: younger are the requests of two slots and, for the last one, those of the codes
+                        wait_requests_all_but<2 * kReq + (k == 3 ? kRegLoads : 0)>();
                         meet();
                         if constexpr (k == 2) load_codes(s + 4);  // (not sooner: half of the operand words make room for them)
                         __builtin_amdgcn_sched_barrier(0);
@@ -335,6 +339,7 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __
                     step(std::integral_constant<int, 1>{}, x1, x0);
                     step(std::integral_constant<int, 2>{}, x2, x1);
                     step(std::integral_constant<int, 3>{}, x3, x2);
+                    wait_requests_all_but<2 * kReq>();
                 }
                 // lane (c, g4) holds channel ch0 + 16 t + c for tokens 16 n + 4 g4 + i
                 int tok0 = 4 * g4;
