@@ -237,7 +237,7 @@ LayerWs layer_plan(const floe_layer* L, int T, Wide form = Wide::kChosen, int ma
     w.misscount_off = o; o += L->gd_on_host ? align_up((size_t)w.n_tasks * 4) : 0;
     const size_t wgroups = w.use_wide ? (size_t)w.wp.max_groups : 0;
     w.wgroups_off = o; o += w.use_wide ? align_up(wgroups * sizeof(WideGroup) + 4) : 0;  // (+ their number)
-    w.up_split = w.use_wide && up_split_pays(L->s.d, L->s.f, L->s.bits, L->s.group, w.wp.nt);
+    w.up_split = w.use_wide && up_split_pays(L->s.d, L->s.f, L->s.bits, L->s.group, n_all, w.n_tasks, w.wp);
     w.up_wide = w.use_wide && !w.up_split && up_wide_pays(L->s.d, L->s.f, L->s.bits, L->s.group, n_all, w.n_tasks);
     const bool room_for_x = room && up_wide_shape(L->s.d, L->s.f, L->s.bits, L->s.group) && grouped_gemv_mode() != 2;
     w.xsum_off = o;    o += w.up_wide || w.up_split || room_for_x ? align_up(x_operand_sum_bytes(w.wp.h_tiles, L->s.d, L->s.group)) : 0;
@@ -514,7 +514,7 @@ int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, cons
         // (scales and zeros need no more than their own alignment here; the wide kernel loads them 16 bytes at a time)
         if (up_wide_shape(e->s.d, e->s.f, e->s.bits, e->s.group) && aligned(e->up_scale, 16) && aligned(e->up_zero, 16)) {
             UpWideArgs u{};
-            const bool split = up_split_pays(e->s.d, e->s.f, e->s.bits, e->s.group, w.wp.nt);
+            const bool split = up_split_pays(e->s.d, e->s.f, e->s.bits, e->s.group, 1, T, w.wp);
             u.groups = groups; u.n_groups = n_groups; u.order = order; u.x = xh; u.v = v;
             u.task_tau = tau; u.mask_words = mask; u.x_frag = base + w.hbuf_off; u.x_sums = base + w.xsum_off;
             u.T = T; u.n_tasks = T; u.d = e->s.d; u.f = e->s.f; u.slots = 1; u.nt = w.wp.nt;

@@ -276,11 +276,22 @@ inline bool up_split_shape(int d, int f, int bits, int group) { return up_wide_s
 // More than two token tiles come in parts of two, which up_wide.hip does at once: INT2 at 130 tokens 485 / 470, d 2048 f 4096 (4 experts)
 // at 90: 89 / 86; the wider codes leave it fewer token tiles: INT4 g32 d 2048 f 5632 at 200 tokens, that or grouped kernel / this, 184 / 162,
 // INT3 g64 d 2048 f 7000 at 200: 196 / 182, INT3 g32 d 4096 f 3000 (4) at 90: 152 / 109.
-inline bool up_split_pays(int d, int f, int bits, int group, int nt) {
+// Still more tiles in parts as well where up_wide.hip has few blocks of 32 channels to deal to eight waves of each compute unit.  INT3 and
+// INT4 by its blocks (layers and one expert, 85 to 250 tokens on an expert): below 512 1.01 to 1.49 times as long as in parts, 512 to 800
+// 1.02 to 1.16, 800 to 1200 0.94 to 1.12, beyond 0.83 to 1.15.  INT4 g32 d 4096 f 500 (4 experts) at 260: 159 / 119, f 1408: 176 / 148;
+// one expert INT3 g64 f 4000 at 130: 146 / 120.  INT2, where no grouped kernel is the alternative: below 128 1.03 to 1.53 (one expert d 4096
+// f 2048 at 130: 148 / 99), 128 to 512 1.00 to 1.36, then even.
+inline int up_wide_blocks(int f, int bits, int n_tasks, int est_groups) {
+    const int most = bits == 2 ? 144 : 80, per = (n_tasks + est_groups - 1) / est_groups;  // tokens of a part at most, of a group
+    return est_groups * ((per + most - 1) / most) * ((f + 31) / 32);
+}
+inline bool up_split_pays(int d, int f, int bits, int group, int n_all, int n_tasks, const WidePlan& p) {
     if (!up_split_shape(d, f, bits, group)) return false;
-    const bool grouped = mfma_grouped_shape(d, bits, group);
-    if (grouped && grouped_gemv_mode() == 2) return false;  // the caller wants one pass per task
-    return nt <= (bits == 2 ? 2 : 4) && !(grouped && bits == 2 && nt == 1);
+    const bool grouped = mfma_grouped_shape(d, bits, group) && n_all > 1;
+    if (mfma_grouped_shape(d, bits, group) && grouped_gemv_mode() == 2) return false;  // the caller wants one pass per task
+    const int blocks = up_wide_blocks(f, bits, n_tasks, p.est_groups);
+    if (bits != 2) return p.nt <= 4 || blocks < 800;
+    return grouped ? p.nt == 2 : p.nt <= 2 || blocks < 512;
 }
 hipError_t launch_up_split(UpWideArgs a, int bits, int group, hipStream_t stream);
 

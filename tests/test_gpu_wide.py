@@ -59,6 +59,10 @@ def test_up_projection_split_over_columns(d, f, bits, group, n, n_shared, top_k,
     (1024, 400, 4, 64, 3, 1, 2, 200, 70),    # groups of different sizes, a shared expert
     (4608, 96, 4, 32, 0, 1, 0, 20, 50),      # a width that the columns are not split for
     (512, 64, 2, 64, 40, 4, 6, 300, 60),     # more parts than a wave scans
+    (512, 8193, 2, 64, 0, 1, 0, 150, 85),    # blocks enough for eight waves of every compute unit: ten tiles in two parts of five
+    (512, 13001, 4, 64, 0, 1, 0, 150, 90),   # the same for the wider codes
+    (512, 6500, 3, 32, 0, 2, 0, 130, 90),    # two experts, nine tiles: parts of five and four
+    (1024, 5003, 2, 64, 4, 0, 2, 80, 85),    # groups of three tiles, of two and of one
 ])
 def test_up_projection_of_many_tokens(d, f, bits, group, n, n_shared, top_k, T, pct):
     _run_layer_case(370 + T, 11, d, f, bits, group, n, n_shared, top_k, False, T, pct, gap=f * (100 - pct) >= 6400)
