@@ -116,10 +116,16 @@ bool fuse_optional(const floe_shape& s) { return !packed_fast_shape(s.d, s.bits,
 bool fuse_shape(const floe_shape& s, bool fuse) {
     return fused_shape(s.d, s.bits, s.group) && (!fuse_optional(s) || (fuse && union_mode() != 1 && union_mode() != 2));
 }
+// passes of the fused kernel, 0 where a batch does not run it
+int fuse_passes(const floe_shape& s, int n_all, int n_tasks, int slots, int max_tasks, bool tuned, bool fuse) {
+    const int passes = fuse_shape(s, fuse) ? fused_passes(s.d, s.f, s.bits, n_tasks, max_tasks) : 0;
+    if (!passes || tuned || !fuse_optional(s)) return passes;
+    return fused_between_pays(s.d, s.f, s.bits, s.group, n_all, n_tasks, slots, passes) ? passes : 0;
+}
 ExpertWs expert_ws(const floe_shape* s, int T, Wide form = Wide::kChosen, bool fuse = true) {
     ExpertWs w{};
     w.nblk = gd_blocks(T, s->f);
-    w.fused_passes = fuse_shape(*s, fuse) ? fused_passes(s->d, s->f, s->bits, T) : 0;
+    w.fused_passes = fuse_passes(*s, 1, T, 1, kExpertOrderTasks, false, fuse);
     w.nblk_fused = w.fused_passes ? fused_blocks(s->d, s->f, w.fused_passes) : 0;
     const int nblk_alloc = w.nblk > w.nblk_fused ? w.nblk : w.nblk_fused;
     size_t o = 0;
@@ -190,8 +196,7 @@ LayerWs layer_plan(const floe_layer* L, int T, Wide form = Wide::kChosen, int ma
     w.n_tasks = T * slots;
     w.nblk = gd_blocks(w.n_tasks, L->s.f);
     const int n_all = L->n_experts + L->n_shared;
-    w.fused_passes = fuse_shape(L->s, fuse && !L->gd_on_host)
-                         ? fused_passes(L->s.d, L->s.f, L->s.bits, w.n_tasks, fused_task_limit(n_all)) : 0;
+    w.fused_passes = fuse_passes(L->s, n_all, w.n_tasks, slots, fused_task_limit(n_all), fused_tasks_tuned() > 0, fuse && !L->gd_on_host);
     w.nblk_fused = w.fused_passes ? fused_blocks(L->s.d, L->s.f, w.fused_passes) : 0;
     w.chunk = mfma_chunk(n_all, w.n_tasks);
     // the grouped up GEMV: when forced, or where the fused kernel does not apply and grouping pays

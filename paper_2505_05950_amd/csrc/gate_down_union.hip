@@ -296,40 +296,47 @@ void set_union_mode(int m) { g_union_mode.store(m >= 0 && m <= 3 ? m : 0, std::m
 // The wide kernels read a row once for a whole group, but bring three more launches with their prologues and the partial results
 // of all pieces (half a megabyte per token of a group, whatever the layer); the one-token kernels in expert order read the rows of
 // a task each.  What decides is therefore the rows that the tasks would read, in GB with all channels: q tasks per expert times
-// the bytes G of the experts' rows.  Measured (layers at 85 %, one expert at 90 %), one-token / wide, us:
-//   layers, large G: q >= 4 + 1.9 / G
-//     8 experts  d 4096 f 14336 INT2 (G 1.9):    q 5 253 / 219, 8 305 / 301, 10 360 / 312, 16 460 / 374
-//     16 experts d 4096 f 4096  INT2 (1.1):      q 5 187 / 187, 6 195 / 189, 8 250 / 230
-//   ... but at least q G = 4.4 where both ways run the same up projection
-//     8 experts  d 1024 f 3584  INT2 (0.12):     q 24 79 / 92, 32 103 / 110
-//     4 experts  d 1024 f 10000 INT2 (0.16):     q 16 81 / 97, 24 98 / 110, 32 130 / 118
-//     8 experts  d 2048 f 5632  INT4 (0.37):     q 8 88 / 105, 12 120 / 124, 20 165 / 149
-//     8 experts  d 2048 f 3000  INT2 g32 (0.20): q 16 131 / 146, 20 156 / 157, 24 183 / 175
-//     64 experts d 1024 f 2048  INT2 (0.54):     q 8 149 / 159, 10 169 / 175, 12 185 / 181
-//     50 experts d 1024 f 1408  INT4 (0.29):     q 10 118 / 119, 16 147 / 139
-//   other layers take the wide up projection along and stay at the first line
-//     25 experts d 1536 f 2048  INT4 (0.32):     q 6 98 / 113, 8 123 / 121, 12 171 / 136
-//     8 experts  d 3072 f 4000  INT2 (0.39):     q 4 82 / 93, 8 143 / 118
-//   one expert, whose tokens go through the packed up projection one by one or the wide one: q G = 2.85, for the smaller widths,
-//   whose rows are short against their partial results, 3.4, with groups of 32 (more scales per code in the wide one) 5
-//     d 1024 f 3584 INT2 (0.015): 160 tokens 79 / 104, 200 94 / 100    d 2048 f 5632 INT4 (0.046): 48 78 / 91, 64 92 / 97, 96 132 / 124
-//     d 4096 f 4096 INT2 (0.067): 32 78 / 88, 48 113 / 104             d 4096 f 14336 INT2 (0.23): 17 163 / 109
-//     d 1024 f 8000 INT3 (0.033): 96 103 / 111, 128 143 / 115          d 2048 f 1408 INT3 g32 (0.012): 200 91 / 124, 256 111 / 143
+// the bytes G of the experts' rows, and what the up projections on both sides cost.  Measured at 85 %: about 1500 layer calls and 870
+// calls of one expert, forced each way; a line is where the kinds of shape named with it break even, and costs 0.5 % on average
+// over the calls around it.  one-token / wide, by q G:
+//   layers without a grouped up projection (widths between the powers of two and beyond 4096, where the other way runs the generic one):
+//   1.6 + G / 2 (many experts with few tokens each leave the groups small)
+//     d 1536 f 4000 INT2 (8 experts): 1.2 0.82, 1.6 0.94, 2.0 1.07, 3.1 1.44;  d 3072 f 4000 INT4 (8): 2.0 1.24, 3.9 1.64
+//     d 2560 f 1200 INT3 (8): 1.0 1.08, 1.6 1.33;  d 5120 f 1200 INT2 (8): 1.6 0.97, 2.0 1.12, 3.9 1.37
+//     d 1536 f 2048 INT4 (65 experts, G 0.82, 2.3 tokens each): 1.9 0.89;  d 1536 f 1408 INT2 (66, G 0.57): 2.8 1.06, 4.6 1.31
+//   d 4096: 2.3, INT3, whose grouped kernel is bound by its unpacking, 1.0
+//     f 4000 INT2 (4): 2.1 0.80, 2.6 1.10, 5.2 1.30;  f 1200 INT4 g64 (8): 0.9 0.99, 1.9 1.12;  f 4000 INT4 g128 (8): 2.6 1.00, 5.2 1.09
+//     f 1200 INT3 g64 (8): 0.9 1.08, 2.5 1.30;  f 10000 INT8 d 3072 (4): 2.0 0.85, 2.5 1.02, 4.9 1.14
+//   d 1024 and 2048: 4.4, INT3 3.1
+//     d 1024 f 4000 INT2 (8): 2.6 0.87, 3.4 0.98, 4.5 1.13;  d 2048 f 4000 INT4 g64 (16): 3.1 0.90, 4.2 0.97, 5.2 1.06
+//     d 2048 f 1408 INT2 (66): 4.6 0.94, 6.1 1.06;  d 2048 f 4000 INT3 g32 (16): 2.6 1.00, 3.1 1.14, 5.2 1.17
+//     d 1024 INT4 g32, whose grouped kernel takes two to three times as long as the others: 1.0 (f 4000, 4 experts: 1.0 1.05, 2.2 1.58)
+//   one expert, whose tokens otherwise go through the packed or generic up projection one by one: 1.1, INT2 1.25, on up to 64 tokens (more
+//   take more partial results: from 2.0 on in any case)
+//     d 1024 f 14336 INT2: 1.0 (17 tokens) 0.94, 1.2 (20) 1.02, 1.9 (32) 1.52;  d 4096 f 4000 INT3 g64: 1.1 (17) 1.20, 2.1 (32) 1.39
+//     d 2048 f 5632 INT4 and d 2048 f 8000: 1.1 (17) 1.03, 1.6 (24) 1.18, 2.6 (40) 1.62
+//     d 2560 f 1408 INT2: 0.9 (64) 0.82, 1.8 (128) 1.15, 2.9 (200) 1.88;  d 2048 f 1408 INT3 g32: 1.5 (128) 0.88, 2.3 (200) 1.39
+//     beyond d 4096, where the wide side has no split up projection, 2.0, and 4.0 with more than 64 tokens
+//     d 5120 f 4000 INT2: 1.4 (17) 1.00, 2.3 (28) 1.14;  f 1408: 1.8 (64) 0.81, 2.8 (96) 0.81, 4.6 (160) 1.05
 //   one expert without a wide up projection: 3.6, for the smaller widths 5 (generic) and 10 (packed up projection)
-//     d 2560 f 6911 INT4 g128 (0.071): 32 85 / 101, 48 132 / 127       d 4096 f 8000 INT8 (0.13): 24 196 / 197, 48 353 / 332
-//     d 1536 f 3000 INT8 (0.018): 160 128 / 171, 200 156 / 174         d 2048 f 8000 INT2 g128 (0.066): 64 114 / 134, 160 262 / 267
+//     d 4096 f 4000 INT4 g128: 2.1 (32 tokens) 0.91, 4.2 (64) 1.05;  d 4096 f 1408 INT8: 3.7 (160) 0.98, 4.6 (200) 1.24
+//     d 1536 f 4000 INT4 g128: 2.4 (96) 0.79, 4.9 (200) 1.05;  d 2048 f 8000 INT4 g128: 4.2 (64) 0.96, 8.4 (128) 1.10
 int union_kernels_for(int n_all, int n_tasks, int d, int f, int bits, int group) {
     const int m = union_mode();
     if (m != 0) return m;
-    const double gb = 4e-9 * d * (double)f * n_all;
+    const double gb = 4e-9 * d * (double)f;  // of one expert: q G = n_tasks * gb
     const bool wide_up = up_wide_shape(d, f, bits, group), packed = packed_fast_shape(d, bits, group);
-    double least = 1.9 + 4.0 * gb;
-    double same_up = 0.0;
-    if (n_all > 1) same_up = !wide_up || mfma_grouped_shape(d, bits, group) ? 4.4 : 0.0;
-    else if (wide_up && packed) least = d > 2048 ? 2.85 : (group == 32 ? 5.0 : 3.4);
-    else if (!wide_up) least = d > 2048 ? 3.6 : (packed ? 10.0 : 5.0);
-    if (least < same_up) least = same_up;
-    return n_tasks * gb >= least * n_all ? 1 : 3;
+    if (n_all == 1 && wide_up) {
+        const double least = d > 4096 ? 2.0 : (bits == 2 ? 1.25 : 1.1);
+        return (n_tasks < 64 ? n_tasks : 64) * gb >= least || n_tasks * gb >= (d > 4096 ? 4.0 : 2.0) ? 1 : 3;
+    }
+    double least;
+    if (n_all == 1) least = d > 2048 ? 3.6 : (packed ? 10.0 : 5.0);
+    else if (wide_up && !mfma_grouped_shape(d, bits, group)) least = 1.6 + 0.5 * gb * n_all;
+    else if (d > 2048) least = wide_up && bits == 3 ? 1.0 : 2.3;
+    else if (wide_up && bits == 4 && group == 32 && d == 1024) least = 1.0;
+    else least = wide_up && bits == 3 ? 3.1 : 4.4;
+    return n_tasks * gb >= least ? 1 : 3;
 }
 
 // Per expert E[ceil(X / chunk)] = sum over k >= 0 of P(X > k * chunk), X binomial, by its normal approximation.  Terms further

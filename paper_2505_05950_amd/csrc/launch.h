@@ -97,6 +97,7 @@ struct FusedArgs {
 };
 int fused_passes(int d, int f, int bits, int n_tasks, int max_tasks = kExpertOrderTasks);  // 0: not fused
 int fused_blocks(int d, int f, int passes);
+bool fused_between_pays(int d, int f, int bits, int group, int n_all, int n_tasks, int slots, int passes);  // (widths between the powers of two)
 hipError_t launch_fused(const FusedArgs& a, int bits, hipStream_t stream);
 
 // S2 for decode batches on the matrix cores: tokens routed to the same expert share one pass over its codes.
