@@ -392,7 +392,7 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
                         if (n + 1 < NL) load_v(n + 1);
 #pragma unroll
                         for (int k = 0; k < 4; ++k) *reinterpret_cast<uint4*>(&stage[(4 * k + q4) * kSpan + 4 * (tok0 ^ (4 * k + q4))]) = vq[n & 1][k];
-                        __builtin_amdgcn_wave_barrier();  // (a wave's LDS accesses stay in order)
+                        wave_lds_order();
                         float vv[2][4];
 #pragma unroll
                         for (int t = 0; t < 2; ++t)
@@ -401,7 +401,7 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
                                 const int ch = max(row[t][i] - row0, 0);
                                 vv[t][i] = stage[tok0 * kSpan + 4 * ((ch >> 2) ^ tok0) + (ch & 3)];
                             }
-                        __builtin_amdgcn_wave_barrier();
+                        wave_lds_order();
                         finish(n, vv);
                     }
                 } else {
