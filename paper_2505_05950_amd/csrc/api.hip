@@ -522,7 +522,7 @@ int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, cons
             const bool split = up_split_pays(e->s.d, e->s.f, e->s.bits, e->s.group, 1, T, w.wp);
             u.groups = groups; u.n_groups = n_groups; u.order = order; u.x = xh; u.v = v;
             u.task_tau = tau; u.mask_words = mask; u.x_frag = base + w.hbuf_off; u.x_sums = base + w.xsum_off;
-            u.T = T; u.n_tasks = T; u.d = e->s.d; u.f = e->s.f; u.slots = 1; u.nt = w.wp.nt;
+            u.n_tasks = T; u.d = e->s.d; u.f = e->s.f; u.slots = 1; u.nt = w.wp.nt;
             u.max_groups = w.wp.max_groups; u.est_groups = w.wp.est_groups;
             u.single = &map.single; u.chunk = w.wp.chunk;
             FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st, split ? launch_up_split(u, e->s.bits, e->s.group, st) : launch_up_wide(u, e->s.bits, e->s.group, st));
@@ -758,7 +758,7 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
             UpWideArgs u{};
             u.groups = wide; u.n_groups = n_wide; u.order = order; u.x = xh; u.v = v;
             u.task_tau = task_tau; u.mask_words = mask; u.x_frag = base + w.hbuf_off; u.x_sums = base + w.xsum_off;
-            u.T = T; u.n_tasks = w.n_tasks; u.d = L->s.d; u.f = L->s.f; u.slots = slots; u.nt = w.wp.nt;
+            u.n_tasks = w.n_tasks; u.d = L->s.d; u.f = L->s.f; u.slots = slots; u.nt = w.wp.nt;
             u.max_groups = w.wp.max_groups; u.est_groups = w.wp.est_groups;
             FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st,
                         w.up_split ? launch_up_split(u, L->s.bits, L->s.group, st) : launch_up_wide(u, L->s.bits, L->s.group, st));

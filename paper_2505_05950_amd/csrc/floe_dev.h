@@ -163,14 +163,18 @@ __device__ __forceinline__ int wave_inclusive_scan(int x, int lane) {
 // ---- memory straight into LDS (global_load_lds_dwordx4).  Destinations are arrays of their own per ring slot: the compiler then knows which
 // requests a read of LDS has to wait for, instead of waiting for all of them.
 #define FLOE_LDS __attribute__((address_space(3)))
-__device__ __forceinline__ void dma16(const void* src, uint4* lds_wave_base) {  // lane l's 16 bytes land at base + 16 l
+__device__ __forceinline__ void dma16(const void* src, void* lds_wave_base) {  // lane l's 16 bytes land at base + 16 l
     __builtin_amdgcn_global_load_lds((const FLOE_GLOBAL void*)src, (FLOE_LDS void*)lds_wave_base, 16, 0, 0);
 }
 template <int N>
-__device__ __forceinline__ void wait_requests_all_but() {  // s_waitcnt vmcnt(N)
+__device__ __forceinline__ void wait_vm_all_but() {  // s_waitcnt vmcnt(N) only (gfx9 encoding: bits 3:0 and 15:14)
     static_assert(N >= 0 && N < 64, "vmcnt has six bits");
-    __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+template <int N>
+__device__ __forceinline__ void wait_requests_all_but() {  // the same, and nothing moves past it
+    __builtin_amdgcn_sched_barrier(0);
+    wait_vm_all_but<N>();
     asm volatile("" ::: "memory");
 }
 __device__ __forceinline__ void meet() {  // barrier alone: what is in flight stays in flight

@@ -51,7 +51,6 @@ constexpr int kFusedThreads = (kFusedProducers + kFusedConsumers) * 64;
 // Queue words are read and written with volatile accesses that are typed as LDS: a volatile access through a generic
 // pointer becomes a FLAT instruction with system scope, which ticks the vector-memory counter as well and makes the
 // producer wait for its code loads whenever it pushes an entry.
-#define FLOE_LDS __attribute__((address_space(3)))
 __device__ __forceinline__ int lds_peek(const int* p) { return *(const volatile FLOE_LDS int*)p; }
 __device__ __forceinline__ void lds_poke(int* p, int v) { *(volatile FLOE_LDS int*)p = v; }
 __device__ __forceinline__ void lds_poke(float* p, float v) { *(volatile FLOE_LDS float*)p = v; }
@@ -61,12 +60,7 @@ __device__ __forceinline__ void lds_poke(float* p, float v) { *(volatile FLOE_LD
 // knows no finer rule for such a load than "wait for all of them before any LDS read that may touch the same
 // array", which would serialise the pipeline; the read-back is therefore issued here by hand, after a wait that
 // names how many younger vector-memory operations may still be outstanding.
-template <int N>
-__device__ __forceinline__ void wait_vm_all_but() {  // s_waitcnt vmcnt(N) only (gfx9 encoding: bits 3:0 and 15:14)
-    static_assert(N >= 0 && N < 64, "vmcnt has six bits");
-    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-// the same for a count that is known once the surrounding loop has been unrolled (a count without a case waits for everything)
+// wait_vm_all_but for a count that is known once the surrounding loop has been unrolled (a count without a case waits for everything)
 __device__ __forceinline__ void wait_vm_all_but(int n) {
 #define FLOE_W(N) case N: wait_vm_all_but<N>(); break;
     switch (n) {
@@ -86,9 +80,6 @@ template <> struct StageTraits<4> { static constexpr int kPieces = 0, kPieceByte
 template <int BITS> constexpr int stage_slot_bytes() { return StageTraits<BITS>::kPieces * StageTraits<BITS>::kPieceBytes * 64; }
 template <int BITS> constexpr bool staged_codes() { return StageTraits<BITS>::kPieces > 0; }
 
-__device__ __forceinline__ void dma16_to_lds(const void* src, void* lds_wave_base) {
-    __builtin_amdgcn_global_load_lds((const FLOE_GLOBAL void*)src, (FLOE_LDS void*)lds_wave_base, 16, 0, 0);
-}
 // Read a lane's piece back.  The compiler does not know that this LDS read exists (it would make it wait for every
 // direct-to-LDS load), so request and arrival are two statements, one pass apart: nothing may touch the registers
 // between them, which the second statement enforces by taking them as in/out operands.
@@ -262,7 +253,7 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
             if constexpr (kStaged) {
                 const unsigned char* src = lane_codes + (size_t)j * (UPC * BITS * 8);
 #pragma unroll
-                for (int pc = 0; pc < St::kPieces; ++pc) dma16_to_lds(src + pc * 16, stage + slot * kSlot + pc * 1024);
+                for (int pc = 0; pc < St::kPieces; ++pc) dma16(src + pc * 16, stage + slot * kSlot + pc * 1024);
                 ld[slot].issue_meta_at(lane_scale, lane_zero, (size_t)j * G);
             } else {
                 ld[slot].issue(e, j, u, G, gshift);

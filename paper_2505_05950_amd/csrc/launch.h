@@ -253,7 +253,7 @@ struct UpWideArgs {
     uint32_t* mask_words;
     void* x_frag;   // h_tiles * 16 * d halves: the activations as operands
     void* x_sums;   // x_operand_sum_bytes()
-    int32_t T, n_tasks, d, f, slots, nt, max_groups, est_groups, parts, workgroups;  // (parts, workgroups: set by the launcher)
+    int32_t n_tasks, d, f, slots, nt, max_groups, est_groups;
     const DevExpert* single;  // one expert that every task belongs to: the launcher fills groups, n_groups and order in as well
     int32_t chunk;            // (single) tasks per group at most
 };
@@ -265,7 +265,7 @@ struct XOperand {
 };
 size_t x_operand_sum_bytes(int tiles, int d, int group);  // tiles: token tiles that the groups can have together
 hipError_t launch_x_operand(const UpWideArgs& a, int bits, int group, XOperand& x, hipStream_t stream);
-hipError_t launch_up_wide(UpWideArgs a, int bits, int group, hipStream_t stream);
+hipError_t launch_up_wide(const UpWideArgs& a, int bits, int group, hipStream_t stream);
 
 // S2 for groups of up to two token tiles, the columns split over the waves of a workgroup (up_split.hip)
 inline bool up_split_shape(int d, int f, int bits, int group) { return up_wide_shape(d, f, bits, group) && d <= 4096; }
@@ -294,7 +294,7 @@ inline bool up_split_pays(int d, int f, int bits, int group, int n_all, int n_ta
     if (bits != 2) return p.nt <= 4 || blocks < 800;
     return grouped ? p.nt == 2 : p.nt <= 2 || blocks < 512;
 }
-hipError_t launch_up_split(UpWideArgs a, int bits, int group, hipStream_t stream);
+hipError_t launch_up_split(const UpWideArgs& a, int bits, int group, hipStream_t stream);
 
 WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared, int max_down);
 WidePlan wide_room(int d, int f, int T, int n_experts, int top_k, int n_shared);

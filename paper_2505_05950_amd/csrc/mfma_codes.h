@@ -1,5 +1,5 @@
 // Codes as matrix-core operands, shared by the kernels that run the up projection of several tokens on the matrix cores
-// (up_gemv_mfma.hip, up_wide.hip): how the codes of a unit are dealt to the lanes of an instruction, and how they become
+// (up_gemv_mfma.hip, up_wide.hip, up_split.hip): how the codes of a unit are dealt to the lanes of an instruction, and how they become
 // fp16 numbers without a conversion.
 #pragma once
 
@@ -156,7 +156,5 @@ __device__ __forceinline__ void deal_units(const uint4 (&q)[VECS], int p, uint32
         }
     }
 }
-
-// TILES channel tiles of 16 per block
 
 }  // namespace floe

@@ -450,7 +450,7 @@ static hipError_t launch_split(const UpWideArgs& a, hipStream_t stream) {
         if (rc != hipSuccess) return rc;
         attr_set[dev].store(true, std::memory_order_release);
     }
-    const long long blocks = (long long)a.est_groups * a.parts * ((32 * mask_words_per_task(a.f) + 16 * TILES - 1) / (16 * TILES));
+    const long long blocks = (long long)a.est_groups * ((a.nt + 1) / 2) * ((32 * mask_words_per_task(a.f) + 16 * TILES - 1) / (16 * TILES));
     const int room = num_cus() * (8 / nw > 1 ? 8 / nw : 1);  // workgroups that the registers hold at a time (eight waves per compute unit)
     int wgs = (int)(blocks < room ? blocks : room);
     if (wgs > 8) wgs &= ~7;  // (see wide_piece)
@@ -462,9 +462,8 @@ static hipError_t launch_split(const UpWideArgs& a, hipStream_t stream) {
     return hipGetLastError();
 }
 
-hipError_t launch_up_split(UpWideArgs a, int bits, int group, hipStream_t stream) {
+hipError_t launch_up_split(const UpWideArgs& a, int bits, int group, hipStream_t stream) {
     if (!up_split_shape(a.d, a.f, bits, group)) return hipErrorInvalidValue;
-    a.parts = (a.nt + 1) / 2;
     const bool g32 = group == 32, two = a.nt > 1;
     if (bits == 2) return two ? launch_split<2, false, 2>(a, stream) : launch_split<2, false, 1>(a, stream);
     if (bits == 3) {

@@ -404,7 +404,7 @@ static hipError_t launch_bits(const UpWideArgs& a, hipStream_t stream) {
     }
 }
 
-hipError_t launch_up_wide(UpWideArgs a, int bits, int group, hipStream_t stream) {
+hipError_t launch_up_wide(const UpWideArgs& a, int bits, int group, hipStream_t stream) {
     if (!up_wide_shape(a.d, a.f, bits, group)) return hipErrorInvalidValue;
     const bool g32 = group == 32;
     if (bits == 2) return launch_bits<2, false>(a, stream);
