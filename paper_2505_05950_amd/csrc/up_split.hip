@@ -1,4 +1,4 @@
-// S2 for token groups of up to 32 tokens: V = X . W_up^Q on the matrix cores with the columns split over the waves of a
+// S2 for token groups of up to 32 tokens, larger ones in parts of 32: V = X . W_up^Q on the matrix cores with the columns split over the waves of a
 // workgroup (Alg. 1 line 2; the paper itself is batch-1, each token keeps its own threshold, mask and result).  The arithmetic
 // is that of up_gemv_mfma.hip: codes masked in place as fp16 subnormals, activations scaled by powers of two, scale and zero
 // applied per quantization group in fp32.
@@ -6,18 +6,19 @@
 //   x_operand_kernel  per task, once: the activations in operand order, their group sums, the factor that undoes the scaling.
 //   up_split_kernel   a wave owns 512 columns (eight units) of every channel its workgroup works on.  The activations that meet
 //                     them are loaded once per group and stay in the wave's registers (64 per token tile; half of the second
-//                     tile's lie in LDS), so that nothing but codes, scales and zeros moves in the loop over channel blocks and
-//                     the next block is on its way while one is worked on.  The partial sums of the waves meet in LDS, two
-//                     buffers in turn, one barrier per block.
+//                     tile's lie in LDS), so that nothing but codes, scales and zeros moves in the loop over channel blocks; those
+//                     of the next block are requested as the vectors of this one are used up, half a block at a time, and all of them are
+//                     waited for at its top (the compiler copies them there).  The partial sums of the waves meet in LDS, two buffers in
+//                     turn, one barrier per block.
 //
 // What bounds it: vector instructions (12 per unit and channel tile to mask codes and widen scale and zero, 8 per token tile to
-// apply them: 29 of 42 us in the loop at 64 tokens on 8 experts of d 4096 f 14336 INT2), before them the cache's accesses: lanes that
-// read 16 bytes each from rows of their own cost one access apiece whatever they use, so a lane brings in two whole units, and the
-// quarters of a channel's lanes one vector of scales or zeros each, handed around by lane exchanges.  Measured, with the kernels in
-// front of it (grouped or wide kernel before / this, us): one expert d 4096 f 14336 INT2, 24 tokens 42.5 / 19.9 (256 workgroups of
-// up_wide.hip had two of sixteen waves at work); 8 such experts, 64 tokens 70 / 65; 64 + 2 experts d 2048 f 1408 INT3 g32, 128 tokens
-// 79 / 53.  Tried: one token tile and half the registers, so that four waves share a SIMD (116 against 73 us at 64 tokens: twice the
-// accesses); the four reducing waves of a block in turn (the same).
+// apply them), before them the cache's accesses: lanes that read 16 bytes each from rows of their own cost one access apiece whatever
+// they use, so a lane brings in two whole units, and the quarters of a channel's lanes one vector of scales or zeros each, handed around by
+// lane exchanges.  Measured, the kernels traced one by one, this one and x_operand in front of it (grouped or wide kernel, with what
+// prepared its activations / the two, us): one expert d 4096 f 14336 INT2, 24 tokens 34 / 15.8 + 3.7 (256 workgroups of up_wide.hip had two
+// of sixteen waves at work); 8 such experts, 64 tokens 72 / 61.6 + 6.0; 64 + 2 experts d 2048 f 1408 INT3 g32, 128 tokens 79 / 44.3 + 8.4.
+// Tried: one token tile and half the registers, so that four waves share a SIMD (64 tokens 116 us: twice the accesses); the four reducing
+// waves of a block in turn (the same).
 //
 // Division of work: the channel blocks of all groups form one sequence that is cut into pieces of equal cost, one workgroup each.
 #include <atomic>
@@ -150,11 +151,12 @@ __global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restri
     const int blocks = (32 * nwords + kCh - 1) / kCh;    // whole mask words
     FLOE_TL(0);
     // Equal pieces by what a block costs with one and with two token tiles and by what the start of a part costs.  INT2 with two channel
-    // tiles per block: vector instructions, 20 and 28 per unit and channel tile, and the rest alike; the wider codes, one channel tile
-    // and more to unpack, 7 to 8 (8 experts d 4096 f 14336 INT4, 150 tokens: 544 us with 3 to 4, 534; 190 tokens 544, 533).
+    // tiles per block: vector instructions, 20 and 28 per unit and channel tile, and the rest alike: 3 to 4.  The wider codes have one channel
+    // tile and more to unpack, 7 to 8 (us with 3 to 4 / 7 to 8, 8 experts d 4096 f 14336 INT4 g64, 150 tokens 544 / 534; g32 552 / 545; INT3 g64,
+    // 6 experts, 130 tokens 425 / 420); INT3 with groups of 32 again 3 to 4 (64 + 2 experts d 2048 f 1408, 128 tokens 240 / 243).
     const int ng = n_groups[0];
     constexpr int kStart = 12;
-    auto weight = [](int n) { return n > 16 ? 8 : (BITS == 2 ? 6 : 7); };
+    auto weight = [](int n) { return n > 16 ? 8 : (BITS == 2 || (BITS == 3 && G32) ? 6 : 7); };
     // a group of more than 32 tokens comes in parts of 32 and a last one of the rest: what the last one and a full one weigh
     auto parts_of = [](int n) { return (n + 31) >> 5; };
     const int full_weight = weight(32) * blocks + kStart;
