@@ -745,10 +745,12 @@ __global__ __launch_bounds__(256) void wide_single_kernel(DevExpert e, int n_tas
 // ---------------------------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------------------------
-// Token tiles per group: the fewest expected reads of the experts' rows, weighed by what a read costs.  Measured (8
-// experts, d = 4096, f = 14336, 90 %, gate + down): 64 tokens 330 us with one tile (12 groups), 293 with two (8
-// groups), 308 with three; 512 tokens 637 us with five tiles (16 groups, the two of an expert share rows in the L2),
-// 565 with ten (8 groups: each workgroup passes twice the activations through LDS).
+// Token tiles per group: the fewest expected reads of the experts' rows, weighed by what a read costs.  Calls with each number of
+// tiles forced, us: 8 experts d 4096 f 14336 INT2 at 85 %, 56 tokens 410 (one tile) 390 394 404 405 416 (ten), 72 tokens 503 419 421 430 432
+// 445, 512 tokens 2611 1663 1342 1126 799 740; 64 + 2 experts d 2048 f 1408 INT3 g32, 148 tokens 272 257 259 265 319 355.  Over 255 calls
+// the choice costs 4 % on average against the best of the six.  It misses most where one number holds a group and a smaller one its
+// halves: 8 experts, 320 tokens 718 (five, taken) 608 (ten); one expert of the same size, 160 tokens 169 (five) 198 (ten, taken), 200
+// tokens 240 (five, taken) 203 (ten).
 static int wide_tiles_for(int T, int n_experts, int top_k, int n_shared, double& groups) {
     double best = 0.0;
     int best_nt = 0;
