@@ -65,17 +65,18 @@ int fused_passes(int d, int f, int bits, int n_tasks, int max_tasks) {
 //     INT4 g64 d 2560 f 2048, 48 + 2 experts top-6, 18 tokens (512 in two rounds, 288 if it were even)  1.72 2.18 2.84 3.35
 //     INT3 g32 d 1536 f 2048, the same (256, even 144)                     1.05 1.24 1.43 1.54
 //     just inside: the same, 12 tokens (128, even 96)                      0.89 0.96 1.09 1.16
-//   many passes, where tokens share rows on the matrix cores with an up projection of their own: those
-//     one expert INT3 g64 d 2560 f 7000, 16 tokens (109 passes)            64/93/60  61/68/60  60/54/56  59/49/52
-//     one expert INT2 g64 d 2560 f 14336, 10 tokens (140) 74/124/75 65/88/71 63/64/65 62/54/56, 16 (224) 97/161/76 90/110/75 87/87/69 86/74/63
-//     INT4 g64 d 2560 f 8000, 8 experts, 16 tokens (250)                   0.97 0.97 1.17 1.24 times the wide kernels; 12 (188) 0.92 0.92 1.01 1.04
+//   many passes, where tokens are enough for the wide kernels by their own line: those, but for INT3, whose v the matrix cores form
+//   less accurately (1e-5 against 8e-8 here)
+//     one expert INT2 g64 d 2560 f 14336, 16 tokens (224 passes)           97/161/76  90/110/75  87/87/69  86/74/63
+//     one expert INT4 g64 d 3072 f 14336, 16 tokens (224)                  1.60 1.51 1.53 1.71 times the wide kernels (INT3; INT4 alike)
+//     INT4 g64 d 2560 f 8000, 8 experts, 16 tokens (250)                   0.97 0.97 1.17 1.24; 12 (188) 0.92 0.92 1.01 1.04
 //     INT2 g64 d 2560 f 12000, 16 experts, 16 tokens (375)                 0.80 0.88 1.07 (80, 90, 95 %)
 bool fused_between_pays(int d, int f, int bits, int group, int n_all, int n_tasks, int slots, int passes) {
     const int cus = num_cus() * fused_wgs_per_cu;
     if ((long long)fused_blocks(d, f, passes) * n_tasks > cus) return false;  // a second round
     const double even = (double)n_tasks * f / ((double)cus * fused_producers * (64 / fused_lanes(d)));
     if (passes > kFusedMinPasses && passes > 1.25 * even + 20.0) return false;
-    const bool wide = union_mode() == 0 && n_tasks >= 2 * slots && up_wide_shape(d, f, bits, group) && mask_words_per_task(f) <= kWideMaxMaskWords &&
+    const bool wide = union_mode() == 0 && bits != 3 && n_tasks >= 2 * slots && up_wide_shape(d, f, bits, group) && mask_words_per_task(f) <= kWideMaxMaskWords &&
                       union_kernels_for(n_all, n_tasks, d, f, bits, group) == 1;
     if (!wide) return true;
     return passes < (n_all == 1 ? (bits == 2 ? 170 : 105) : (bits == 2 ? 300 : 200));

@@ -299,11 +299,6 @@ void set_union_mode(int m) { g_union_mode.store(m >= 0 && m <= 3 ? m : 0, std::m
 // the bytes G of the experts' rows, and what the up projections on both sides cost.  Measured at 85 %: about 1500 layer calls and 870
 // calls of one expert, forced each way; a line is where the kinds of shape named with it break even, and costs 0.5 % on average
 // over the calls around it.  one-token / wide, by q G:
-//   layers without a grouped up projection (widths between the powers of two and beyond 4096, where the other way runs the generic one):
-//   1.6 + G / 2 (many experts with few tokens each leave the groups small)
-//     d 1536 f 4000 INT2 (8 experts): 1.2 0.82, 1.6 0.94, 2.0 1.07, 3.1 1.44;  d 3072 f 4000 INT4 (8): 2.0 1.24, 3.9 1.64
-//     d 2560 f 1200 INT3 (8): 1.0 1.08, 1.6 1.33;  d 5120 f 1200 INT2 (8): 1.6 0.97, 2.0 1.12, 3.9 1.37
-//     d 1536 f 2048 INT4 (65 experts, G 0.82, 2.3 tokens each): 1.9 0.89;  d 1536 f 1408 INT2 (66, G 0.57): 2.8 1.06, 4.6 1.31
 //   d 4096: 2.3, INT3, whose grouped kernel is bound by its unpacking, 1.0
 //     f 4000 INT2 (4): 2.1 0.80, 2.6 1.10, 5.2 1.30;  f 1200 INT4 g64 (8): 0.9 0.99, 1.9 1.12;  f 4000 INT4 g128 (8): 2.6 1.00, 5.2 1.09
 //     f 1200 INT3 g64 (8): 0.9 1.08, 2.5 1.30;  f 10000 INT8 d 3072 (4): 2.0 0.85, 2.5 1.02, 4.9 1.14
@@ -311,32 +306,38 @@ void set_union_mode(int m) { g_union_mode.store(m >= 0 && m <= 3 ? m : 0, std::m
 //     d 1024 f 4000 INT2 (8): 2.6 0.87, 3.4 0.98, 4.5 1.13;  d 2048 f 4000 INT4 g64 (16): 3.1 0.90, 4.2 0.97, 5.2 1.06
 //     d 2048 f 1408 INT2 (66): 4.6 0.94, 6.1 1.06;  d 2048 f 4000 INT3 g32 (16): 2.6 1.00, 3.1 1.14, 5.2 1.17
 //     d 1024 INT4 g32, whose grouped kernel takes two to three times as long as the others: 1.0 (f 4000, 4 experts: 1.0 1.05, 2.2 1.58)
-//   one expert, whose tokens otherwise go through the packed or generic up projection one by one: 1.1, INT2 1.25, on up to 64 tokens (more
-//   take more partial results: from 2.0 on in any case)
-//     d 1024 f 14336 INT2: 1.0 (17 tokens) 0.94, 1.2 (20) 1.02, 1.9 (32) 1.52;  d 4096 f 4000 INT3 g64: 1.1 (17) 1.20, 2.1 (32) 1.39
-//     d 2048 f 5632 INT4 and d 2048 f 8000: 1.1 (17) 1.03, 1.6 (24) 1.18, 2.6 (40) 1.62
-//     d 2560 f 1408 INT2: 0.9 (64) 0.82, 1.8 (128) 1.15, 2.9 (200) 1.88;  d 2048 f 1408 INT3 g32: 1.5 (128) 0.88, 2.3 (200) 1.39
-//     beyond d 4096, where the wide side has no split up projection, 2.0, and 4.0 with more than 64 tokens
-//     d 5120 f 4000 INT2: 1.4 (17) 1.00, 2.3 (28) 1.14;  f 1408: 1.8 (64) 0.81, 2.8 (96) 0.81, 4.6 (160) 1.05
+//   one expert, whose tokens otherwise go through the packed up projection one by one: 1.1, INT2 1.25, on up to 64 tokens (more take more
+//   partial results: from 2.0 on in any case)
+//     d 1024 f 14336 INT2: 1.0 (17 tokens) 0.94, 1.2 (20) 1.02, 1.9 (32) 1.52;  d 4096 f 1408 INT4 g32: 0.9 (40) 0.95, 1.5 (64) 1.06
+//     d 2048 f 8000 INT4: 1.1 (17) 1.03, 1.6 (24) 1.18, 2.6 (40) 1.62;  d 4096 f 4000 INT2: 1.1 (17) 1.08, 2.1 (32) 1.21
 //   one expert without a wide up projection: 3.6, for the smaller widths 5 (generic) and 10 (packed up projection)
 //     d 4096 f 4000 INT4 g128: 2.1 (32 tokens) 0.91, 4.2 (64) 1.05;  d 4096 f 1408 INT8: 3.7 (160) 0.98, 4.6 (200) 1.24
 //     d 1536 f 4000 INT4 g128: 2.4 (96) 0.79, 4.9 (200) 1.05;  d 2048 f 8000 INT4 g128: 4.2 (64) 0.96, 8.4 (128) 1.10
+// Where the wide way's v is less accurate than the other's the line lies by that, not by the time: the matrix cores drop low bits of
+// products with subnormals, error of v against 64 bits (norm) INT2 2e-7 .. 3.6e-7, INT4 2.8e-7 .. 6.5e-7, INT3, whose fields lie lowest,
+// 0.9e-5 .. 2.9e-5.  The packed up projection has 1.4e-6 .. 2.8e-6, the generic one 7e-8 .. 8e-8; the grouped one is the same arithmetic.
+//   widths without packed and grouped kernels, whose other way is the generic one: 1.9 + 4 G, the former line
+//     one-token / wide there: 8 experts d 3072 f 4000 INT2 (G 0.39) 3.1 1.27, 3.9 1.51;  d 1536 f 4000 INT4 (0.20) 2.0 1.21, 3.1 1.53
+//     and with more than 64 tokens on one expert of a width beyond 4096, which has no split up projection, not below 4.0: d 5120 f 1408
+//     INT2: 2.8 (96) 0.81, 4.6 (160) 1.05
+//   one expert INT3 at the packed widths: 2.85, for the smaller widths 3.4, with groups of 32 5, the former lines
+//     d 2048 f 4000 INT3 g32: 2.1 (64) 1.32, 4.2 (128) 1.77;  d 4096 f 4000 INT3 g64: 2.1 (32) 1.39, 3.1 (48) 1.99
 int union_kernels_for(int n_all, int n_tasks, int d, int f, int bits, int group) {
     const int m = union_mode();
     if (m != 0) return m;
-    const double gb = 4e-9 * d * (double)f;  // of one expert: q G = n_tasks * gb
+    const double gb = 4e-9 * d * (double)f, qg = n_tasks * gb;  // gb: of one expert
     const bool wide_up = up_wide_shape(d, f, bits, group), packed = packed_fast_shape(d, bits, group);
-    if (n_all == 1 && wide_up) {
-        const double least = d > 4096 ? 2.0 : (bits == 2 ? 1.25 : 1.1);
-        return (n_tasks < 64 ? n_tasks : 64) * gb >= least || n_tasks * gb >= (d > 4096 ? 4.0 : 2.0) ? 1 : 3;
+    if (wide_up && !packed) {
+        if (n_all == 1 && d > 4096 && n_tasks > 64 && 64 * gb < 2.0 && qg < 4.0) return 3;
+        return qg >= 1.9 + 4.0 * gb * n_all ? 1 : 3;
     }
+    if (n_all == 1 && wide_up && bits != 3) return (n_tasks < 64 ? n_tasks : 64) * gb >= (bits == 2 ? 1.25 : 1.1) || qg >= 2.0 ? 1 : 3;
     double least;
-    if (n_all == 1) least = d > 2048 ? 3.6 : (packed ? 10.0 : 5.0);
-    else if (wide_up && !mfma_grouped_shape(d, bits, group)) least = 1.6 + 0.5 * gb * n_all;
+    if (n_all == 1) least = wide_up ? (d > 2048 ? 2.85 : (group == 32 ? 5.0 : 3.4)) : (d > 2048 ? 3.6 : (packed ? 10.0 : 5.0));
     else if (d > 2048) least = wide_up && bits == 3 ? 1.0 : 2.3;
     else if (wide_up && bits == 4 && group == 32 && d == 1024) least = 1.0;
     else least = wide_up && bits == 3 ? 3.1 : 4.4;
-    return n_tasks * gb >= least ? 1 : 3;
+    return qg >= least ? 1 : 3;
 }
 
 // Per expert E[ceil(X / chunk)] = sum over k >= 0 of P(X > k * chunk), X binomial, by its normal approximation.  Terms further
