@@ -320,6 +320,7 @@ void set_union_mode(int m) { g_union_mode.store(m >= 0 && m <= 3 ? m : 0, std::m
 //     one-token / wide there: 8 experts d 3072 f 4000 INT2 (G 0.39) 3.1 1.27, 3.9 1.51;  d 1536 f 4000 INT4 (0.20) 2.0 1.21, 3.1 1.53
 //     and with more than 64 tokens on one expert of a width beyond 4096, which has no split up projection, not below 4.0: d 5120 f 1408
 //     INT2: 2.8 (96) 0.81, 4.6 (160) 1.05
+//   INT3 layers with fewer than 3.5 tasks per expert, whose other way is the packed one (mfma_batch_pays): 1.9 + 4 G
 //   one expert INT3 at the packed widths: 2.85, for the smaller widths 3.4, with groups of 32 5, the former lines
 //     d 2048 f 4000 INT3 g32: 2.1 (64) 1.32, 4.2 (128) 1.77;  d 4096 f 4000 INT3 g64: 2.1 (32) 1.39, 3.1 (48) 1.99
 int union_kernels_for(int n_all, int n_tasks, int d, int f, int bits, int group) {
@@ -333,7 +334,8 @@ int union_kernels_for(int n_all, int n_tasks, int d, int f, int bits, int group)
     }
     if (n_all == 1 && wide_up && bits != 3) return (n_tasks < 64 ? n_tasks : 64) * gb >= (bits == 2 ? 1.25 : 1.1) || qg >= 2.0 ? 1 : 3;
     double least;
-    if (n_all == 1) least = wide_up ? (d > 2048 ? 2.85 : (group == 32 ? 5.0 : 3.4)) : (d > 2048 ? 3.6 : (packed ? 10.0 : 5.0));
+    if (n_all > 1 && wide_up && bits == 3 && 2 * n_tasks < 7 * n_all) least = 1.9 + 4.0 * gb * n_all;  // (no grouped kernel: see above)
+    else if (n_all == 1) least = wide_up ? (d > 2048 ? 2.85 : (group == 32 ? 5.0 : 3.4)) : (d > 2048 ? 3.6 : (packed ? 10.0 : 5.0));
     else if (d > 2048) least = wide_up && bits == 3 ? 1.0 : 2.3;
     else if (wide_up && bits == 4 && group == 32 && d == 1024) least = 1.0;
     else least = wide_up && bits == 3 ? 3.1 : 4.4;

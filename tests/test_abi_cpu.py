@@ -203,6 +203,7 @@ def test_one_kernel_between_the_powers_of_two_is_not_a_condition(lib, d, f, bits
     ((4096, 4000, 3, 64), (8, 2, 0), (), (17, 40)),
     ((4096, 1200, 4, 64), (8, 2, 0), (24, 40), (64, 136)),
     ((1024, 4000, 4, 32), (4, 2, 0), (), (40, 68)),
+    ((2048, 1408, 3, 32), (128, 6, 2), (40,), (80,)),                    # (40: 2.5 tasks per expert, no grouped kernel: the packed one is more accurate)
     ((2560, 8000, 4, 64), (8, 2, 0), (6, 9, 24), (32, 64)),
     ((2560, 2048, 2, 64), (48, 6, 2), (4, 8, 18), (40,)),                # (18: the fused launch would be uneven)
 ])
