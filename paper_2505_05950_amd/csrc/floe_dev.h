@@ -184,14 +184,6 @@ __device__ __forceinline__ void meet() {  // barrier alone: what is in flight st
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// Between LDS accesses of one wave that other lanes wrote: the hardware keeps them in order, and so must the compiler, also where the two
-// sides see the bytes as different types.
-__device__ __forceinline__ void wave_lds_order() {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_wave_barrier();
-    asm volatile("" ::: "memory");
-}
-
 // ---- equal division of a launch's work (wide_batch.hip, up_wide.hip)
 // a pointer that every lane holds alike, as a scalar (loads then take it as their base and a 32-bit offset per lane)
 __device__ __forceinline__ const unsigned char* scalar_ptr(const void* p) {

@@ -391,8 +391,12 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
                     for (int n = 0; n < NL; ++n) {
                         if (n + 1 < NL) load_v(n + 1);
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) *reinterpret_cast<uint4*>(&stage[(4 * k + q4) * kSpan + 4 * (tok0 ^ (4 * k + q4))]) = vq[n & 1][k];
-                        wave_lds_order();
+                        for (int k = 0; k < 4; ++k) {
+                            // (stored as a native vector of what is read back: a wave's LDS accesses stay in order, and the compiler
+                            // must not take the two for different objects)
+                            *reinterpret_cast<f32x4*>(&stage[(4 * k + q4) * kSpan + 4 * (tok0 ^ (4 * k + q4))]) = __builtin_bit_cast(f32x4, vq[n & 1][k]);
+                        }
+                        __builtin_amdgcn_wave_barrier();
                         float vv[2][4];
 #pragma unroll
                         for (int t = 0; t < 2; ++t)
@@ -401,7 +405,7 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
                                 const int ch = max(row[t][i] - row0, 0);
                                 vv[t][i] = stage[tok0 * kSpan + 4 * ((ch >> 2) ^ tok0) + (ch & 3)];
                             }
-                        wave_lds_order();
+                        __builtin_amdgcn_wave_barrier();
                         finish(n, vv);
                     }
                 } else {
