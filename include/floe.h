@@ -107,8 +107,8 @@ int floe_profile_kernel(int kernel_id, void* start_event, void* stop_event);
  *                            1 = whenever the shape allows, 2 = never (one pass per (token, slot)).
  *   FLOE_TUNE_FUSED_TASKS    up to how many (token, slot) pairs a layer call runs Alg. 1 in one kernel (every workgroup
  *                            takes a block of channels of one pair through all steps) instead of the batch kernels:
- *                            0 = the library's rule (16, or four per expert if that is more), else the limit itself
- *                            (at most 256).
+ *                            0 = the library's rule (16, or four per expert if that is more; at d 1536, 2560 and 3072
+ *                            not where the other kernels measured faster), else the limit itself (at most 256).
  * Process-wide.  Workspace sizes depend on FLOE_TUNE_UNION_KERNELS, FLOE_TUNE_GROUPED_GEMV and FLOE_TUNE_FUSED_TASKS: do not change them
  * between a *_workspace_bytes query and the decode call that uses the workspace.  Unknown key or value: FLOE_EINVAL.
  */
