@@ -296,49 +296,51 @@ void set_union_mode(int m) { g_union_mode.store(m >= 0 && m <= 3 ? m : 0, std::m
 // The wide kernels read a row once for a whole group, but bring three more launches with their prologues and the partial results
 // of all pieces (half a megabyte per token of a group, whatever the layer); the one-token kernels in expert order read the rows of
 // a task each.  What decides is therefore the rows that the tasks would read, in GB with all channels: q tasks per expert times
-// the bytes G of the experts' rows, and what the up projections on both sides cost.  Measured at 85 %: about 1500 layer calls and 870
-// calls of one expert, forced each way; a line is where the kinds of shape named with it break even, and costs 0.5 % on average
-// over the calls around it.  one-token / wide, by q G:
-//   d 4096: 2.3, INT3, whose grouped kernel is bound by its unpacking, 1.0
-//     f 4000 INT2 (4): 2.1 0.80, 2.6 1.10, 5.2 1.30;  f 1200 INT4 g64 (8): 0.9 0.99, 1.9 1.12;  f 4000 INT4 g128 (8): 2.6 1.00, 5.2 1.09
-//     f 1200 INT3 g64 (8): 0.9 1.08, 2.5 1.30;  f 10000 INT8 d 3072 (4): 2.0 0.85, 2.5 1.02, 4.9 1.14
-//   d 1024 and 2048: 4.4, INT3 3.1
-//     d 1024 f 4000 INT2 (8): 2.6 0.87, 3.4 0.98, 4.5 1.13;  d 2048 f 4000 INT4 g64 (16): 3.1 0.90, 4.2 0.97, 5.2 1.06
-//     d 2048 f 1408 INT2 (66): 4.6 0.94, 6.1 1.06;  d 2048 f 4000 INT3 g32 (16): 2.6 1.00, 3.1 1.14, 5.2 1.17
-//     d 1024 INT4 g32, whose grouped kernel takes two to three times as long as the others: 1.0 (f 4000, 4 experts: 1.0 1.05, 2.2 1.58)
-//   one expert, whose tokens otherwise go through the packed up projection one by one: 1.1, INT2 1.25, on up to 64 tokens (more take more
-//   partial results: from 2.0 on in any case)
-//     d 1024 f 14336 INT2: 1.0 (17 tokens) 0.94, 1.2 (20) 1.02, 1.9 (32) 1.52;  d 4096 f 1408 INT4 g32: 0.9 (40) 0.95, 1.5 (64) 1.06
-//     d 2048 f 8000 INT4: 1.1 (17) 1.03, 1.6 (24) 1.18, 2.6 (40) 1.62;  d 4096 f 4000 INT2: 1.1 (17) 1.08, 2.1 (32) 1.21
-//   one expert without a wide up projection: 3.6, for the smaller widths 5 (generic) and 10 (packed up projection)
+// the bytes G of the experts' rows, and what the up projections on both sides cost.  Measured, about 3000 calls of layers and 1200 of
+// one expert, forced each way, at sparsities of 70, 85 and 95 %: the sparser, the fewer rows there are to share and the later the wide
+// way pays.  A line is where it is no slower at 95 %.  one-token / wide, by q G, at 70, 85 and 95 %:
+//   layers: 1.9 + 4 G, but at least 4.4 at the widths of the grouped up projection and where there is no wide one
+//     8 experts  d 4096 f 4000 INT2 (G 0.52): q G 2.6 1.4 1.04 0.9, 5.2 1.6 1.14 0.95, 6.3 1.8 1.10 1.0;  d 2048 f 4000 INT4 g64: 4.2 0.93 and 5.2 1.05 at 85 %
+//     d 4096 INT4 g128, 4 to 16 experts: 2.3 .. 2.8 1.28 - 0.90, 4.6 .. 5.4 1.47 - 0.93;  d 2048 INT3 g32: 2.8 .. 3.4 1.38 1.1 0.96, 4.6 .. 5.4 1.49 1.17 1.03
+//     without a grouped kernel (1.9 + 4 G alone): d 3072 f 4000 INT2 (8 experts, G 0.39) 3.1 1.27, 3.9 1.51 at 85 %
+//   d 4096 INT3, whose grouped kernel is bound by its unpacking: 2.0
+//     f 1200 .. 10000, 4 to 16 experts: 1.3 .. 1.8 1.28 1.15 1.05, 2.3 .. 2.8 1.5 1.25 1.09, 4.6 .. 5.4 1.75 1.45 1.25
+//   d 1024 INT4 g32, whose grouped kernel takes two to three times as long as the others: 1.0
+//     f 1200 .. 10000, 4 to 66 experts: 0.9 .. 1.3 1.30 1.1 1.09, 2.3 .. 2.8 1.83 1.65 1.50
+//   one expert, whose tokens otherwise go through the packed up projection one by one: 2.25 on up to 64 tokens (INT4 from 1.8
+//   on, INT2 from 2.0), more take more partial results: 3.0 in any case
+//     INT2 d 1024 f 14336: 1.6 (28 tokens) 1.52 1.07 0.91, 2.3 (40) 2.39 1.56 1.10;  d 4096 f 4000: 1.6 (24) 1.51 1.18 0.97, 2.1 (32) 1.59 1.21 1.02
+//     INT4 d 2048 f 8000: 1.3 (20) 1.41 1.09 0.94, 1.8 (28) 1.56 1.25 1.09;  d 4096 f 1408 g32: 1.5 (64) 1.30 1.06 0.89, 2.2 (96) 1.42 1.13 0.95, 3.0 (128) 1.71 1.38 1.12
+//     INT2 d 2048 f 1408: 1.8 (160) 1.08 0.86 0.71, 3.0 (256) 1.76 1.37 1.19
+//   one expert without a wide up projection: 3.6, for the smaller widths 5 (generic) and 10 (packed up projection); at 85 %
 //     d 4096 f 4000 INT4 g128: 2.1 (32 tokens) 0.91, 4.2 (64) 1.05;  d 4096 f 1408 INT8: 3.7 (160) 0.98, 4.6 (200) 1.24
 //     d 1536 f 4000 INT4 g128: 2.4 (96) 0.79, 4.9 (200) 1.05;  d 2048 f 8000 INT4 g128: 4.2 (64) 0.96, 8.4 (128) 1.10
-// Where the wide way's v is less accurate than the other's the line lies by that, not by the time: the matrix cores drop low bits of
+// Where the wide way's v is less accurate than the other's, the line lies by that and not by the time: the matrix cores drop low bits of
 // products with subnormals, error of v against 64 bits (norm) INT2 2e-7 .. 3.6e-7, INT4 2.8e-7 .. 6.5e-7, INT3, whose fields lie lowest,
 // 0.9e-5 .. 2.9e-5.  The packed up projection has 1.4e-6 .. 2.8e-6, the generic one 7e-8 .. 8e-8; the grouped one is the same arithmetic.
-//   widths without packed and grouped kernels, whose other way is the generic one: 1.9 + 4 G, the former line
-//     one-token / wide there: 8 experts d 3072 f 4000 INT2 (G 0.39) 3.1 1.27, 3.9 1.51;  d 1536 f 4000 INT4 (0.20) 2.0 1.21, 3.1 1.53
-//     and with more than 64 tokens on one expert of a width beyond 4096, which has no split up projection, not below 4.0: d 5120 f 1408
-//     INT2: 2.8 (96) 0.81, 4.6 (160) 1.05
-//   INT3 layers with fewer than 3.5 tasks per expert, whose other way is the packed one (mfma_batch_pays): 1.9 + 4 G
-//   one expert INT3 at the packed widths: 2.85, for the smaller widths 3.4, with groups of 32 5, the former lines
-//     d 2048 f 4000 INT3 g32: 2.1 (64) 1.32, 4.2 (128) 1.77;  d 4096 f 4000 INT3 g64: 2.1 (32) 1.39, 3.1 (48) 1.99
+//   widths whose other way is the generic one: 1.9 + 4 G stays (85 %: d 1536 f 4000 INT4, 8 experts, 2.0 1.21, 3.1 1.53); with more than 64
+//   tokens on one expert of a width beyond 4096, which has no split up projection, not below 4.0 (d 5120 f 1408 INT2: 2.8 0.81, 4.6 1.05)
+//   INT3 layers with fewer than 3.5 tasks per expert, whose other way is the packed one (mfma_batch_pays): 1.9 + 4 G stays
+//   one expert INT3 at the packed widths: 2.85, for the smaller widths 3.4, with groups of 32 5 (85 %: d 4096 f 4000 g64 2.1 1.39, 3.1 1.99)
 int union_kernels_for(int n_all, int n_tasks, int d, int f, int bits, int group) {
     const int m = union_mode();
     if (m != 0) return m;
     const double gb = 4e-9 * d * (double)f, qg = n_tasks * gb;  // gb: of one expert
     const bool wide_up = up_wide_shape(d, f, bits, group), packed = packed_fast_shape(d, bits, group);
-    if (wide_up && !packed) {
-        if (n_all == 1 && d > 4096 && n_tasks > 64 && 64 * gb < 2.0 && qg < 4.0) return 3;
-        return qg >= 1.9 + 4.0 * gb * n_all ? 1 : 3;
+    double least = 1.9 + 4.0 * gb * n_all;
+    if (n_all == 1) {
+        if (wide_up && packed && bits != 3)
+            return (n_tasks < 64 ? n_tasks : 64) * gb >= 2.25 || qg >= 3.0 ? 1 : 3;
+        if (wide_up && d > 4096 && n_tasks > 64 && 64 * gb < 2.0) least = 4.0;
+        else if (wide_up && packed) least = d > 2048 ? 2.85 : (group == 32 ? 5.0 : 3.4);
+        else if (!wide_up) least = d > 2048 ? 3.6 : (packed ? 10.0 : 5.0);
+    } else if (wide_up && d == 4096 && bits == 3 && 2 * n_tasks >= 7 * n_all) {
+        least = 2.0;
+    } else if (wide_up && d == 1024 && bits == 4 && group == 32) {
+        least = 1.0;
+    } else if ((!wide_up || packed) && least < 4.4) {
+        least = 4.4;
     }
-    if (n_all == 1 && wide_up && bits != 3) return (n_tasks < 64 ? n_tasks : 64) * gb >= (bits == 2 ? 1.25 : 1.1) || qg >= 2.0 ? 1 : 3;
-    double least;
-    if (n_all > 1 && wide_up && bits == 3 && 2 * n_tasks < 7 * n_all) least = 1.9 + 4.0 * gb * n_all;  // (no grouped kernel: see above)
-    else if (n_all == 1) least = wide_up ? (d > 2048 ? 2.85 : (group == 32 ? 5.0 : 3.4)) : (d > 2048 ? 3.6 : (packed ? 10.0 : 5.0));
-    else if (d > 2048) least = wide_up && bits == 3 ? 1.0 : 2.3;
-    else if (wide_up && bits == 4 && group == 32 && d == 1024) least = 1.0;
-    else least = wide_up && bits == 3 ? 3.1 : 4.4;
     return qg >= least ? 1 : 3;
 }
 
