@@ -68,9 +68,9 @@ int fused_passes(int d, int f, int bits, int n_tasks, int max_tasks) {
 //   many passes, where tokens are enough for the wide kernels by their own line: those, but for INT3, whose v the matrix cores form
 //   less accurately (1e-5 against 8e-8 here)
 //     one expert INT2 g64 d 2560 f 14336, 16 tokens (224 passes)           97/161/76  90/110/75  87/87/69  86/74/63
-//     one expert INT4 g64 d 3072 f 14336, 16 tokens (224)                  1.60 1.51 1.53 1.71 times the wide kernels (INT3; INT4 alike)
-//     INT4 g64 d 2560 f 8000, 8 experts, 16 tokens (250)                   0.97 0.97 1.17 1.24; 12 (188) 0.92 0.92 1.01 1.04
-//     INT2 g64 d 2560 f 12000, 16 experts, 16 tokens (375)                 0.80 0.88 1.07 (80, 90, 95 %)
+//     one expert INT4 g64 d 3072 f 14336, 16 tokens (224)                  112/154/76 at 70 %, 99/87/62 at 95 %
+//     layers, which reach that line with two or three experts only, break even later: INT4 g64 d 2560 f 8000, 8 experts, 16 tokens (250)
+//     0.97 0.97 1.17 1.24 times the wide kernels, 12 (188) 0.92 0.92 1.01 1.04; INT2 f 12000, 16 experts, 16 tokens (375) 0.80 0.88 1.07
 bool fused_between_pays(int d, int f, int bits, int group, int n_all, int n_tasks, int slots, int passes) {
     const int cus = num_cus() * fused_wgs_per_cu;
     if ((long long)fused_blocks(d, f, passes) * n_tasks > cus) return false;  // a second round
