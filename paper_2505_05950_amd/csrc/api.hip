@@ -91,7 +91,7 @@ TaskMap single_map(const floe_expert* e) {
 // workspace of the one-expert entry points: [v: T*f floats][mask words][counts][idx when not fused][partial: T*nblk*d floats]
 struct ExpertWs {
     size_t v_off, mask_off, count_off, idx_off, partial_off, total;
-    size_t order_off, wgroups_off, xsum_off, urow_off, ucount_off, hbuf_off, hmax_off, trows_off;  // wide path
+    size_t order_off, ptau_off, wgroups_off, xsum_off, rows_off, segs_off, hbuf_off, hmax_off, trows_off;  // wide path
     int nblk, fused_passes, nblk_fused;
     bool wide;  // many tokens: one read of every row that any of a group of tokens selected (wide_batch.hip)
     WidePlan wp;
@@ -102,7 +102,7 @@ bool mask_path_ok(int f);
 enum class Wide { kChosen, kNone, kRoom };
 // h of the wide groups; before it is formed the activations that the up projection reads lie in the same place
 size_t wide_h_bytes(const WidePlan& p, int d) {
-    const size_t h = (size_t)p.h_tiles * p.pairs * 128 * sizeof(uint4), x = (size_t)p.h_tiles * 16 * d * 2;
+    const size_t h = p.h_vecs * sizeof(uint4), x = (size_t)p.h_tiles * 16 * d * 2;
     return h > x ? h : x;
 }
 // partial results; before them the activations that the gate kernel reads
@@ -136,10 +136,11 @@ ExpertWs expert_ws(const floe_shape* s, int T, Wide form = Wide::kChosen, bool f
     if (w.wide) {
         w.wp = form == Wide::kRoom ? wide_room(s->d, s->f, T, 1, 1, 0) : wide_plan(s->d, s->f, T, 1, 1, 0, 0);
         w.order_off = o;   o += align_up((size_t)T * 4);
+        w.ptau_off = o;    o += align_up((size_t)T * 8);  // thresholds and weights by position
         w.wgroups_off = o; o += align_up((size_t)w.wp.max_groups * sizeof(WideGroup) + 4);
         w.xsum_off = o;    o += align_up(x_operand_sum_bytes(w.wp.h_tiles, s->d, s->group));
-        w.urow_off = o;    o += align_up((size_t)w.wp.max_groups * s->f * 4);
-        w.ucount_off = o;  o += align_up((size_t)w.wp.max_groups * 4);
+        w.rows_off = o;    o += align_up(w.wp.row_slots * 32 * 4);
+        w.segs_off = o;    o += align_up((size_t)w.wp.segments * sizeof(int4));
         w.hbuf_off = o;    o += align_up(wide_h_bytes(w.wp, s->d));
         w.hmax_off = o;    o += align_up((size_t)T * 4);
         w.trows_off = o;   o += align_up((size_t)T * sizeof(int2));
@@ -178,7 +179,7 @@ bool mask_path_ok(int f) { return mask_words_per_task(f) <= 2048; }
 // workspace of the layer: per-task table, counts, mask words, v, idx, partial
 struct LayerWs {
     size_t table_off, expert_off, weight_off, tau_off, logit_off, count_off, mask_off, groups_off, ngroups_off, order_off, v_off, idx_off,
-        rows_off, missidx_off, missrows_off, misscount_off, wgroups_off, xsum_off, urow_off, ucount_off, hbuf_off, hmax_off, trows_off, partial_off, total;
+        rows_off, missidx_off, missrows_off, misscount_off, ptau_off, wgroups_off, xsum_off, urow_off, segs_off, hbuf_off, hmax_off, trows_off, partial_off, total;
     int n_tasks, nblk, nblk_fused, fused_passes;
     bool batch_mfma;  // tokens of an expert share one pass over its codes (matrix-core up GEMV)
     bool use_wide;    // batches: one read of every row an expert group selected, on the matrix cores (wide_batch.hip)
@@ -241,13 +242,14 @@ LayerWs layer_plan(const floe_layer* L, int T, Wide form = Wide::kChosen, int ma
     w.missrows_off = o;  o += per_list;
     w.misscount_off = o; o += L->gd_on_host ? align_up((size_t)w.n_tasks * 4) : 0;
     const size_t wgroups = w.use_wide ? (size_t)w.wp.max_groups : 0;
+    w.ptau_off = o;    o += w.use_wide ? align_up((size_t)w.n_tasks * 8) : 0;  // thresholds and weights by position
     w.wgroups_off = o; o += w.use_wide ? align_up(wgroups * sizeof(WideGroup) + 4) : 0;  // (+ their number)
     w.up_split = w.use_wide && up_split_pays(L->s.d, L->s.f, L->s.bits, L->s.group, n_all, w.n_tasks, w.wp);
     w.up_wide = w.use_wide && !w.up_split && up_wide_pays(L->s.d, L->s.f, L->s.bits, L->s.group, n_all, w.n_tasks);
     const bool room_for_x = room && up_wide_shape(L->s.d, L->s.f, L->s.bits, L->s.group) && grouped_gemv_mode() != 2;
     w.xsum_off = o;    o += w.up_wide || w.up_split || room_for_x ? align_up(x_operand_sum_bytes(w.wp.h_tiles, L->s.d, L->s.group)) : 0;
-    w.urow_off = o;    o += align_up(wgroups * L->s.f * 4);
-    w.ucount_off = o;  o += align_up(wgroups * 4);
+    w.urow_off = o;    o += w.use_wide ? align_up(w.wp.row_slots * 32 * 4) : 0;
+    w.segs_off = o;    o += w.use_wide ? align_up((size_t)w.wp.segments * sizeof(int4)) : 0;
     w.hbuf_off = o;    o += w.use_wide ? align_up(wide_h_bytes(w.wp, L->s.d)) : 0;
     w.hmax_off = o;    o += w.use_wide ? align_up((size_t)w.n_tasks * 4) : 0;
     w.trows_off = o;   o += w.use_wide ? align_up((size_t)w.n_tasks * sizeof(int2)) : 0;
@@ -516,33 +518,38 @@ int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, cons
         WideGroup* groups = reinterpret_cast<WideGroup*>(base + w.wgroups_off);
         int32_t* n_groups = reinterpret_cast<int32_t*>(groups + w.wp.max_groups);
         int32_t* order = reinterpret_cast<int32_t*>(base + w.order_off);
+        const WidePrep prep{reinterpret_cast<uint4*>(partial), reinterpret_cast<int32_t*>(base + w.count_off),
+                            reinterpret_cast<uint32_t*>(base + w.hmax_off), reinterpret_cast<int2*>(base + w.trows_off),
+                            reinterpret_cast<int4*>(base + w.segs_off), w.wp.segments, tau, out_scale,
+                            reinterpret_cast<float*>(base + w.ptau_off), reinterpret_cast<float*>(base + w.ptau_off) + T};
+        WideArgs wa{};
+        wa.groups = groups; wa.n_groups = n_groups; wa.order = order; wa.x = xh; wa.v = v;
+        wa.tau = prep.tau; wa.scale = prep.scale;
+        wa.count = prep.count;
+        wa.rows = reinterpret_cast<int32_t*>(base + w.rows_off);
+        wa.segments = prep.segments;
+        wa.hbuf = reinterpret_cast<uint4*>(base + w.hbuf_off);
+        wa.hmax = prep.hmax;
+        wa.task_rows = prep.task_rows;
+        wa.partial = partial;
+        wa.xop = prep.xop;
+        wa.slots = 1; wa.f = e->s.f; wa.max_groups = w.wp.max_groups; wa.pieces = w.wp.wg_gate;
         // (scales and zeros need no more than their own alignment here; the wide kernel loads them 16 bytes at a time)
         if (up_wide_shape(e->s.d, e->s.f, e->s.bits, e->s.group) && aligned(e->up_scale, 16) && aligned(e->up_zero, 16)) {
             UpWideArgs u{};
             const bool split = up_split_pays(e->s.d, e->s.f, e->s.bits, e->s.group, 1, T, w.wp);
             u.groups = groups; u.n_groups = n_groups; u.order = order; u.x = xh; u.v = v;
-            u.task_tau = tau; u.mask_words = mask; u.x_frag = base + w.hbuf_off; u.x_sums = base + w.xsum_off;
+            u.mask_words = mask; u.x_frag = base + w.hbuf_off; u.x_sums = base + w.xsum_off;
             u.n_tasks = T; u.d = e->s.d; u.f = e->s.f; u.slots = 1; u.nt = w.wp.nt;
             u.max_groups = w.wp.max_groups; u.est_groups = w.wp.est_groups;
-            u.single = &map.single; u.chunk = w.wp.chunk;
+            u.single = &map.single; u.chunk = w.wp.chunk; u.prep = prep;
             FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st, split ? launch_up_split(u, e->s.bits, e->s.group, st) : launch_up_wide(u, e->s.bits, e->s.group, st));
         } else {
             FLOE_HIP(launch_wide_single(map.single, T, w.wp.chunk, groups, n_groups, order, st));
+            FLOE_HIP(launch_wide_prepare(prep, wa, T, e->s.d, st));
             FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st,
                         launch_up_gemv(map, xh, nullptr, v, tau, mask, e->s.d, e->s.f, e->s.bits, e->s.group, T, st));
         }
-        WideArgs wa{};
-        wa.groups = groups; wa.n_groups = n_groups; wa.order = order; wa.x = xh; wa.v = v;
-        wa.task_tau = tau; wa.task_scale = out_scale;
-        wa.count = reinterpret_cast<int32_t*>(base + w.count_off);
-        wa.urow = reinterpret_cast<int32_t*>(base + w.urow_off);
-        wa.ucount = reinterpret_cast<int32_t*>(base + w.ucount_off);
-        wa.hbuf = reinterpret_cast<uint4*>(base + w.hbuf_off);
-        wa.hmax = reinterpret_cast<uint32_t*>(base + w.hmax_off);
-        wa.task_rows = reinterpret_cast<int2*>(base + w.trows_off);
-        wa.partial = partial;
-        wa.xop = reinterpret_cast<uint4*>(partial);
-        wa.slots = 1; wa.f = e->s.f;
         FLOE_LAUNCH(FLOE_KERNEL_GATE_DOWN, st, launch_gate_down_wide(wa, w.wp, mask, e->s.d, st));
         if (idx) FLOE_LAUNCH(FLOE_KERNEL_SELECT, st, launch_select(v, e->s.f, T, tau, idx, count, st));
         FLOE_LAUNCH(FLOE_KERNEL_COMBINE, st, launch_combine_wide(wa, w.wp, e->s.d, T, y_acc, nullptr, st));
@@ -749,7 +756,27 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
         WideGroup* wide = reinterpret_cast<WideGroup*>(base + w.wgroups_off);
         int32_t* n_wide = reinterpret_cast<int32_t*>(wide + w.wp.max_groups);
         int32_t* order = reinterpret_cast<int32_t*>(base + w.order_off);
-        if (w.use_wide)
+        const bool group_here = (w.up_wide || w.up_split) && w.n_tasks <= kOperandGroups;  // by the kernel that prepares the activations
+        WideArgs wa{};
+        WidePrep prep{};
+        if (w.use_wide) {
+            prep = WidePrep{reinterpret_cast<uint4*>(partial), count, reinterpret_cast<uint32_t*>(base + w.hmax_off),
+                            reinterpret_cast<int2*>(base + w.trows_off), reinterpret_cast<int4*>(base + w.segs_off), w.wp.segments, task_tau, task_weight,
+                            reinterpret_cast<float*>(base + w.ptau_off), reinterpret_cast<float*>(base + w.ptau_off) + w.n_tasks};
+            wa.groups = wide; wa.n_groups = n_wide; wa.order = order; wa.x = xh; wa.v = v;
+            wa.tau = prep.tau; wa.scale = prep.scale; wa.count = count;
+            wa.by_task = !w.up_wide && !w.up_split;
+            wa.rows = reinterpret_cast<int32_t*>(base + w.urow_off);
+            wa.segments = prep.segments;
+            wa.hbuf = reinterpret_cast<uint4*>(base + w.hbuf_off);
+            wa.hmax = prep.hmax;
+            wa.task_rows = prep.task_rows;
+            wa.partial = partial;
+            wa.xop = prep.xop;
+            wa.slots = slots; wa.f = L->s.f; wa.max_groups = w.wp.max_groups; wa.pieces = w.wp.wg_gate;
+        }
+        if (group_here) {
+        } else if (w.use_wide)
             FLOE_HIP(launch_group_tokens(task_expert, w.n_tasks, n_all, w.chunk, groups, n_groups, st, order, w.wp.chunk, wide, n_wide,
                                          static_cast<const DevExpert*>(L->dev_table)));
         else
@@ -757,9 +784,10 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
         if (w.up_wide || w.up_split) {
             UpWideArgs u{};
             u.groups = wide; u.n_groups = n_wide; u.order = order; u.x = xh; u.v = v;
-            u.task_tau = task_tau; u.mask_words = mask; u.x_frag = base + w.hbuf_off; u.x_sums = base + w.xsum_off;
+            u.mask_words = mask; u.x_frag = base + w.hbuf_off; u.x_sums = base + w.xsum_off;
             u.n_tasks = w.n_tasks; u.d = L->s.d; u.f = L->s.f; u.slots = slots; u.nt = w.wp.nt;
-            u.max_groups = w.wp.max_groups; u.est_groups = w.wp.est_groups;
+            u.max_groups = w.wp.max_groups; u.est_groups = w.wp.est_groups; u.chunk = w.wp.chunk; u.prep = prep;
+            u.task_expert = group_here ? task_expert : nullptr; u.table = static_cast<const DevExpert*>(L->dev_table); u.n_all = n_all;
             FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st,
                         w.up_split ? launch_up_split(u, L->s.bits, L->s.group, st) : launch_up_wide(u, L->s.bits, L->s.group, st));
         } else if (batch_mfma)
@@ -772,17 +800,7 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
                         launch_up_gemv(map, xh, nullptr, v, task_tau, mask, L->s.d, L->s.f, L->s.bits, L->s.group,
                                        w.n_tasks, st));
         if (w.use_wide) {
-            WideArgs wa{};
-            wa.groups = wide; wa.n_groups = n_wide; wa.order = order; wa.x = xh; wa.v = v;
-            wa.task_tau = task_tau; wa.task_scale = task_weight; wa.count = count;
-            wa.urow = reinterpret_cast<int32_t*>(base + w.urow_off);
-            wa.ucount = reinterpret_cast<int32_t*>(base + w.ucount_off);
-            wa.hbuf = reinterpret_cast<uint4*>(base + w.hbuf_off);
-            wa.hmax = reinterpret_cast<uint32_t*>(base + w.hmax_off);
-            wa.task_rows = reinterpret_cast<int2*>(base + w.trows_off);
-            wa.partial = partial;
-            wa.xop = reinterpret_cast<uint4*>(partial);
-            wa.slots = slots; wa.f = L->s.f;
+            if (!w.up_wide && !w.up_split) FLOE_HIP(launch_wide_prepare(prep, wa, w.n_tasks, L->s.d, st));
             FLOE_LAUNCH(FLOE_KERNEL_GATE_DOWN, st, launch_gate_down_wide(wa, w.wp, mask, L->s.d, st));
             FLOE_LAUNCH(FLOE_KERNEL_COMBINE, st, launch_combine_wide(wa, w.wp, L->s.d, T, nullptr, reinterpret_cast<h16*>(y), st));
             if (stats)

@@ -151,14 +151,18 @@ static __device__ unsigned long long* g_timeline = nullptr;  // one copy per tra
 #endif
 #define FLOE_TL(slot) FLOE_TL_AT(slot, 0)
 
+// sums over the lanes up to and with this one
 __device__ __forceinline__ int wave_inclusive_scan(int x, int lane) {
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int up = __shfl_up(x, o, kWave);
-        if (lane >= o) x += up;
-    }
+    (void)lane;
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr:1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // rows 1 and 3 += last lane of rows 0 and 2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // rows 2 and 3 += lane 31
     return x;
 }
+__device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_inclusive_scan(x, 0), kWave - 1); }
 
 // ---- memory straight into LDS (global_load_lds_dwordx4).  Destinations are arrays of their own per ring slot: the compiler then knows which
 // requests a read of LDS has to wait for, instead of waiting for all of them.
@@ -177,6 +181,11 @@ __device__ __forceinline__ void wait_requests_all_but() {  // the same, and noth
     wait_vm_all_but<N>();
     asm volatile("" ::: "memory");
 }
+__device__ __forceinline__ void wait_lds() {  // s_waitcnt lgkmcnt(0) only
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
+    asm volatile("" ::: "memory");
+}
 __device__ __forceinline__ void meet() {  // barrier alone: what is in flight stays in flight
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
@@ -191,8 +200,17 @@ __device__ __forceinline__ const unsigned char* scalar_ptr(const void* p) {
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
     return (const unsigned char*)(((uint64_t)hi << 32) | lo);
 }
+// floor(a * b / c) and floor((a * b - 1) / c); in 32 bits where the product fits (a 64-bit quotient is 200 instructions of a kernel's first
+// microseconds)
+__device__ __forceinline__ int scaled(int a, int b, int less, int c) {
+    if ((uint32_t)a < (1u << 21) && (uint32_t)b < (1u << 11)) return (int)(((uint32_t)a * (uint32_t)b - (uint32_t)less) / (uint32_t)c);
+    return (int)(((long long)a * b - less) / c);
+}
 // piece w of W equal pieces starts at pair floor(total * w / W)
-__device__ __forceinline__ int wide_cut(int total, int W, int w) { return (int)((long long)total * w / W); }
+__device__ __forceinline__ int wide_cut(int total, int W, int w) { return scaled(total, w, 0, W); }
+// n / d as a whole number from 1 / d, for n up to a few hundred thousand and quotients up to a few hundred: taken half a unit above a
+// whole number, so that rounding cannot matter
+__device__ __forceinline__ int small_quotient(int n, float inverse) { return (int)(((float)n + 0.5f) * inverse); }
 // Workgroups go to the eight XCDs in turn.  Neighbouring pieces run on one XCD, so that its L2 holds the activations of few
 // groups, and the groups of one expert, which read the same rows, are next to each other.
 __device__ __forceinline__ int wide_piece(int W) {

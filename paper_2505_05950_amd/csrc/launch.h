@@ -207,25 +207,44 @@ struct WidePlan {
     int h_tiles;            // token tiles that the groups can have together
     int pairs;              // pairs of 16-row tiles an expert can have
     int wg_gate, wg_down;   // workgroups (the down kernel: per 512 output columns)
+    size_t row_slots;       // pairs of row ids (wide_layout.h)
+    size_t h_vecs;          // vectors of h
+    int segments;           // entries of the segment table
     size_t partial_rows;    // rows of d floats
+};
+constexpr int kWideMaxSegments = 4096;
+// What the gate kernel and those behind it find ready: the activations in the order of its operand, [token tile][k-step of 32
+// columns][lane], and cleared counters.
+struct WidePrep {
+    uint4* xop;
+    int32_t* count;
+    uint32_t* hmax;
+    int2* task_rows;
+    int4* segments;
+    int32_t n_segments;
+    const float* task_tau;    // [n_tasks] and by position of the order
+    const float* task_scale;  // or nullptr: ones
+    float* tau;
+    float* scale;
 };
 struct WideArgs {
     const WideGroup* groups;
     const int32_t* n_groups;
     const int32_t* order;     // [n_tasks] tasks sorted by expert
     const h16* x;
-    const float* v;           // [n_tasks][f]
-    const float* task_tau;    // [n_tasks]
-    const float* task_scale;  // [n_tasks] or nullptr
+    const float* v;           // [n_tasks][f] (see by_task)
+    const float* tau;         // [n_tasks] by position of the order, as all that follows but count and task_rows
+    const float* scale;       // [n_tasks]
     int32_t* count;           // [n_tasks] selected channels
-    int32_t* urow;            // [max_groups][f] union rows, ascending
-    int32_t* ucount;          // [max_groups]
+    int32_t* rows;            // [row_slots][32] union rows of the segments (wide_layout.h)
+    int4* segments;           // pairs, pair slot in the group, group, first of its group
     uint4* xop;               // [h_tiles][d / 32][64] activations in operand order (in the place of `partial`, which nobody has written yet)
-    uint4* hbuf;              // [h_tiles * pairs][2][64] h (four floats: rows of a 16-row tile) in lane order
+    uint4* hbuf;              // [h_vecs] h (four floats: rows of a 16-row tile) in lane order
     uint32_t* hmax;           // [n_tasks] bits of the largest finite |h| of task order[i]
     int2* task_rows;          // [n_tasks] first partial row, number of partial rows (chunk rows apart)
     float* partial;           // [partial_rows][d]
-    int32_t slots, f;
+    int32_t slots, f, max_groups, pieces;  // pieces: workgroups of the gate kernel
+    int32_t by_task;          // v and the mask words are kept by task (up projections that do not know the groups), else by position
 };
 // S2 for the same groups (up_wide.hip)
 inline bool up_wide_shape(int d, int f, int bits, int group) {
@@ -248,15 +267,19 @@ struct UpWideArgs {
     const int32_t* n_groups;
     const int32_t* order;
     const h16* x;
-    float* v;
-    const float* task_tau;
+    float* v;               // by position of the order, like the mask words
     uint32_t* mask_words;
     void* x_frag;   // h_tiles * 16 * d halves: the activations as operands
     void* x_sums;   // x_operand_sum_bytes()
     int32_t n_tasks, d, f, slots, nt, max_groups, est_groups;
     const DevExpert* single;  // one expert that every task belongs to: the launcher fills groups, n_groups and order in as well
-    int32_t chunk;            // (single) tasks per group at most
+    int32_t chunk;            // tasks per group at most
+    const int32_t* task_expert;  // (not single, may be null) the same from the tasks' experts, of n_all in `table`; up to kOperandGroups tasks
+    const DevExpert* table;
+    int32_t n_all;
+    WidePrep prep;
 };
+constexpr int kOperandGroups = 2048;
 // the activations as matrix operands (up_split.hip)
 struct XOperand {
     uint4* frag;   // [token tile][unit][two instructions][lane]
@@ -298,6 +321,8 @@ hipError_t launch_up_split(const UpWideArgs& a, int bits, int group, hipStream_t
 
 WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared, int max_down);
 WidePlan wide_room(int d, int f, int T, int n_experts, int top_k, int n_shared);
+// clears and copies what WidePrep names, where no up projection of wide groups has done so
+hipError_t launch_wide_prepare(const WidePrep& prep, const WideArgs& a, int n_tasks, int d, hipStream_t stream);
 hipError_t launch_gate_down_wide(const WideArgs& a, const WidePlan& p, const uint32_t* mask_words, int d, hipStream_t stream);
 hipError_t launch_wide_single(const DevExpert& e, int n_tasks, int chunk, WideGroup* groups, int32_t* n_groups, int32_t* order,
                               hipStream_t stream);

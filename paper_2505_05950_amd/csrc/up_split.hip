@@ -27,6 +27,7 @@
 #include "floe_dev.h"
 #include "launch.h"
 #include "mfma_codes.h"
+#include "wide_layout.h"
 
 namespace floe {
 
@@ -38,46 +39,103 @@ typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 // The activations of every task as the operand of the matrix instruction, [token tile][unit][instruction of the unit][lane],
 // their sums per quantization group and the factor that undoes the scaling.  One task per workgroup, one unit per thread (d <= 8192).  (Every
 // workgroup of the kernel below would otherwise gather them for itself, 16 bytes per lane from as many rows: 11 of its first 15 us.)
-// single: all tasks belong to one expert; groups and order are filled in here.
-template <int BITS, bool G32>
-__global__ __launch_bounds__(128) void x_operand_kernel(const h16* __restrict__ x, int slots, int d, WideGroup* __restrict__ groups,
-                                                       int32_t* __restrict__ n_groups, int32_t* __restrict__ order, int max_groups,
-                                                       bool single, DevExpert e, int n_tasks, int chunk, uint4* __restrict__ frag,
-                                                       float* __restrict__ gsum, float* __restrict__ back) {
+// In front of that the grouping, where nobody has done it: every workgroup counts the tasks of each expert for itself (a few hundred
+// numbers; a kernel of one workgroup in front took 5 to 10 us).
+struct XOperandArgs {
+    const h16* x;
+    int32_t slots, d, max_groups, n_tasks, chunk, n_all;
+    WideGroup* groups;
+    int32_t* n_groups;
+    int32_t* order;
+    const int32_t* task_expert;
+    const DevExpert* table;
+    DevExpert e;
+    uint4* frag;
+    float* gsum;
+    float* back;
+    WidePrep prep;
+};
+enum class Grouping { kReady, kSingle, kHere };  // the tables are there; all tasks belong to one expert; from the tasks' experts
+template <int BITS, bool G32, Grouping HOW>
+__global__ __launch_bounds__(128) void x_operand_kernel(XOperandArgs a) {
     using Tr = MfmaTraits<BITS, G32>;
     constexpr int kGroups = G32 ? 2 : 1;
     constexpr float kScaleBack = (float)(1 << (24 - Tr::kPmax));
     __shared__ float wave_max[2];
-    const int i = blockIdx.x, U = threadIdx.x, lane = U & 63, units = d >> 6;
-    int task = i, row = 0;  // row: of the token tiles
-    if (single) {
-        const int len = wide_single_len(n_tasks, chunk), g = i / len;
-        row = ((i + 15 * g - (i - g * len)) >> 4) * 16 + (i - g * len);
-        if (U == 0) {
-            order[i] = i;
-            if (i < wide_single_groups(n_tasks, chunk)) groups[i] = wide_single_group(e, n_tasks, chunk, i);
-            if (i == 0) n_groups[0] = wide_single_groups(n_tasks, chunk);
-        }
-    } else {
-        task = order[i];
-        const int ng = n_groups[0];
-        for (int g0 = 0; g0 < ng; g0 += kWave) {
-            const WideGroup* mine = groups + min(g0 + lane, max_groups - 1);
-            const int n = mine->n, first = mine->first, tile = mine->tile;
-            const unsigned long long m = __ballot(g0 + lane < ng && i >= first && i < first + n);
-            if (m) {
-                const int l = __ffsll((long long)m) - 1;
-                row = __builtin_amdgcn_readlane(tile * 16 + i - first, l);
-                break;
-            }
-        }
-    }
+    const int i = blockIdx.x, U = threadIdx.x, lane = U & 63, units = a.d >> 6;
+    int task = i, pos = i, row = 0;  // row: of the token tiles
     const bool live = U < units;
+    if constexpr (HOW == Grouping::kReady) task = a.order[i];
     uint4 q[8];
-    u16x2 top2 = {0, 0};
-    const uint4* xr = reinterpret_cast<const uint4*>(x + (size_t)(task / slots) * d) + (live ? U : 0) * 8;
+    const uint4* xr = reinterpret_cast<const uint4*>(a.x + (size_t)(task / a.slots) * a.d) + (live ? U : 0) * 8;
 #pragma unroll
     for (int r = 0; r < 8; ++r) q[r] = xr[r];
+    if constexpr (HOW == Grouping::kSingle) {
+        const int len = wide_single_len(a.n_tasks, a.chunk), g = i / len;
+        row = ((i + 15 * g - (i - g * len)) >> 4) * 16 + (i - g * len);
+        if (U == 0) {
+            a.order[i] = i;
+            if (i < wide_single_groups(a.n_tasks, a.chunk)) a.groups[i] = wide_single_group(a.e, a.n_tasks, a.chunk, i);
+            if (i == 0) a.n_groups[0] = wide_single_groups(a.n_tasks, a.chunk);
+        }
+    } else if constexpr (HOW == Grouping::kHere) {
+        // workgroup i is task i; groups of equal size per expert, tasks of a group ascending
+        __shared__ int tasks_of[1024 + 64];
+        __shared__ int sums_of[2][4];  // tasks before this one in its expert; tasks and groups of the experts before; groups
+        const int e = a.task_expert[i], threads = blockDim.x;
+        for (int k = U; k < a.n_all; k += threads) tasks_of[k] = 0;
+        __syncthreads();
+        int before = 0;
+        for (int j0 = U; j0 < a.n_tasks; j0 += 8 * threads) {
+            int ej[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) ej[k] = j0 + k * threads < a.n_tasks ? a.task_expert[j0 + k * threads] : -1;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                if ((unsigned)ej[k] < (unsigned)a.n_all) atomicAdd(&tasks_of[ej[k]], 1);  // (sums of integers: in any order)
+                before += ej[k] == e && j0 + k * threads < i;
+            }
+        }
+        __syncthreads();
+        int tasks = 0, groups = 0, all = 0;
+        const float per_chunk = 1.0f / (float)a.chunk;
+        for (int k = U; k < a.n_all; k += threads) {
+            const int n = tasks_of[k], ng = small_quotient(n + a.chunk - 1, per_chunk);
+            tasks += k < e ? n : 0;
+            groups += k < e ? ng : 0;
+            all += ng;
+        }
+        int sum[4] = {wave_sum(before), wave_sum(tasks), wave_sum(groups), wave_sum(all)};
+        if (threads > kWave) {
+            if (lane == 0) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) sums_of[U >> 6][k] = sum[k];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sum[k] = sums_of[0][k] + sums_of[1][k];
+        }
+        if ((unsigned)e >= (unsigned)a.n_all) {  // an id outside the table belongs to no group
+            if (U == 0) a.prep.count[i] = 0, a.prep.task_rows[i] = make_int2(0, 0);
+            return;
+        }
+        const int n = tasks_of[e], ng = small_quotient(n + a.chunk - 1, per_chunk), len = small_quotient(n + ng - 1, 1.0f / (float)ng);
+        const int gl = small_quotient(sum[0], 1.0f / (float)len), g = sum[2] + gl, first = sum[1] + gl * len, tile = (first + 15 * g) >> 4;
+        pos = sum[1] + sum[0];
+        row = tile * 16 + sum[0] - gl * len;
+        if (U == 0) {
+            a.order[pos] = i;
+            if (sum[0] == gl * len) a.groups[g] = WideGroup{e, min(len, n - gl * len), first, tile, a.table[e]};
+            if (i == 0) a.n_groups[0] = sum[3];
+        }
+    } else {
+        row = wide_token_row(a.groups, a.n_groups[0], a.max_groups, i, lane);
+    }
+    const int d = a.d;
+    uint4* __restrict__ frag = a.frag;
+    float* __restrict__ gsum = a.gsum;
+    if (U == 0) wide_clear(a.prep, pos, task, a.n_tasks);
+    u16x2 top2 = {0, 0};
     uint32_t xv[32];
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
@@ -93,11 +151,14 @@ __global__ __launch_bounds__(128) void x_operand_kernel(const h16* __restrict__ 
         amax = fmaxf(wave_max[0], wave_max[1]);
     }
     const int down = (amax >= 512.0f && amax < 3.0e38f) ? ilogbf(amax) - 8 : 0;  // |x'| < 512: 2^(pmax - p) x' stays finite
-    if (U == 0) back[row] = ldexpf(1.0f, down) * kScaleBack;
+    if (U == 0) a.back[row] = ldexpf(1.0f, down) * kScaleBack;
     if (!live) return;
     const h16 ps = (h16)ldexpf(1.0f, -down);
     const h16x2 ps2 = {ps, ps};
     const int tile = row >> 4, c = row & 15;
+    uint4* xop = a.prep.xop + ((size_t)tile * (d / 32) + 2 * U) * 64 + c;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) xop[(r >> 2) * 64 + (r & 3) * 16] = q[r];
     uint4* out = frag + ((size_t)tile * units + U) * 128 + c;
     float sum[2] = {0.0f, 0.0f};
 #pragma unroll
@@ -126,9 +187,9 @@ __global__ __launch_bounds__(128) void x_operand_kernel(const h16* __restrict__ 
 
 template <int BITS, bool G32, int NT, int TILES>
 __global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restrict__ groups, const int32_t* __restrict__ n_groups,
-                                                       int max_groups, const int32_t* __restrict__ order, const uint4* __restrict__ frag,
+                                                       int max_groups, const uint4* __restrict__ frag,
                                                        const float* __restrict__ gsum, const float* __restrict__ back,
-                                                       float* __restrict__ v, const float* __restrict__ task_tau,
+                                                       float* __restrict__ v, const float* __restrict__ tau,
                                                        uint32_t* __restrict__ mask_words, int d, int f) {
     constexpr int kTok = 16 * NT;
     constexpr int kGroups = G32 ? 2 : 1;                 // quantization groups per unit
@@ -141,7 +202,6 @@ __global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restri
     float2* red = reinterpret_cast<float2*>(lds);        // [2][nw][TILES * NT * 2][64]
     uint4* park = reinterpret_cast<uint4*>(red + (size_t)2 * nw * (TILES * NT * 2 * 64));  // [nw][4][2][64] where NT == 2
     float* xg = reinterpret_cast<float*>(park + (NT == 2 ? nw * kSpParked : 0));  // [nw][NT][8 * kGroups][16]
-    __shared__ __align__(8) int s_task[kTok];
     __shared__ __align__(8) float s_tau[kTok], s_back[kTok];
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -161,12 +221,14 @@ __global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restri
     auto parts_of = [](int n) { return (n + 31) >> 5; };
     const int full_weight = weight(32) * blocks + kStart;
     auto last_weight = [&](int n) { return weight(n - 32 * (parts_of(n) - 1)) * blocks + kStart; };
-    auto group_weight = [&](int g0) {  // of lane's group (the load does not wait for ng)
-        const int n = groups[min(g0 + lane, max_groups - 1)].n;
+    const int n_head = groups[min(lane, max_groups - 1)].n;  // (the first 64 groups are asked for once, without waiting for their number)
+    auto tokens_of = [&](int g0) { return g0 == 0 ? n_head : groups[min(g0 + lane, max_groups - 1)].n; };
+    auto group_weight = [&](int g0) {  // of lane's group
+        const int n = tokens_of(g0);
         return g0 + lane < ng ? (parts_of(n) - 1) * full_weight + last_weight(n) : 0;
     };
     int total = 0;
-    for (int g0 = 0; g0 < ng; g0 += kWave) total += __builtin_amdgcn_readlane(wave_inclusive_scan(group_weight(g0), lane), kWave - 1);
+    for (int g0 = 0; g0 < ng; g0 += kWave) total += wave_sum(group_weight(g0));
     const int piece = wide_piece(gridDim.x);
     int pos = wide_cut(total, gridDim.x, piece);
     const int end = wide_cut(total, gridDim.x, piece + 1);
@@ -240,9 +302,7 @@ __global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restri
         __syncthreads();  // the previous group's arrays are no longer read
         if (tid < kTok) {
             const int row = tid < n_tok ? tid : 0;  // dead token rows repeat the first one
-            const int task = order[grp.first + tok_first + row];
-            s_task[tid] = task;
-            s_tau[tid] = task_tau ? task_tau[task] : 0.0f;
+            s_tau[tid] = tau[grp.first + tok_first + row];
             s_back[tid] = back[tile0 * 16 + row];
         }
 #pragma unroll
@@ -363,7 +423,6 @@ __global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restri
             for (int it = wave; it < TILES * NL * 2; it += nw) {
                 const int t = it / (NL * 2), n = (it >> 1) % NL, h = it & 1;
                 const int tok0 = 16 * n + 4 * g4 + 2 * h;
-                const int2 task2 = *reinterpret_cast<const int2*>(&s_task[tok0]);
                 const float2 tau2 = *reinterpret_cast<const float2*>(&s_tau[tok0]), back2 = *reinterpret_cast<const float2*>(&s_back[tok0]);
                 float2 r = make_float2(0.f, 0.f);
                 for (int w0 = 0; w0 < nw; w0 += 4) {  // four reads under way at a time
@@ -380,7 +439,7 @@ __global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restri
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
                     const bool live = tok0 + e < n_tok;
-                    const int task = e ? task2.y : task2.x;
+                    const int task = grp.first + tok_first + tok0 + e;
                     const float val = e ? r.y * back2.y : r.x * back2.x;
                     if (live && ch < f) v[(size_t)task * f + ch] = val;
                     const uint64_t m = __ballot(live && ch < f && fabsf(val) > (e ? tau2.y : tau2.x));
@@ -418,9 +477,14 @@ size_t x_operand_sum_bytes(int tiles, int d, int group) { return (size_t)tiles *
 
 template <int BITS, bool G32>
 static hipError_t operand_bits(const UpWideArgs& a, const XOperand& x, hipStream_t stream) {
-    x_operand_kernel<BITS, G32><<<dim3(a.n_tasks), dim3(a.d > 4096 ? 128 : 64), 0, stream>>>(
-        a.x, a.slots, a.d, const_cast<WideGroup*>(a.groups), const_cast<int32_t*>(a.n_groups), const_cast<int32_t*>(a.order), a.max_groups,
-        a.single != nullptr, a.single ? *a.single : DevExpert{}, a.n_tasks, a.chunk, x.frag, x.gsum, x.back);
+    const bool here = !a.single && a.task_expert && a.n_tasks <= kOperandGroups;
+    const XOperandArgs p{a.x, a.slots, a.d, a.max_groups, a.n_tasks, a.chunk, a.n_all, const_cast<WideGroup*>(a.groups),
+                         const_cast<int32_t*>(a.n_groups), const_cast<int32_t*>(a.order), a.task_expert, a.table,
+                         a.single ? *a.single : DevExpert{}, x.frag, x.gsum, x.back, a.prep};
+    const dim3 grid(a.n_tasks), block(a.d > 4096 ? 128 : 64);
+    if (a.single) x_operand_kernel<BITS, G32, Grouping::kSingle><<<grid, block, 0, stream>>>(p);
+    else if (here) x_operand_kernel<BITS, G32, Grouping::kHere><<<grid, block, 0, stream>>>(p);
+    else x_operand_kernel<BITS, G32, Grouping::kReady><<<grid, block, 0, stream>>>(p);
     return hipGetLastError();
 }
 hipError_t launch_x_operand(const UpWideArgs& a, int bits, int group, XOperand& x, hipStream_t stream) {
@@ -459,7 +523,7 @@ static hipError_t launch_split(const UpWideArgs& a, hipStream_t stream) {
     XOperand x;
     const hipError_t rc = launch_x_operand(a, BITS, G32 ? 32 : 64, x, stream);
     if (rc != hipSuccess) return rc;
-    kernel<<<dim3(wgs), dim3(64 * nw), lds, stream>>>(a.groups, a.n_groups, a.max_groups, a.order, x.frag, x.gsum, x.back, a.v, a.task_tau,
+    kernel<<<dim3(wgs), dim3(64 * nw), lds, stream>>>(a.groups, a.n_groups, a.max_groups, x.frag, x.gsum, x.back, a.v, a.prep.tau,
                                                     a.mask_words, a.d, a.f);
     return hipGetLastError();
 }

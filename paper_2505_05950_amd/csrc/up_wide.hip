@@ -30,10 +30,9 @@ constexpr int kUpSlotUnits = 2;
 
 template <int BITS, bool G32, int NT>
 __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __restrict__ groups, const int32_t* __restrict__ n_groups,
-                                                             int max_groups, const int32_t* __restrict__ order,
-                                                             const uint4* __restrict__ frag, const float* __restrict__ gsum,
+                                                             int max_groups, const uint4* __restrict__ frag, const float* __restrict__ gsum,
                                                              const float* __restrict__ back, float* __restrict__ v,
-                                                             const float* __restrict__ task_tau, uint32_t* __restrict__ mask_words,
+                                                             const float* __restrict__ tau, uint32_t* __restrict__ mask_words,
                                                              int d, int f) {
     constexpr int CT = 2;                                // channel tiles of 16 per wave: one mask word
     constexpr int kTok = 16 * NT;
@@ -45,7 +44,6 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __
     constexpr int kXVecs = kUpSlotUnits * 2 * NT * 64;   // per slot: activations, and behind them the group sums
     constexpr int kSumVecs = (kUpSlotUnits * kGroups * NT * 4 + 63) / 64 * 64;
     __shared__ uint4 x0[kXVecs + kSumVecs], x1[kXVecs + kSumVecs], x2[kXVecs + kSumVecs], x3[kXVecs + kSumVecs];
-    __shared__ __align__(16) int s_task[kTok];
     __shared__ __align__(16) float s_tau[kTok], s_back[kTok];
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -60,8 +58,9 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __
     auto part_tiles = [&](int n) { return (wide_tiles(n) + parts_of(n) - 1) / parts_of(n); };
     auto weight = [&](int n) { return part_tiles(n) + 2; };
     struct Share { int parts, part_weight; };
+    const int n_here = groups[min(lane, max_groups - 1)].n;  // (the first 64 groups are asked for once)
     auto share_of = [&](int g0) {  // lane's group (the load does not wait for ng)
-        const int n = groups[min(g0 + lane, max_groups - 1)].n;
+        const int n = g0 == 0 ? n_here : groups[min(g0 + lane, max_groups - 1)].n;
         return g0 + lane < ng ? Share{parts_of(n), weight(n) * blocks} : Share{0, 0};
     };
     int total = 0, n_parts = 0;
@@ -133,9 +132,7 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __
         __syncthreads();  // the previous part's arrays are no longer read
         if (tid < kTok) {
             const int row = tok_first + (tid < n_tok ? tid : 0);  // dead token rows repeat the first one
-            const int task = order[grp.first + row];
-            s_task[tid] = task;
-            s_tau[tid] = task_tau ? task_tau[task] : 0.0f;
+            s_tau[tid] = tau[grp.first + row];
             s_back[tid] = back[grp.tile * 16 + row];
         }
         const int np = (len + kUpWaves - 1) / kUpWaves;
@@ -346,15 +343,14 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __
                 asm volatile("" : "+v"(tok0));  // or the addresses below are formed ahead of the loop and held across it
 #pragma unroll
                 for (int n = 0; n < NL; ++n) {
-                    const int4 task4 = *reinterpret_cast<const int4*>(&s_task[16 * n + tok0]);
                     const float4 tau4 = *reinterpret_cast<const float4*>(&s_tau[16 * n + tok0]);
                     const float4 back4 = *reinterpret_cast<const float4*>(&s_back[16 * n + tok0]);
-                    const int task[4] = {task4.x, task4.y, task4.z, task4.w};
-                    const float tau[4] = {tau4.x, tau4.y, tau4.z, tau4.w}, bk[4] = {back4.x, back4.y, back4.z, back4.w};
+                    const int pos0 = grp.first + tok_first + 16 * n + tok0;
+                    const float limit[4] = {tau4.x, tau4.y, tau4.z, tau4.w}, bk[4] = {back4.x, back4.y, back4.z, back4.w};
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         const bool used = 16 * n + tok0 + i < n_tok;
-                        float* vt = v + (size_t)task[i] * f;
+                        float* vt = v + (size_t)(pos0 + i) * f;
 #pragma unroll
                         for (int t2 = 0; t2 < CT / 2; ++t2) {
                             uint32_t w = 0u;
@@ -363,11 +359,11 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __
                                 const int t = 2 * t2 + h, ch = ch0 + 16 * t + c;
                                 const float val = acc[t][n][i] * bk[i];
                                 if (used && ch < f) vt[ch] = val;
-                                const uint64_t m = __ballot(used && ch < f && fabsf(val) > tau[i]);
+                                const uint64_t m = __ballot(used && ch < f && fabsf(val) > limit[i]);
                                 w |= ((uint32_t)(m >> (16 * g4)) & 0xFFFFu) << (16 * h);
                             }
                             const int word = ch0 / 32 + t2;
-                            if (mask_words && used && c == 0 && word < nwords) mask_words[(size_t)task[i] * nwords + word] = w;
+                            if (mask_words && used && c == 0 && word < nwords) mask_words[(size_t)(pos0 + i) * nwords + word] = w;
                         }
                     }
                 }
@@ -385,8 +381,8 @@ static hipError_t launch_nt(const UpWideArgs& a, hipStream_t stream) {
     XOperand x;
     const hipError_t rc = launch_x_operand(a, BITS, G32 ? 32 : 64, x, stream);
     if (rc != hipSuccess) return rc;
-    up_wide_kernel<BITS, G32, NT><<<dim3(wgs), dim3(kUpThreads), 0, stream>>>(a.groups, a.n_groups, a.max_groups, a.order, x.frag, x.gsum,
-                                                                               x.back, a.v, a.task_tau, a.mask_words, a.d, a.f);
+    up_wide_kernel<BITS, G32, NT><<<dim3(wgs), dim3(kUpThreads), 0, stream>>>(a.groups, a.n_groups, a.max_groups, x.frag, x.gsum,
+                                                                               x.back, a.v, a.prep.tau, a.mask_words, a.d, a.f);
     return hipGetLastError();
 }
 template <int BITS, bool G32>

@@ -2,11 +2,12 @@
 // its own threshold, mask and result).  The tokens of an expert form groups of up to 16 * NT (NT token tiles of the matrix
 // instruction); every row that any token of a group selected is read once for the whole group.
 //
-//   wide_rows_kernel   per group: ascending list of the union of the tokens' selected channels (from the mask bits), the
-//                      selected counts of its tasks.  Beside that the activations in the order of the gate kernel's operand.
+//   wide_prepare_kernel  where x_operand_kernel (up_split.hip) has not run: the activations in the order of the gate kernel's operand, cleared
+//                      counters.
 //   gate_wide_kernel   A[row][token] = gate_row . x_token.  A wave takes a pair of 16-row tiles.  Rows and activations travel
 //                      from memory straight into a ring of three or four slots in LDS, 64 columns of 256 rows and of the group's
-//                      tokens each; one barrier per slot.  h = SiLU(A) * v * weight where |v| > tau, else 0, leaves in fp32 in
+//                      tokens each; one barrier per slot.  In front of that the segment's row list: the ascending union of the tokens' selected
+//                      channels, from the mask bits (wide_layout.h).  h = SiLU(A) * v * weight where |v| > tau, else 0, leaves in fp32 in
 //                      the lane order of the down kernel's operand, and the largest |h| of each task beside it.
 //   down_wide_kernel   Y[token][col] += h[token][row] * down[row][col].  A workgroup owns 512 output columns and a range of
 //                      row pairs; a lane fetches 8-byte pieces of eight rows per pair (four pairs in flight), a register
@@ -15,17 +16,23 @@
 //                      to that the split is good to 2^-23, whatever the size of h, and no token depends on another.
 //   combine_wide       adds a task's partial results.
 //
-// Division of work: the row pairs of all groups form one sequence; the workgroups cut it into equal pieces, whatever the
-// routing did to the group sizes, so the launch is one even round and no compute unit waits for a crowded expert.
+// Division of work.  Gate: the channels of all groups in equal pieces, by what a group's rows are expected to be.  Down: the row pairs of all
+// groups form one sequence; the workgroups cut it into equal pieces, whatever the routing did to the group sizes, so the launch is one even
+// round and no compute unit waits for a crowded expert.
+//
+// The lists were a launch of their own between the up projection and the gate kernel, 6 to 8 us (17 at 512 tokens, the activations with
+// it), so that the gate kernel could cut by rows.  Made in the gate kernel they cost its workgroups 4 us before their first row; together with
+// pieces that end where groups do, layer calls: one expert with 24 tokens 96 -> 89 us, 64 tokens on 8 experts 372 -> 357, 64 + 2 experts of d 2048
+// f 1408 with 128 tokens 235 -> 220 (the grouping of tasks, a launch of one workgroup, is in these as well: x_operand_kernel).
 //
 // What bounds it: the rows (a kernel that only reads them in these pieces runs at 5.9 TB/s whatever the pieces are) and what stands
 // between: the start of the streams, once per pass of eight pairs, SiLU behind them, and in the down kernel twice the matrix products.
 // Hence groups as large as the accumulators allow (a second group reads the rows again).  Rows that go to registers instead, 16 bytes per
 // lane from sixteen rows, cost the cache 64 accesses per request; with the activations' it was busy for half of the cycles and the
-// waves stood behind their own requests.  The same holds for v gathered by lane (a tenth of the kernel).  Measured, gate, 8 experts
+// waves stood behind their own requests.  The same holds for v gathered by lane (a tenth of the kernel).  Requests cost the cache their 1 KB
+// whether or not rows repeat: the rows of a segment dealt to all eight waves, few each, took 37 us for one expert with 24 tokens, not 27.  Measured, gate, 8 experts
 // d 4096 f 14336 at 90 %: 512 tokens 280 -> 232 us, 64 tokens 152 -> 144, one expert with 24 tokens 28.4 -> 24.6.  Gate + down before
-// groups of more than 16 tokens: 64 tokens 364 us, 512 tokens 2425.  Tried: pieces that end where groups end (one expert with 24 tokens
-// 24.6 -> 27.8, the others the same).  Down, the same layer with 512 tokens 277 -> 254 us: half of its cycles were matrix products, a
+// groups of more than 16 tokens: 64 tokens 364 us, 512 tokens 2425.  Down, the same layer with 512 tokens 277 -> 254 us: half of its cycles were matrix products, a
 // fifth of these for token tiles that a group does not fill, and the waves stood for the LDS reads in front of each tile's.  (A body per
 // number of live tiles, as in the gate kernel, spills: 284.  So does reading one tile ahead with an address register per entry of h, 309:
 // a reload waits for every row in flight.)  Up to two tiles it is bound by the rows and did not change.
@@ -34,6 +41,7 @@
 
 #include "floe_dev.h"
 #include "launch.h"
+#include "wide_layout.h"
 
 namespace floe {
 
@@ -48,135 +56,19 @@ constexpr int kSliceCols = 64;   // columns of rows and activations per ring slo
 constexpr int kSpan = 64;        // channels of v that a wave brings in for a pair of row tiles
 constexpr int kDownCols = 512;   // output columns per workgroup of the down kernel (64 per wave)
 
-// pairs of union rows of group g
-__device__ __forceinline__ int wide_pairs(const int32_t* ucount, int g) { return (ucount[g] + kPairRows - 1) / kPairRows; }
-
-// h of a group lies in [pair][token tile][half of the pair's rows][lane], the group's own tiles only, from this entry on.
-__device__ __forceinline__ size_t wide_h_first(const WideGroup& g, int pmax) { return (size_t)g.tile * pmax * 128; }
-
-__device__ __forceinline__ int wide_total(const WideArgs& a, int ng, int lane) {
-    int total = 0;
-    for (int g0 = 0; g0 < ng; g0 += kWave) {
-        const int p = g0 + lane < ng ? wide_pairs(a.ucount, g0 + lane) : 0;
-        total += __builtin_amdgcn_readlane(wave_inclusive_scan(p, lane), kWave - 1);
-    }
-    return total;
-}
-// the group that holds pair `pos` of the sequence (pos < total) and the position of its first pair; every lane the same
-__device__ __forceinline__ void wide_find(const WideArgs& a, int ng, int lane, int pos, int& g, int& base) {
-    int run = 0;
-    for (int g0 = 0; g0 < ng; g0 += kWave) {
-        const int p = g0 + lane < ng ? wide_pairs(a.ucount, g0 + lane) : 0;
-        const int inc = wave_inclusive_scan(p, lane);
-        const unsigned long long past = __ballot(run + inc > pos);
-        if (past) {
-            const int l = __ffsll((long long)past) - 1;
-            g = g0 + l;
-            base = run + __builtin_amdgcn_readlane(inc - p, l);
-            return;
-        }
-        run += __builtin_amdgcn_readlane(inc, kWave - 1);
-    }
-    g = ng - 1;  // not reached for pos < total
-    base = pos;
-}
 // pair p belongs to piece ((p + 1) * W - 1) / total (see wide_cut)
-__device__ __forceinline__ int wide_owner(int total, int W, int p) { return (int)(((long long)(p + 1) * W - 1) / total); }
+__device__ __forceinline__ int wide_owner(int total, int W, int p) { return scaled(p + 1, W, 1, total); }
 
-// ---------------------------------------------------------------------------------------------------------------
-// union lists
-// ---------------------------------------------------------------------------------------------------------------
-// The activations of a token tile in the order of the matrix instruction's operand, [k-step of 32 columns][lane]: what the gate kernel
-// copies into LDS as it is.  A wave per token, one block per 2048 columns.  (Beside the lists in one launch: neither needs the other.)
-constexpr int kOperandCols = 2048;
-__device__ __forceinline__ void operand_tile(const WideArgs& a, int tile, int col0, int max_groups, int d) {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int ng = a.n_groups[0];
-    int first = 0, n = 0;
-    for (int g0 = 0; g0 < ng; g0 += kWave) {
-        const WideGroup* mine = a.groups + min(g0 + lane, max_groups - 1);
-        const int t0 = mine->tile, len = mine->n, f0 = mine->first;
-        const unsigned long long m = __ballot(g0 + lane < ng && tile >= t0 && tile < t0 + wide_tiles(len));
-        if (m) {
-            const int l = __ffsll((long long)m) - 1;
-            first = __builtin_amdgcn_readlane(f0 + 16 * (tile - t0), l);
-            n = __builtin_amdgcn_readlane(len - 16 * (tile - t0), l);
-            break;
-        }
-    }
-    if (wave >= n) return;  // no such token: nobody looks at its results
-    // pieces of 16 bytes: piece p is quarter p % 4 of k-step p / 4; 64 of them per 512 columns
-    const uint4* x = reinterpret_cast<const uint4*>(a.x + (size_t)(a.order[first + wave] / a.slots) * d + col0) + lane;
-    uint4* out = a.xop + ((size_t)tile * (d / 32) + col0 / 32 + (lane >> 2)) * 64 + (lane & 3) * 16 + wave;
-    const int last = min(d - col0, kOperandCols) / 512 - 1;
-    const uint4 q0 = x[0], q1 = x[min(1, last) * kWave], q2 = x[min(2, last) * kWave], q3 = x[min(3, last) * kWave];
-    out[0] = q0;  // (past the last one the last one again: the same bytes)
-    out[min(1, last) * 1024] = q1;
-    out[min(2, last) * 1024] = q2;
-    out[min(3, last) * 1024] = q3;
-}
-
-__global__ __launch_bounds__(1024) void wide_rows_kernel(WideArgs a, const uint32_t* __restrict__ mask_words, int max_groups, int d) {
-    constexpr int kWaves = 16;
-    __shared__ uint32_t u[kWideMaxMaskWords];
-    __shared__ int before[kWideMaxMaskWords];
-    __shared__ int wave_tot[kWaves];
-    const int parts = (d + kOperandCols - 1) / kOperandCols, op = (int)blockIdx.x - max_groups;
-    if (op >= 0) return operand_tile(a, op / parts, op % parts * kOperandCols, max_groups, d);
-    const int g = blockIdx.x;
-    if (g >= a.n_groups[0]) return;  // the grid is sized for the worst case
-    const WideGroup grp = a.groups[g];
-    const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int nwords = mask_words_per_task(a.f);
-    for (int w = tid; w < nwords; w += 1024) u[w] = 0u;
-    __syncthreads();
-    for (int i = wave; i < grp.n; i += kWaves) {  // a wave per task
-        const int task = a.order[grp.first + i];
-        const uint32_t* mw = mask_words + (size_t)task * nwords;
-        int c = 0;
-        for (int w0 = lane; w0 < nwords; w0 += 8 * kWave) {
-            uint32_t m[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) m[q] = w0 + q * kWave < nwords ? mw[w0 + q * kWave] : 0u;
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                c += __popc(m[q]);
-                if (m[q]) atomicOr(&u[w0 + q * kWave], m[q]);
-            }
-        }
-        c = __builtin_amdgcn_readlane(wave_inclusive_scan(c, lane), kWave - 1);
-        if (lane == 0) {
-            a.count[task] = c;
-            a.hmax[grp.first + i] = 0u;
-            a.task_rows[task] = make_int2(0, 0);  // filled in by the down kernel unless the group has no rows at all
-        }
-    }
-    __syncthreads();
-    // exclusive prefix of the words' populations; a thread owns two consecutive words
-    const int w2 = 2 * tid;
-    const int c0 = w2 < nwords ? __popc(u[w2]) : 0, c1 = w2 + 1 < nwords ? __popc(u[w2 + 1]) : 0;
-    const int inc = wave_inclusive_scan(c0 + c1, lane);
-    if (lane == kWave - 1) wave_tot[wave] = inc;
-    __syncthreads();
-    int run = inc - c0 - c1, all = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        run += w < wave ? wave_tot[w] : 0;
-        all += wave_tot[w];
-    }
-    if (w2 < nwords) before[w2] = run;
-    if (w2 + 1 < nwords) before[w2 + 1] = run + c0;
-    if (tid == 0) a.ucount[g] = all;
-    __syncthreads();
-    int32_t* out = a.urow + (size_t)g * a.f;
-    for (int w0 = 2 * wave; w0 < nwords; w0 += 2 * kWaves) {  // two words per wave, a lane per bit
-        const int w = w0 + (lane >> 5), b = lane & 31;
-        if (w < nwords) {
-            const uint32_t m = u[w];
-            if ((m >> b) & 1u) out[before[w] + __popc(m & ((1u << b) - 1u))] = w * 32 + b;
-        }
-    }
+// What x_operand_kernel does beside its own work, where the up projection is another one: the activations in the order of the gate
+// kernel's operand, and cleared counters.  A workgroup per position of the order.
+__global__ __launch_bounds__(128) void wide_prepare_kernel(WidePrep prep, WideArgs a, int n_tasks, int d) {
+    const int i = blockIdx.x, tid = threadIdx.x;
+    const int task = a.order[i], row = wide_token_row(a.groups, a.n_groups[0], a.max_groups, i, tid & 63);
+    if (tid == 0) wide_clear(prep, i, task, n_tasks);
+    // vector p of the row is quarter p % 4 of k-step p / 4
+    const uint4* x = reinterpret_cast<const uint4*>(a.x + (size_t)(task / a.slots) * d);
+    uint4* out = prep.xop + (size_t)(row >> 4) * (d / 32) * 64 + (row & 15);
+    for (int p = tid; p < d / 8; p += 128) out[(p >> 2) * 64 + (p & 3) * 16] = x[p];
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -186,69 +78,216 @@ __global__ __launch_bounds__(1024) void wide_rows_kernel(WideArgs a, const uint3
 // that the compiler can tell which requests a read has to wait for.  The waits that matter are placed by hand, in front of the barrier
 // that makes a slot everybody's.
 template <int NT>
-__global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int d) {
+__global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, const uint32_t* __restrict__ mask_words, int d) {
     constexpr int kTok = 16 * NT;
     constexpr int kSlots = NT <= 3 ? 4 : 3;                  // ring slots that fit 160 KB of LDS
     constexpr int kRowVecs = kWideWaves * 256, kXVecs = 2 * NT * 64;  // per slot: 32 rows x 128 bytes per wave; two k-steps of x
     __shared__ uint4 r0[kRowVecs], r1[kRowVecs], r2[kRowVecs], r3[kSlots > 3 ? kRowVecs : 1];
     __shared__ uint4 x0[kXVecs], x1[kXVecs], x2[kXVecs], x3[kSlots > 3 ? kXVecs : 1];
-    __shared__ int s_task[kTok];
+    __shared__ int s_row[kTok];  // of v and the mask words
     __shared__ float s_w[kTok], s_tau[kTok];
     __shared__ uint32_t s_hmax[kTok];  // bits of the largest finite |h| of this workgroup's rows (ordered like the numbers)
+    __shared__ int s_count[kTok], s_wave[kWideWaves];
+    constexpr bool kIds = NT <= 5;  // (there is room for the row ids of a pass)
+    __shared__ __align__(16) int s_ids[kIds ? kWideWaves * kPairRows : 4];
+    uint32_t* s_union = reinterpret_cast<uint32_t*>(r0);  // before the rows: mask words of the segment's union,
+    int* s_before = reinterpret_cast<int*>(r1);           // selected channels before each
+    int* s_list = reinterpret_cast<int*>(r2);             // and its first rows
+    constexpr int kList = kRowVecs * 4;
+    static_assert(kRowVecs * 4 > kWideMaxMaskWords, "a segment's mask words fit a slot");
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int l16 = lane & 15, q4 = lane >> 4;
     const int ng = a.n_groups[0];
-    const int total = wide_total(a, ng, lane);
     const int W = gridDim.x, piece = wide_piece(W);
-    int pos = wide_cut(total, W, piece);
-    const int end = wide_cut(total, W, piece + 1);
+    const int units = wide_piece_units(a.f);
+    // a group's record in the lane of its number; the first 64 are asked for once, without waiting for their number
+    auto record_of = [&](int g0) { return a.groups[min(g0 + lane, a.max_groups - 1)]; };
+    const WideGroup head = record_of(0);
+    auto tokens_of = [&](int g0) { return g0 == 0 ? head.n : a.groups[min(g0 + lane, a.max_groups - 1)].n; };
+    int total = 0;
+    for (int g0 = 0; g0 < ng; g0 += kWave) {
+        const int n = tokens_of(g0);
+        total += wave_sum(g0 + lane < ng ? wide_weight(n) * units : 0);
+    }
+    // Pieces end where groups end: a second segment costs its start and its end again, 10 us, and the launch waits for the few workgroups that
+    // have one (64 tokens on 8 experts: the mean workgroup done at 139 us, the last at 163).  Each group is cut into as few equal pieces of
+    // at most `most` as it takes, `most` the smallest that leaves no more than W pieces.
+    const bool whole = ng <= W;
+    int most = max((total + W - 1) / W, 1);
+    while (whole) {
+        int sum = 0;
+        const float per_most = 1.0f / (float)most;
+        for (int g0 = 0; g0 < ng; g0 += kWave) {
+            const int n = tokens_of(g0);
+            sum += wave_sum(g0 + lane < ng ? small_quotient(wide_weight(n) * units + most - 1, per_most) : 0);
+        }
+        if (sum <= W) break;  // (at the largest group at the latest: a piece each)
+        most += (most + 31) / 32;
+    }
+    const float per_most = 1.0f / (float)most;
+    auto share_of = [&](int n) { return whole ? small_quotient(wide_weight(n) * units + most - 1, per_most) : wide_weight(n) * units; };
+    int pos = whole ? piece : wide_cut(total, W, piece);
+    const int end = whole ? piece + 1 : wide_cut(total, W, piece + 1);
     const int ns = d / kSliceCols;  // a multiple of eight (d % 512 == 0)
     const int pmax = (a.f + kPairRows - 1) / kPairRows;
+    const int nwords = mask_words_per_task(a.f);
     // where in its 128 bytes a row's piece lies in LDS: at piece ^ swizzle(row), so that the sixteen rows of a tile meet all banks
     auto swizzle = [](int row) { return (row & 7) ^ ((row >> 3) & 1); };
 
     while (pos < end) {  // one group's part of this workgroup's piece at a time
-        int g, base;
-        wide_find(a, ng, lane, pos, g, base);
-        g = __builtin_amdgcn_readfirstlane(g);
-        base = __builtin_amdgcn_readfirstlane(base);
-        const WideGroup grp = a.groups[g];
-        const int count = a.ucount[g];
-        const int32_t* rows = a.urow + (size_t)g * a.f;
-        const unsigned char* gd = scalar_ptr(grp.e.gd);
-        const int seg0 = pos - base, seg1 = min((count + kPairRows - 1) / kPairRows, end - base);
-        pos = base + seg1;
-        __syncthreads();  // the previous group's task arrays are no longer read
-        if (tid < kTok) {
-            const int task = a.order[grp.first + (tid < grp.n ? tid : 0)];  // dead token rows repeat the first one
-            s_task[tid] = task;
-            s_w[tid] = a.task_scale ? a.task_scale[task] : 1.0f;
-            s_tau[tid] = a.task_tau[task];
-            s_hmax[tid] = 0u;
+        int g = -1, base = 0;  // the group that `pos` lies in and where it begins
+        WideGroup grp{};
+        for (int g0 = 0; g0 < ng; g0 += kWave) {
+            WideGroup rec;
+            if (NT <= 5 && g0 == 0) rec = head;  // (ten token tiles have no registers to keep it in)
+            else rec = record_of(g0);
+            const int w = g0 + lane < ng ? share_of(rec.n) : 0;
+            const int inc = wave_inclusive_scan(w, lane);
+            const unsigned long long past = __ballot(base + inc > pos);
+            if (past) {
+                const int l = __ffsll((long long)past) - 1;
+                g = g0 + l;
+                base += __builtin_amdgcn_readlane(inc - w, l);
+                grp = wide_record(rec, l);
+                break;
+            }
+            base += __builtin_amdgcn_readlane(inc, kWave - 1);
         }
+        if (g < 0) break;  // fewer pieces than workgroups
+        int u0, u1, first_piece;
+        if (whole) {
+            // (long pieces end at multiples of 32 channels: where every channel is selected, as in groups of a hundred tokens, no pair is padded)
+            const int k = share_of(grp.n), step = units >= 64 * k ? 4 : 1, steps = (units + step - 1) / step;
+            u0 = steps * (pos - base) / k * step;
+            u1 = min(units, steps * (pos - base + 1) / k * step);
+            first_piece = base;
+            pos = end;
+        } else {  // eight channels belong to the piece that holds the start of their share
+            const int wgt = wide_weight(grp.n);
+            u0 = max(pos - base + wgt - 1, 0) / wgt;
+            u1 = min(units, max(end - base + wgt - 1, 0) / wgt);
+            first_piece = wide_owner(total, W, base);
+            pos = base + units * wgt;  // the next group, or past the end
+        }
+        u0 = __builtin_amdgcn_readfirstlane(u0);
+        u1 = __builtin_amdgcn_readfirstlane(u1);
+        if (u1 <= u0) continue;
+        const int slot = (u0 >> 2) + piece - first_piece;
+        int32_t* rows = a.rows + (wide_row_slot(g, first_piece, pmax) + slot) * kPairRows;
+        const unsigned char* gd = scalar_ptr(grp.e.gd);
+        // ---- the tokens' mask words, the first ones requested ahead of all else
+        const int c0 = 8 * u0, c1 = min(8 * u1, a.f), w0 = c0 >> 5, nws = ((c1 + 31) >> 5) - w0;
+        const float per_segment = 1.0f / (float)nws;
+        const uint32_t first_mask = ~0u << (c0 & 31), last_mask = (c1 & 31) ? (1u << (c1 & 31)) - 1u : ~0u;
+        uint32_t m[4];
+        int tok[4], j[4];
+        auto load_masks = [&](int i0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int i = min(i0 + k * kWideThreads, grp.n * nws - 1);
+                tok[k] = small_quotient(i, per_segment);
+                j[k] = i - tok[k] * nws;
+                const int at = grp.first + tok[k];
+                m[k] = gload4(mask_words + (size_t)(a.by_task ? a.order[at] : at) * nwords + w0 + j[k]);
+            }
+        };
+        load_masks(tid);
+        __syncthreads();  // the previous segment's arrays and slots are no longer read
+        int my_task = 0;  // of token tid, into LDS further down (nobody waits for them yet)
+        float my_w = 0.0f, my_tau = 0.0f;
+        if (tid < kTok) {
+            const int at = grp.first + (tid < grp.n ? tid : 0);  // dead token rows repeat the first one
+            my_task = a.order[at];
+            my_w = a.scale[at];
+            my_tau = a.tau[at];
+            s_hmax[tid] = 0u;
+            s_count[tid] = 0;
+        }
+        // ---- the union of the tokens' selected channels in this segment, ascending
+        for (int i = tid; i < nws; i += kWideThreads) s_union[i] = 0u;
+        __syncthreads();
+        for (int i0 = tid;;) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (i0 + k * kWideThreads >= grp.n * nws) continue;
+                m[k] &= (j[k] == 0 ? first_mask : ~0u) & (j[k] == nws - 1 ? last_mask : ~0u);
+                if (m[k]) {
+                    atomicOr(&s_union[j[k]], m[k]);
+                    atomicAdd(&s_count[tok[k]], __popc(m[k]));
+                }
+            }
+            i0 += 4 * kWideThreads;
+            if (i0 >= grp.n * nws) break;
+            load_masks(i0);
+        }
+        __syncthreads();
+        const int per_thread = (nws + kWideThreads - 1) / kWideThreads;
+        int mine = 0;
+        for (int k = 0; k < per_thread; ++k) mine += tid * per_thread + k < nws ? __popc(s_union[tid * per_thread + k]) : 0;
+        const int inc = wave_inclusive_scan(mine, lane);
+        if (lane == kWave - 1) s_wave[wave] = inc;
+        __syncthreads();
+        int run = inc - mine, count = 0;
+#pragma unroll
+        for (int w = 0; w < kWideWaves; ++w) {
+            run += w < wave ? s_wave[w] : 0;
+            count += s_wave[w];
+        }
+        count = __builtin_amdgcn_readfirstlane(count);
+        for (int k = 0; k < per_thread; ++k) {
+            const int w = tid * per_thread + k;
+            if (w < nws) {
+                s_before[w] = run;
+                run += __popc(s_union[w]);
+            }
+        }
+        __syncthreads();
+        const int npairs = (count + kPairRows - 1) / kPairRows;
+        for (int i = tid; i < 32 * nws; i += kWideThreads) {
+            const uint32_t m = s_union[i >> 5], bit = 1u << (i & 31);
+            if (m & bit) {
+                const int k = s_before[i >> 5] + __popc(m & (bit - 1u)), row = 32 * w0 + i;
+                rows[k] = row;
+                if (k < kList) s_list[k] = row;
+                if (count > kList && k == count - 1)
+                    for (int p = count; p < npairs * kPairRows; ++p) rows[p] = row;
+            }
+        }
+        if (tid == 0) a.segments[piece + g] = make_int4(npairs, slot, g, u0 == 0);
+        if (tid < kTok) {
+            s_row[tid] = a.by_task ? my_task : grp.first + (tid < grp.n ? tid : 0);
+            s_w[tid] = my_w;
+            s_tau[tid] = my_tau;
+            if (tid < grp.n && s_count[tid]) atomicAdd(&a.count[my_task], s_count[tid]);
+        }
+        // (the first pass takes its rows from LDS; when others read the list back, the first slice has been waited for by every wave, and with it
+        // the stores before)
+        wait_lds();
+        meet();
+        if (count <= kList && count + tid < npairs * kPairRows) rows[count + tid] = s_list[count - 1];
+        if (count == 0) continue;
         const int tiles = wide_tiles(grp.n);
         const unsigned char* xop = scalar_ptr(a.xop + (size_t)grp.tile * (d / 32) * 64);
         // Workgroups start at different column slices: rows are 4 d bytes apart, so workgroups that walk the columns in step
         // ask for the same few memory channels at the same time.  (Two groups of one expert that work on the same rows
         // start alike and share them through the L2.)
-        const int rot = (int)((unsigned)(seg0 / 8) * 10u % (unsigned)ns);
+        const int rot = (int)((unsigned)(u0 >> 5) * 10u % (unsigned)ns);
         auto col_slice = [&](int s) {  // s-th slice of this workgroup (past the last one: the last one again)
             const int c = min(s, ns - 1) + rot;
             return c < ns ? c : c - ns;
         };
-        // equal passes of at most one pair per wave
-        const int len = seg1 - seg0;
-        const int np = (len + kWideWaves - 1) / kWideWaves;
-        const int per = (len + np - 1) / np;
+        // equal passes of at most a pair per wave
+        const int passes = (npairs + kWideWaves - 1) / kWideWaves, per_pass = (npairs + passes - 1) / passes * kPairRows;
+        uint4* hseg = a.hbuf + wide_h_first(grp, g, first_piece, pmax, NT) + (size_t)slot * tiles * 128;
         // live: token tiles that this group fills, of NT at most (a tile without tokens would cost as much as any other)
         auto segment = [&](auto live) __attribute__((always_inline)) {
             constexpr int NL = decltype(live)::value;
             constexpr int kXReq = (2 * NL + kWideWaves - 1) / kWideWaves;  // a wave's share of a slice's activations
             constexpr int kReq = 4 + kXReq;                                // ... and its rows
-            for (int p0 = seg0; p0 < seg1; p0 += per) {
-                const int pair = p0 + wave;
-                const bool active = wave < per && pair < seg1;  // the others only help to bring x in
+            for (int p0 = 0; p0 < count; p0 += per_pass) {
+                const int first = p0 + wave * kPairRows;  // the wave's rows
+                const bool active = first < min(count, p0 + per_pass);  // the others only help to bring x in
                 auto load_x = [&](uint4* x, int s) {
 #pragma unroll
                     for (int k = 0; k < kXReq; ++k) {
@@ -256,6 +295,40 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
                         dma16(xop + ((uint32_t)(min(n, tiles - 1) * (d / 32) + 2 * col_slice(s) + ks) * 1024u + 16u * lane), x + it * 64);
                     }
                 };
+                uint32_t wo[4];  // byte offsets from gd of the rows' pieces this lane brings in: at most f * 4 d <= 2^31
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int r = 8 * j + (lane >> 3);
+                    const int k = min(first + r, count - 1);  // rows past the end repeat the last one
+                    const int id = p0 == 0 ? s_list[min(k, kList - 1)] : rows[k];  // (kWideWaves * kPairRows of them at most)
+                    if (kIds && (lane & 7) == 0) s_ids[wave * kPairRows + r] = id;
+                    wo[j] = (uint32_t)id * (uint32_t)(4 * d) + 16u * (uint32_t)((lane & 7) ^ swizzle(r));
+                }
+                // The v that meet these rows.  Gathered by the lane that needs them they are 64 accesses of 4 bytes to the cache per
+                // instruction and a tenth of the kernel's time; where the wave's rows lie within kSpan channels (half of the channels
+                // or more selected by somebody) the wave brings the whole span in instead, 16 bytes per lane, and picks from LDS.  Up to three
+                // token tiles it does so ahead of the loop (behind it the round trip stood bare, 2 us).
+                constexpr bool kEarlyV = NT <= 3;
+                const int last_in = min(first + kPairRows, count) - first - 1;
+                auto row_at = [&](int r) {  // (a scalar)
+                    return __builtin_amdgcn_readfirstlane(kIds ? s_ids[wave * kPairRows + r] : rows[first + r]);
+                };
+                int row0 = 0;
+                bool span = false;
+                uint4 vq[kEarlyV ? NL : 2][4];
+                auto load_v = [&](int n) __attribute__((always_inline)) {  // four tokens per request
+#pragma unroll
+                    for (int k = 0; k < 4; ++k)
+                        vq[kEarlyV ? n : n & 1][k] = gload16u(a.v + (size_t)s_row[16 * n + 4 * k + q4] * a.f + row0 + 4 * l16);
+                };
+                if (kEarlyV && active) {
+                    row0 = min(row_at(0), a.f - kSpan);
+                    span = row0 >= 0 && row_at(last_in) - row0 < kSpan;
+                    if (span) {
+#pragma unroll
+                        for (int n = 0; n < NL; ++n) load_v(n);
+                    }
+                }
                 __syncthreads();  // the slots are no longer read
                 if (!active) {  // the same barriers as the waves below
                     load_x(x0, 0);
@@ -279,13 +352,6 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
                         if (s + 1 < ns) step(x0, s + 1);
                     }
                     continue;
-                }
-                uint32_t wo[4];  // byte offsets from gd of the rows' pieces this lane brings in: at most f * 4 d <= 2^31
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int r = 8 * j + (lane >> 3);
-                    const int k = min(pair * kPairRows + r, count - 1);  // rows past the end repeat the last one
-                    wo[j] = (uint32_t)rows[k] * (uint32_t)(4 * d) + 16u * (uint32_t)((lane & 7) ^ swizzle(r));
                 }
                 auto load_rows = [&](uint4* r, int s) {
                     const uint32_t c = (uint32_t)col_slice(s) * (2u * kSliceCols);
@@ -350,17 +416,15 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
                 for (int t = 0; t < 2; ++t)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const int k = pair * kPairRows + 16 * t + 4 * q4 + i;
-                        row[t][i] = k < count ? rows[k] : -1;
+                        const int r = 16 * t + 4 * q4 + i;
+                        row[t][i] = first + r < count ? (kIds ? s_ids[wave * kPairRows + r] : rows[first + r]) : -1;
                     }
                 int tok0 = l16;
                 asm volatile("" : "+v"(tok0));  // or the addresses below are formed ahead of the loop and held across it
-                // The v that meet these rows.  Gathered by the lane that needs them they are 64 accesses of 4 bytes to the cache per
-                // instruction and a tenth of the kernel's time; where the pair's rows lie within kSpan channels (half of the channels
-                // or more selected by somebody) the wave brings the whole span in instead, 16 bytes per lane, and picks from LDS.
-                const int last_row = __builtin_amdgcn_readfirstlane(rows[min((pair + 1) * kPairRows, count) - 1]);
-                const int row0 = min(__builtin_amdgcn_readfirstlane(rows[pair * kPairRows]), a.f - kSpan);
-                const bool span = row0 >= 0 && last_row - row0 < kSpan;
+                if (!kEarlyV) {
+                    row0 = min(row_at(0), a.f - kSpan);
+                    span = row0 >= 0 && row_at(last_in) - row0 < kSpan;
+                }
                 float* stage = reinterpret_cast<float*>(r0 + wave * 256);  // [16 tokens][64 channels], pieces of 16 bytes at piece ^ token
                 auto finish = [&](int n, const float (&vv)[2][4]) __attribute__((always_inline)) {
                     const float w = s_w[16 * n + tok0], tau = s_tau[16 * n + tok0];
@@ -380,21 +444,15 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
                     atomicMax(&s_hmax[16 * n + tok0], top);  // (no result wanted: fire and forget)
                 };
                 if (span) {
-                    uint4 vq[2][4];
-                    auto load_v = [&](int n) {  // four tokens per request
-#pragma unroll
-                        for (int k = 0; k < 4; ++k)
-                            vq[n & 1][k] = gload16u(a.v + (size_t)s_task[16 * n + 4 * k + q4] * a.f + row0 + 4 * tok0);
-                    };
-                    load_v(0);
+                    if (!kEarlyV) load_v(0);
 #pragma unroll
                     for (int n = 0; n < NL; ++n) {
-                        if (n + 1 < NL) load_v(n + 1);
+                        if (!kEarlyV && n + 1 < NL) load_v(n + 1);
 #pragma unroll
                         for (int k = 0; k < 4; ++k) {
                             // (stored as a native vector of what is read back: a wave's LDS accesses stay in order, and the compiler
                             // must not take the two for different objects)
-                            *reinterpret_cast<f32x4*>(&stage[(4 * k + q4) * kSpan + 4 * (tok0 ^ (4 * k + q4))]) = __builtin_bit_cast(f32x4, vq[n & 1][k]);
+                            *reinterpret_cast<f32x4*>(&stage[(4 * k + q4) * kSpan + 4 * (tok0 ^ (4 * k + q4))]) = __builtin_bit_cast(f32x4, vq[kEarlyV ? n : n & 1][k]);
                         }
                         __builtin_amdgcn_wave_barrier();
                         float vv[2][4];
@@ -415,7 +473,7 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
                         float vv[kBatch][2][4];
 #pragma unroll
                         for (int n = n0; n < n0 + kBatch && n < NL; ++n) {
-                            const unsigned char* vt = reinterpret_cast<const unsigned char*>(a.v + (size_t)s_task[16 * n + tok0] * a.f);
+                            const unsigned char* vt = reinterpret_cast<const unsigned char*>(a.v + (size_t)s_row[16 * n + tok0] * a.f);
 #pragma unroll
                             for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -425,7 +483,7 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, int
                         for (int n = n0; n < n0 + kBatch && n < NL; ++n) finish(n, vv[n - n0]);
                     }
                 }
-                uint4* hb = a.hbuf + wide_h_first(grp, pmax) + (size_t)pair * tiles * 128 + lane;
+                uint4* hb = hseg + (size_t)(first / kPairRows) * tiles * 128 + lane;
 #pragma unroll
                 for (int n = 0; n < NL; ++n)
                     if (n < tiles) {
@@ -456,51 +514,120 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
     __shared__ uint4 hs[2][SL * NT * 128];  // [pair][token tile][hi, lo][lane]
     __shared__ float s_scale[kTok], s_back[kTok];  // the token's power of two and its reciprocal
     __shared__ __align__(16) int ids[kRing][SL * kPairRows];
+    __shared__ int s_pair[kWideMaxSegments + 1];       // first pair of each segment in the sequence of all
+    __shared__ uint32_t s_slot[kWideMaxSegments];      // its pair slot in the group; group in the upper half
+    __shared__ uint16_t s_first[kWideMaxSegments];     // a group's first segment
+    __shared__ int s_wave[kWideWaves], s_at;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int l16 = lane & 15, q4 = lane >> 4;
     const int ng = a.n_groups[0];
-    const int total = wide_total(a, ng, lane);
+    const WideGroup head = a.groups[min(lane, a.max_groups - 1)];  // the first 64 groups' records, in the lane of their number
+    const int nseg = min(a.pieces + ng, kWideMaxSegments);
+    int total = 0;
+    for (int i0 = 0; i0 < nseg; i0 += kWideThreads) {
+        const int i = i0 + tid;
+        const int4 seg = i < nseg ? a.segments[i] : make_int4(0, 0, 0, 0);
+        const int inc = wave_inclusive_scan(seg.x, lane);
+        if (lane == kWave - 1) s_wave[wave] = inc;
+        __syncthreads();
+        int at = total + inc - seg.x;
+#pragma unroll
+        for (int w = 0; w < kWideWaves; ++w) {
+            at += w < wave ? s_wave[w] : 0;
+            total += s_wave[w];
+        }
+        if (i < nseg) {
+            s_pair[i] = at;
+            s_slot[i] = (uint32_t)seg.y | (uint32_t)seg.z << 16;
+            if (seg.w) s_first[seg.z] = (uint16_t)i;
+        }
+        __syncthreads();
+    }
+    total = __builtin_amdgcn_readfirstlane(total);
+    if (tid == 0) s_pair[nseg] = total;
+    __syncthreads();
+    auto segment_of = [&](int pair) {  // the last one that begins at or before it (those without rows begin where the next does)
+        int lo = 0, hi = nseg;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (s_pair[mid] <= pair) lo = mid;
+            else hi = mid;
+        }
+        return lo;
+    };
     // no more pieces than the actual rows fill with four pairs each: every piece up to the last one holds some rows, so the
     // pieces of a group are consecutive and all of them write a partial result
     const int W = min((int)gridDim.x, (total + 3) / 4), piece = wide_piece(gridDim.x);
     if (piece >= W) return;
     int pos = wide_cut(total, W, piece);
     const int end = wide_cut(total, W, piece + 1);
+    for (int i = tid; i < nseg; i += kWideThreads)
+        if (s_pair[i] <= pos && pos < s_pair[i + 1]) s_at = i;
+    __syncthreads();
+    int seg_at = __builtin_amdgcn_readfirstlane(s_at);  // the segment that `pos` lies in
     const int pmax = (a.f + kPairRows - 1) / kPairRows;
     const int col = blockIdx.y * kDownCols + wave * 64 + 4 * l16;  // this lane's four columns (d % 512 == 0)
 
     while (pos < end) {
-        int g, base;
-        wide_find(a, ng, lane, pos, g, base);
-        g = __builtin_amdgcn_readfirstlane(g);
-        base = __builtin_amdgcn_readfirstlane(base);
-        const WideGroup grp = a.groups[g];
-        const int count = a.ucount[g];
-        const int32_t* rows = a.urow + (size_t)g * a.f;
+        const int g = __builtin_amdgcn_readfirstlane((int)(s_slot[seg_at] >> 16));
+        const int first_seg = __builtin_amdgcn_readfirstlane((int)s_first[g]);
+        const int base = __builtin_amdgcn_readfirstlane(s_pair[first_seg]);
+        const int gend = g + 1 < ng ? __builtin_amdgcn_readfirstlane(s_pair[s_first[min(g + 1, ng - 1)]]) : total;
+        WideGroup grp;
+        if (NT <= 5 && g < kWave) grp = wide_record(head, g);
+        else grp = a.groups[g];
+        const int32_t* rows = a.rows + wide_row_slot(g, first_seg - g, pmax) * kPairRows;
         const unsigned char* gd = scalar_ptr(grp.e.gd);
         const uint32_t dcol = 2 * (uint32_t)(d + col);
-        const int npairs = (count + kPairRows - 1) / kPairRows;
-        const int seg0 = pos - base, seg1 = min(npairs, end - base);
-        const int len = seg1 - seg0;
-        pos = base + seg1;
+        const int npairs = gend - base;
+        const int pair0 = pos, len = min(gend, end) - pos;
+        pos = pair0 + len;
+        // the pair slots of the pairs one after the other (past the end the last pair's), as scalars
+        int seg = seg_at, seg_end = __builtin_amdgcn_readfirstlane(s_pair[seg_at + 1]);
+        int seg_slot = __builtin_amdgcn_readfirstlane((int)(s_slot[seg_at] & 0xFFFFu) - s_pair[seg_at]);
+        auto slots_of = [&](int (&r)[SL], int s) __attribute__((always_inline)) {
+#pragma unroll
+            for (int p = 0; p < SL; ++p) {
+                const int pair = pair0 + min(s * SL + p, len - 1);
+                while (pair >= seg_end) {
+                    ++seg;
+                    seg_end = __builtin_amdgcn_readfirstlane(s_pair[seg + 1]);
+                    seg_slot = __builtin_amdgcn_readfirstlane((int)(s_slot[seg] & 0xFFFFu) - s_pair[seg]);
+                }
+                r[p] = seg_slot + pair;
+            }
+        };
+        if (pos < end) {  // where the next part begins
+            seg_at = __builtin_amdgcn_readfirstlane((int)s_first[g + 1]);
+            while (__builtin_amdgcn_readfirstlane(s_pair[seg_at + 1]) <= pos) ++seg_at;
+        }
+        auto slot_at = [](const int (&r)[SL], int p) __attribute__((always_inline)) {  // (p: a scalar)
+            int v = r[0];
+#pragma unroll
+            for (int k = 1; k < SL; ++k) {
+                const int other = __builtin_amdgcn_readfirstlane(r[k]);  // (left alone, the choice becomes an array in memory)
+                v = p == k ? other : v;
+            }
+            return v;
+        };
         const int w_first = wide_owner(total, W, base);
         if (piece == w_first && blockIdx.y == 0) {  // where a task's partial results are
             const int slots = wide_owner(total, W, base + npairs - 1) - w_first + 1;
             if (tid < grp.n) a.task_rows[a.order[grp.first + tid]] = make_int2(grp.first + tid + w_first * kTok, slots);
         }
         const int tiles = __builtin_amdgcn_readfirstlane(wide_tiles(grp.n));
-        const unsigned char* hsrc = scalar_ptr(a.hbuf + wide_h_first(grp, pmax) + (size_t)seg0 * tiles * 128);
+        const unsigned char* hsrc = scalar_ptr(a.hbuf + wide_h_first(grp, g, first_seg - g, pmax, NT));
         const int ns = (len + SL - 1) / SL;
         uint4 hq[kHRounds];
         int idq = 0;
         // (requests are unconditional, as in the gate kernel: past the end they repeat a valid entry and the value is
         // replaced by zero on its way into LDS)
-        auto load_h = [&](int s) {  // h of slice s
+        auto load_h = [&](const int (&slots)[SL]) __attribute__((always_inline)) {  // h of the slice that has these slots
 #pragma unroll
             for (int r = 0; r < kHRounds; ++r) {
                 const int first = wave * kWave + r * kWideThreads;  // (a wave's entries belong to one pair and one tile)
-                const int pr = min(s * SL + first / (NT * 128), len - 1);
+                const int pr = slot_at(slots, first / (NT * 128));
                 const int tile = min(first % (NT * 128) / 128, tiles - 1);  // (past the group's tiles: token rows that nobody reads)
                 hq[r] = gload16(hsrc + (uint32_t)(pr * tiles + tile) * 2048u + (uint32_t)(tid & 127) * 16u);
             }
@@ -538,8 +665,9 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
                 out[2 * 64] = __builtin_bit_cast(uint2, __builtin_convertvector(rest, h16x4));
             }
         };
-        auto load_ids = [&](int s) {
-            idq = (int)gload4(rows + min((seg0 + s * SL) * kPairRows + (tid & (SL * kPairRows - 1)), count - 1));
+        auto load_ids = [&](const int (&slots)[SL]) __attribute__((always_inline)) {
+            const int pr = (2 * wave) & (SL - 1), lower = slot_at(slots, pr), upper = slot_at(slots, pr + 1);
+            idq = (int)gload4(rows + (lane < 32 ? lower : upper) * kPairRows + (lane & 31));
         };
         auto store_ids = [&](int s) {
             int k = tid;
@@ -561,8 +689,10 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
             for (int n = 0; n < NT; ++n) acc[j][n] = f32x4{0.f, 0.f, 0.f, 0.f};
 
         __syncthreads();  // the previous group's LDS contents are no longer read
-        load_ids(0);
-        load_h(0);
+        int slots[SL];  // of the coming slice
+        slots_of(slots, 0);
+        load_ids(slots);
+        load_h(slots);
         const int e = exponent(min(tid, kTok - 1));
         if constexpr (kScaleRegs) {
 #pragma unroll
@@ -573,7 +703,8 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
             s_back[tid] = power(e);
         }
         store_ids(0);
-        load_ids(1);
+        slots_of(slots, 1);
+        load_ids(slots);
         if constexpr (!kScaleRegs) __syncthreads();
         store_h(0);
         store_ids(1);
@@ -586,8 +717,9 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
 #pragma unroll 1
         for (int s = 0; s < ns; ++s) {
             const int buf = s & 1;
-            load_h(s + 1);
-            load_ids(s + 2);
+            load_h(slots);
+            slots_of(slots, s + 2);
+            load_ids(slots);
 #pragma unroll
             for (int p = 0; p < SL; ++p) {
                 uint32_t b[4][4];  // operand of column j: rows 0..7 of this lane's quarter
@@ -659,7 +791,11 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
         if (lanes == 0ull) continue;
         __threadfence_block();  // the stores above are done before others to the same places
         const float* hp = reinterpret_cast<const float*>(hsrc);
-        const int first = seg0 * kPairRows, last = min(count, seg1 * kPairRows);
+        const int last = len * kPairRows;
+        auto slot_of = [&](int p) {  // pair slot of pair p of this part
+            const int s = segment_of(pair0 + p);
+            return (int)(s_slot[s] & 0xFFFFu) + pair0 + p - s_pair[s];
+        };
         for (uint64_t left = lanes; left != 0ull; left &= left - 1ull) {
             const int src = __ffsll((long long)left) - 1;  // the lane that holds these columns, for a quarter of the tokens
             uint64_t toks = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)odd, src) |
@@ -667,27 +803,31 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
             const int c0 = blockIdx.y * kDownCols + wave * 64 + 4 * (src & 15);
             for (; toks != 0ull; toks &= toks - 1ull) {
                 const int bit = __ffsll((long long)toks) - 1, n = bit >> 2, tok = 16 * n + 4 * (src >> 4) + (bit & 3);
-                const int task = a.order[grp.first + tok];
-                const float* vt = a.v + (size_t)task * a.f;
-                const float tau = a.task_tau[task];
+                const int at = grp.first + tok;
+                const float* vt = a.v + (size_t)(a.by_task ? a.order[at] : at) * a.f;
+                const float tau = a.tau[at];
                 float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
                 constexpr int kRows = 4;  // per lane, requested together
-                for (int r0 = first; r0 < last; r0 += kRows * kWave) {
-                    int row[kRows];
+                for (int r0 = 0; r0 < last; r0 += kRows * kWave) {
+                    int row[kRows], before[kRows];
                     float vr[kRows], h[kRows];
                     uint2 w[kRows];
 #pragma unroll
-                    for (int i = 0; i < kRows; ++i) row[i] = rows[min(r0 + i * kWave + lane, last - 1)];
+                    for (int i = 0; i < kRows; ++i) {
+                        const int r = min(r0 + i * kWave + lane, last - 1), sl = slot_of(r / kPairRows), in = r % kPairRows;
+                        row[i] = rows[sl * kPairRows + in];
+                        before[i] = in ? rows[sl * kPairRows + in - 1] : -1;
+                        h[i] = hp[((size_t)(sl * tiles + n) * 128 + (in >> 4) * 64 + ((in >> 2) & 3) * 16 + (tok & 15)) * 4 + (in & 3)];
+                    }
 #pragma unroll
                     for (int i = 0; i < kRows; ++i) {
-                        const int r = min(r0 + i * kWave + lane, last - 1), p = r / kPairRows - seg0, in = r % kPairRows;
                         vr[i] = vt[row[i]];
-                        h[i] = hp[((size_t)(p * tiles + n) * 128 + (in >> 4) * 64 + ((in >> 2) & 3) * 16 + (tok & 15)) * 4 + (in & 3)];
                         w[i] = gload8(gd + ((uint32_t)row[i] * (uint32_t)(4 * d) + 2 * (uint32_t)(d + c0)));
                     }
 #pragma unroll
                     for (int i = 0; i < kRows; ++i) {
-                        if (!(r0 + i * kWave + lane < last && fabsf(vr[i]) > tau)) continue;
+                        // (the last row of a segment is repeated up to a whole pair)
+                        if (!(r0 + i * kWave + lane < last && row[i] != before[i] && fabsf(vr[i]) > tau)) continue;
                         const h16x2 lo = as_h2(w[i].x), hi = as_h2(w[i].y);
                         sum.x = fmaf(h[i], (float)lo.x, sum.x);
                         sum.y = fmaf(h[i], (float)lo.y, sum.y);
@@ -782,13 +922,17 @@ static WidePlan wide_plan_for(int nt, int max_groups, int est_groups, int d, int
     const long long est_pairs = (long long)p.est_groups * p.pairs;
     // one workgroup per compute unit; a piece is at least one pair (gate) or four (down: each piece costs a partial result)
     p.wg_gate = (int)(est_pairs < num_cus() ? est_pairs : num_cus());
+    if (p.wg_gate > 8) p.wg_gate &= ~7;
+    // (see wide_layout.h)
+    p.row_slots = (size_t)max_groups * (p.pairs + 2) + p.wg_gate;
+    p.h_vecs = ((size_t)p.h_tiles * p.pairs + (size_t)nt * (p.wg_gate + 2 * max_groups)) * 128;
+    p.segments = p.wg_gate + max_groups;
     const int per_col = num_cus() / (d / kDownCols);
     const long long by_len = (est_pairs + 3) / 4;
     p.wg_down = (int)(by_len < per_col ? by_len : per_col);
     if (max_down > 0 && p.wg_down > max_down) p.wg_down = max_down;
     if (p.wg_down > 8) p.wg_down &= ~7;  // (see wide_piece)
     if (p.wg_down < 1) p.wg_down = 1;
-    if (p.wg_gate > 8) p.wg_gate &= ~7;
     p.partial_rows = (size_t)n_tasks + (size_t)p.chunk * (p.wg_down - 1);
     return p;
 }
@@ -818,8 +962,8 @@ WidePlan wide_room(int d, int f, int T, int n_experts, int top_k, int n_shared) 
 }
 
 template <int NT>
-static hipError_t launch_wide_nt(const WideArgs& a, const WidePlan& p, int d, hipStream_t stream) {
-    gate_wide_kernel<NT><<<dim3(p.wg_gate), dim3(kWideThreads), 0, stream>>>(a, d);
+static hipError_t launch_wide_nt(const WideArgs& a, const WidePlan& p, const uint32_t* mask_words, int d, hipStream_t stream) {
+    gate_wide_kernel<NT><<<dim3(p.wg_gate), dim3(kWideThreads), 0, stream>>>(a, mask_words, d);
     hipError_t rc = hipGetLastError();
     if (rc != hipSuccess) return rc;
     down_wide_kernel<NT><<<dim3(p.wg_down, d / kDownCols), dim3(kWideThreads), 0, stream>>>(a, d);
@@ -827,19 +971,21 @@ static hipError_t launch_wide_nt(const WideArgs& a, const WidePlan& p, int d, hi
 }
 
 hipError_t launch_gate_down_wide(const WideArgs& a, const WidePlan& p, const uint32_t* mask_words, int d, hipStream_t stream) {
-    if (d % kDownCols != 0 || mask_words_per_task(a.f) > kWideMaxMaskWords) return hipErrorInvalidValue;
-    wide_rows_kernel<<<dim3(p.max_groups + p.h_tiles * ((d + kOperandCols - 1) / kOperandCols)), dim3(1024), 0, stream>>>(a, mask_words, p.max_groups, d);
-    hipError_t rc = hipGetLastError();
-    if (rc != hipSuccess) return rc;
+    if (d % kDownCols != 0 || mask_words_per_task(a.f) > kWideMaxMaskWords || p.segments > kWideMaxSegments) return hipErrorInvalidValue;
     switch (p.nt) {
-        case 1: return launch_wide_nt<1>(a, p, d, stream);
-        case 2: return launch_wide_nt<2>(a, p, d, stream);
-        case 3: return launch_wide_nt<3>(a, p, d, stream);
-        case 4: return launch_wide_nt<4>(a, p, d, stream);
-        case 5: return launch_wide_nt<5>(a, p, d, stream);
-        case 10: return launch_wide_nt<10>(a, p, d, stream);
+        case 1: return launch_wide_nt<1>(a, p, mask_words, d, stream);
+        case 2: return launch_wide_nt<2>(a, p, mask_words, d, stream);
+        case 3: return launch_wide_nt<3>(a, p, mask_words, d, stream);
+        case 4: return launch_wide_nt<4>(a, p, mask_words, d, stream);
+        case 5: return launch_wide_nt<5>(a, p, mask_words, d, stream);
+        case 10: return launch_wide_nt<10>(a, p, mask_words, d, stream);
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_wide_prepare(const WidePrep& prep, const WideArgs& a, int n_tasks, int d, hipStream_t stream) {
+    wide_prepare_kernel<<<dim3(n_tasks), dim3(128), 0, stream>>>(prep, a, n_tasks, d);
+    return hipGetLastError();
 }
 
 hipError_t launch_wide_single(const DevExpert& e, int n_tasks, int chunk, WideGroup* groups, int32_t* n_groups, int32_t* order,

@@ -79,6 +79,18 @@ def test_gate_rows_and_activations_through_lds(d, f, n, n_shared, top_k, T, pct)
     _run_layer_case(270 + T, 9, d, f, 2, 64, n, n_shared, top_k, False, T, pct, gap=f * (100 - pct) >= 6400)
 
 
+@pytest.mark.parametrize("d,f,bits,group,n,n_shared,top_k,T,pct", [
+    (512, 40, 2, 64, 600, 0, 8, 100, 50),    # more groups than workgroups: pieces that hold several segments
+    (512, 2100, 2, 64, 0, 1, 0, 20, 60),     # a piece of eight or sixteen channels per workgroup, the last one of four
+    (512, 3001, 4, 64, 44, 0, 4, 200, 40),   # pieces of 512 channels and more, several passes each; groups by the activations' kernel
+    (512, 70, 2, 64, 20, 0, 8, 257, 50),     # one task more than that kernel groups: the grouping kernel in front
+    (512, 70, 8, 64, 20, 0, 8, 40, 50),      # an up projection that keeps v and the masks by task
+    (8192, 45, 4, 64, 5, 1, 2, 12, 50),      # two waves group the tasks
+])
+def test_segments_and_groups(d, f, bits, group, n, n_shared, top_k, T, pct):
+    _run_layer_case(470 + T, 13, d, f, bits, group, n, n_shared, top_k, False, T, pct, gap=f * (100 - pct) >= 6400)
+
+
 @pytest.mark.parametrize("d,f,n,n_shared,top_k,T,pct", [
     (1024, 300, 3, 1, 1, 150, 60),   # ten tiles, of which the routed experts fill two to four; an odd number of pairs
     (512, 97, 2, 1, 1, 155, 30),     # five to six; one row in the last pair
