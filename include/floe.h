@@ -189,6 +189,10 @@ int floe_gate_down_sparse(const floe_expert* e, const floe_half* x, int T, const
 int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, const float* tau,
                            const float* out_scale, float* y_acc, int32_t* idx, int32_t* count, void* workspace,
                            size_t workspace_bytes, void* stream);
+/* The same; when the list is asked for, idx[t][count[t] .. f) = -1 as well (floe_expert_ffn_sparse leaves those entries untouched). */
+int floe_expert_ffn_sparse_padded(const floe_expert* e, const floe_half* x, int T, const float* tau,
+                                  const float* out_scale, float* y_acc, int32_t* idx, int32_t* count, void* workspace,
+                                  size_t workspace_bytes, void* stream);
 
 /*
  * The three candidates for sparsification that Sec. 3.2.1 compares (Eq. 3-5): the sparsity function S_t applied to

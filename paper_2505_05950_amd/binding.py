@@ -87,6 +87,7 @@ def load():
     lib.floe_expert_workspace_bytes.argtypes = [C.POINTER(_Shape), i32]
     lib.floe_gate_down_sparse.argtypes = [C.POINTER(_Expert), vp, i32, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.floe_expert_ffn_sparse.argtypes = [C.POINTER(_Expert), vp, i32, vp, vp, vp, vp, vp, vp, sz, vp]
+    lib.floe_expert_ffn_sparse_padded.argtypes = lib.floe_expert_ffn_sparse.argtypes
     lib.floe_expert_sparsified_workspace_bytes.restype = sz
     lib.floe_expert_sparsified_workspace_bytes.argtypes = [C.POINTER(_Shape), i32]
     lib.floe_expert_ffn_sparsified.argtypes = [C.POINTER(_Expert), i32, vp, i32, vp, vp, vp, vp, vp, vp, sz, vp]
@@ -241,9 +242,11 @@ def floe_expert_ffn_sparse(e: Expert, x, tau, out_scale, y_acc, idx=None, count=
                            want_list=True):
     """Alg. 1 for T tokens; returns (y_acc, idx, count); want_list=False passes no list buffers (idx, count = None)."""
     T = x.shape[0]
+    call = load().floe_expert_ffn_sparse
     if want_list:
-        if idx is None:
-            idx = torch.full((T, e.f), -1, dtype=torch.int32, device=x.device)
+        if idx is None:  # a list of our own: the call that writes it also sets what lies behind its end
+            call = load().floe_expert_ffn_sparse_padded
+            idx = torch.empty((T, e.f), dtype=torch.int32, device=x.device)
         if count is None:
             count = torch.empty((T,), dtype=torch.int32, device=x.device)
     else:
@@ -252,8 +255,8 @@ def floe_expert_ffn_sparse(e: Expert, x, tau, out_scale, y_acc, idx=None, count=
         workspace = _workspace(floe_expert_workspace_bytes(e.d, e.f, e.bits, e.group, T), x.device)
     wp, wn = _aligned_ptr(workspace)
     es = e.c_struct()
-    _check(load().floe_expert_ffn_sparse(C.byref(es), _ptr(x), T, _ptr(tau), _ptr(out_scale), _ptr(y_acc), _ptr(idx),
-                                         _ptr(count), wp, wn, _stream(stream)), "floe_expert_ffn_sparse")
+    _check(call(C.byref(es), _ptr(x), T, _ptr(tau), _ptr(out_scale), _ptr(y_acc), _ptr(idx), _ptr(count), wp, wn,
+                _stream(stream)), "floe_expert_ffn_sparse")
     return y_acc, idx, count
 
 

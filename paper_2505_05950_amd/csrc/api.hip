@@ -473,9 +473,10 @@ int floe_gate_down_sparse(const floe_expert* e, const floe_half* x, int T, const
     return FLOE_OK;
 }
 
-int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, const float* tau, const float* out_scale,
-                           float* y_acc, int32_t* idx, int32_t* count, void* workspace, size_t workspace_bytes,
-                           void* stream) {
+// pad: the entries of idx behind a list become -1 (floe_expert_ffn_sparse_padded)
+static int expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, const float* tau, const float* out_scale,
+                             float* y_acc, int32_t* idx, int32_t* count, bool pad, void* workspace, size_t workspace_bytes,
+                             void* stream) {
     if (!e) return FLOE_EINVAL;
     int rc = check_shape(&e->s);
     if (rc) return rc;
@@ -510,7 +511,7 @@ int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, cons
         nblk = w.nblk_fused;
         if (idx) {
             Bracket list(FLOE_KERNEL_SELECT, st);  // one launch that is both: whichever of the two is armed sees it
-            FLOE_LAUNCH(FLOE_KERNEL_COMBINE, st, launch_combine_select(partial, e->s.d, T, nblk, y_acc, v, e->s.f, tau, idx, count, st));
+            FLOE_LAUNCH(FLOE_KERNEL_COMBINE, st, launch_combine_select(partial, e->s.d, T, nblk, y_acc, v, e->s.f, tau, idx, count, pad, st));
             return FLOE_OK;
         }
     } else if (w.wide) {
@@ -551,11 +552,12 @@ int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, cons
                         launch_up_gemv(map, xh, nullptr, v, tau, mask, e->s.d, e->s.f, e->s.bits, e->s.group, T, st));
         }
         FLOE_LAUNCH(FLOE_KERNEL_GATE_DOWN, st, launch_gate_down_wide(wa, w.wp, mask, e->s.d, st));
-        if (idx) FLOE_LAUNCH(FLOE_KERNEL_SELECT, st, launch_select(v, e->s.f, T, tau, idx, count, st));
+        if (idx) FLOE_LAUNCH(FLOE_KERNEL_SELECT, st, launch_select(v, e->s.f, T, tau, idx, count, st, pad));
         FLOE_LAUNCH(FLOE_KERNEL_COMBINE, st, launch_combine_wide(wa, w.wp, e->s.d, T, y_acc, nullptr, st));
         return FLOE_OK;
     } else {
         // a caller that wants no list still gets one built, in the workspace
+        if (idx && pad) FLOE_HIP(launch_pad_list(idx, e->s.f, T, st));
         int32_t* idx_ws = idx ? idx : reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + w.idx_off);
         int32_t* count_ws = count ? count : reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + w.count_off);
         if (mask_path_ok(e->s.f)) {
@@ -576,6 +578,18 @@ int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, cons
     }
     FLOE_LAUNCH(FLOE_KERNEL_COMBINE, st, launch_combine(partial, e->s.d, T, 1, nblk, y_acc, nullptr, st));
     return FLOE_OK;
+}
+
+int floe_expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, const float* tau, const float* out_scale,
+                           float* y_acc, int32_t* idx, int32_t* count, void* workspace, size_t workspace_bytes,
+                           void* stream) {
+    return expert_ffn_sparse(e, x, T, tau, out_scale, y_acc, idx, count, false, workspace, workspace_bytes, stream);
+}
+
+int floe_expert_ffn_sparse_padded(const floe_expert* e, const floe_half* x, int T, const float* tau, const float* out_scale,
+                                  float* y_acc, int32_t* idx, int32_t* count, void* workspace, size_t workspace_bytes,
+                                  void* stream) {
+    return expert_ffn_sparse(e, x, T, tau, out_scale, y_acc, idx, count, true, workspace, workspace_bytes, stream);
 }
 
 // workspace of the sparsification variants: [v][act][h: T*f floats each][partial: T*nblk*d floats]

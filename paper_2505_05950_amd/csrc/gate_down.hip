@@ -367,14 +367,16 @@ __global__ __launch_bounds__(256) void combine_kernel(const float* __restrict__ 
 // The same sums with the index list cut from v beside them (one-expert calls that ask for the list: both need the fused
 // kernel's results and nothing of each other): workgroup x = 0 of a token runs the selection, the others four blocks of
 // columns each.  One launch instead of two dependent ones: d 1024 f 3584, one token, 25.4 -> 22.5 us per call (4.0 us against 3.8 + 3.1 us and the gap).
+// The -1 behind a list that the call allocated for its caller is written here too: a call is bound by its launches, and a fill in front was
+// one more (the same shape, 21.2 -> 18.4 us per call).
 __global__ __launch_bounds__(1024) void combine_select_kernel(const float* __restrict__ partial, int d, int per_token,
                                                               float* __restrict__ y_acc, const float* __restrict__ v, int f,
                                                               const float* __restrict__ tau, int32_t* __restrict__ idx,
-                                                              int32_t* __restrict__ count) {
+                                                              int32_t* __restrict__ count, int pad) {
     __shared__ float4 red[4][4][8];
     const int t = blockIdx.y;
     if (blockIdx.x == 0) {
-        select_task(v + (size_t)t * f, f, tau[t], idx + (size_t)t * f, count + t);
+        select_task(v + (size_t)t * f, f, tau[t], idx + (size_t)t * f, count + t, pad != 0);
         return;
     }
     const int sub = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
@@ -382,10 +384,10 @@ __global__ __launch_bounds__(1024) void combine_select_kernel(const float* __res
 }
 
 hipError_t launch_combine_select(const float* partial, int d, int T, int nblk, float* y_acc, const float* v, int f, const float* tau,
-                                 int32_t* idx, int32_t* count, hipStream_t stream) {
+                                 int32_t* idx, int32_t* count, bool pad, hipStream_t stream) {
     if (T == 0) return hipSuccess;
     if (d % 128 != 0) return hipErrorInvalidValue;
-    combine_select_kernel<<<dim3(1 + d / 128, T), dim3(1024), 0, stream>>>(partial, d, nblk, y_acc, v, f, tau, idx, count);
+    combine_select_kernel<<<dim3(1 + d / 128, T), dim3(1024), 0, stream>>>(partial, d, nblk, y_acc, v, f, tau, idx, count, pad);
     return hipGetLastError();
 }
 

@@ -138,7 +138,8 @@ hipError_t launch_up_gemv_grouped(const DevExpert* table, const TokenGroup* grou
 
 // S3 as a kernel of its own: per task threshold tau[task]
 hipError_t launch_select(const float* v, int f, int n_tasks, const float* tau, int32_t* idx, int32_t* count,
-                         hipStream_t stream);
+                         hipStream_t stream, bool pad = false);  // pad: -1 behind the last entry of a list
+hipError_t launch_pad_list(int32_t* idx, int f, int n_tasks, hipStream_t stream);  // -1 everywhere
 
 // S3 (compaction) + S4 + S5.  Index lists come either from mask_words (then idx/count are WRITTEN, both
 // may be nullptr) or, with mask_words == nullptr, from idx/count (read).  partial[task][blk][d].
@@ -342,7 +343,7 @@ hipError_t launch_combine(const float* partial, int d, int T, int slots, int nbl
 
 // S6 of a one-expert call together with S3's index lists (from v and tau)
 hipError_t launch_combine_select(const float* partial, int d, int T, int nblk, float* y_acc, const float* v, int f, const float* tau,
-                                 int32_t* idx, int32_t* count, hipStream_t stream);
+                                 int32_t* idx, int32_t* count, bool pad, hipStream_t stream);
 
 // S1: router + per-task table (resolved expert pointers, weight, tau)
 struct RouterArgs {

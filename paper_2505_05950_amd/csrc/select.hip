@@ -10,15 +10,28 @@
 namespace floe {
 
 __global__ __launch_bounds__(1024) void select_kernel(const float* __restrict__ v, int f, const float* __restrict__ tau,
-                                                      int32_t* __restrict__ idx, int32_t* __restrict__ count) {
+                                                      int32_t* __restrict__ idx, int32_t* __restrict__ count, int pad) {
     const int task = blockIdx.x;
-    select_task(v + (size_t)task * f, f, tau[task], idx + (size_t)task * f, count + task);
+    select_task(v + (size_t)task * f, f, tau[task], idx + (size_t)task * f, count + task, pad != 0);
 }
 
 hipError_t launch_select(const float* v, int f, int n_tasks, const float* tau, int32_t* idx, int32_t* count,
-                         hipStream_t stream) {
+                         hipStream_t stream, bool pad) {
     if (n_tasks == 0) return hipSuccess;
-    select_kernel<<<dim3(n_tasks), dim3(1024), 0, stream>>>(v, f, tau, idx, count);
+    select_kernel<<<dim3(n_tasks), dim3(1024), 0, stream>>>(v, f, tau, idx, count, pad);
+    return hipGetLastError();
+}
+
+__global__ __launch_bounds__(256) void pad_list_kernel(int32_t* __restrict__ idx, long long n) {
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) idx[i] = -1;
+}
+
+hipError_t launch_pad_list(int32_t* idx, int f, int n_tasks, hipStream_t stream) {
+    const long long n = (long long)n_tasks * f, blocks = (n + 255) / 256;
+    if (n == 0) return hipSuccess;
+    if (blocks > 0x7fffffffll) return hipErrorInvalidValue;
+    pad_list_kernel<<<dim3((unsigned)blocks), dim3(256), 0, stream>>>(idx, n);
     return hipGetLastError();
 }
 

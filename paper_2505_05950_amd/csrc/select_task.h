@@ -7,9 +7,10 @@ namespace floe {
 
 // idx[0 .. count) = ascending { j : |v_j| > th }.  Each wave owns a contiguous slice of the channels and requests all its
 // values (or kHold chunks of it at a time) before it looks at the first one: taken chunk by chunk, the slice cost one round
-// trip to memory per chunk and pass (two tasks, f 14336: 10.4 -> 5.4 us).
+// trip to memory per chunk and pass (two tasks, f 14336: 10.4 -> 5.4 us).  pad: entries past count become -1, otherwise they
+// stay as they are.
 __device__ __forceinline__ void select_task(const float* __restrict__ vt, int f, float th, int32_t* __restrict__ it,
-                                            int32_t* __restrict__ count) {
+                                            int32_t* __restrict__ count, bool pad) {
     constexpr int kWaves = 16;
     constexpr int kHold = 16;  // chunks whose values a wave holds: one request round up to f = 16384
     __shared__ int wave_total[kWaves];
@@ -46,6 +47,8 @@ __device__ __forceinline__ void select_task(const float* __restrict__ vt, int f,
         all += n;
     }
     if (tid == 0) *count = all;
+    if (pad)
+        for (int i = all + tid; i < f; i += kWaves * kWave) it[i] = -1;
     const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
     for (int c = c0; c < c1; c += kHold) {
         if (c1 - c0 > kHold) look(c);  // (a slice of one round is still in its masks)

@@ -255,6 +255,32 @@ def test_expert_ffn_without_a_list_gives_the_same_result(d, f, bits, group, T):
         assert G.rel_err(y1[t], w * O.sparse_ffn(ex_np[3], x[t], v_ref[t], got)[1]) <= G.Y_TIGHT
 
 
+@pytest.mark.parametrize("d,f,bits,group,T,pct", [
+    (1024, 1025, 2, 64, 1, 80), (2048, 333, 4, 32, 16, 0), (1024, 64, 2, 64, 3, 101),  # the fused kernel; every channel, none
+    (2048, 1100, 2, 64, 40, 75),                                                       # wide kernels
+    (512, 400, 8, 64, 3, 90), (512, 70000, 2, 64, 2, 95),                              # separate kernels, masks and beyond them
+])
+def test_list_behind_its_end(d, f, bits, group, T, pct):
+    """A list allocated by the call holds -1 behind its last entry, whatever the memory held; a caller's own list stays as it was there."""
+    G = _gc()
+    import paper_2505_05950_amd as F
+    ex_np, ex_dev, x = _expert_case(12, 61, d, f, bits, group, T)
+    v = [O.up_gemv(*ex_np[:3], d, bits, group, x[t]) for t in range(min(T, 2))]
+    level = -1.0 if pct == 0 else 1e30 if pct > 100 else max(O.threshold_for_sparsity(r, pct) for r in v)
+    tau = torch.full((T,), float(level), device=G.DEV)
+    own = torch.full((T, f), 7, dtype=torch.int32, device=G.DEV)
+    own_count = torch.empty((T,), dtype=torch.int32, device=G.DEV)
+    y = torch.zeros((T, d), dtype=torch.float32, device=G.DEV)
+    F.floe_expert_ffn_sparse(ex_dev, G.dev(x), tau, None, y, own, own_count)
+    for _ in range(2):  # (the second list may well lie where this one was)
+        dirty = torch.full((T, f), 7, dtype=torch.int32, device=G.DEV)
+        del dirty
+        _, idx, count = F.floe_expert_ffn_sparse(ex_dev, G.dev(x), tau, None, y.zero_())
+        assert torch.equal(count, own_count)
+        behind = torch.arange(f, device=G.DEV)[None] >= count[:, None]
+        assert torch.equal(idx, torch.where(behind, -1, own)) and bool((own[behind] == 7).all())
+
+
 @pytest.mark.parametrize("f,T,want_list", [(448, 1, False), (448, 2, True), (450, 1, False), (2240, 1, False)])
 def test_expert_ffn_with_every_channel_selected_meets_the_tight_bar(f, T, want_list):
     """tau < 0 selects every channel: every queue of the fused kernel runs full, so a consumer leaves its loop because
