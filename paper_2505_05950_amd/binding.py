@@ -4,6 +4,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 
 import numpy as np
 import torch
@@ -31,6 +32,12 @@ class _Shape(C.Structure):
 class _Expert(C.Structure):
     _fields_ = [("s", _Shape), ("up_codes", C.c_void_p), ("up_scale", C.c_void_p), ("up_zero", C.c_void_p),
                 ("gd", C.c_void_p), ("gd_is_staged", C.c_int32), ("gd_rows", C.c_int32)]
+
+
+# The same fields for struct.pack: a call on a small expert is bound by the host, and a structure filled field by field cost it 2.3 us,
+# a packed one 1.1 (it is built for every call, so that it always holds the tensors that the expert holds then)
+_EXPERT_FIELDS = struct.Struct("4i4P2i")
+assert _EXPERT_FIELDS.size == C.sizeof(_Expert)
 
 
 class _Layer(C.Structure):
@@ -146,13 +153,13 @@ def _ptr(t):
     if t is None:
         return None
     assert t.is_contiguous(), "tensors handed to the C ABI must be contiguous"
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()  # (ctypes makes a pointer of it; 0, an empty tensor's, is NULL)
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    if stream is None:  # the current stream, without a Python object for it
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _check(rc: int, where: str):
@@ -174,10 +181,10 @@ class Expert:
         self.gd_rows = int(gd_rows if gd_rows is not None else (gd.shape[0] if gd is not None else f))
 
     def c_struct(self) -> _Expert:
-        def p(t):
-            return None if t is None else t.data_ptr()
-        return _Expert(_shape(self.d, self.f, self.bits, self.group), p(self.up_codes), p(self.up_scale),
-                       p(self.up_zero), p(self.gd), int(self.staged), self.gd_rows)
+        codes, scale, zero, gd = self.up_codes, self.up_scale, self.up_zero, self.gd
+        return _Expert.from_buffer_copy(_EXPERT_FIELDS.pack(
+            self.d, self.f, self.bits, self.group, 0 if codes is None else codes.data_ptr(), 0 if scale is None else scale.data_ptr(),
+            0 if zero is None else zero.data_ptr(), 0 if gd is None else gd.data_ptr(), self.staged, self.gd_rows))
 
 
 def floe_quantize_expert(w_up_cm: torch.Tensor, bits: int, group: int, stream=None):
@@ -224,7 +231,7 @@ def _workspace(nbytes: int, device) -> torch.Tensor:
 def _aligned_ptr(ws: torch.Tensor):
     base = ws.data_ptr()
     off = (-base) % 256
-    return C.c_void_p(base + off), ws.numel() - off
+    return base + off, ws.numel() - off
 
 
 def floe_gate_down_sparse(e: Expert, x, v, idx, count, out_scale, y_acc, workspace=None, stream=None):
@@ -246,9 +253,9 @@ def floe_expert_ffn_sparse(e: Expert, x, tau, out_scale, y_acc, idx=None, count=
     if want_list:
         if idx is None:  # a list of our own: the call that writes it also sets what lies behind its end
             call = load().floe_expert_ffn_sparse_padded
-            idx = torch.empty((T, e.f), dtype=torch.int32, device=x.device)
+            idx = torch.empty(T, e.f, dtype=torch.int32, device=x.device)
         if count is None:
-            count = torch.empty((T,), dtype=torch.int32, device=x.device)
+            count = torch.empty(T, dtype=torch.int32, device=x.device)
     else:
         idx = count = None
     if workspace is None:
@@ -336,7 +343,7 @@ def floe_moe_layer_decode(L: Layer, x: torch.Tensor, y: torch.Tensor = None, sta
     """x fp16 [T][d] -> y fp16 [T][d]; stats (optional) int32 [T][slots][4] viewed as floe_slot_stat."""
     T = x.shape[0]
     if y is None:
-        y = torch.empty((T, L.d), dtype=torch.float16, device=x.device)
+        y = torch.empty(T, L.d, dtype=torch.float16, device=x.device)
     if workspace is None:
         workspace = L.workspace(T)
     wp, wn = _aligned_ptr(workspace)
@@ -360,7 +367,7 @@ def floe_moe_layer_decode_offloaded(L: Layer, x, staging, capacity_rows, side_st
     """Offloaded layer: experts' gd are pinned host tensors; staging dev [T*slots][capacity_rows][2][d]."""
     T = x.shape[0]
     if y is None:
-        y = torch.empty((T, L.d), dtype=torch.float16, device=x.device)
+        y = torch.empty(T, L.d, dtype=torch.float16, device=x.device)
     if workspace is None:
         workspace = L.workspace(T)
     wp, wn = _aligned_ptr(workspace)
@@ -427,7 +434,7 @@ def floe_moe_layer_decode_prefetched(L: Layer, P: Prefetch, M: MissPath, x, y=No
     """Layer decode on staging rows that floe_moe_layer_prefetch has (partly) filled; only the misses are copied now."""
     T = x.shape[0]
     if y is None:
-        y = torch.empty((T, L.d), dtype=torch.float16, device=x.device)
+        y = torch.empty(T, L.d, dtype=torch.float16, device=x.device)
     if workspace is None:
         workspace = L.workspace(T)
     wp, wn = _aligned_ptr(workspace)
@@ -458,7 +465,7 @@ def floe_moe_layer_decode_cached(L: Layer, cache: ChannelCache, M: MissPath, x, 
                                  workspace=None, stream=None):
     T = x.shape[0]
     if y is None:
-        y = torch.empty((T, L.d), dtype=torch.float16, device=x.device)
+        y = torch.empty(T, L.d, dtype=torch.float16, device=x.device)
     if workspace is None:
         workspace = L.workspace(T)
     wp, wn = _aligned_ptr(workspace)
