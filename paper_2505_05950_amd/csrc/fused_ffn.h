@@ -92,9 +92,17 @@ __device__ __forceinline__ void lds_piece_arrived(u32x4& q) { asm volatile("s_wa
 // ROUTED: 2 = the workgroup routes in place (<= 16 experts), 1 = it picks in place on logits formed by a kernel in front
 // (<= 64 experts), 0 = the task's expert comes from `map`, its
 // threshold from task_tau and its output scale from task_scale (nullptr = 1).
+// kAhead: consumers request the next entry while they work on one, and producers that hold codes in registers request without
+// conditions (a request that may not happen makes the compiler wait, at the first and the last pass of every round, for all that are in
+// flight: four passes deep became one).  Consumers had waited for a whole chunk, then for the rest of its down row, with nothing else on
+// its way.  us before / now: INT4 g64 d 4096 f 14336, 8 experts top-2, 90 %: 8 tokens 137 / 113, 16 tokens 235 / 187, at 60 % 237 / 238 and
+// 342 / 346; INT2 16 tokens 60 % 370 / 313, 90 % 170 / 168; INT3 g32 d 2048 f 1408, 64 + 2 experts top-6, 32 tokens 118 / 109; INT4 g128
+// d 2560 f 6911, 3 tokens 30.7 / 26.6; d 1536 f 4096 INT2 g64 4 tokens 60 % 23.5 / 21.8.  (Tried on top: a limit to how far a producer may be
+// ahead of its consumers: no difference.  Instead: 8 producers and 4 consumers, INT2 16 tokens 60 / 90 % 443 / 177, or 6 and 6: 12 tokens 368 /
+// 147 against 358 / 143; codes in registers seven passes deep: INT4 90 % -8 %, 60 % +7 %.)
 // n_pass channels-per-wave passes per producer (at most kPasses, which sizes the queues), kDepth of them in flight; with
 // codes staged through LDS n_pass is a multiple of kDepth.  v_out (optional): v[task][f].
-template <int BITS, int UPC, bool G32, int ROUTED, int kPasses, int kDepth>
+template <int BITS, int UPC, bool G32, int ROUTED, bool kAhead, int kPasses, int kDepth>
 __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_kernel(TaskMap map, const h16* __restrict__ x, RouteArgs ro,
                                                                   const float* __restrict__ task_tau,
                                                                   const float* __restrict__ task_scale, int f,
@@ -238,7 +246,6 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
         constexpr bool kStaged = staged_codes<BITS>();
         constexpr int kSlot = stage_slot_bytes<BITS>();
         constexpr int kVmPerPass = St::kPieces + 2;  // requests per pass: the pieces, scale, zero
-        constexpr bool kSingleRound = kPasses != kFusedMaxPasses && kPasses == kDepth;  // n_pass is kPasses: all of them in flight at once
         unsigned char* stage = reinterpret_cast<unsigned char*>(&yred[kFusedCpp * wave][0]);
         static_assert(!kStaged || kDepth * kSlot <= kFusedCpp * d * 4, "the staging ring must fit the two slabs");
         static_assert(!kStaged || kVmPerPass * (kDepth - 1) < 64, "the wait counts outstanding requests in six bits");
@@ -324,11 +331,12 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
             lds_piece_request(stage + lane * 16, cw_next);
         }
         auto round = [&](auto last, int p0) __attribute__((always_inline)) {
-            constexpr bool kLast = decltype(last)::value;  // (staged codes) nothing is requested behind this round
+            constexpr bool kLast = decltype(last)::value;  // nothing is requested behind this round
+            constexpr bool kCut = !kStaged && !kAhead;     // the last round may be shorter (staged: n_pass % kDepth == 0)
 #pragma unroll
             for (int i = 0; i < kDepth; ++i) {
                 const int p = p0 + i;
-                if (!kStaged && p >= n_pass) break;  // last, shorter round (wave-uniform); staged: n_pass % kDepth == 0
+                if (kCut && p >= n_pass) break;  // (wave-uniform)
                 const int j = jw + p * CPW + sub;
                 if constexpr (kStaged) {
                     lds_piece_arrived(cw_next);
@@ -345,10 +353,11 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
                 float part;
                 if constexpr (kSub) part = unit_value_sub<BITS, UPC, G32>(ld[i], xs, Xg);
                 else part = unit_value<BITS, UPC, G32>(ld[i], xs, Xoff, Xg, magic);
-                if constexpr (kStaged) {
-                    if constexpr (!kLast) issue(i, p + kDepth);
-                } else {
+                // (codes in registers, kAhead: the passes that the last round is short of repeat the final one and are not used)
+                if constexpr (kCut) {
                     if (p + kDepth < n_pass) issue(i, p + kDepth);
+                } else if constexpr (!kLast) {
+                    issue(i, kStaged ? p + kDepth : min(p + kDepth, n_pass - 1));
                 }
                 if constexpr (UPC != LPC) part = lane % LPC < UPC ? part : 0.0f;  // (0 times a scale that is not finite is no zero)
                 part = group_reduce_sum_to_last<LPC>(part) * inv_p;
@@ -370,16 +379,17 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
                 __builtin_amdgcn_sched_barrier(0);  // keep the request for pass p + kDepth where it is
             }
         };
-        if constexpr (kStaged) {
-            if constexpr (!kSingleRound) {
-#pragma unroll 1
-                for (; p0 + kDepth < n_pass; p0 += kDepth) round(std::false_type{}, p0);
-            }
-            round(std::true_type{}, p0);
-        } else {
+        if constexpr (!kStaged && !kAhead) {
 #pragma unroll 1
             for (; p0 < n_pass; p0 += kDepth) round(std::false_type{}, p0);
+        } else if constexpr (kPasses == kFusedMaxPasses) {
+#pragma unroll 1
+            for (; p0 + kDepth < n_pass; p0 += kDepth) round(std::false_type{}, p0);
+        } else {
+#pragma unroll
+            for (; p0 + kDepth < kPasses; p0 += kDepth) round(std::false_type{}, p0);
         }
+        if constexpr (kStaged || kAhead) round(std::true_type{}, p0);
         if constexpr (kStaged) lds_piece_arrived(cw_next);  // the read-ahead of the last pass: its registers are free only now
         if constexpr (kStaged) wait_vm_all_but<0>();  // the ring lies in the consumers' result slabs: nothing may land later
         if (lane == 0) {
@@ -399,52 +409,134 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
         float acc[8 * NV];
 #pragma unroll
         for (int i = 0; i < 8 * NV; ++i) acc[i] = 0.0f;
-        int k = c % kFusedCpp;
-        while (k < nq) {  // the queue cannot hold more than its producer has channels
-            // The wait is a loop of its own that touches no accumulator: as a second way back to the head of the
-            // outer loop it made the compiler copy all of them (64 moves) on every empty poll.
-            int j;
-            for (;;) {
-                j = __builtin_amdgcn_readfirstlane(lds_peek(&qj[qc][k]));
-                if (j >= 0) break;
-                if (__builtin_amdgcn_readfirstlane(lds_peek(&done[qc])) != 0) {
-                    // the flag is raised after the last push: look once more, then the queue is known to be empty
-                    j = __builtin_amdgcn_readfirstlane(lds_peek(&qj[qc][k]));
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(8);
-            }
-            if (j < 0) break;
-            const float h0 = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(lds_peek(reinterpret_cast<const int*>(&qh[qc][k]))));
-            const uint4* gp = reinterpret_cast<const uint4*>(e.gd + (size_t)j * 2 * d);
+        if constexpr (kAhead) {
+            constexpr bool kPatient = !fused_always_ahead(d);
+            const unsigned char* rows = scalar_ptr(e.gd);
             uint4 gv[NV], dv[NV];
+            // A chunk as a buffer: its address is all scalar, which leaves the registers to its two halves.  (The barriers keep the requests in
+            // this order and where they are: gate column, then down row.)
+            auto request = [&](uint4 (&q)[NV], int j, int half, int bytes) __attribute__((always_inline)) {
+                __builtin_amdgcn_sched_barrier(0);
+                const auto chunk = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char*>(rows) + (size_t)j * (4 * d) + half * 2 * d, 0, bytes, 0x00027000);
 #pragma unroll
-            // (plain loads on purpose: measured 5 us faster here than loads typed as global memory)
-            for (int r = 0; r < NV; ++r) gv[r] = gp[r * kWave + lane];
+                for (int r = 0; r < NV; ++r) {
+                    const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(chunk, lane * 16 + r * 1024, 0, 0);
+                    q[r] = make_uint4(w.x, w.y, w.z, w.w);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto weight_of = [&](int k) { return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(lds_peek(reinterpret_cast<const int*>(&qh[qc][k])))); };
+            // entry k of the queue, -1 once it is known that there is none.  The wait is a loop of its own that touches no accumulator.
+            auto wait_entry = [&](int k) {
+                if (k >= nq) return -1;  // the queue cannot hold more than its producer has channels
+                for (;;) {
+                    const int j = __builtin_amdgcn_readfirstlane(lds_peek(&qj[qc][k]));
+                    if (j >= 0) return j;
+                    // the flag is raised after the last push: look once more, then the queue is known to be empty
+                    if (__builtin_amdgcn_readfirstlane(lds_peek(&done[qc])) != 0) return __builtin_amdgcn_readfirstlane(lds_peek(&qj[qc][k]));
+                    __builtin_amdgcn_s_sleep(8);
+                }
+            };
+            auto down_sums = [&](float g, float h0) __attribute__((always_inline)) {
+                g = wave_allreduce_sum(g);
+                const float h = silu(g) * h0;
 #pragma unroll
-            for (int r = 0; r < NV; ++r) dv[r] = gp[(d / 8) + r * kWave + lane];
-            float g = 0.0f;
+                for (int r = 0; r < NV; ++r) {
+                    const uint32_t wds[4] = {dv[r].x, dv[r].y, dv[r].z, dv[r].w};
 #pragma unroll
-            for (int r = 0; r < NV; ++r) {
-                const uint4 xr = xlds[r * kWave + lane];
-                g = dot2(xr.x, gv[r].x, g);
-                g = dot2(xr.y, gv[r].y, g);
-                g = dot2(xr.z, gv[r].z, g);
-                g = dot2(xr.w, gv[r].w, g);
-            }
-            g = wave_allreduce_sum(g);
-            const float h = silu(g) * h0;
+                    for (int q = 0; q < 4; ++q) {
+                        const h16x2 pr = as_h2(wds[q]);
+                        acc[r * 8 + 2 * q + 0] = fmaf(h, (float)pr.x, acc[r * 8 + 2 * q + 0]);
+                        acc[r * 8 + 2 * q + 1] = fmaf(h, (float)pr.y, acc[r * 8 + 2 * q + 1]);
+                    }
+                }
+            };
+            int k = c % kFusedCpp;
+            int j = wait_entry(k);
+            if (j >= 0) {
+                float h0 = weight_of(k);
+                request(gv, j, 0, 2 * d);
+                request(dv, j, 1, 2 * d);
+                for (;;) {
+                    float g = 0.0f;
 #pragma unroll
-            for (int r = 0; r < NV; ++r) {
-                const uint32_t wds[4] = {dv[r].x, dv[r].y, dv[r].z, dv[r].w};
+                    for (int r = 0; r < NV; ++r) {
+                        const uint4 xr = xlds[r * kWave + lane];
+                        g = dot2(xr.x, gv[r].x, g);
+                        g = dot2(xr.y, gv[r].y, g);
+                        g = dot2(xr.z, gv[r].z, g);
+                        g = dot2(xr.w, gv[r].w, g);
+                    }
+                    // The next entry's gate column and down row are requested as the registers of this one's come free.  Where there is
+                    // none yet, a buffer of no bytes stands in for the column, which asks the memory for nothing: with a request that may
+                    // not happen in front of them the sums would wait for all that are in flight.  The widest rows, which come here with
+                    // long queues only, wait for the entry instead (16 tokens top-2 of 8, d 4096 f 14336 INT2, 60 / 90 %: 317 / 173 -> 313 /
+                    // 168 us; with one token the sums that wait cost 1 of 22).
+                    k += kFusedCpp;
+                    asm volatile("" : "+v"(g));  // (the products stay in front of what follows, and so do the sums below)
+                    if constexpr (kPatient) j = wait_entry(k);
+                    else j = __builtin_amdgcn_readfirstlane(lds_peek(&qj[qc][min(k, nq - 1)])) | (nq - 1 - k) >> 31;  // (none behind the end)
+                    request(gv, max(j, 0), 0, j < 0 ? 0 : 2 * d);
+                    down_sums(g, h0);
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const h16x2 pr = as_h2(wds[q]);
-                    acc[r * 8 + 2 * q + 0] = fmaf(h, (float)pr.x, acc[r * 8 + 2 * q + 0]);
-                    acc[r * 8 + 2 * q + 1] = fmaf(h, (float)pr.y, acc[r * 8 + 2 * q + 1]);
+                    for (int i = 0; i < 8 * NV; ++i) asm volatile("" : "+v"(acc[i]));
+                    if (!kPatient && j < 0) {
+                        j = wait_entry(k);
+                        request(gv, max(j, 0), 0, j < 0 ? 0 : 2 * d);
+                    }
+                    request(dv, max(j, 0), 1, j < 0 ? 0 : 2 * d);
+                    if (j < 0) break;
+                    h0 = weight_of(k);
                 }
             }
-            k += kFusedCpp;
+        } else {
+            int k = c % kFusedCpp;
+            while (k < nq) {  // the queue cannot hold more than its producer has channels
+                // The wait is a loop of its own that touches no accumulator: as a second way back to the head of the
+                // outer loop it made the compiler copy all of them (64 moves) on every empty poll.
+                int j;
+                for (;;) {
+                    j = __builtin_amdgcn_readfirstlane(lds_peek(&qj[qc][k]));
+                    if (j >= 0) break;
+                    if (__builtin_amdgcn_readfirstlane(lds_peek(&done[qc])) != 0) {
+                        // the flag is raised after the last push: look once more, then the queue is known to be empty
+                        j = __builtin_amdgcn_readfirstlane(lds_peek(&qj[qc][k]));
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(8);
+                }
+                if (j < 0) break;
+                const float h0 = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(lds_peek(reinterpret_cast<const int*>(&qh[qc][k]))));
+                const uint4* gp = reinterpret_cast<const uint4*>(e.gd + (size_t)j * 2 * d);
+                uint4 gv[NV], dv[NV];
+#pragma unroll
+                // (plain loads on purpose: measured 5 us faster here than loads typed as global memory)
+                for (int r = 0; r < NV; ++r) gv[r] = gp[r * kWave + lane];
+#pragma unroll
+                for (int r = 0; r < NV; ++r) dv[r] = gp[(d / 8) + r * kWave + lane];
+                float g = 0.0f;
+#pragma unroll
+                for (int r = 0; r < NV; ++r) {
+                    const uint4 xr = xlds[r * kWave + lane];
+                    g = dot2(xr.x, gv[r].x, g);
+                    g = dot2(xr.y, gv[r].y, g);
+                    g = dot2(xr.z, gv[r].z, g);
+                    g = dot2(xr.w, gv[r].w, g);
+                }
+                g = wave_allreduce_sum(g);
+                const float h = silu(g) * h0;
+#pragma unroll
+                for (int r = 0; r < NV; ++r) {
+                    const uint32_t wds[4] = {dv[r].x, dv[r].y, dv[r].z, dv[r].w};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const h16x2 pr = as_h2(wds[q]);
+                        acc[r * 8 + 2 * q + 0] = fmaf(h, (float)pr.x, acc[r * 8 + 2 * q + 0]);
+                        acc[r * 8 + 2 * q + 1] = fmaf(h, (float)pr.y, acc[r * 8 + 2 * q + 1]);
+                    }
+                }
+                k += kFusedCpp;
+            }
         }
         // The producer's staging ring lies in this consumer's result slab.  A consumer that left the loop because its
         // queue was full to capacity (every channel of the block selected) has not seen the producer's flag yet, and
@@ -480,7 +572,7 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
 }
 
 // ---- launch: bits fixed by the translation unit, the rest chosen here
-template <int BITS, int UPC, bool G32>
+template <int BITS, int UPC, bool G32, bool LARGE_AHEAD = false>
 static hipError_t fused_launch_shape(const FusedArgs& a, int gshift, hipStream_t stream) {
     const dim3 grid(fused_blocks(a.d, a.f, a.passes), a.n_tasks), block(kFusedThreads);
     const RouteArgs ro = a.route ? *a.route : RouteArgs{};
@@ -489,6 +581,7 @@ static hipError_t fused_launch_shape(const FusedArgs& a, int gshift, hipStream_t
     constexpr int kWant = BITS == 2 ? 14 : 7;
     constexpr int kFit = staged_codes<BITS>() ? kFusedCpp * UPC * 64 * 4 / stage_slot_bytes<BITS>() : 4;
     constexpr int kDepth = staged_codes<BITS>() ? (kWant < kFit ? kWant : kFit) : 4;
+    constexpr bool kAhead = LARGE_AHEAD || fused_always_ahead(UPC * 64);
     // a.passes passes per producer at run time; the template argument only sizes the queues and caps the depth
     if (a.passes < kFusedMinPasses || a.passes > kFusedMaxPasses) return hipErrorInvalidValue;  // (the grid follows a.passes)
     static_assert(kDepth == fused_depth(UPC * 64, BITS), "the host rounds the pass count to this depth");
@@ -496,11 +589,13 @@ static hipError_t fused_launch_shape(const FusedArgs& a, int gshift, hipStream_t
     // staged codes: whole rounds of the ring (the waits in the kernel count on it)
     if (staged_codes<BITS>() && a.passes % (a.passes <= kFusedMinPasses ? kDepthSmall : kDepth) != 0) return hipErrorInvalidValue;
 #define FLOE_FUSED_GO(ROUTED, P)                                                                                 \
-    fused_ffn_kernel<BITS, UPC, G32, ROUTED, P, (kDepth < P ? kDepth : P)><<<grid, block, 0, stream>>>(a.map, a.x, ro, a.task_tau,   \
+    fused_ffn_kernel<BITS, UPC, G32, ROUTED, kAhead, P, (kDepth < P ? kDepth : P)><<<grid, block, 0, stream>>>(a.map, a.x, ro, a.task_tau,   \
                                                                                     a.task_scale, a.f, a.passes, gshift, \
                                                                                     a.v_out, a.partial, a.wg_count)
 #define FLOE_FUSED_PASSES(ROUTED)                                               \
-    if (a.passes <= kFusedMinPasses) {                                          \
+    if constexpr (LARGE_AHEAD) {                                                \
+        FLOE_FUSED_GO(ROUTED, kFusedMaxPasses);                                 \
+    } else if (a.passes <= kFusedMinPasses) {                                   \
         FLOE_FUSED_GO(ROUTED, kFusedMinPasses);                                 \
     } else {                                                                    \
         FLOE_FUSED_GO(ROUTED, kFusedMaxPasses);                                 \
@@ -534,6 +629,16 @@ static hipError_t fused_launch_bits(const FusedArgs& a, hipStream_t stream) {
         case 1024: return g32 ? fused_launch_shape<BITS, 16, true>(a, gshift, stream) : fused_launch_shape<BITS, 16, false>(a, gshift, stream);
         default: return hipErrorInvalidValue;
     }
+}
+
+// the widest with many passes
+template <int BITS>
+static hipError_t fused_launch_ahead(const FusedArgs& a, hipStream_t stream) {
+    if (a.f == 0 || a.n_tasks == 0) return hipSuccess;
+    if (a.d != 4096 || a.passes <= kFusedMinPasses) return hipErrorInvalidValue;
+    int gshift = 0;
+    while ((1 << gshift) < a.group) ++gshift;
+    return a.group == 32 ? fused_launch_shape<BITS, 64, true, true>(a, gshift, stream) : fused_launch_shape<BITS, 64, false, true>(a, gshift, stream);
 }
 
 // the widths between the powers of two: kernels of translation units of their own

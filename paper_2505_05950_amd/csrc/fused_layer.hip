@@ -24,6 +24,9 @@ void set_fused_tasks_tuned(int n) { g_fused_tasks.store(n > 0 ? n : 0, std::memo
 hipError_t launch_fused_int2(const FusedArgs& a, hipStream_t stream);
 hipError_t launch_fused_int3(const FusedArgs& a, hipStream_t stream);
 hipError_t launch_fused_int4(const FusedArgs& a, hipStream_t stream);
+hipError_t launch_fused_ahead_int2(const FusedArgs& a, hipStream_t stream);
+hipError_t launch_fused_ahead_int3(const FusedArgs& a, hipStream_t stream);
+hipError_t launch_fused_ahead_int4(const FusedArgs& a, hipStream_t stream);
 hipError_t launch_fused_between_int2(const FusedArgs& a, hipStream_t stream);
 hipError_t launch_fused_between_int3(const FusedArgs& a, hipStream_t stream);
 hipError_t launch_fused_between_int4(const FusedArgs& a, hipStream_t stream);
@@ -82,12 +85,29 @@ bool fused_between_pays(int d, int f, int bits, int group, int n_all, int n_task
     return passes < (n_all == 1 ? (bits == 2 ? 170 : 105) : (bits == 2 ? 300 : 200));
 }
 
+// Whether d 4096 takes the kernels whose consumers are one entry ahead: with few passes per producer the queues are short, and the code stream
+// that the producers of those kernels keep in flight stands in the way of the first chunks.  us, without / with, d 4096 f 14336 g64, 8 experts
+// top-2, sparsities 60, 75, 90 %:
+//   INT2   1 token (28 passes) 41.9 / 42.4  30.8 / 31.9  22.7 / 23.7     4 (112) 136 / 136  100 / 99  51.2 / 51.8    8 (224) 234 / 225  166 / 165  97.6 / 98.6
+//         16 (448) 372 / 313  240 / 238  168 / 168
+//   INT4   1 (28) 44.9 / 44.8  33.9 / 34.0  24.7 / 25.8    4 (112) 141 / 142  108 / 111  75 / 65    8 (224) 237 / 238  182 / 182  137 / 112
+//         16 (448) 342 / 346  286 / 264  235 / 186
+static bool fused_ahead_pays(int bits, int passes) { return passes >= (bits == 2 ? 300 : 160); }
+
 hipError_t launch_fused(const FusedArgs& a, int bits, hipStream_t stream) {
     if ((a.d & (a.d - 1)) != 0) {
         switch (bits) {
             case 2: return launch_fused_between_int2(a, stream);
             case 3: return launch_fused_between_int3(a, stream);
             case 4: return launch_fused_between_int4(a, stream);
+            default: return hipErrorInvalidValue;
+        }
+    }
+    if (!fused_always_ahead(a.d) && fused_ahead_pays(bits, a.passes)) {
+        switch (bits) {
+            case 2: return launch_fused_ahead_int2(a, stream);
+            case 3: return launch_fused_ahead_int3(a, stream);
+            case 4: return launch_fused_ahead_int4(a, stream);
             default: return hipErrorInvalidValue;
         }
     }

@@ -84,6 +84,8 @@ inline int fused_task_limit(int n_all) {
 }
 constexpr int kExpertOrderTasks = 16;     // batches of more tasks run their per-task kernels in expert order
 constexpr int kFusedMaxWorkgroups = 2048;
+// Widths whose kernels always have their consumers one entry ahead (kAhead in fused_ffn.h); d 4096 has kernels of both kinds.
+constexpr bool fused_always_ahead(int d) { return d < 4096; }
 struct FusedArgs {
     TaskMap map;
     const h16* x;

@@ -162,6 +162,21 @@ def test_layer_small_batches_at_widths_between_the_powers_of_two(d, f, bits, gro
     _run_layer_case(50 + T, 5, d, f, bits, group, n, n_shared, top_k, True, T, pct, gap=f * (100 - pct) >= 6400)
 
 
+@pytest.mark.parametrize("f,bits,group,pct", [
+    (10303, 4, 64, 60), (10241, 4, 32, 0), (9600, 3, 128, 99), (10303, 3, 32, 85),   # from 160 passes per producer on; ragged ends
+    (10239, 4, 64, 80), (9537, 4, 64, 80),                                           # passes that are no multiple of four; just below the line
+    (19301, 2, 64, 60), (18817, 2, 128, 97),                                         # from 300 on, whole rounds of the ring
+])
+def test_layer_many_passes_with_consumers_one_entry_ahead(f, bits, group, pct):
+    _run_layer_case(60 + bits, 5, 4096, f, bits, group, 0, 1, 0, False, 16, pct)
+
+
+@pytest.mark.parametrize("d,bits,f,pct", [(1024, 2, 16 * 28, 0), (1024, 4, 451, 99), (2048, 3, 229, 50), (1536, 4, 900, 0), (3072, 2, 1700, 95)])
+def test_layer_queues_that_run_full_or_stay_empty(d, bits, f, pct):
+    # the next entry of a consumer: always there, never, and the one behind the end of a full queue
+    _run_layer_case(70 + bits, 5, d, f, bits, 64, 0, 2, 0, False, 2, pct)
+
+
 def test_layer_small_batches_pick_in_place_among_up_to_64_experts():
     """17 to 64 routed experts and at most 16 (token, slot) tasks: x . W_r is formed by a kernel in front, softmax and
     top-k run inside the fused kernel with a lane per expert.  64 experts (every lane live), 33 (one live lane in the

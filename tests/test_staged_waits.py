@@ -85,6 +85,27 @@ def test_the_same_at_widths_between_the_powers_of_two(tmp_path):
     assert check(out.read_text()) == 36
 
 
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs the compiler")
+def test_the_same_with_consumers_one_entry_ahead(tmp_path):
+    out = tmp_path / "fused_ahead_int2.s"
+    subprocess.run([HIPCC, *FLAGS, "-S", "--cuda-device-only", os.path.join(CSRC, "fused_ahead_int2.hip"), "-o", str(out)], check=True)
+    seen = 0
+    for m in re.finditer(r"^(_ZN4floe16fused_ffn_kernelILi2E\w*Li448ELi14EE\w+):(.*?)^\.Lfunc_end", out.read_text(), re.M | re.S):
+        body = m.group(2).split("\n")
+        first = next(i for i, l in enumerate(body) if "global_load_lds_dwordx4" in l)
+        begin, end = steady_loop(body, first, 14)
+        head, tail = body[first:begin], body[end + 1:]
+        if late_read_backs(head)[1] > 1:  # the last round stands in front of the loop: from the label behind the first read back on
+            read = next(i for i, l in enumerate(head) if l.strip().startswith("ds_read_b128") and "ASMSTART" in head[i - 1])
+            cut = next(i for i, l in enumerate(head) if i > read and l.startswith(".LBB"))
+            head, tail = head[:cut], head[cut:]
+        bad, reads = late_read_backs(head + STEADY_ROUNDS * body[begin:end + 1] + tail)
+        assert reads == 14 * (1 + STEADY_ROUNDS), (m.group(1), reads)
+        assert not bad, (m.group(1), "read back too early: passes", bad)
+        seen += 1
+    assert seen == 6
+
+
 def ring_loops(body):
     """(first, last line, barriers, direct loads) of the innermost loops that meet once per slot of a ring of three or four."""
     labels = {l.split(":")[0]: i for i, l in enumerate(body) if re.match(r"\.LBB\w+:", l)}
