@@ -60,6 +60,7 @@ int fused_passes(int d, int f, int bits, int n_tasks, int max_tasks) {
 // Whether a batch at a width between the powers of two is better off in the fused kernel than in the separate ones.  What counts is how
 // many channel passes its producers do one after another (a pass 0.35 to 0.45 us, whatever the selection is): a launch that is one
 // even round does n_tasks f / (1024 producers x channels per pass).  Calls fused / one-token / wide kernels, us, at sparsities 60, 80, 90, 95 %:
+// (taken before its consumers worked one entry ahead, which made the fused kernel 1 to 15 % faster at these widths)
 //   few passes: the fused kernel saves launches and overlaps the two streams
 //     INT4 g64 d 2560 f 8000, 4 experts top-2, 3 tokens (47 passes)        39/56/81  32/44/68  30/37/63  29/31/60
 //     INT2 g64 d 3072 f 8000, 8 experts, 10 tokens (156)                   0.56 0.58 0.75 0.94 times the one-token kernels
