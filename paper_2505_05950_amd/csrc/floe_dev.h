@@ -6,6 +6,8 @@
 
 #include <type_traits>
 
+#include "wide_cut.h"
+
 namespace floe {
 
 typedef _Float16 h16;
@@ -200,17 +202,6 @@ __device__ __forceinline__ const unsigned char* scalar_ptr(const void* p) {
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)u), hi = __builtin_amdgcn_readfirstlane((uint32_t)(u >> 32));
     return (const unsigned char*)(((uint64_t)hi << 32) | lo);
 }
-// floor(a * b / c) and floor((a * b - 1) / c); in 32 bits where the product fits (a 64-bit quotient is 200 instructions of a kernel's first
-// microseconds)
-__device__ __forceinline__ int scaled(int a, int b, int less, int c) {
-    if ((uint32_t)a < (1u << 21) && (uint32_t)b < (1u << 11)) return (int)(((uint32_t)a * (uint32_t)b - (uint32_t)less) / (uint32_t)c);
-    return (int)(((long long)a * b - less) / c);
-}
-// piece w of W equal pieces starts at pair floor(total * w / W)
-__device__ __forceinline__ int wide_cut(int total, int W, int w) { return scaled(total, w, 0, W); }
-// n / d as a whole number from 1 / d, for n up to a few hundred thousand and quotients up to a few hundred: taken half a unit above a
-// whole number, so that rounding cannot matter
-__device__ __forceinline__ int small_quotient(int n, float inverse) { return (int)(((float)n + 0.5f) * inverse); }
 // Workgroups go to the eight XCDs in turn.  Neighbouring pieces run on one XCD, so that its L2 holds the activations of few
 // groups, and the groups of one expert, which read the same rows, are next to each other.
 __device__ __forceinline__ int wide_piece(int W) {

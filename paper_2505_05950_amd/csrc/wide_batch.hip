@@ -56,9 +56,6 @@ constexpr int kSliceCols = 64;   // columns of rows and activations per ring slo
 constexpr int kSpan = 64;        // channels of v that a wave brings in for a pair of row tiles
 constexpr int kDownCols = 512;   // output columns per workgroup of the down kernel (64 per wave)
 
-// pair p belongs to piece ((p + 1) * W - 1) / total (see wide_cut)
-__device__ __forceinline__ int wide_owner(int total, int W, int p) { return scaled(p + 1, W, 1, total); }
-
 // What x_operand_kernel does beside its own work, where the up projection is another one: the activations in the order of the gate
 // kernel's operand, and cleared counters.  A workgroup per position of the order.
 __global__ __launch_bounds__(128) void wide_prepare_kernel(WidePrep prep, WideArgs a, int n_tasks, int d) {
@@ -120,13 +117,13 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, con
         const float per_most = 1.0f / (float)most;
         for (int g0 = 0; g0 < ng; g0 += kWave) {
             const int n = tokens_of(g0);
-            sum += wave_sum(g0 + lane < ng ? small_quotient(wide_weight(n) * units + most - 1, per_most) : 0);
+            sum += wave_sum(g0 + lane < ng ? wide_share(wide_weight(n), units, most, per_most) : 0);
         }
         if (sum <= W) break;  // (at the largest group at the latest: a piece each)
         most += (most + 31) / 32;
     }
     const float per_most = 1.0f / (float)most;
-    auto share_of = [&](int n) { return whole ? small_quotient(wide_weight(n) * units + most - 1, per_most) : wide_weight(n) * units; };
+    auto share_of = [&](int n) { return whole ? wide_share(wide_weight(n), units, most, per_most) : wide_weight(n) * units; };
     int pos = whole ? piece : wide_cut(total, W, piece);
     const int end = whole ? piece + 1 : wide_cut(total, W, piece + 1);
     const int ns = d / kSliceCols;  // a multiple of eight (d % 512 == 0)
@@ -155,25 +152,21 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, con
             base += __builtin_amdgcn_readlane(inc, kWave - 1);
         }
         if (g < 0) break;  // fewer pieces than workgroups
-        int u0, u1, first_piece;
+        WideUnits part;
+        int first_piece;
         if (whole) {
-            // (long pieces end at multiples of 32 channels: where every channel is selected, as in groups of a hundred tokens, no pair is padded)
-            const int k = share_of(grp.n), step = units >= 64 * k ? 4 : 1, steps = (units + step - 1) / step;
-            u0 = steps * (pos - base) / k * step;
-            u1 = min(units, steps * (pos - base + 1) / k * step);
+            part = wide_units_of_share(units, share_of(grp.n), pos - base);
             first_piece = base;
             pos = end;
-        } else {  // eight channels belong to the piece that holds the start of their share
+        } else {
             const int wgt = wide_weight(grp.n);
-            u0 = max(pos - base + wgt - 1, 0) / wgt;
-            u1 = min(units, max(end - base + wgt - 1, 0) / wgt);
+            part = wide_units_of_span(units, wgt, pos - base, end - base);
             first_piece = wide_owner(total, W, base);
             pos = base + units * wgt;  // the next group, or past the end
         }
-        u0 = __builtin_amdgcn_readfirstlane(u0);
-        u1 = __builtin_amdgcn_readfirstlane(u1);
+        const int u0 = __builtin_amdgcn_readfirstlane(part.begin), u1 = __builtin_amdgcn_readfirstlane(part.end);
         if (u1 <= u0) continue;
-        const int slot = (u0 >> 2) + piece - first_piece;
+        const int slot = wide_slot(u0, piece, first_piece);
         int32_t* rows = a.rows + (wide_row_slot(g, first_piece, pmax) + slot) * kPairRows;
         const unsigned char* gd = scalar_ptr(grp.e.gd);
         // ---- the tokens' mask words, the first ones requested ahead of all else
@@ -279,7 +272,7 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, con
         };
         // equal passes of at most a pair per wave
         const int passes = (npairs + kWideWaves - 1) / kWideWaves, per_pass = (npairs + passes - 1) / passes * kPairRows;
-        uint4* hseg = a.hbuf + wide_h_first(grp, g, first_piece, pmax, NT) + (size_t)slot * tiles * 128;
+        uint4* hseg = a.hbuf + wide_h_first(grp.tile, g, first_piece, pmax, NT) + (size_t)slot * tiles * 128;
         // live: token tiles that this group fills, of NT at most (a tile without tokens would cost as much as any other)
         auto segment = [&](auto live) __attribute__((always_inline)) {
             constexpr int NL = decltype(live)::value;
@@ -617,7 +610,7 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
             if (tid < grp.n) a.task_rows[a.order[grp.first + tid]] = make_int2(grp.first + tid + w_first * kTok, slots);
         }
         const int tiles = __builtin_amdgcn_readfirstlane(wide_tiles(grp.n));
-        const unsigned char* hsrc = scalar_ptr(a.hbuf + wide_h_first(grp, g, first_seg - g, pmax, NT));
+        const unsigned char* hsrc = scalar_ptr(a.hbuf + wide_h_first(grp.tile, g, first_seg - g, pmax, NT));
         const int ns = (len + SL - 1) / SL;
         uint4 hq[kHRounds];
         int idq = 0;
@@ -924,8 +917,8 @@ static WidePlan wide_plan_for(int nt, int max_groups, int est_groups, int d, int
     p.wg_gate = (int)(est_pairs < num_cus() ? est_pairs : num_cus());
     if (p.wg_gate > 8) p.wg_gate &= ~7;
     // (see wide_layout.h)
-    p.row_slots = (size_t)max_groups * (p.pairs + 2) + p.wg_gate;
-    p.h_vecs = ((size_t)p.h_tiles * p.pairs + (size_t)nt * (p.wg_gate + 2 * max_groups)) * 128;
+    p.row_slots = wide_row_slots(max_groups, p.pairs, p.wg_gate);
+    p.h_vecs = wide_h_vecs(p.h_tiles, p.pairs, nt, max_groups, p.wg_gate);
     p.segments = p.wg_gate + max_groups;
     const int per_col = num_cus() / (d / kDownCols);
     const long long by_len = (est_pairs + 3) / 4;

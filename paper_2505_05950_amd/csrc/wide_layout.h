@@ -12,7 +12,7 @@
 
 namespace floe {
 
-// What eight channels of a group of n tokens cost, up to 32: the rows that n tokens select between them if each takes one of eight.  (The
+// What eight channels of a group of n tokens cost, 5 to 32: the rows that n tokens select between them if each takes one of eight.  (The
 // share is not known before the masks are; a cut by rows counted beforehand costs a launch of its own.)
 __device__ __forceinline__ int wide_weight(int n) { return 32 - (int)(32.0f * __builtin_amdgcn_exp2f(-0.2f * (float)n)); }
 
@@ -26,14 +26,6 @@ __device__ __forceinline__ WideGroup wide_record(const WideGroup& rec, int l) {
     g.e.gd = (const h16*)((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)p, l) |
                           (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(p >> 32), l) << 32);
     return g;
-}
-
-__device__ __forceinline__ int wide_piece_units(int f) { return (f + 7) >> 3; }
-// first: the first piece that has a segment of the group
-__device__ __forceinline__ size_t wide_row_slot(int g, int first, int pmax) { return (size_t)g * pmax + first + 2 * g; }
-// h of a group lies in [pair slot][token tile][half of the pair's rows][lane], the group's own tiles only, from this vector on
-__device__ __forceinline__ size_t wide_h_first(const WideGroup& grp, int g, int first, int pmax, int nt) {
-    return ((size_t)grp.tile * pmax + (size_t)nt * (first + 2 * g)) * 128;
 }
 
 // token row of the tiles that position i of the order has; every lane the same

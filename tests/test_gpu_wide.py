@@ -81,7 +81,7 @@ def test_gate_rows_and_activations_through_lds(d, f, n, n_shared, top_k, T, pct)
 
 @pytest.mark.parametrize("d,f,bits,group,n,n_shared,top_k,T,pct", [
     (512, 40, 2, 64, 600, 0, 8, 100, 50),    # more groups than workgroups: pieces that hold several segments
-    (512, 2100, 2, 64, 0, 1, 0, 20, 60),     # a piece of eight or sixteen channels per workgroup, the last one of four
+    (512, 2100, 2, 64, 0, 1, 0, 20, 60),     # pieces of 32 or 40 channels, the last eight of them half there
     (512, 3001, 4, 64, 44, 0, 4, 200, 40),   # pieces of 512 channels and more, several passes each; groups by the activations' kernel
     (512, 70, 2, 64, 20, 0, 8, 257, 50),     # one task more than that kernel groups: the grouping kernel in front
     (512, 70, 8, 64, 20, 0, 8, 40, 50),      # an up projection that keeps v and the masks by task
@@ -89,6 +89,44 @@ def test_gate_rows_and_activations_through_lds(d, f, n, n_shared, top_k, T, pct)
 ])
 def test_segments_and_groups(d, f, bits, group, n, n_shared, top_k, T, pct):
     _run_layer_case(470 + T, 13, d, f, bits, group, n, n_shared, top_k, False, T, pct, gap=f * (100 - pct) >= 6400)
+
+
+@pytest.mark.parametrize("d,f,bits,group,n,n_shared,top_k,T,elsewhere", [
+    (512, 1408, 4, 64, 6, 0, 1, 16, 0),      # one group where six were expected: 176 pieces of eight channels, 256 workgroups
+    (4096, 900, 3, 32, 8, 1, 1, 80, 0),      # two groups of nine
+    (4096, 900, 3, 32, 8, 1, 1, 80, 1),      # and a token of its own beside them
+    (512, 960, 8, 64, 8, 1, 1, 80, 2),       # the same where v and the masks are kept by task
+    (1024, 384, 2, 64, 16, 2, 2, 70, 3),     # four crowded experts of eighteen
+    (512, 161, 4, 64, 24, 1, 1, 16, 16),     # a shared expert beside groups of a token or two
+])
+def test_routing_that_fills_few_of_the_groups(d, f, bits, group, n, n_shared, top_k, T, elsewhere):
+    """Equal or padding tokens, a collapsed router: all but `elsewhere` tokens go to the first top_k experts."""
+    import gpu_common as G
+    import paper_2505_05950_amd as F
+    experts = [G.make_expert(*S.expert_weights(570, 13, d, f, 0, e), bits, group) for e in range(n + n_shared)]
+    wr = S.router_weights(570, 13, n, d)
+    x = S.tokens(570, 13, T, d)
+    wr[:, 0] = 0.0
+    wr[:top_k, 0] = 1.0 + 0.25 * np.arange(top_k, 0, -1)     # (the order among them is no near-tie either)
+    x[:, 0] = 8.0
+    x[T - elsewhere:, 0] = -8.0
+    routed = np.argsort(-(x.astype(np.float64) @ wr.astype(np.float64).T), axis=1)[:, :top_k]
+    slots = np.concatenate([routed, np.tile(n + np.arange(n_shared), (T, 1))], axis=1)
+    tau, size = np.zeros((T, n + n_shared), np.float32), np.zeros(slots.shape, np.int32)
+    for t in range(T):
+        for s, e in enumerate(slots[t]):
+            v = O.up_gemv(*experts[e][0][:3], d, bits, group, x[t])
+            tau[t, e] = G.tau_in_widest_gap(v, 70, window=min(64, f // 8))[0]
+            size[t, s] = O.select(v, float(tau[t, e])).size
+    ref = O.moe_layer([e[0] for e in experts], n_shared, top_k, False, wr, x, tau, bits, group)
+    L = F.Layer([e[1] for e in experts], n_shared, top_k, False, G.dev(wr), G.dev(tau), True)
+    L.workspace(T).fill_(255)
+    stats = torch.zeros((T, top_k + n_shared, 4), dtype=torch.int32, device=G.DEV)
+    y = F.floe_moe_layer_decode(L, G.dev(x), stats=stats).cpu().numpy().astype(np.float64)
+    st = stats.cpu().numpy()
+    assert np.array_equal(st[:, :, 0], slots) and np.array_equal(st[:, :, 1], size)
+    for t in range(T):
+        assert G.rel_err(y[t], ref["y"][t]) <= G.Y_TIGHT, (t, G.rel_err(y[t], ref["y"][t]))
 
 
 @pytest.mark.parametrize("d,f,n,n_shared,top_k,T,pct", [
