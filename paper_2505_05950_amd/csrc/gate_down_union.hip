@@ -344,18 +344,6 @@ int union_kernels_for(int n_all, int n_tasks, int d, int f, int bits, int group)
     return qg >= least ? 1 : 3;
 }
 
-// Per expert E[ceil(X / chunk)] = sum over k >= 0 of P(X > k * chunk), X binomial, by its normal approximation.  Terms further
-// than 8.5 deviations from the mean are 1 and 0 to the last bit of a double: every layer call plans, so only the others are formed.
-double expected_token_groups(int n_experts, int T, int top_k, int chunk) {
-    if (n_experts <= 0 || top_k <= 0) return 0.0;
-    const double pr = (double)top_k / n_experts, mu = T * pr, sd = sqrt(T * pr * (1.0 - pr)) + 1e-9;
-    const double lo = (mu - 8.5 * sd - 0.5) / chunk, hi = mu + 8.5 * sd;
-    int k = lo > 0.0 ? (int)lo : 0;
-    double per = k;
-    for (; k * chunk < T && k * chunk < hi; ++k) per += 0.5 * erfc(((double)k * chunk + 0.5 - mu) / (sd * 1.4142135623730951));
-    return per * n_experts;
-}
-
 UnionPlan union_plan(int d, int f, int n_tasks, int n_all, int chunk) {
     UnionPlan p{};
     const int nwords = mask_words_per_task(f);

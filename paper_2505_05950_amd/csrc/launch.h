@@ -7,6 +7,7 @@
 
 #include "floe_dev.h"
 #include "route.h"
+#include "wide_plan.h"
 #include "xprep.h"
 
 namespace floe {
@@ -181,8 +182,6 @@ struct UnionArgs {
 UnionPlan union_plan(int d, int f, int n_tasks, int n_all, int chunk);
 bool union_shape_ok(int d, int f, const UnionPlan& p);
 hipError_t launch_gate_down_union(const UnionArgs& a, const UnionPlan& p, int d, hipStream_t stream);
-// Expected number of groups of `chunk` tokens when each of T tokens goes to top_k of n_experts experts uniformly
-double expected_token_groups(int n_experts, int T, int top_k, int chunk);
 
 // S4 + S5 on the matrix cores for batches in which experts see many tokens (wide_batch.hip): groups of up to 16 * nt tokens.
 struct WideGroup {
@@ -215,7 +214,6 @@ struct WidePlan {
     int segments;           // entries of the segment table
     size_t partial_rows;    // rows of d floats
 };
-constexpr int kWideMaxSegments = 4096;
 // What the gate kernel and those behind it find ready: the activations in the order of its operand, [token tile][k-step of 32
 // columns][lane], and cleared counters.
 struct WidePrep {

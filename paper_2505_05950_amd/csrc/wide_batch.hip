@@ -882,27 +882,6 @@ __global__ __launch_bounds__(256) void wide_single_kernel(DevExpert e, int n_tas
 // ---------------------------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------------------------
-// Token tiles per group: the fewest expected reads of the experts' rows, weighed by what a read costs.  Calls with each number of
-// tiles forced, us: 8 experts d 4096 f 14336 INT2 at 85 %, 56 tokens 410 (one tile) 390 394 404 405 416 (ten), 72 tokens 503 419 421 430 432
-// 445, 512 tokens 2611 1663 1342 1126 799 740; 64 + 2 experts d 2048 f 1408 INT3 g32, 148 tokens 272 257 259 265 319 355.  Over 255 calls
-// the choice costs 4 % on average against the best of the six.  It misses most where one number holds a group and a smaller one its
-// halves: 8 experts, 320 tokens 718 (five, taken) 608 (ten); one expert of the same size, 160 tokens 169 (five) 198 (ten, taken), 200
-// tokens 240 (five, taken) 203 (ten).
-static int wide_tiles_for(int T, int n_experts, int top_k, int n_shared, double& groups) {
-    double best = 0.0;
-    int best_nt = 0;
-    for (const int nt : {1, 2, 3, 4, 5, 10}) {
-        const double g = expected_token_groups(n_experts, T, top_k, 16 * nt) + (double)n_shared * ((T + 16 * nt - 1) / (16 * nt));
-        const double score = g * (1.0 + (nt <= 5 ? 0.05 : 0.09) * nt);
-        if (best_nt == 0 || score < best) {
-            best = score;
-            best_nt = nt;
-            groups = g;
-        }
-    }
-    return best_nt;
-}
-
 // what follows from the token tiles; est_groups: the groups to be expected
 static WidePlan wide_plan_for(int nt, int max_groups, int est_groups, int d, int f, int n_tasks, int max_down) {
     WidePlan p{};
@@ -934,7 +913,7 @@ WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared, 
     const int n_tasks = T * (top_k + n_shared), n_all = n_experts + n_shared;
     double groups = 0.0;
     const int nt = wide_tiles_for(T, n_experts, top_k, n_shared, groups);
-    return wide_plan_for(nt, (n_all < n_tasks ? n_all : n_tasks) + n_tasks / (16 * nt), (int)(groups + 0.5), d, f, n_tasks, max_down);
+    return wide_plan_for(nt, wide_max_groups(n_all, n_tasks, nt), (int)(groups + 0.5), d, f, n_tasks, max_down);
 }
 
 // No plan of this layer for up to T tokens needs more of anything: the groups of one tile, of which there are most, with as many
@@ -943,7 +922,7 @@ WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared, 
 // for up to 160 routed and four shared experts.)
 WidePlan wide_room(int d, int f, int T, int n_experts, int top_k, int n_shared) {
     const int n_tasks = T * (top_k + n_shared), n_all = n_experts + n_shared;
-    const int max_groups = (n_all < n_tasks ? n_all : n_tasks) + n_tasks / 16;
+    const int max_groups = wide_max_groups(n_all, n_tasks, 1);
     double groups = 0.0;
     int nt = wide_tiles_for(T, n_experts, top_k, n_shared, groups);
     for (int t = T / 16 * 16; t > 0 && nt < 10; t -= 16)

@@ -129,6 +129,33 @@ def test_routing_that_fills_few_of_the_groups(d, f, bits, group, n, n_shared, to
         assert G.rel_err(y[t], ref["y"][t]) <= G.Y_TIGHT, (t, G.rel_err(y[t], ref["y"][t]))
 
 
+def test_a_layer_of_thousands_of_groups():
+    """1024 + 48 experts, 64 slots, 3712 tokens: about 4000 groups and 256 pieces.  Experts share four sets of weights, and select every
+    channel or none, so that a token's result is the weighted sum of four."""
+    import gpu_common as G
+    import paper_2505_05950_amd as F
+    d, f, bits, group, n, n_shared, top_k, T = 512, 64, 4, 64, 1024, 48, 16, 3712
+    kinds = [G.make_expert(*S.expert_weights(580, 13, d, f, 0, e), bits, group) for e in range(4)]
+    x = S.tokens(580, 13, T, d)
+    out = []
+    for ex_np, _ in kinds:
+        w_up = O.dequantize(*ex_np[:3], d, bits, group).astype(np.float64)
+        v, g = x.astype(np.float64) @ w_up.T, x.astype(np.float64) @ ex_np[3][:, 0].astype(np.float64).T
+        out.append((g / (1.0 + np.exp(-g)) * v) @ ex_np[3][:, 1].astype(np.float64))
+    tau = np.where(np.arange(n + n_shared) % 3 == 2, 1e30, -1.0).astype(np.float32)
+    L = F.Layer([kinds[e % 4][1] for e in range(n + n_shared)], n_shared, top_k, False, G.dev(S.router_weights(580, 13, n, d)), G.dev(tau), False)
+    F.floe_tuning(F.TUNE_UNION_KERNELS, 0)
+    stats = torch.zeros((T, top_k + n_shared, 4), dtype=torch.int32, device=G.DEV)
+    y = F.floe_moe_layer_decode(L, G.dev(x), stats=stats).cpu().numpy().astype(np.float64)
+    st = stats.cpu().numpy().view(F.SLOT_STAT_DTYPE).reshape(T, top_k + n_shared)
+    assert np.array_equal(st["count"], np.where(tau[st["expert"]] > 0, 0, f))
+    ref = np.zeros((T, d))
+    for e in range(4):
+        ref += np.where((st["expert"] % 4 == e) & (tau[st["expert"]] < 0), st["weight"], 0.0).sum(axis=1)[:, None] * out[e]
+    worst = max(range(T), key=lambda t: G.rel_err(y[t], ref[t]))
+    assert G.rel_err(y[worst], ref[worst]) <= G.Y_TIGHT, (worst, G.rel_err(y[worst], ref[worst]))
+
+
 @pytest.mark.parametrize("d,f,n,n_shared,top_k,T,pct", [
     (1024, 300, 3, 1, 1, 150, 60),   # ten tiles, of which the routed experts fill two to four; an odd number of pairs
     (512, 97, 2, 1, 1, 155, 30),     # five to six; one row in the last pair

@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "wide_cut.h"
+#include "wide_plan.h"
 
 using namespace floe;
 
@@ -125,7 +126,27 @@ static void walk(const std::vector<Group>& groups, int max_groups, int h_tiles, 
     for (int g = 0; g < ng; ++g) CHECK(met[g] == (int)list[g].size(), "group %d: %d of %d pairs are met", g, met[g], (int)list[g].size());
 }
 
+// The segment table holds what any layer that the argument checks accept can ask for: up to 1024 routed experts, 64 slots, 4096 tokens.
+static int plans() {
+    int most = 0;
+    double groups;
+    for (const int experts : {1024, 1023, 960, 700, 300, 64, 0})
+        for (int slots = 1; slots <= 64; slots += slots < 61 ? 4 : 1)
+            for (int top_k = 0; top_k <= slots && top_k <= experts; ++top_k)
+                for (int T = 1; T <= 4096; T += slots > 60 ? 3 : 45) {
+                    const int shared = slots - top_k, nt = wide_tiles_for(T, experts, top_k, shared, groups);
+                    const int entries = wide_max_groups(experts + shared, T * slots, nt) + 256;
+                    if (entries > kWideMaxSegments) {
+                        printf("%d experts top-%d, %d shared, %d tokens: %d segments\n", experts, top_k, shared, T, entries);
+                        exit(1);
+                    }
+                    most = std::max(most, entries);
+                }
+    return most;
+}
+
 int main() {
+    const int most = plans();
     long walked = 0;
     // tasks per expert from one routing to another: even, all on one, all on a few, one crowded among single tokens, random
     for (const int nt : {1, 2, 3, 4, 5, 10})
@@ -166,6 +187,6 @@ int main() {
                             ++walked;
                         }
                 }
-    printf("ok %ld\n", walked);
+    printf("ok %ld cuts, up to %d segments\n", walked, most);
     return 0;
 }
