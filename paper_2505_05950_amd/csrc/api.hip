@@ -547,9 +547,9 @@ static int expert_ffn_sparse(const floe_expert* e, const floe_half* x, int T, co
             FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st, split ? launch_up_split(u, e->s.bits, e->s.group, st) : launch_up_wide(u, e->s.bits, e->s.group, st));
         } else {
             FLOE_HIP(launch_wide_single(map.single, T, w.wp.chunk, groups, n_groups, order, st));
-            FLOE_HIP(launch_wide_prepare(prep, wa, T, e->s.d, st));
             FLOE_LAUNCH(FLOE_KERNEL_UP_GEMV, st,
                         launch_up_gemv(map, xh, nullptr, v, tau, mask, e->s.d, e->s.f, e->s.bits, e->s.group, T, st));
+            FLOE_HIP(launch_wide_prepare(prep, wa, mask, T, e->s.d, st));
         }
         FLOE_LAUNCH(FLOE_KERNEL_GATE_DOWN, st, launch_gate_down_wide(wa, w.wp, mask, e->s.d, st));
         if (idx) FLOE_LAUNCH(FLOE_KERNEL_SELECT, st, launch_select(v, e->s.f, T, tau, idx, count, st, pad));
@@ -814,7 +814,7 @@ int floe_moe_layer_decode(const floe_layer* L, const floe_half* x, int T, floe_h
                         launch_up_gemv(map, xh, nullptr, v, task_tau, mask, L->s.d, L->s.f, L->s.bits, L->s.group,
                                        w.n_tasks, st));
         if (w.use_wide) {
-            if (!w.up_wide && !w.up_split) FLOE_HIP(launch_wide_prepare(prep, wa, w.n_tasks, L->s.d, st));
+            if (!w.up_wide && !w.up_split) FLOE_HIP(launch_wide_prepare(prep, wa, mask, w.n_tasks, L->s.d, st));
             FLOE_LAUNCH(FLOE_KERNEL_GATE_DOWN, st, launch_gate_down_wide(wa, w.wp, mask, L->s.d, st));
             FLOE_LAUNCH(FLOE_KERNEL_COMBINE, st, launch_combine_wide(wa, w.wp, L->s.d, T, nullptr, reinterpret_cast<h16*>(y), st));
             if (stats)

@@ -185,7 +185,8 @@ hipError_t launch_gate_down_union(const UnionArgs& a, const UnionPlan& p, int d,
 
 // S4 + S5 on the matrix cores for batches in which experts see many tokens (wide_batch.hip): groups of up to 16 * nt tokens.
 struct WideGroup {
-    int32_t expert, n, first;  // tasks order[first .. first + n)
+    int32_t share;             // of its channels, selected, in 2^-20 (from the up projection's first piece, or wide_prepare_kernel)
+    int32_t n, first;          // tasks order[first .. first + n)
     int32_t tile;              // number of its first token tile: (first + 15 * group) / 16, so that no two groups share one
     DevExpert e;               // the expert's arrays, so that nobody has to look them up behind this load
 };
@@ -229,7 +230,7 @@ struct WidePrep {
     float* scale;
 };
 struct WideArgs {
-    const WideGroup* groups;
+    WideGroup* groups;
     const int32_t* n_groups;
     const int32_t* order;     // [n_tasks] tasks sorted by expert
     const h16* x;
@@ -264,7 +265,7 @@ inline bool up_wide_pays(int d, int f, int bits, int group, int n_all, int n_tas
     return bits != 2 || (n_tasks >= 32 * n_all && n_all * ((f + 31) / 32) >= 600);
 }
 struct UpWideArgs {
-    const WideGroup* groups;
+    WideGroup* groups;
     const int32_t* n_groups;
     const int32_t* order;
     const h16* x;
@@ -322,8 +323,8 @@ hipError_t launch_up_split(const UpWideArgs& a, int bits, int group, hipStream_t
 
 WidePlan wide_plan(int d, int f, int T, int n_experts, int top_k, int n_shared, int max_down);
 WidePlan wide_room(int d, int f, int T, int n_experts, int top_k, int n_shared);
-// clears and copies what WidePrep names, where no up projection of wide groups has done so
-hipError_t launch_wide_prepare(const WidePrep& prep, const WideArgs& a, int n_tasks, int d, hipStream_t stream);
+// clears and copies what WidePrep names and fills in the groups' shares, where no up projection of wide groups has done so
+hipError_t launch_wide_prepare(const WidePrep& prep, const WideArgs& a, const uint32_t* mask_words, int n_tasks, int d, hipStream_t stream);
 hipError_t launch_gate_down_wide(const WideArgs& a, const WidePlan& p, const uint32_t* mask_words, int d, hipStream_t stream);
 hipError_t launch_wide_single(const DevExpert& e, int n_tasks, int chunk, WideGroup* groups, int32_t* n_groups, int32_t* order,
                               hipStream_t stream);

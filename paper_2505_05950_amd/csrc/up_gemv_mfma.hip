@@ -458,7 +458,7 @@ __global__ __launch_bounds__(1024) void group_tokens_kernel(const int32_t* __res
             const int len = nw ? (c + nw - 1) / nw : 0;  // equal sizes
             for (int g = 0; g < nw; ++g) {
                 const int first = first_task[e] + g * len;
-                wide[w0 + g] = WideGroup{e, min(len, c - g * len), first, (first + 15 * (w0 + g)) >> 4, table[e]};
+                wide[w0 + g] = WideGroup{0, min(len, c - g * len), first, (first + 15 * (w0 + g)) >> 4, table[e]};
             }
         }
         count[e] = 0;

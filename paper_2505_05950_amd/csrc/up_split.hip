@@ -125,11 +125,12 @@ __global__ __launch_bounds__(128) void x_operand_kernel(XOperandArgs a) {
         row = tile * 16 + sum[0] - gl * len;
         if (U == 0) {
             a.order[pos] = i;
-            if (sum[0] == gl * len) a.groups[g] = WideGroup{e, min(len, n - gl * len), first, tile, a.table[e]};
+            if (sum[0] == gl * len) a.groups[g] = WideGroup{0, min(len, n - gl * len), first, tile, a.table[e]};
             if (i == 0) a.n_groups[0] = sum[3];
         }
     } else {
-        row = wide_token_row(a.groups, a.n_groups[0], a.max_groups, i, lane);
+        int g;
+        row = wide_token_row(a.groups, a.n_groups[0], a.max_groups, i, lane, g);
     }
     const int d = a.d;
     uint4* __restrict__ frag = a.frag;
@@ -186,7 +187,7 @@ __global__ __launch_bounds__(128) void x_operand_kernel(XOperandArgs a) {
 }
 
 template <int BITS, bool G32, int NT, int TILES>
-__global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restrict__ groups, const int32_t* __restrict__ n_groups,
+__global__ __launch_bounds__(512) void up_split_kernel(WideGroup* __restrict__ groups, const int32_t* __restrict__ n_groups,
                                                        int max_groups, const uint4* __restrict__ frag,
                                                        const float* __restrict__ gsum, const float* __restrict__ back,
                                                        float* __restrict__ v, const float* __restrict__ tau,
@@ -250,7 +251,8 @@ __global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restri
             }
             base += __builtin_amdgcn_readlane(inc, kWave - 1);
         }
-        const WideGroup grp = groups[__builtin_amdgcn_readfirstlane(g)];
+        g = __builtin_amdgcn_readfirstlane(g);
+        const WideGroup grp = groups[g];
         const int part = __builtin_amdgcn_readfirstlane(min((pos - base) / full_weight, parts_of(grp.n) - 1));
         const int tok_first = 32 * part, n_tok = min(32, grp.n - tok_first);
         // block k of a part belongs to the piece that holds the start of its share, kStart + k * wgt behind the part's
@@ -320,6 +322,7 @@ __global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restri
         FLOE_TL(2);
         __syncthreads();  // the group sums and s_back are complete
         FLOE_TL(3);
+        int selected = 0;  // channels of this part's tokens that this wave found above their thresholds
         // live: token tiles that hold tokens
         auto body = [&](auto live, int i) __attribute__((always_inline)) {
             constexpr int NL = decltype(live)::value;
@@ -443,6 +446,7 @@ __global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restri
                     const float val = e ? r.y * back2.y : r.x * back2.x;
                     if (live && ch < f) v[(size_t)task * f + ch] = val;
                     const uint64_t m = __ballot(live && ch < f && fabsf(val) > (e ? tau2.y : tau2.x));
+                    selected += __builtin_amdgcn_readfirstlane(__popcll(m));
                     if (mask16 && live && c == 0 && base < 32 * nwords)
                         mask16[(size_t)task * nwords * 2 + (base >> 4)] = (uint16_t)(m >> (16 * g4));
                 }
@@ -455,14 +459,11 @@ __global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restri
                 if (i == 0) FLOE_TL(4);
             }
         };
-        if constexpr (NT > 1) {
-            if (n_tok <= 16) {
-                walk(std::integral_constant<int, 1>{});
-                FLOE_TL(5);
-                continue;
-            }
-        }
-        walk(std::integral_constant<int, NT>{});
+        if (NT > 1 && n_tok <= 16) walk(std::integral_constant<int, 1>{});
+        else walk(std::integral_constant<int, NT>{});
+        // a group's share from the workgroup that has its first channels (from all of them it would be 256 additions to one place)
+        if (part == 0 && b0 == 0 && lane == 0 && selected)
+            atomicAdd(&groups[g].share, wide_selected_share(selected, min(len * kCh, f) * n_tok));
     }
     FLOE_TL(5);
 }
@@ -478,7 +479,7 @@ size_t x_operand_sum_bytes(int tiles, int d, int group) { return (size_t)tiles *
 template <int BITS, bool G32>
 static hipError_t operand_bits(const UpWideArgs& a, const XOperand& x, hipStream_t stream) {
     const bool here = !a.single && a.task_expert && a.n_tasks <= kOperandGroups;
-    const XOperandArgs p{a.x, a.slots, a.d, a.max_groups, a.n_tasks, a.chunk, a.n_all, const_cast<WideGroup*>(a.groups),
+    const XOperandArgs p{a.x, a.slots, a.d, a.max_groups, a.n_tasks, a.chunk, a.n_all, a.groups,
                          const_cast<int32_t*>(a.n_groups), const_cast<int32_t*>(a.order), a.task_expert, a.table,
                          a.single ? *a.single : DevExpert{}, x.frag, x.gsum, x.back, a.prep};
     const dim3 grid(a.n_tasks), block(a.d > 4096 ? 128 : 64);

@@ -29,7 +29,7 @@ constexpr int kUpThreads = kUpWaves * 64;
 constexpr int kUpSlotUnits = 2;
 
 template <int BITS, bool G32, int NT>
-__global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __restrict__ groups, const int32_t* __restrict__ n_groups,
+__global__ __launch_bounds__(kUpThreads) void up_wide_kernel(WideGroup* __restrict__ groups, const int32_t* __restrict__ n_groups,
                                                              int max_groups, const uint4* __restrict__ frag, const float* __restrict__ gsum,
                                                              const float* __restrict__ back, float* __restrict__ v,
                                                              const float* __restrict__ tau, uint32_t* __restrict__ mask_words,
@@ -104,7 +104,8 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __
             base += __builtin_amdgcn_readlane(inc, kWave - 1);
         }
         if (g < 0) break;  // fewer pieces than workgroups
-        const WideGroup grp = groups[__builtin_amdgcn_readfirstlane(g)];
+        g = __builtin_amdgcn_readfirstlane(g);
+        const WideGroup grp = groups[g];
         const int wgt = weight(grp.n), part_weight = wgt * blocks;
         const int in_part = whole ? (part_weight + most - 1) / most : part_weight;
         const int part = __builtin_amdgcn_readfirstlane((pos - base) / in_part);
@@ -138,6 +139,7 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __
         const int np = (len + kUpWaves - 1) / kUpWaves;
         const int per = (len + np - 1) / np;
 
+        int selected = 0;  // channels of this part's first 16 tokens that this wave found above their thresholds
         // live: token tiles that this part has, of NT at most
         auto run = [&](auto live) __attribute__((always_inline)) {
             constexpr int NL = decltype(live)::value;
@@ -360,6 +362,7 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __
                                 const float val = acc[t][n][i] * bk[i];
                                 if (used && ch < f) vt[ch] = val;
                                 const uint64_t m = __ballot(used && ch < f && fabsf(val) > limit[i]);
+                                if (n == 0) selected += __builtin_amdgcn_readfirstlane(__popcll(m));
                                 w |= ((uint32_t)(m >> (16 * g4)) & 0xFFFFu) << (16 * h);
                             }
                             const int word = ch0 / 32 + t2;
@@ -370,6 +373,9 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __
             }
         };
         with_live_tiles<NT>(tiles, run);
+        // a group's share from the workgroup that has its first channels (from all of them it would be 256 additions to one place)
+        if (part == 0 && b0 == 0 && lane == 0 && selected)
+            atomicAdd(&groups[g].share, wide_selected_share(selected, min(len * 16 * CT, f) * min(n_tok, 16)));
     }
 }
 

@@ -16,9 +16,15 @@
 //                      to that the split is good to 2^-23, whatever the size of h, and no token depends on another.
 //   combine_wide       adds a task's partial results.
 //
-// Division of work.  Gate: the channels of all groups in equal pieces, by what a group's rows are expected to be.  Down: the row pairs of all
+// Division of work.  Gate: the channels of all groups in equal pieces, by what a group's rows are expected to be from its tokens and the share
+// of channels they selected (wide_weight).  Down: the row pairs of all
 // groups form one sequence; the workgroups cut it into equal pieces, whatever the routing did to the group sizes, so the launch is one even
 // round and no compute unit waits for a crowded expert.
+// The share is what the up projection found in a group's first piece.  Without it (one channel in eight, whatever the layer's sparsity) groups of
+// few tokens were given pieces too large at 60 %: layer calls, cut by counted rows in a launch of its own / by one in eight / by the share, us, 96 + 1
+// experts top-4 d 2048 f 2048 INT2, 128 tokens 397 / 446 / 397, 16 experts top-2 d 4096 f 4000, 64 tokens 271 / 282 / 264, 128 experts top-8
+// d 2048 f 768 INT4, 128 tokens 281 / 285 / 266.  Pieces that end where groups end, without the limit to how uneven they may be / with it: the
+// last one with 384 tokens (134 groups, 256 workgroups) 378 / 355, 256 experts top-8 d 4096 f 1408, 150 tokens 962 / 926.
 //
 // The lists were a launch of their own between the up projection and the gate kernel, 6 to 8 us (17 at 512 tokens, the activations with
 // it), so that the gate kernel could cut by rows.  Made in the gate kernel they cost its workgroups 4 us before their first row; together with
@@ -56,11 +62,27 @@ constexpr int kSliceCols = 64;   // columns of rows and activations per ring slo
 constexpr int kSpan = 64;        // channels of v that a wave brings in for a pair of row tiles
 constexpr int kDownCols = 512;   // output columns per workgroup of the down kernel (64 per wave)
 
-// What x_operand_kernel does beside its own work, where the up projection is another one: the activations in the order of the gate
-// kernel's operand, and cleared counters.  A workgroup per position of the order.
-__global__ __launch_bounds__(128) void wide_prepare_kernel(WidePrep prep, WideArgs a, int n_tasks, int d) {
-    const int i = blockIdx.x, tid = threadIdx.x;
-    const int task = a.order[i], row = wide_token_row(a.groups, a.n_groups[0], a.max_groups, i, tid & 63);
+// What x_operand_kernel and the wide up projections do beside their own work, behind an up projection of another kind: the activations in the
+// order of the gate kernel's operand, cleared counters, and each group's share of selected channels.  A workgroup per position of the order.
+__global__ __launch_bounds__(128) void wide_prepare_kernel(WidePrep prep, WideArgs a, const uint32_t* __restrict__ mask_words, int n_tasks, int d) {
+    const int i = blockIdx.x, tid = threadIdx.x, nwords = mask_words_per_task(a.f);
+    int g;
+    const int task = a.order[i], row = wide_token_row(a.groups, a.n_groups[0], a.max_groups, i, tid & 63, g);
+    // (a group's share from its first four tokens: additions of all of them to one place take longer than the rest, 400 tokens on 6 experts 6 -> 17 us)
+    const int seen = min(a.groups[g].n, 4);
+    if (i - a.groups[g].first < seen) {
+        const uint32_t* mw = mask_words + (size_t)(a.by_task ? task : i) * nwords;
+        int selected = 0;
+        for (int w0 = tid; w0 < nwords; w0 += 8 * 128) {
+            uint32_t m[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) m[k] = w0 + k * 128 < nwords ? mw[w0 + k * 128] : 0u;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) selected += __popc(m[k]);
+        }
+        selected = wave_sum(selected);
+        if ((tid & 63) == 0 && selected) atomicAdd(&a.groups[g].share, wide_selected_share(selected, seen * a.f));
+    }
     if (tid == 0) wide_clear(prep, i, task, n_tasks);
     // vector p of the row is quarter p % 4 of k-step p / 4
     const uint4* x = reinterpret_cast<const uint4*>(a.x + (size_t)(task / a.slots) * d);
@@ -85,6 +107,9 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, con
     __shared__ float s_w[kTok], s_tau[kTok];
     __shared__ uint32_t s_hmax[kTok];  // bits of the largest finite |h| of this workgroup's rows (ordered like the numbers)
     __shared__ int s_count[kTok], s_wave[kWideWaves];
+    constexpr bool kKept = NT <= 5;  // (ten token tiles have no registers to keep the groups' records and weights)
+    constexpr int kHeld = 4;
+    __shared__ uint8_t s_weight[kKept ? kHeld * kWave : 1];  // of the first groups
     constexpr bool kIds = NT <= 5;  // (there is room for the row ids of a pass)
     __shared__ __align__(16) int s_ids[kIds ? kWideWaves * kPairRows : 4];
     uint32_t* s_union = reinterpret_cast<uint32_t*>(r0);  // before the rows: mask words of the segment's union,
@@ -98,32 +123,49 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, con
     const int ng = a.n_groups[0];
     const int W = gridDim.x, piece = wide_piece(W);
     const int units = wide_piece_units(a.f);
-    // a group's record in the lane of its number; the first 64 are asked for once, without waiting for their number
-    auto record_of = [&](int g0) { return a.groups[min(g0 + lane, a.max_groups - 1)]; };
-    const WideGroup head = record_of(0);
-    auto tokens_of = [&](int g0) { return g0 == 0 ? head.n : a.groups[min(g0 + lane, a.max_groups - 1)].n; };
-    int total = 0;
-    for (int g0 = 0; g0 < ng; g0 += kWave) {
-        const int n = tokens_of(g0);
-        total += wave_sum(g0 + lane < ng ? wide_weight(n) * units : 0);
+    // The records of the first 64 groups, in the lane of their number, and the weights of the first 256 are asked for once, without waiting
+    // for the number of groups (the search below asked for them in every round: 0.4 us each).
+    const WideGroup head = a.groups[min(lane, a.max_groups - 1)];
+    auto weight_at = [&](int g0) {  // of the group in this lane
+        const WideGroup& rec = a.groups[min(g0 + lane, a.max_groups - 1)];
+        return wide_weight(rec.n, rec.share);
+    };
+    const bool many = a.max_groups > kWave;
+    int held[kHeld] = {};
+    held[0] = weight_at(0);
+    if (many) {
+#pragma unroll
+        for (int q = 1; q < kHeld; ++q) held[q] = weight_at(q * kWave);
     }
+#pragma unroll
+    for (int q = 0; q < kHeld; ++q) held[q] = q * kWave + lane < ng ? held[q] : 0;  // 0 behind the last group
+    if (kKept && many) {  // (every wave writes the same, and reads what it wrote)
+#pragma unroll
+        for (int q = 1; q < kHeld; ++q) s_weight[q * kWave + lane] = (uint8_t)held[q];
+    }
+    int total = (held[0] + held[1] + held[2] + held[3]) * units;
+    for (int g0 = kHeld * kWave; g0 < ng; g0 += kWave) total += g0 + lane < ng ? weight_at(g0) * units : 0;
+    total = wave_sum(total);
     // Pieces end where groups end: a second segment costs its start and its end again, 10 us, and the launch waits for the few workgroups that
     // have one (64 tokens on 8 experts: the mean workgroup done at 139 us, the last at 163).  Each group is cut into as few equal pieces of
-    // at most `most` as it takes, `most` the smallest that leaves no more than W pieces.
-    const bool whole = ng <= W;
+    // at most `most` as it takes, `most` the smallest that leaves no more than W pieces - if that is not too large (wide_most_limit).
+    bool whole = ng <= min(W, kHeld * kWave);
     int most = max((total + W - 1) / W, 1);
+    const int limit = wide_most_limit(most);
     while (whole) {
-        int sum = 0;
         const float per_most = 1.0f / (float)most;
-        for (int g0 = 0; g0 < ng; g0 += kWave) {
-            const int n = tokens_of(g0);
-            sum += wave_sum(g0 + lane < ng ? wide_share(wide_weight(n), units, most, per_most) : 0);
+        int sum = wide_share(held[0], units, most, per_most);
+        if (many) {
+#pragma unroll
+            for (int q = 1; q < kHeld; ++q) sum += wide_share(held[q], units, most, per_most);
         }
-        if (sum <= W) break;  // (at the largest group at the latest: a piece each)
-        most += (most + 31) / 32;
+        sum = wave_sum(sum);
+        if (sum <= W) break;
+        most = wide_next_most(most);
+        whole = most <= limit;
     }
     const float per_most = 1.0f / (float)most;
-    auto share_of = [&](int n) { return whole ? wide_share(wide_weight(n), units, most, per_most) : wide_weight(n) * units; };
+    auto share_of = [&](int weight) { return whole ? wide_share(weight, units, most, per_most) : weight * units; };
     int pos = whole ? piece : wide_cut(total, W, piece);
     const int end = whole ? piece + 1 : wide_cut(total, W, piece + 1);
     const int ns = d / kSliceCols;  // a multiple of eight (d % 512 == 0)
@@ -133,19 +175,22 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, con
     auto swizzle = [](int row) { return (row & 7) ^ ((row >> 3) & 1); };
 
     while (pos < end) {  // one group's part of this workgroup's piece at a time
-        int g = -1, base = 0;  // the group that `pos` lies in and where it begins
+        int g = -1, base = 0, weight = 0;  // the group that `pos` lies in and where it begins
         WideGroup grp{};
         for (int g0 = 0; g0 < ng; g0 += kWave) {
-            WideGroup rec;
-            if (NT <= 5 && g0 == 0) rec = head;  // (ten token tiles have no registers to keep it in)
-            else rec = record_of(g0);
-            const int w = g0 + lane < ng ? share_of(rec.n) : 0;
+            const WideGroup rec = kKept && g0 == 0 ? head : a.groups[min(g0 + lane, a.max_groups - 1)];
+            int wgt;
+            if (kKept && g0 == 0) wgt = held[0];
+            else if (kKept && g0 < kHeld * kWave) wgt = s_weight[g0 + lane];
+            else wgt = g0 + lane < ng ? wide_weight(rec.n, rec.share) : 0;
+            const int w = share_of(wgt);
             const int inc = wave_inclusive_scan(w, lane);
             const unsigned long long past = __ballot(base + inc > pos);
             if (past) {
                 const int l = __ffsll((long long)past) - 1;
                 g = g0 + l;
                 base += __builtin_amdgcn_readlane(inc - w, l);
+                weight = __builtin_amdgcn_readlane(wgt, l);
                 grp = wide_record(rec, l);
                 break;
             }
@@ -155,14 +200,13 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, con
         WideUnits part;
         int first_piece;
         if (whole) {
-            part = wide_units_of_share(units, share_of(grp.n), pos - base);
+            part = wide_units_of_share(units, share_of(weight), pos - base);
             first_piece = base;
             pos = end;
         } else {
-            const int wgt = wide_weight(grp.n);
-            part = wide_units_of_span(units, wgt, pos - base, end - base);
+            part = wide_units_of_span(units, weight, pos - base, end - base);
             first_piece = wide_owner(total, W, base);
-            pos = base + units * wgt;  // the next group, or past the end
+            pos = base + units * weight;  // the next group, or past the end
         }
         const int u0 = __builtin_amdgcn_readfirstlane(part.begin), u1 = __builtin_amdgcn_readfirstlane(part.end);
         if (u1 <= u0) continue;
@@ -955,8 +999,8 @@ hipError_t launch_gate_down_wide(const WideArgs& a, const WidePlan& p, const uin
     }
 }
 
-hipError_t launch_wide_prepare(const WidePrep& prep, const WideArgs& a, int n_tasks, int d, hipStream_t stream) {
-    wide_prepare_kernel<<<dim3(n_tasks), dim3(128), 0, stream>>>(prep, a, n_tasks, d);
+hipError_t launch_wide_prepare(const WidePrep& prep, const WideArgs& a, const uint32_t* mask_words, int n_tasks, int d, hipStream_t stream) {
+    wide_prepare_kernel<<<dim3(n_tasks), dim3(128), 0, stream>>>(prep, a, mask_words, n_tasks, d);
     return hipGetLastError();
 }
 

@@ -2,6 +2,7 @@
 // (wide_layout.h): whole numbers only, for the kernels and for a host program alike.
 #pragma once
 
+#include <math.h>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -29,6 +30,27 @@ FLOE_BOTH int small_quotient(int n, float inverse) { return (int)(((float)n + 0.
 
 // ---- gate: the channels of a group are units of eight, each of the group's weight
 FLOE_BOTH int wide_piece_units(int f) { return (f + 7) >> 3; }
+// The share of a group's channels that its tokens selected, in 2^-20, as far as the part of them goes that a wave has seen.
+constexpr float kWideShareOne = 1048576.0f;
+FLOE_BOTH int wide_selected_share(int selected, int seen) { return (int)((float)selected * (kWideShareOne / (float)seen)); }
+// What eight channels of a group of n tokens cost, 1 to 32: the share of rows that somebody selected, if each token takes a channel with the
+// group's own probability.
+FLOE_BOTH int wide_weight(int n, int share) {
+    const float rest = fmaxf(1.0f - (float)share * (1.0f / kWideShareOne), 0.0f);  // of a token's channels
+#ifdef __HIP_DEVICE_COMPILE__
+    const float nobody = __builtin_amdgcn_exp2f((float)n * __builtin_amdgcn_logf(rest));
+#else
+    const float nobody = exp2f((float)n * log2f(rest));
+#endif
+    const int w = 32 - (int)(32.0f * nobody);
+    return w < 1 ? 1 : w;
+}
+// Pieces end where groups end (wide_share) unless the largest then has 96 rows more than an equal cut's: a second segment costs a workgroup
+// about as much, at any d.  Layer calls, whole pieces / equal ones, us, by the rows that whole ones have more: INT4 g64 d 2048 f 768 (128 experts
+// top-8) 29 259 / 267, 77 248 / 253, 62 236 / 233, 490 394 / 358; INT3 d 2048 f 1408 (64 + 2) 68 218 / 222, 93 239 / 239; d 4096 f 1024 (100) 102
+// 580 / 589, 120 466 / 461; d 1024 f 1024 (200) 55 165 / 169, 104 200 / 193, 336 264 / 250; d 5120 f 1536 (160 + 2) 129 726 / 722, 570 1323 / 1278.
+FLOE_BOTH int wide_most_limit(int most) { return most + 96 * 32 / 8; }
+FLOE_BOTH int wide_next_most(int most) { return most + (most >> 5) + 4; }
 // Pieces of a group, of at most `most` each (per_most: its reciprocal), and never more than it has units: a piece without channels writes no
 // segment, and the down kernel takes a group's first segment for the start of its slots.  (Few tokens' worth of groups in a launch sized
 // for many, as where a router sends a whole batch to one expert, leaves `most` below a unit's weight.)

@@ -12,10 +12,6 @@
 
 namespace floe {
 
-// What eight channels of a group of n tokens cost, 5 to 32: the rows that n tokens select between them if each takes one of eight.  (The
-// share is not known before the masks are; a cut by rows counted beforehand costs a launch of its own.)
-__device__ __forceinline__ int wide_weight(int n) { return 32 - (int)(32.0f * __builtin_amdgcn_exp2f(-0.2f * (float)n)); }
-
 // a group's record, held by lane l of the wave, in scalars (the fields that gate and down look at)
 __device__ __forceinline__ WideGroup wide_record(const WideGroup& rec, int l) {
     WideGroup g{};
@@ -28,14 +24,19 @@ __device__ __forceinline__ WideGroup wide_record(const WideGroup& rec, int l) {
     return g;
 }
 
-// token row of the tiles that position i of the order has; every lane the same
-__device__ __forceinline__ int wide_token_row(const WideGroup* __restrict__ groups, int ng, int max_groups, int i, int lane) {
+// token row of the tiles that position i of the order has, and its group; every lane the same
+__device__ __forceinline__ int wide_token_row(const WideGroup* __restrict__ groups, int ng, int max_groups, int i, int lane, int& g) {
     for (int g0 = 0; g0 < ng; g0 += kWave) {
         const WideGroup* mine = groups + min(g0 + lane, max_groups - 1);
         const int n = mine->n, first = mine->first, tile = mine->tile;
         const unsigned long long m = __ballot(g0 + lane < ng && i >= first && i < first + n);
-        if (m) return __builtin_amdgcn_readlane(tile * 16 + i - first, __ffsll((long long)m) - 1);
+        if (m) {
+            const int l = __ffsll((long long)m) - 1;
+            g = g0 + l;
+            return __builtin_amdgcn_readlane(tile * 16 + i - first, l);
+        }
     }
+    g = 0;
     return 0;  // (not reached: every position belongs to a group)
 }
 

@@ -22,8 +22,6 @@ struct Written {  // who wrote a slot
     int g = -1, index = 0;
 };
 
-static int weight_of(int n) { return 32 - (int)(32.0f * exp2f(-0.2f * (float)n)); }
-
 static unsigned g_seed = 1;
 static unsigned rnd() { return g_seed = g_seed * 1664525u + 1013904223u; }
 
@@ -37,32 +35,41 @@ static unsigned rnd() { return g_seed = g_seed * 1664525u + 1013904223u; }
         }                                                                                                                         \
     } while (0)
 
-// keep: of 100 channels the ones that somebody selected
+// keep: of 100 channels the ones that a token selects
 static void walk(const std::vector<Group>& groups, int max_groups, int h_tiles, int nt, int f, int W, int keep) {
     const int ng = (int)groups.size(), units = wide_piece_units(f), pmax = (f + 31) / 32;
-    std::vector<std::vector<char>> chosen(ng, std::vector<char>(f));
-    for (auto& c : chosen)
-        for (auto& b : c) b = (int)(rnd() >> 8) % 100 < keep;
+    std::vector<std::vector<char>> chosen(ng, std::vector<char>(f));  // by somebody
+    std::vector<int> weight(ng);
+    for (int g = 0; g < ng; ++g) {
+        const double somebody = 1.0 - pow(1.0 - 0.01 * keep, groups[g].n);
+        for (auto& b : chosen[g]) b = (rnd() >> 8) * 0x1p-24 < somebody;
+        weight[g] = wide_weight(groups[g].n, wide_selected_share((int)(0.01 * keep * groups[g].n * f), groups[g].n * f));
+        CHECK(weight[g] >= 1 && weight[g] <= 32 && fabs(weight[g] - 32.0 * somebody) <= 1.01 + 32.0 / f, "weight %d of group %d", weight[g], g);
+    }
     std::vector<Written> rows(wide_row_slots(max_groups, pmax, W)), h(wide_h_vecs(h_tiles, pmax, nt, max_groups, W) / 128);
     std::vector<Segment> table(W + max_groups);
     std::vector<std::vector<int>> list(ng);  // what the down kernel should meet: pairs of a group, in order
     std::vector<int> unit_seen(ng, 0);
     // ---- gate
     int total = 0;
-    for (const Group& g : groups) total += weight_of(g.n) * units;
-    const bool whole = ng <= W;
+    for (int g = 0; g < ng; ++g) total += weight[g] * units;
+    bool whole = ng <= std::min(W, 256);
     int most = std::max((total + W - 1) / W, 1);
+    const int limit = wide_most_limit(most);
     while (whole) {
         int sum = 0;
-        for (const Group& g : groups) sum += wide_share(weight_of(g.n), units, most, 1.0f / (float)most);
+        for (int g = 0; g < ng; ++g) sum += wide_share(weight[g], units, most, 1.0f / (float)most);
         if (sum <= W) break;
-        most += (most + 31) / 32;
+        most = wide_next_most(most);
+        whole = most <= limit;
     }
     std::vector<int> starts(ng + 1, 0);  // in pieces, or in weighted units
     auto share = [&](int g) { return starts[g + 1] - starts[g]; };
     for (int g = 0; g < ng; ++g)
-        starts[g + 1] = starts[g] + (whole ? wide_share(weight_of(groups[g].n), units, most, 1.0f / (float)most) : weight_of(groups[g].n) * units);
+        starts[g + 1] = starts[g] + (whole ? wide_share(weight[g], units, most, 1.0f / (float)most) : weight[g] * units);
+    long rows_all = 0, rows_most = 0;
     for (int piece = 0; piece < W; ++piece) {
+        long rows_here = 0;
         int pos = whole ? piece : wide_cut(total, W, piece);
         const int end = whole ? piece + 1 : wide_cut(total, W, piece + 1);
         while (pos < end) {
@@ -75,7 +82,7 @@ static void walk(const std::vector<Group>& groups, int max_groups, int h_tiles, 
                 first = base;
                 pos = end;
             } else {
-                u = wide_units_of_span(units, weight_of(groups[g].n), pos - base, end - base);
+                u = wide_units_of_span(units, weight[g], pos - base, end - base);
                 first = wide_owner(total, W, base);
                 pos = base + share(g);
             }
@@ -85,6 +92,7 @@ static void walk(const std::vector<Group>& groups, int max_groups, int h_tiles, 
             unit_seen[g] = u.end;
             int count = 0;
             for (int c = 8 * u.begin; c < std::min(8 * u.end, f); ++c) count += chosen[g][c];
+            rows_here += count;
             const int pairs = (count + 31) / 32, slot = wide_slot(u.begin, piece, first), tiles = (groups[g].n + 15) / 16;
             Segment& s = table[piece + g];
             CHECK(s.pairs == 0 && s.first == 0, "segment %d is written twice", piece + g);
@@ -101,7 +109,11 @@ static void walk(const std::vector<Group>& groups, int max_groups, int h_tiles, 
                 }
             }
         }
+        rows_all += rows_here;
+        rows_most = std::max(rows_most, rows_here);
     }
+    // (96 rows more than an even cut, whole units or 32 channels, and what the weights' rounding makes of it)
+    CHECK(ng > 300 || (double)(rows_most - 96 - 32) * W <= 1.25 * rows_all, "the largest piece has %ld rows of %ld", rows_most, rows_all);
     for (int g = 0; g < ng; ++g) CHECK(unit_seen[g] == units, "group %d ends at unit %d of %d", g, unit_seen[g], units);
     // ---- down
     std::vector<int> first_seg(ng, -1), met(ng, 0);
@@ -146,7 +158,7 @@ static int plans() {
 }
 
 int main() {
-    const int most = plans();
+    const int most = plans(), keeps[5] = {0, 5, 20, 40, 100};
     long walked = 0;
     // tasks per expert from one routing to another: even, all on one, all on a few, one crowded among single tokens, random
     for (const int nt : {1, 2, 3, 4, 5, 10})
@@ -183,7 +195,7 @@ int main() {
                             int W = (int)std::min(pairs, 256l);  // as the plan has it
                             if (W > 8) W &= ~7;
                             if ((long)groups.size() * f > 150000) continue;
-                            walk(groups, max_groups, h_tiles, nt, f, W, (int)(rnd() >> 8) % 3 * 50);
+                            walk(groups, max_groups, h_tiles, nt, f, W, keeps[(rnd() >> 8) % 5]);
                             ++walked;
                         }
                 }
