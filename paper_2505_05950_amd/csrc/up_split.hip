@@ -79,7 +79,8 @@ __global__ __launch_bounds__(128) void x_operand_kernel(XOperandArgs a) {
             if (i == 0) a.n_groups[0] = wide_single_groups(a.n_tasks, a.chunk);
         }
     } else if constexpr (HOW == Grouping::kHere) {
-        // workgroup i is task i; groups of equal size per expert, tasks of a group ascending
+        // workgroup i is task i; groups of equal size per expert, tasks of a group ascending.  (Every task has an expert of the table: the routers pick
+        // among n_all whatever the logits are, and every task is in a group.)
         __shared__ int tasks_of[1024 + 64];
         __shared__ int sums_of[2][4];  // tasks before this one in its expert; tasks and groups of the experts before; groups
         const int e = a.task_expert[i], threads = blockDim.x;
@@ -92,7 +93,7 @@ __global__ __launch_bounds__(128) void x_operand_kernel(XOperandArgs a) {
             for (int k = 0; k < 8; ++k) ej[k] = j0 + k * threads < a.n_tasks ? a.task_expert[j0 + k * threads] : -1;
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
-                if ((unsigned)ej[k] < (unsigned)a.n_all) atomicAdd(&tasks_of[ej[k]], 1);  // (sums of integers: in any order)
+                if (ej[k] >= 0) atomicAdd(&tasks_of[ej[k]], 1);  // (sums of integers: in any order)
                 before += ej[k] == e && j0 + k * threads < i;
             }
         }
@@ -114,10 +115,6 @@ __global__ __launch_bounds__(128) void x_operand_kernel(XOperandArgs a) {
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < 4; ++k) sum[k] = sums_of[0][k] + sums_of[1][k];
-        }
-        if ((unsigned)e >= (unsigned)a.n_all) {  // an id outside the table belongs to no group
-            if (U == 0) a.prep.count[i] = 0, a.prep.task_rows[i] = make_int2(0, 0);
-            return;
         }
         const int n = tasks_of[e], ng = small_quotient(n + a.chunk - 1, per_chunk), len = small_quotient(n + ng - 1, 1.0f / (float)ng);
         const int gl = small_quotient(sum[0], 1.0f / (float)len), g = sum[2] + gl, first = sum[1] + gl * len, tile = (first + 15 * g) >> 4;

@@ -129,6 +129,31 @@ def test_routing_that_fills_few_of_the_groups(d, f, bits, group, n, n_shared, to
         assert G.rel_err(y[t], ref["y"][t]) <= G.Y_TIGHT, (t, G.rel_err(y[t], ref["y"][t]))
 
 
+@pytest.mark.parametrize("n,top_k", [(8, 2), (70, 4)])   # picked by a wave, by one lane
+def test_tokens_that_are_not_numbers_leave_the_others_alone(n, top_k):
+    """Their logits are NaN: the router still picks experts of the table, and every task stands in a group."""
+    import gpu_common as G
+    import paper_2505_05950_amd as F
+    d, f, bits, group, T = 512, 130, 4, 64, 40
+    experts = [G.make_expert(*S.expert_weights(590, 13, d, f, 0, e), bits, group) for e in range(n)]
+    wr, x = S.router_weights(590, 13, n, d), S.tokens(590, 13, T + 20, d)
+    top = -np.sort(-(x.astype(np.float64) @ wr.astype(np.float64).T), axis=1)
+    x = x[top[:, top_k - 1] - top[:, top_k] > 1e-3][:T]
+    tau = np.full((T, n), -1.0, np.float32)
+    ref = O.moe_layer([e[0] for e in experts], 0, top_k, True, wr, x, tau, bits, group)
+    x = x.copy()
+    x[[0, 17, T - 1]] = np.nan
+    L = F.Layer([e[1] for e in experts], 0, top_k, True, G.dev(wr), G.dev(tau), True)
+    L.workspace(T).fill_(255)
+    stats = torch.zeros((T, top_k, 4), dtype=torch.int32, device=G.DEV)
+    y = F.floe_moe_layer_decode(L, G.dev(x), stats=stats).cpu().numpy().astype(np.float64)
+    ids = stats.cpu().numpy()[:, :, 0]
+    assert ids.min() >= 0 and ids.max() < n
+    for t in range(T):
+        if t not in (0, 17, T - 1):
+            assert G.rel_err(y[t], ref["y"][t]) <= G.Y_TIGHT, (t, G.rel_err(y[t], ref["y"][t]))
+
+
 def test_a_layer_of_thousands_of_groups():
     """1024 + 48 experts, 64 slots, 3712 tokens: about 4000 groups and 256 pieces.  Experts share four sets of weights, and select every
     channel or none, so that a token's result is the weighted sum of four."""
