@@ -156,10 +156,14 @@ def _ptr(t):
     return t.data_ptr()  # (ctypes makes a pointer of it; 0, an empty tensor's, is NULL)
 
 
+# The current stream's handle without a Python object for it, 1 us a call (a name that torch does not promise: without it the object is made)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
-    if stream is None:  # the current stream, without a Python object for it
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
-    return stream.cuda_stream
+    if stream is None and _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 def _check(rc: int, where: str):

@@ -154,8 +154,7 @@ static __device__ unsigned long long* g_timeline = nullptr;  // one copy per tra
 #define FLOE_TL(slot) FLOE_TL_AT(slot, 0)
 
 // sums over the lanes up to and with this one
-__device__ __forceinline__ int wave_inclusive_scan(int x, int lane) {
-    (void)lane;
+__device__ __forceinline__ int wave_inclusive_scan(int x) {
     x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr:1, 2, 4, 8
     x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
     x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
@@ -164,7 +163,7 @@ __device__ __forceinline__ int wave_inclusive_scan(int x, int lane) {
     x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // rows 2 and 3 += lane 31
     return x;
 }
-__device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_inclusive_scan(x, 0), kWave - 1); }
+__device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_inclusive_scan(x), kWave - 1); }
 
 // ---- memory straight into LDS (global_load_lds_dwordx4).  Destinations are arrays of their own per ring slot: the compiler then knows which
 // requests a read of LDS has to wait for, instead of waiting for all of them.

@@ -238,7 +238,7 @@ __global__ __launch_bounds__(512) void up_split_kernel(WideGroup* __restrict__ g
         int g = ng - 1, base = 0;  // the group that `pos` lies in and where it begins
         for (int g0 = 0; g0 < ng; g0 += kWave) {
             const int w = group_weight(g0);
-            const int inc = wave_inclusive_scan(w, lane);
+            const int inc = wave_inclusive_scan(w);
             const unsigned long long past = __ballot(base + inc > pos);
             if (past) {
                 const int l = __ffsll((long long)past) - 1;

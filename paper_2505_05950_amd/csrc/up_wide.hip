@@ -66,8 +66,8 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(WideGroup* __restri
     int total = 0, n_parts = 0;
     for (int g0 = 0; g0 < ng; g0 += kWave) {
         const Share sh = share_of(g0);
-        total += __builtin_amdgcn_readlane(wave_inclusive_scan(sh.parts * sh.part_weight, lane), kWave - 1);
-        n_parts += __builtin_amdgcn_readlane(wave_inclusive_scan(sh.parts, lane), kWave - 1);
+        total += wave_sum(sh.parts * sh.part_weight);
+        n_parts += wave_sum(sh.parts);
     }
     const int W = gridDim.x, piece = wide_piece(W);
     // Pieces end where parts end: a pass of the workgroup takes as long with one wave at work as with eight, so a piece that holds the
@@ -79,7 +79,7 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(WideGroup* __restri
         int sum = 0;
         for (int g0 = 0; g0 < ng; g0 += kWave) {
             const Share sh = share_of(g0);
-            sum += __builtin_amdgcn_readlane(wave_inclusive_scan(sh.parts * ((sh.part_weight + most - 1) / most), lane), kWave - 1);
+            sum += wave_sum(sh.parts * ((sh.part_weight + most - 1) / most));
         }
         if (sum <= W) break;  // (at the largest part at the latest: a piece each)
         most += (most + 31) / 32;
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(WideGroup* __restri
         for (int g0 = 0; g0 < ng; g0 += kWave) {
             const Share sh = share_of(g0);
             const int w = sh.parts * (whole ? (sh.part_weight + most - 1) / most : sh.part_weight);
-            const int inc = wave_inclusive_scan(w, lane);
+            const int inc = wave_inclusive_scan(w);
             const unsigned long long past = __ballot(base + inc > pos);
             if (past) {
                 const int l = __ffsll((long long)past) - 1;

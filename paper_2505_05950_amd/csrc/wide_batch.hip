@@ -184,7 +184,7 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, con
             else if (kKept && g0 < kHeld * kWave) wgt = s_weight[g0 + lane];
             else wgt = g0 + lane < ng ? wide_weight(rec.n, rec.share) : 0;
             const int w = share_of(wgt);
-            const int inc = wave_inclusive_scan(w, lane);
+            const int inc = wave_inclusive_scan(w);
             const unsigned long long past = __ballot(base + inc > pos);
             if (past) {
                 const int l = __ffsll((long long)past) - 1;
@@ -262,7 +262,7 @@ __global__ __launch_bounds__(kWideThreads) void gate_wide_kernel(WideArgs a, con
         const int per_thread = (nws + kWideThreads - 1) / kWideThreads;
         int mine = 0;
         for (int k = 0; k < per_thread; ++k) mine += tid * per_thread + k < nws ? __popc(s_union[tid * per_thread + k]) : 0;
-        const int inc = wave_inclusive_scan(mine, lane);
+        const int inc = wave_inclusive_scan(mine);
         if (lane == kWave - 1) s_wave[wave] = inc;
         __syncthreads();
         int run = inc - mine, count = 0;
@@ -565,7 +565,7 @@ __global__ __launch_bounds__(kWideThreads) void down_wide_kernel(WideArgs a, int
     for (int i0 = 0; i0 < nseg; i0 += kWideThreads) {
         const int i = i0 + tid;
         const int4 seg = i < nseg ? a.segments[i] : make_int4(0, 0, 0, 0);
-        const int inc = wave_inclusive_scan(seg.x, lane);
+        const int inc = wave_inclusive_scan(seg.x);
         if (lane == kWave - 1) s_wave[wave] = inc;
         __syncthreads();
         int at = total + inc - seg.x;
