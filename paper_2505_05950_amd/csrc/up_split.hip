@@ -184,7 +184,7 @@ __global__ __launch_bounds__(128) void x_operand_kernel(XOperandArgs a) {
 }
 
 template <int BITS, bool G32, int NT, int TILES>
-__global__ __launch_bounds__(512) void up_split_kernel(WideGroup* __restrict__ groups, const int32_t* __restrict__ n_groups,
+__global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restrict__ groups, int32_t* __restrict__ shares, const int32_t* __restrict__ n_groups,
                                                        int max_groups, const uint4* __restrict__ frag,
                                                        const float* __restrict__ gsum, const float* __restrict__ back,
                                                        float* __restrict__ v, const float* __restrict__ tau,
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(512) void up_split_kernel(WideGroup* __restrict__ g
         else walk(std::integral_constant<int, NT>{});
         // a group's share from the workgroup that has its first channels (from all of them it would be 256 additions to one place)
         if (part == 0 && b0 == 0 && lane == 0 && selected)
-            atomicAdd(&groups[g].share, wide_selected_share(selected, min(len * kCh, f) * n_tok));
+            atomicAdd(shares + g * kWideGroupWords, wide_selected_share(selected, min(len * kCh, f) * n_tok));
     }
     FLOE_TL(5);
 }
@@ -521,7 +521,7 @@ static hipError_t launch_split(const UpWideArgs& a, hipStream_t stream) {
     XOperand x;
     const hipError_t rc = launch_x_operand(a, BITS, G32 ? 32 : 64, x, stream);
     if (rc != hipSuccess) return rc;
-    kernel<<<dim3(wgs), dim3(64 * nw), lds, stream>>>(a.groups, a.n_groups, a.max_groups, x.frag, x.gsum, x.back, a.v, a.prep.tau,
+    kernel<<<dim3(wgs), dim3(64 * nw), lds, stream>>>(a.groups, &a.groups->share, a.n_groups, a.max_groups, x.frag, x.gsum, x.back, a.v, a.prep.tau,
                                                     a.mask_words, a.d, a.f);
     return hipGetLastError();
 }

@@ -29,7 +29,7 @@ constexpr int kUpThreads = kUpWaves * 64;
 constexpr int kUpSlotUnits = 2;
 
 template <int BITS, bool G32, int NT>
-__global__ __launch_bounds__(kUpThreads) void up_wide_kernel(WideGroup* __restrict__ groups, const int32_t* __restrict__ n_groups,
+__global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __restrict__ groups, int32_t* __restrict__ shares, const int32_t* __restrict__ n_groups,
                                                              int max_groups, const uint4* __restrict__ frag, const float* __restrict__ gsum,
                                                              const float* __restrict__ back, float* __restrict__ v,
                                                              const float* __restrict__ tau, uint32_t* __restrict__ mask_words,
@@ -375,7 +375,7 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(WideGroup* __restri
         with_live_tiles<NT>(tiles, run);
         // a group's share from the workgroup that has its first channels (from all of them it would be 256 additions to one place)
         if (part == 0 && b0 == 0 && lane == 0 && selected)
-            atomicAdd(&groups[g].share, wide_selected_share(selected, min(len * 16 * CT, f) * min(n_tok, 16)));
+            atomicAdd(shares + g * kWideGroupWords, wide_selected_share(selected, min(len * 16 * CT, f) * min(n_tok, 16)));
     }
 }
 
@@ -387,7 +387,7 @@ static hipError_t launch_nt(const UpWideArgs& a, hipStream_t stream) {
     XOperand x;
     const hipError_t rc = launch_x_operand(a, BITS, G32 ? 32 : 64, x, stream);
     if (rc != hipSuccess) return rc;
-    up_wide_kernel<BITS, G32, NT><<<dim3(wgs), dim3(kUpThreads), 0, stream>>>(a.groups, a.n_groups, a.max_groups, x.frag, x.gsum,
+    up_wide_kernel<BITS, G32, NT><<<dim3(wgs), dim3(kUpThreads), 0, stream>>>(a.groups, &a.groups->share, a.n_groups, a.max_groups, x.frag, x.gsum,
                                                                                x.back, a.v, a.prep.tau, a.mask_words, a.d, a.f);
     return hipGetLastError();
 }
