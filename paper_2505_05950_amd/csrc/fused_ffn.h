@@ -26,11 +26,11 @@
 // Widths between the powers of two (24, 40 or 48 units a channel): a channel still has 32 or 64 lanes, so that the sums stay DPP
 // steps within one wave; the lanes without a unit repeat its last one (same cache line, no further bytes) with activations of
 // zero.  The GEMV loses their share of its arithmetic, which the stream hides for a few tasks: INT4 g128 d 2560 f 6911, three tokens
-// top-2 of six, 37.4 us with separate kernels, 28.5 so (the traffic alone is 21 at the rate of a copy).  Separate kernels at these
+// top-2 of six, 37.4 us with separate kernels, 26.6 so (the traffic alone is 21 at the rate of a copy).  Separate kernels at these
 // widths read codes as subnormals, without an offset in the sums, and so do these instances: error of v against 64 bits 7e-8
-// (norm), with the packed kernels' offset 1.7e-6 .. 3.2e-6.  It costs 1 to 7 %: offset / this, us, INT2 g64 d 3072 f 8192 (8 experts,
-// top-2, 90 %) 1 token 19.5 / 20.5, 4 33.5 / 36.0; INT4 g128 d 2560 f 6911 3 tokens 27.1 / 28.5.  (Tried: the 1 taken off by a packed
-// subtraction and v_dot2 kept: 22.0, 40.2, 28.3, as exact.)
+// (norm), with the packed kernels' offset 1.7e-6 .. 3.2e-6.  It cost 1 to 7 % (measured with consumers that did not yet work
+// one entry ahead): offset / this, us, INT2 g64 d 3072 f 8192 (8 experts, top-2, 90 %) 1 token 19.5 / 20.5, 4 33.5 / 36.0; INT4 g128 d 2560 f 6911
+// 3 tokens 27.1 / 28.5.  (Tried then: the 1 taken off by a packed subtraction and v_dot2 kept: 22.0, 40.2, 28.3, as exact.)
 #pragma once
 
 #include <type_traits>
@@ -243,8 +243,10 @@ __global__ __launch_bounds__(kFusedThreads, fused_wgs_per_cu) void fused_ffn_ker
         // The codes of a pass travel straight into LDS, into the two result slabs of this producer's own consumers
         // (unused until those have seen the producer's flag); only scale and zero take registers.
         using St = StageTraits<BITS>;
-        // Requests without conditions.  Not INT4 at d 2048, which they slow down where few channels are selected (f 6857, 8 experts top-2, 9
-        // tokens, 60 / 72 / 90 %: 81.7 / 63.0 / 37.7 us without, 82.2 / 64.1 / 40.0 with them).
+        // Requests without conditions.  Not INT4 at d 2048, which they slow down by up to 6 % in middling batches and where many channels are
+        // selected; large ones at 90 % would be faster with them.  us, without / with them at 60, 75, 90 %, 8 experts top-2: f 6857, 9 tokens 78.0 / 79.7
+        // 56.8 / 58.2  39.3 / 40.4, 16 94.2 / 95.9  78.4 / 74.2  57.2 / 49.5; f 14000, 16 182 / 185  152 / 144  125 / 96; 16 experts f 5632 g32, 32 tokens
+        // 158 / 169  128 / 125  101 / 81; 64 + 2 f 1408 top-6, 8 57.2 / 58.2  45.4 / 45.9  35.5 / 32.5.  (Why this width alone is not known.)
         constexpr bool kFree = kAhead && !(BITS == 4 && UPC == 32);
         constexpr bool kStaged = staged_codes<BITS>();
         constexpr int kSlot = stage_slot_bytes<BITS>();

@@ -60,21 +60,20 @@ int fused_passes(int d, int f, int bits, int n_tasks, int max_tasks) {
 // Whether a batch at a width between the powers of two is better off in the fused kernel than in the separate ones.  What counts is how
 // many channel passes its producers do one after another (a pass 0.35 to 0.45 us, whatever the selection is): a launch that is one
 // even round does n_tasks f / (1024 producers x channels per pass).  Calls fused / one-token / wide kernels, us, at sparsities 60, 80, 90, 95 %:
-// (taken before its consumers worked one entry ahead, which made the fused kernel 1 to 15 % faster at these widths)
 //   few passes: the fused kernel saves launches and overlaps the two streams
-//     INT4 g64 d 2560 f 8000, 4 experts top-2, 3 tokens (47 passes)        39/56/81  32/44/68  30/37/63  29/31/60
-//     INT2 g64 d 3072 f 8000, 8 experts, 10 tokens (156)                   0.56 0.58 0.75 0.94 times the one-token kernels
-//     INT4 g128 d 2560 f 8000, 8 experts, 16 tokens (250)                  0.77 0.94 1.13 1.22
+//     INT4 g64 d 2560 f 8000, 4 experts top-2, 3 tokens (47 passes)        45/59/77  32/44/70  28/37/64  27/31/62
+//     INT2 g64 d 3072 f 8000, 8 experts, 10 tokens (156)                   0.58 0.59 0.65 0.79 times the one-token kernels
+//     INT4 g128 d 2560 f 8000, 8 experts, 16 tokens (250)                  0.67 0.74 0.88 1.08
 //   a launch of a second round, or one that leaves so many compute units idle that it takes a quarter longer: not that
-//     INT4 g64 d 2560 f 2048, 48 + 2 experts top-6, 18 tokens (512 in two rounds, 288 if it were even)  1.72 2.18 2.84 3.35
-//     INT3 g32 d 1536 f 2048, the same (256, even 144)                     1.05 1.24 1.43 1.54
-//     just inside: the same, 12 tokens (128, even 96)                      0.89 0.96 1.09 1.16
+//     INT4 g64 d 2560 f 2048, 48 + 2 experts top-6, 18 tokens (512 in two rounds, 288 if it were even)  1.49 1.77 2.33 2.83
+//     INT3 g32 d 1536 f 2048, the same (256, even 144)                     0.98 1.04 1.28 1.40
+//     just inside: INT4 g64 d 2560 f 2048, 12 tokens (256, even 192)       0.81 0.84 1.04 1.23
 //   many passes, where tokens are enough for the wide kernels by their own line: those, but for INT3, whose v the matrix cores form
 //   less accurately (1e-5 against 8e-8 here)
-//     one expert INT2 g64 d 2560 f 14336, 16 tokens (224 passes)           97/161/76  90/110/75  87/87/69  86/74/63
-//     one expert INT4 g64 d 3072 f 14336, 16 tokens (224)                  112/154/76 at 70 %, 99/87/62 at 95 %
+//     one expert INT2 g64 d 2560 f 14336, 16 tokens (224 passes)           98/162/67  91/116/67  88/94/65  87/79/63
+//     one expert INT4 g64 d 3072 f 14336, 16 tokens (224)                  110/171/69 at 60 %, 91/89/60 at 95 %
 //     layers, which reach that line with two or three experts only, break even later: INT4 g64 d 2560 f 8000, 8 experts, 16 tokens (250)
-//     0.97 0.97 1.17 1.24 times the wide kernels, 12 (188) 0.92 0.92 1.01 1.04; INT2 f 12000, 16 experts, 16 tokens (375) 0.80 0.88 1.07
+//     0.95 0.87 1.02 1.17 times the wide kernels, 12 (188) 0.94 0.80 0.91 1.01; INT2 f 12000, 16 experts, 16 tokens (375) 0.83 0.75 0.84 1.00
 bool fused_between_pays(int d, int f, int bits, int group, int n_all, int n_tasks, int slots, int passes) {
     const int cus = num_cus() * fused_wgs_per_cu;
     if ((long long)fused_blocks(d, f, passes) * n_tasks > cus) return false;  // a second round
@@ -93,6 +92,12 @@ bool fused_between_pays(int d, int f, int bits, int group, int n_all, int n_task
 //         16 (448) 372 / 313  240 / 238  168 / 168
 //   INT4   1 (28) 44.9 / 44.8  33.9 / 34.0  24.7 / 25.8    4 (112) 141 / 142  108 / 111  75 / 65    8 (224) 237 / 238  182 / 182  137 / 112
 //         16 (448) 342 / 346  286 / 264  235 / 186
+//   INT3   1 (28) 53.2 / 52.8  38.6 / 39.1  27.8 / 26.3    4 (112) 146 / 146  110 / 112  76 / 66    8 (224) 231 / 234  180 / 182  137 / 111
+//         16 (448) 356 / 350  299 / 271  247 / 194   groups of 32: 8 240 / 244  186 / 187  140 / 111    16 365 / 363  303 / 277  254 / 194
+// With many experts and more than 32 tasks it costs up to a tenth at 60 % and saves a fifth at 90 %: 32 tokens top-2 of 16, INT4 f 4894 (306) 271 / 294
+// 219 / 219  174 / 137, INT3 f 4894 275 / 288  213 / 206  176 / 142, f 7000 (448) 370 / 401  297 / 287  245 / 196; of 24, INT4 f 4000 258 / 274
+// 198 / 206  151 / 123.  Producers that do not wait for each other's rows let the tasks of an expert drift apart, and they find less of each
+// other's rows in the L2 (INT4 f 4894 at 60 %: 7.8 / 6.0 million hits, 1.84 / 2.07 GB from HBM).
 static bool fused_ahead_pays(int bits, int passes) { return passes >= (bits == 2 ? 300 : 160); }
 
 hipError_t launch_fused(const FusedArgs& a, int bits, hipStream_t stream) {

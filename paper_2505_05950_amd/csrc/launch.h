@@ -53,9 +53,9 @@ inline int fused_route_mode(int n_experts, int top_k, int n_shared) {
 // Besides the widths of the packed GEMV also 1536, 2560 and 3072, where a quarter to three eighths of a channel's lanes have no
 // unit: the separate kernels there read codes with the generic GEMV, whose precision these instances keep (fused_ffn.h).  The widths
 // left, 512 and 3584, have no instances (36 kernels each) and run the separate kernels; unmeasured.
-// Calls, separate kernels / this, us: INT4 g128 d 2560 f 6911 (6 experts, top-2) 1 token 25.0 / 17.2, 3 37.4 / 28.5, 8 66.9 / 55.6;
-// INT2 g64 d 1536 f 5000 (8) 1 token 20.7 / 12.8, 8 45.5 / 29.5; INT3 g64 d 3072 f 8000 (8) 4 tokens 61.2 / 39.6; INT4 g32 d 1536
-// f 1408 (64 + 2, top-6) 16 tokens 72.7 / 54.0.
+// Calls at 80 %, separate kernels / this, us: INT4 g128 d 2560 f 6911 (6 experts, top-2) 1 token 26.2 / 16.9, 3 43.8 / 29.8, 8 75.1 / 53.7;
+// INT2 g64 d 1536 f 5000 (8) 1 token 21.3 / 12.8, 8 46.9 / 29.4; INT3 g64 d 3072 f 8000 (8) 4 tokens 64.8 / 43.1; INT4 g32 d 1536
+// f 1408 (64 + 2, top-6) 16 tokens 82.8 / 57.6.
 inline bool fused_shape(int d, int bits, int group) {
     return (bits == 2 || bits == 3 || bits == 4) && group >= 32 && (packed_fast_shape(d, bits, group) || d == 1536 || d == 2560 || d == 3072);
 }
@@ -71,9 +71,12 @@ constexpr int kFusedMinPasses = 7, kFusedMaxPasses = 448;
 constexpr int fused_depth(int d, int bits) { return bits == 2 ? (d / 128 < 14 ? d / 128 : 14) : 4; }
 constexpr int kFusedMaxRouted = 64;       // routed experts a workgroup can pick among in place (one per lane)
 constexpr int kFusedMaxTasks = 256;       // (token, slot) tasks up to which the fused kernel is considered
-// Up to how many tasks a layer call takes the fused kernel.  Measured against the batch kernels (grouped up GEMV, union
-// gate/down), it wins while experts see few tokens each: config 3 (8 experts) 16 tasks 97 against 132 us, 32 tasks 181
-// against 184, 64 tasks 348 against 313; config 5 (66 experts) 64 tasks 38 against 54, 256 tasks 131 against 145.
+// Up to how many tasks a layer call takes the fused kernel.  Measured against the batch kernels (one-token, grouped or wide, whichever
+// the call would run), it wins while experts see few tokens each.  us, fused / batch at 60, 80, 90, 95 %: 8 experts d 4096 f 14336 INT2 16 tasks
+// 257 / 291  166 / 205  114 / 151  90 / 118, 32 367 / 461  249 / 311  184 / 219  158 / 159, 48 658 / 388  443 / 342  331 / 279  300 / 218; INT4 32 tasks 370 / 453
+// 250 / 298  188 / 208  166 / 155; 64 + 2 experts d 2048 f 1408 INT3 128 tasks 106 / 132  69 / 97  51 / 79  47 / 67; 16 experts d 2048 f 5632 INT4 64 tasks
+// 156 / 188  118 / 137  100 / 100  86 / 76, 96 261 / 263  206 / 182  185 / 130  164 / 96.  (At d 1024 and 1536 it would win beyond: 8 experts d 1024 f 3584
+// INT2 48 tasks 52 / 73  37 / 54  29 / 44  27 / 37.)
 // Rule: up to 16 tasks always, beyond that up to four tasks per expert.  fused_tasks_tuned() > 0 replaces the rule.
 int fused_tasks_tuned();
 void set_fused_tasks_tuned(int n);
@@ -301,7 +304,9 @@ inline bool up_split_shape(int d, int f, int bits, int group) { return up_wide_s
 // (8 experts, top-2) at 40 tokens 314 / 308, 96: 430 / 415; 4 experts 32 tokens 224 / 217; INT3 g64 d 2048 f 7000 at 64: 177 / 152;
 // INT3 g32 d 4096 f 4096 (16 experts) at 128: 420 / 284; d 2048 f 1408 (66 experts, top-6) at 64: 220 / 195, 128: 260 / 245;
 // INT4 g64 d 4096 f 7000 (6) at 48: 222 / 202; INT4 g32 d 2048 f 5632 at 64: 138 / 137; widths without a grouped kernel the same.
-// With one token tile INT2 leaves the grouped kernel little to share a pass with and less to unpack: 24 tokens 243 / 251.
+// With one token tile INT2 leaves the grouped kernel little to share a pass with and less to unpack: 24 tokens 243 / 251.  (Measured since this one
+// brings the grouping with it, two launches fewer, at 80 %: 24 tokens 349 / 343, 16 experts d 4096 f 4000 64 tokens 253 / 240, d 2048 f 14336 404 / 375;
+// three and four tiles, 66 experts d 2048 f 1408 200 tokens 288 / 258.  The line for INT2 is where it was.)
 // More than two token tiles come in parts of two, which up_wide.hip does at once: INT2 at 130 tokens 485 / 470, d 2048 f 4096 (4 experts)
 // at 90: 89 / 86; the wider codes leave it fewer token tiles: INT4 g32 d 2048 f 5632 at 200 tokens, that or grouped kernel / this, 184 / 162,
 // INT3 g64 d 2048 f 7000 at 200: 196 / 182, INT3 g32 d 4096 f 3000 (4) at 90: 152 / 109.

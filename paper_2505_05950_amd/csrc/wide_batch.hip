@@ -37,8 +37,9 @@
 // lane from sixteen rows, cost the cache 64 accesses per request; with the activations' it was busy for half of the cycles and the
 // waves stood behind their own requests.  The same holds for v gathered by lane (a tenth of the kernel).  Requests cost the cache their 1 KB
 // whether or not rows repeat: the rows of a segment dealt to all eight waves, few each, took 37 us for one expert with 24 tokens, not 27.  Measured, gate, 8 experts
-// d 4096 f 14336 at 90 %: 512 tokens 280 -> 232 us, 64 tokens 152 -> 144, one expert with 24 tokens 28.4 -> 24.6.  Gate + down before
-// groups of more than 16 tokens: 64 tokens 364 us, 512 tokens 2425.  Down, the same layer with 512 tokens 277 -> 254 us: half of its cycles were matrix products, a
+// d 4096 f 14336 at 90 %: 512 tokens 280 -> 232 us, 64 tokens 152 -> 144, one expert with 24 tokens 28.4 -> 24.6; with the lists made here 240, 147 and
+// 26.6.  Gate + down before groups of more than 16 tokens: 64 tokens 364 us, 512 tokens 2425.  Down, the same layer with 512 tokens 277 -> 254 us, 267
+// since it walks segments (ten token tiles leave that six registers too few: they are spilled, four before): half of its cycles were matrix products, a
 // fifth of these for token tiles that a group does not fill, and the waves stood for the LDS reads in front of each tile's.  (A body per
 // number of live tiles, as in the gate kernel, spills: 284.  So does reading one tile ahead with an address register per entry of h, 309:
 // a reload waits for every row in flight.)  Up to two tiles it is bound by the rows and did not change.
