@@ -197,6 +197,10 @@ static_assert(sizeof(WideGroup) == 48, "loaded as three vectors");
 // Shares are that many words apart.  (The up projections take them by a pointer of their own: records that a kernel writes to are no longer
 // loaded as scalars, 0.6 us of a call with 24 tokens on one expert.)
 constexpr int kWideGroupWords = sizeof(WideGroup) / 4;
+// all of a record but its share, for kernels that add to the shares meanwhile
+__device__ __forceinline__ WideGroup wide_group_less_share(const WideGroup* __restrict__ groups, int g) {
+    return WideGroup{0, groups[g].n, groups[g].first, groups[g].tile, groups[g].e};
+}
 
 // the groups of a single expert that all of n_tasks tasks belong to: as few of at most `chunk` as possible, of equal size
 __host__ __device__ inline int wide_single_groups(int n_tasks, int chunk) { return (n_tasks + chunk - 1) / chunk; }

@@ -249,7 +249,7 @@ __global__ __launch_bounds__(512) void up_split_kernel(const WideGroup* __restri
             base += __builtin_amdgcn_readlane(inc, kWave - 1);
         }
         g = __builtin_amdgcn_readfirstlane(g);
-        const WideGroup grp = groups[g];
+        const WideGroup grp = wide_group_less_share(groups, g);
         const int part = __builtin_amdgcn_readfirstlane(min((pos - base) / full_weight, parts_of(grp.n) - 1));
         const int tok_first = 32 * part, n_tok = min(32, grp.n - tok_first);
         // block k of a part belongs to the piece that holds the start of its share, kStart + k * wgt behind the part's

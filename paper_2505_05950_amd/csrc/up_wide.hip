@@ -105,7 +105,7 @@ __global__ __launch_bounds__(kUpThreads) void up_wide_kernel(const WideGroup* __
         }
         if (g < 0) break;  // fewer pieces than workgroups
         g = __builtin_amdgcn_readfirstlane(g);
-        const WideGroup grp = groups[g];
+        const WideGroup grp = wide_group_less_share(groups, g);
         const int wgt = weight(grp.n), part_weight = wgt * blocks;
         const int in_part = whole ? (part_weight + most - 1) / most : part_weight;
         const int part = __builtin_amdgcn_readfirstlane((pos - base) / in_part);
